@@ -164,8 +164,18 @@ constexpr size_t fwd_lds_bytes()
     return sizeof(u16) * (size_t)(5 * 64 * (D + 16));      // two K slots, three V slots
 }
 
-template <int D>
-__global__ __launch_bounds__(kFwdWaves * 64, 2) void attn_fwd_bf16(AttnParams p)
+// Key tiles of row block rb (64-key tiles up to the last key its last row sees).
+__device__ __forceinline__ int fwd_row_block_tiles(const AttnParams &p, int rwg, int rb)
+{
+    return (p.M + min(rb * rwg + rwg, p.Ct) - 1) / 64 + 1;
+}
+
+// One workgroup's pass of row block rb of head subgroup hs over the key tiles [t0, t1).  With
+// SPLIT the result is either final (the range covers the whole row block) or goes, unnormalised,
+// to partial slot `slot`; without it the range is the whole row block.
+template <int D, bool SPLIT>
+__device__ __forceinline__ void fwd_segment(const AttnParams &p, u16 *smem, int kvh, int hs, int rb, int t0, int t1,
+                                            long slot)
 {
     constexpr int NW = kFwdWaves;
     constexpr int NT = NW * 64;
@@ -178,7 +188,6 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2) void attn_fwd_bf16(AttnParams p)
     constexpr int NK = 4 * KS;           // K fragments per tile  (key block, k-step)
     constexpr int NV = 2 * DB;           // V^T fragments per tile (key pair, d block)
 
-    extern __shared__ __attribute__((aligned(16))) u16 smem[];
     u16 *ldsK = smem;                          // [2][KTILE]
     u16 *ldsV = smem + 2 * KTILE;              // [3][VTILE]
 
@@ -188,20 +197,15 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2) void attn_fwd_bf16(AttnParams p)
     const int ln = lane & 15;
     const int lg = lane >> 4;
 
-    // block -> (kv head, head subgroup, row block); heavy (late) row blocks first
-    const int bid = blockIdx.x;
-    const int kvh = bid % p.Hkv;
-    const int rest = bid / p.Hkv;
-    const int nsub = p.G / p.gp;
-    const int hs = rest % nsub;
-    const int rb = p.n_row_blocks - 1 - rest / nsub;
     const int slabs = NW / p.gp;
     const int head = kvh * p.G + hs * p.gp + (wave % p.gp);
     const int rwg = slabs * 32;
     const int w0 = rb * rwg + (wave / p.gp) * 32;
 
-    const u16 *Kg = (const u16 *)p.k + (size_t)kvh * p.cap * D;
-    const u16 *Vg = (const u16 *)p.v + (size_t)kvh * p.cap * D;
+    const int jbase = SPLIT ? t0 * BN : 0;               // first key of the range; tiles below count from it
+    const u16 *Kg = (const u16 *)p.k + ((size_t)kvh * p.cap + jbase) * D;
+    const u16 *Vg = (const u16 *)p.v + ((size_t)kvh * p.cap + jbase) * D;
+    const int M = p.M - jbase, n = p.n - jbase;          // both relative to the range
 
     // Q^T operands of the wave's two 16-row query blocks stay in registers for the whole pass
     v4u qreg[2][KS];
@@ -217,9 +221,8 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2) void attn_fwd_bf16(AttnParams p)
         }
     }
 
-    const int wg_last_row = min(rb * rwg + rwg, p.Ct) - 1;
-    const int ntiles = (p.M + wg_last_row) / BN + 1;
-    const int wave_last_key = (w0 < p.Ct) ? p.M + min(w0 + 32, p.Ct) - 1 : -1;
+    const int ntiles = SPLIT ? t1 - t0 : fwd_row_block_tiles(p, rwg, rb);
+    const int wave_last_key = (w0 < p.Ct) ? M + min(w0 + 32, p.Ct) - 1 : -1;
 
     f32x4 o[2][DB];
     float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
@@ -235,9 +238,9 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2) void attn_fwd_bf16(AttnParams p)
 
     Stage st;
     st.init(tid);
-    st.load(Kg, Vg, p.n);
+    st.load(Kg, Vg, n);
     st.store(ldsK, ldsV);
-    if (ntiles > 1) st.load(Kg + BN * D, Vg + BN * D, p.n - BN);
+    if (ntiles > 1) st.load(Kg + BN * D, Vg + BN * D, n - BN);
     __syncthreads();
 
     // Two waves share a SIMD (wave w and w + NW/2), and the barrier per tile keeps them in step.
@@ -246,16 +249,18 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2) void attn_fwd_bf16(AttnParams p)
     // softmax of tile t, keeping the probabilities in registers across the barrier.  V therefore
     // lives in three LDS slots (tile u in slot u%3), K in two.
     const bool lag = wave >= NW / 2;
-    const int tl = wave_last_key >= 0 ? wave_last_key / BN : -1;      // last tile this wave needs
+    // last tile of the range this wave needs
+    const int tl = SPLIT ? (wave_last_key >= 0 ? min(wave_last_key / BN, ntiles - 1) : -1)
+                         : (wave_last_key >= 0 ? wave_last_key / BN : -1);
     v4u pb[2][2];
     int vslot = 0;                                                    // t mod 3
 
     auto mask_tile = [&](f32x4 (&s)[2][4], int j0) {
-        if (j0 + BN - 1 > p.M + w0) {
+        if (j0 + BN - 1 > M + w0) {
             asm volatile("; mask path" ::: "memory");      // diagonal tiles only: keep out of line
 #pragma unroll
             for (int nb = 0; nb < 2; ++nb) {
-                const int lim = p.M + w0 + 16 * nb + ln - j0;   // key offset <= lim is visible
+                const int lim = M + w0 + 16 * nb + ln - j0;   // key offset <= lim is visible
 #pragma unroll
                 for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
@@ -280,7 +285,8 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2) void attn_fwd_bf16(AttnParams p)
                 mx = fmaxf(mx, __shfl_xor(mx, 16));
                 mx = fmaxf(mx, __shfl_xor(mx, 32));
                 const float m_new = fmaxf(mx, m_run[nb]);
-                const float alpha = __builtin_amdgcn_exp2f((m_run[nb] - m_new) * c);
+                // a range may begin on tiles in which a row sees no key yet: nothing to rescale then
+                const float alpha = SPLIT && m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((m_run[nb] - m_new) * c);
                 m_run[nb] = m_new;
                 l_run[nb] *= alpha;
 #pragma unroll
@@ -288,8 +294,8 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2) void attn_fwd_bf16(AttnParams p)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) o[nb][db][e] *= alpha;
             }
-            rs0 = softmax_row(s[0], c, m_run[0] * c, pb[0]);
-            rs1 = softmax_row(s[1], c, m_run[1] * c, pb[1]);
+            rs0 = softmax_row(s[0], c, SPLIT && m_run[0] == -INFINITY ? 0.f : m_run[0] * c, pb[0]);
+            rs1 = softmax_row(s[1], c, SPLIT && m_run[1] == -INFINITY ? 0.f : m_run[1] * c, pb[1]);
         }
         l_run[0] += rs0;
         l_run[1] += rs1;
@@ -422,7 +428,7 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2) void attn_fwd_bf16(AttnParams p)
             st.store(ldsK + ((t + 1) & 1) * KTILE, ldsV + vnext * VTILE);
             if (t + 2 < ntiles) {
                 const size_t off = (size_t)(j0 + 2 * BN) * D;
-                st.load(Kg + off, Vg + off, p.n - (j0 + 2 * BN));
+                st.load(Kg + off, Vg + off, n - (j0 + 2 * BN));
             }
         }
         vslot = vslot == 2 ? 0 : vslot + 1;
@@ -442,7 +448,26 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2) void attn_fwd_bf16(AttnParams p)
         }
     }
 
-    if (wave_last_key < 0) return;
+    if (SPLIT && slot >= 0) {
+        // a partial result: every row of the slot is written (a wave that saw no key leaves m = -inf, l = 0)
+        float *po = p.part_o + (size_t)slot * p.part_rows * D;
+        float2 *pml = p.part_ml + (size_t)slot * p.part_rows;
+        const int rows = p.part_rows / p.gp;             // chunk rows per head in the slot
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) {
+            const int row = w0 + 16 * nb + ln;
+            float l_tot = l_run[nb] + __shfl_xor(l_run[nb], 16);
+            l_tot += __shfl_xor(l_tot, 32);
+            if (row >= p.Ct) continue;
+            const int pr = (wave % p.gp) * rows + (row - rb * rwg);
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+                *(f32x4 *)(po + (size_t)pr * D + db * 16 + 4 * lg) = o[nb][db];
+            if (lg == 0) pml[pr] = make_float2(m_run[nb] * c, l_tot);
+        }
+        return;
+    }
+    if (!SPLIT && wave_last_key < 0) return;
     u16 *Oh = (u16 *)p.out + (size_t)head * p.o_hs;
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) {
@@ -461,6 +486,102 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2) void attn_fwd_bf16(AttnParams p)
         }
         if (lg == 0) p.lse[(size_t)head * p.Ct + row] = (m_run[nb] * c + __builtin_amdgcn_logf(l_tot)) * kLn2;
     }
+}
+
+// SPLIT: for problems with few row blocks (a generated token has one per KV head) or a number of them
+// that fills the last round of workgroups badly.  A KV head's key tiles, over all its row
+// blocks, form one list; `shares` workgroups take equal parts of it, whatever row blocks these cut
+// through.  A row block that one workgroup covers alone is finished there, the pieces of the
+// others are merged by attn_fwd_merge.  blockIdx % Hkv is the KV head in both forms, so with
+// eight of them an XCD's L2 sees one head's K/V.
+template <int D, bool SPLIT>
+__global__ __launch_bounds__(kFwdWaves * 64, 2) void attn_fwd_bf16(AttnParams p)
+{
+    extern __shared__ __attribute__((aligned(16))) u16 smem[];
+    const int bid = blockIdx.x;
+    const int kvh = bid % p.Hkv;
+    const int nsub = p.G / p.gp;
+    if constexpr (SPLIT) {
+        const int rwg = kFwdWaves / p.gp * 32;
+        const int share = bid / p.Hkv;
+        const long begin = share * p.tiles / p.shares, end = (share + 1) * p.tiles / p.shares;
+        int rb = 0, hs = 0;
+        long pos = 0;                                    // list position of (rb, hs)'s first tile
+        int nt = fwd_row_block_tiles(p, rwg, 0);
+        while (pos + nt <= begin) {
+            pos += nt;
+            if (++hs == nsub) { hs = 0; nt = fwd_row_block_tiles(p, rwg, ++rb); }
+        }
+        bool first = true;
+        while (pos < end) {
+            const int t0 = (int)max(begin - pos, 0L), t1 = (int)min(end - pos, (long)nt);
+            // a workgroup leaves at most two pieces: the end of a row block it begins in, and the
+            // beginning of the one it ends in
+            const long slot = t0 == 0 && t1 == nt ? -1 : (long)bid * 2 + (t0 == 0 ? 1 : 0);
+            if (!first) __syncthreads();                 // lagging waves still read the last V tile
+            first = false;
+            fwd_segment<D, true>(p, smem, kvh, hs, rb, t0, t1, slot);
+            pos += nt;
+            if (++hs == nsub) { hs = 0; if (pos < end) nt = fwd_row_block_tiles(p, rwg, ++rb); }
+        }
+    } else {
+        // block -> (kv head, head subgroup, row block); heavy (late) row blocks first
+        const int rest = bid / p.Hkv;
+        fwd_segment<D, false>(p, smem, kvh, rest % nsub, p.n_row_blocks - 1 - rest / nsub, 0, 0, -1);
+    }
+}
+
+// Merges the pieces of the row blocks that several workgroups share: a group of D/4 lanes per
+// query row, four output columns per lane.  grid (row groups of a row block, row block x subgroup, KV head).
+template <int D>
+__global__ __launch_bounds__(256) void attn_fwd_merge(AttnParams p)
+{
+    constexpr int L = D / 4;
+    const int nsub = p.G / p.gp;
+    const int rb = blockIdx.y / nsub, hs = blockIdx.y % nsub, kvh = blockIdx.z;
+    const int rwg = kFwdWaves / p.gp * 32;
+    // list position of the row block: rwg is a multiple of 64, so every whole row block adds rwg/64 tiles
+    const int k64 = rwg / 64, base = fwd_row_block_tiles(p, rwg, 0);
+    const int nt = fwd_row_block_tiles(p, rwg, rb);
+    long pos = (long)hs * nt;
+    if (rb > 0) pos += nsub * ((long)rb * base + (long)k64 * ((long)rb * (rb - 1) / 2));
+    // shares that hold a tile of [pos, pos + nt): share j holds [j*tiles/shares, (j+1)*tiles/shares)
+    const int j0 = (int)(((pos + 1) * p.shares - 1) / p.tiles), j1 = (int)(((pos + nt) * p.shares - 1) / p.tiles);
+    if (j0 == j1) return;                                // finished by one workgroup
+    const int pr = blockIdx.x * (256 / L) + threadIdx.x / L;
+    if (pr >= p.part_rows) return;
+    const int rows = p.part_rows / p.gp;
+    const int row = rb * rwg + pr % rows, head = kvh * p.G + hs * p.gp + pr / rows;
+    if (row >= p.Ct) return;
+    const int c4 = (threadIdx.x % L) * 4;
+    // pieces: share j0's is its end of a row block (slot 0) unless the row block begins the share,
+    // the later shares begin inside the row block (slot 0)
+    auto slot_of = [&](int j) -> long {
+        const long wg = (long)j * p.Hkv + kvh;
+        const bool begins = j == j0 && j * p.tiles / p.shares <= pos;
+        return wg * 2 + (begins ? 1 : 0);
+    };
+    float m = -INFINITY;
+#pragma unroll 8
+    for (int j = j0; j <= j1; ++j) m = fmaxf(m, p.part_ml[(size_t)slot_of(j) * p.part_rows + pr].x);
+    float l = 0.f;
+    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+    for (int j = j0; j <= j1; ++j) {
+        const size_t at = (size_t)slot_of(j) * p.part_rows + pr;
+        const float2 ml = p.part_ml[at];
+        const f32x4 x = *(const f32x4 *)(p.part_o + at * D + c4);
+        const float w = __builtin_amdgcn_exp2f(ml.x - m);    // 0 for a piece without a visible key
+        l = fmaf(w, ml.y, l);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = fmaf(w, x[e], o[e]);
+    }
+    const float inv = 1.0f / l;
+    v2u w;
+    w.x = pack_bf16x2(o[0] * inv, o[1] * inv);
+    w.y = pack_bf16x2(o[2] * inv, o[3] * inv);
+    *(v2u *)((u16 *)p.out + (size_t)head * p.o_hs + (size_t)row * p.o_rs + c4) = w;
+    if (c4 == 0) p.lse[(size_t)head * p.Ct + row] = (m + __builtin_amdgcn_logf(l)) * kLn2;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -725,19 +846,45 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_score_bf16(AttnParams p)
 
 // ------------------------------------------------------------------------------------------
 // Host-side launchers (called from the C-ABI file).
-template <int D>
-static hipError_t launch_fwd(AttnParams p, hipStream_t st)
+// How the forward pass of a problem is cut into workgroups: gp, n_row_blocks and, if the key range
+// is to be split, shares, tiles and part_rows.
+static void fwd_plan(AttnParams &p)
 {
-    constexpr int NW = kFwdWaves;
-    int gp = 1;
-    if (p.G % 4 == 0) gp = 4;
-    else if (p.G % 2 == 0) gp = 2;
-    p.gp = gp;
-    const int rwg = (NW / gp) * 32;
+    p.gp = p.G % 4 == 0 ? 4 : p.G % 2 == 0 ? 2 : 1;
+    const int rwg = kFwdWaves / p.gp * 32, nsub = p.G / p.gp;
     p.n_row_blocks = (p.Ct + rwg - 1) / rwg;
-    const int grid = p.Hkv * (p.G / gp) * p.n_row_blocks;
+    p.shares = 0;
+    p.part_rows = p.gp * (p.Ct < rwg ? p.Ct : rwg);
+    const int cus = device_compute_units() > 0 ? device_compute_units() : 256;
+    const long whole = (long)p.Hkv * nsub * p.n_row_blocks;
+    if (whole > 4l * cus || p.Hkv > cus) return;         // at least four well-filled rounds
+    // rwg is a multiple of 64: every row block but the last has rwg/64 tiles more than the one before
+    const long first = (p.M + rwg - 1) / 64 + 1, nrb = p.n_row_blocks, longest = (p.M + p.Ct - 1) / 64 + 1;
+    p.tiles = nsub * ((nrb - 1) * first + (nrb - 1) * (nrb - 2) / 2 * (rwg / 64) + longest);
+    // Time of either form, in key tiles of one workgroup (one workgroup is resident per compute unit):
+    // whole row blocks run in rounds; equal shares add their partial results, about 24 tiles' time
+    // for a full slot of 256 x 128 written and read back, and a launch that merges them.
+    const long per_head = cus / p.Hkv;
+    long shares = p.tiles / 2 < per_head ? p.tiles / 2 : per_head;
+    if (shares < 2) return;
+    const double rounds = (double)((whole + cus - 1) / cus);
+    const double t_whole = whole <= cus ? (double)longest : rounds * (double)p.tiles * p.Hkv / (double)whole;
+    const double slot = p.part_rows * p.D / (256.0 * 128.0), busy = (double)shares * p.Hkv / cus;
+    const double t_split = (double)p.tiles / shares + 4.0 + slot * (4.0 + 20.0 * busy);
+    if (t_split < t_whole) p.shares = (int)shares;
+}
+
+size_t attend_bf16_split_bytes(AttnParams p)
+{
+    fwd_plan(p);
+    return (size_t)p.shares * p.Hkv * 2 * p.part_rows * (p.D * sizeof(float) + sizeof(float2));
+}
+
+template <int D, bool SPLIT>
+static hipError_t launch_fwd_form(const AttnParams &p, int grid, hipStream_t st)
+{
     const size_t smem = fwd_lds_bytes<D>();
-    auto kern = attn_fwd_bf16<D>;
+    auto kern = attn_fwd_bf16<D, SPLIT>;
     // the kernel needs more than the default 64 KB of LDS: raised once per device, not per launch
     static std::atomic<bool> lds_raised[64];
     int dev = 0;
@@ -748,7 +895,24 @@ static hipError_t launch_fwd(AttnParams p, hipStream_t st)
         if (e != hipSuccess) return e;
         if (dev >= 0 && dev < 64) lds_raised[dev].store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(NW * 64), smem, st, p);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kFwdWaves * 64), smem, st, p);
+    return hipGetLastError();
+}
+
+// `part` (part_bytes): scratch for partial results; the key range is only split if they fit.
+template <int D>
+static hipError_t launch_fwd(AttnParams p, void *part, size_t part_bytes, hipStream_t st)
+{
+    fwd_plan(p);
+    const int nsub = p.G / p.gp;
+    if (!p.shares || !part || part_bytes < attend_bf16_split_bytes(p))
+        return launch_fwd_form<D, false>(p, p.Hkv * nsub * p.n_row_blocks, st);
+    p.part_o = (float *)part;
+    p.part_ml = (float2 *)(p.part_o + (size_t)p.shares * p.Hkv * 2 * p.part_rows * D);
+    hipError_t e = launch_fwd_form<D, true>(p, p.shares * p.Hkv, st);
+    if (e != hipSuccess) return e;
+    const dim3 grid((p.part_rows * (D / 4) + 255) / 256, p.n_row_blocks * nsub, p.Hkv);
+    hipLaunchKernelGGL(attn_fwd_merge<D>, grid, dim3(256), 0, st, p);
     return hipGetLastError();
 }
 
@@ -761,10 +925,10 @@ static hipError_t launch_score(AttnParams p, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t attend_bf16_forward(const AttnParams &p, hipStream_t st)
+hipError_t attend_bf16_forward(const AttnParams &p, void *part, size_t part_bytes, hipStream_t st)
 {
-    if (p.D == 128) return launch_fwd<128>(p, st);
-    return launch_fwd<64>(p, st);
+    if (p.D == 128) return launch_fwd<128>(p, part, part_bytes, st);
+    return launch_fwd<64>(p, part, part_bytes, st);
 }
 
 hipError_t attend_bf16_score(const AttnParams &p, hipStream_t st)

@@ -30,6 +30,12 @@ struct AttnParams {
     int accumulate;
     int gp;          // query heads of one group that share a workgroup (1, 2 or 4)
     int n_row_blocks;
+    // forward pass with the key range split over workgroups (see attn_fwd_bf16); shares == 0: whole
+    int shares;      // workgroups per KV head, each an equal share of the head's key tiles
+    long tiles;      // key tiles of one KV head, over its row blocks and head subgroups
+    int part_rows;   // query rows (heads x chunk rows) of one partial result
+    float *part_o;   // [workgroup][2][part_rows][D] unnormalised outputs
+    float2 *part_ml; // [workgroup][2][part_rows] reference maximum (log2 units) and running sum
 };
 
 #ifndef RF_MOVE_TILE
@@ -135,6 +141,9 @@ struct GatherParams {
     float eps;
     int q0, nq_grp;      // query group handled by this similarity launch
 };
+
+// Compute units of the current device (reform_api.hip; cached per device, 0 if it cannot be told).
+int device_compute_units();
 
 __device__ __forceinline__ float bf16_bits_to_f32(u16 b) { return __uint_as_float(((uint32_t)b) << 16); }
 

@@ -8,7 +8,8 @@
 #include <cstring>
 
 namespace reform {
-hipError_t attend_bf16_forward(const AttnParams &p, hipStream_t st);
+hipError_t attend_bf16_forward(const AttnParams &p, void *part, size_t part_bytes, hipStream_t st);
+size_t attend_bf16_split_bytes(AttnParams p);
 hipError_t attend_bf16_score(const AttnParams &p, hipStream_t st);
 hipError_t attend_f32_forward(const AttnParams &p, hipStream_t st);
 hipError_t attend_f32_score(const AttnParams &p, hipStream_t st);
@@ -25,6 +26,18 @@ hipError_t rope_rerotate_launch(const RopeParams &p, bool bf16, hipStream_t st);
 hipError_t gather_rows_launch(const RowsParams &p, hipStream_t st);
 hipError_t probe_mfma_launch(const void *operands, float *sink, int iters, int workgroups, hipStream_t st);
 hipError_t probe_stream_launch(const void *src, void *dst, size_t bytes, void *sink, hipStream_t st);
+
+int device_compute_units()
+{
+    static std::atomic<int> cached[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
+    int v = cached[dev].load(std::memory_order_relaxed);
+    if (v > 0) return v;
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) return 0;
+    cached[dev].store(v, std::memory_order_relaxed);
+    return v;
+}
 }  // namespace reform
 
 using namespace reform;
@@ -190,10 +203,32 @@ const char *reform_status_string(reform_status s)
 int32_t reform_version(void) { return 100; }
 
 // ---------------------------------------------------------------------------------------
+static AttnParams attn_sizes(const reform_attn_desc *d)
+{
+    AttnParams p;
+    std::memset(&p, 0, sizeof(p));
+    p.Hq = d->n_q_heads; p.Hkv = d->n_kv_heads; p.G = p.Hq / p.Hkv; p.D = d->head_dim;
+    p.M = d->cache_len; p.Ct = d->chunk_len; p.cap = d->capacity; p.n = p.M + p.Ct;
+    p.q_hs = d->q_head_stride; p.q_rs = d->q_row_stride;
+    p.o_hs = d->o_head_stride; p.o_rs = d->o_row_stride;
+    p.scale = d->scale;
+    p.W = d->obs_window ? d->obs_window : d->chunk_len;
+    p.accumulate = d->accumulate;
+    return p;
+}
+
+// lse rows when the caller passes none; they come first in the workspace
+static size_t attn_lse_bytes(const reform_attn_desc *d)
+{
+    return align_up((size_t)d->n_q_heads * d->chunk_len * sizeof(float));
+}
+
 size_t reform_chunk_attend_score_workspace(const reform_attn_desc *d)
 {
     if (check_attn(d) != REFORM_OK) return 0;
-    return align_up((size_t)d->n_q_heads * d->chunk_len * sizeof(float));
+    size_t bytes = attn_lse_bytes(d);
+    if (d->dtype == REFORM_BF16) bytes += align_up(attend_bf16_split_bytes(attn_sizes(d)));
+    return bytes;
 }
 
 reform_status reform_chunk_attend_score(const reform_attn_desc *d, const void *q, const void *k,
@@ -206,27 +241,17 @@ reform_status reform_chunk_attend_score(const reform_attn_desc *d, const void *q
     if (!q || !k || !v || (do_attn && !out)) return REFORM_ERR_INVALID_ARG;
     if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(out)) return REFORM_ERR_INVALID_ARG;
     if (d->phases == 2 && (!lse || !score)) return REFORM_ERR_INVALID_ARG;
-    float *lse_buf = lse;
-    if (!lse_buf) {
-        const size_t need = reform_chunk_attend_score_workspace(d);
-        if (!workspace || workspace_bytes < need || ((uintptr_t)workspace & (kAlign - 1)))
-            return REFORM_ERR_WORKSPACE;
-        lse_buf = (float *)workspace;
-    }
-    AttnParams p;
-    std::memset(&p, 0, sizeof(p));
-    p.q = q; p.k = k; p.v = v; p.out = out; p.lse = lse_buf; p.score = score;
-    p.Hq = d->n_q_heads; p.Hkv = d->n_kv_heads; p.G = p.Hq / p.Hkv; p.D = d->head_dim;
-    p.M = d->cache_len; p.Ct = d->chunk_len; p.cap = d->capacity; p.n = p.M + p.Ct;
-    p.q_hs = d->q_head_stride; p.q_rs = d->q_row_stride;
-    p.o_hs = d->o_head_stride; p.o_rs = d->o_row_stride;
-    p.scale = d->scale;
-    p.W = d->obs_window ? d->obs_window : d->chunk_len;
-    p.accumulate = d->accumulate;
+    const size_t lse_bytes = attn_lse_bytes(d);
+    const bool ws_ok = workspace && workspace_bytes >= lse_bytes && !((uintptr_t)workspace & (kAlign - 1));
+    if (!lse && !ws_ok) return REFORM_ERR_WORKSPACE;
+    AttnParams p = attn_sizes(d);
+    p.q = q; p.k = k; p.v = v; p.out = out; p.lse = lse ? lse : (float *)workspace; p.score = score;
+    void *part = ws_ok ? (char *)workspace + lse_bytes : nullptr;
+    const size_t part_bytes = ws_ok ? workspace_bytes - lse_bytes : 0;
     hipStream_t st = (hipStream_t)hip_stream;
     hipError_t e = hipSuccess;
     if (d->dtype == REFORM_BF16) {
-        if (do_attn) e = attend_bf16_forward(p, st);
+        if (do_attn) e = attend_bf16_forward(p, part, part_bytes, st);
         if (e == hipSuccess && do_score) e = attend_bf16_score(p, st);
     } else {
         if (do_attn) e = attend_f32_forward(p, st);

@@ -17,8 +17,6 @@
 // Candidates in the first n_sink or last n_recent slots get the maximal key (always selected).
 #include "common.h"
 
-#include <atomic>
-
 namespace reform {
 
 constexpr int kSelBlock = 4096;      // candidates per selection workgroup (256 threads x 16)
@@ -676,19 +674,6 @@ __global__ __launch_bounds__(1024) void select_multi(SelParams p, int parts)
         hipError_t e_ = hipGetLastError();    \
         if (e_ != hipSuccess) return e_;      \
     } while (0)
-
-// Compute units of the current device (cached per device; 256 on an unpartitioned MI355X).
-static int device_compute_units()
-{
-    static std::atomic<int> cached[64];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
-    int v = cached[dev].load(std::memory_order_relaxed);
-    if (v > 0) return v;
-    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) return 0;
-    cached[dev].store(v, std::memory_order_relaxed);
-    return v;
-}
 
 hipError_t select_topk(const SelParams &p, hipStream_t st)
 {

@@ -1,0 +1,67 @@
+"""Forward attention with the key range split over workgroups (few row blocks, or a last round of
+workgroups that would be nearly empty), against the fp64 oracle: ranges cut inside the causal
+diagonal, row blocks shared by many workgroups or by two, heads and chunk ends that leave a
+workgroup partly idle; and the same call with a workspace too small for the partial results."""
+import math
+
+import pytest
+import torch
+
+import oracle
+from helpers import assert_close, assert_scores_close, to_np
+from paper_2506_01215_amd import binding
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+SHAPES = [  # Hq, Hkv, d, cache, chunk, window
+    (8, 2, 128, 1000, 1, 0),        # one token: every workgroup holds a few tiles of one row block
+    (8, 2, 64, 127, 1, 0),          # two tiles a head: one workgroup, nothing to merge
+    (8, 8, 128, 4096, 17, 0),
+    (14, 2, 64, 2000, 300, 128),    # seven query heads per KV head
+    (1, 1, 128, 0, 1500, 0),        # no cache: ranges begin on tiles that rows do not see
+    (1, 1, 64, 900, 257, 0),        # last row block of one row
+    (4, 1, 128, 900, 65, 0),
+    (6, 3, 128, 2003, 513, 77),       # two heads of a group in one workgroup
+    (2, 1, 128, 6001, 40, 40),
+]
+
+
+def inputs(Hq, Hkv, d, M, Ct, seed):
+    g = torch.Generator().manual_seed(seed)
+    n = M + Ct
+    q = (torch.randn((Hq, Ct, d), generator=g) * 1.5).to(torch.bfloat16)
+    k = (torch.randn((Hkv, n + 3, d), generator=g) * 1.5).to(torch.bfloat16)   # logits of +-10: rows rescale
+    v = torch.randn((Hkv, n + 3, d), generator=g).to(torch.bfloat16)
+    return q.to(DEV), k.to(DEV), v.to(DEV)
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_split_forward_matches_oracle(shape):
+    Hq, Hkv, d, M, Ct, W = shape
+    q, k, v = inputs(Hq, Hkv, d, M, Ct, seed=M + Ct)
+    scale = 1.0 / math.sqrt(d)
+    desc = binding.attn_desc(q, k, q, M, scale, W)
+    lse_bytes = (Hq * Ct * 4 + 255) // 256 * 256
+    full = torch.full((binding.attend_workspace_bytes(desc) + 256,), 0xff, dtype=torch.uint8, device=DEV)
+    small = torch.full((lse_bytes + 512,), 0xff, dtype=torch.uint8, device=DEV)
+    o_ref, l_ref, s_ref = oracle.attend_score(to_np(q), to_np(k), to_np(v), M, scale, W=W)
+    results = []
+    for ws in (full, full, small):
+        out, lse, score = binding.reform_chunk_attend_score(q, k, v, M, scale, obs_window=W, workspace=ws)
+        torch.cuda.synchronize()
+        # the bounds of the other attention tests: bf16 rounding of P and of the output
+        assert_close(to_np(out), o_ref, 2e-2, "out", row_floor=True)
+        assert_close(to_np(lse), l_ref, 1e-5, "lse")
+        assert_scores_close(to_np(score)[:, :M + Ct], s_ref[:, :M + Ct], 2e-2, "score")
+        results.append((out, lse))
+    assert torch.equal(results[0][0], results[1][0]) and torch.equal(results[0][1], results[1][1])
+
+
+def test_the_shapes_split():
+    """Every shape but the two-tile one asks for more workspace than the lse rows."""
+    for Hq, Hkv, d, M, Ct, W in SHAPES:
+        q, k, _ = inputs(Hq, Hkv, d, M, Ct, seed=1)
+        need = binding.attend_workspace_bytes(binding.attn_desc(q, k, q, M, 0.1, W))
+        whole = (Hq * Ct * 4 + 255) // 256 * 256
+        assert (need > whole) == (M + Ct > 128), (Hq, Hkv, d, M, Ct, need, whole)
