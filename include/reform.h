@@ -97,6 +97,11 @@ typedef struct {
                                                    profiler bracket each kernel separately)       */
 } reform_attn_desc;
 
+/* The query returns room for the lse rows (used if the caller passes lse = NULL) and, for problems
+ * whose keys or rows are shared out over more workgroups than there are row or key blocks, for
+ * their partial results.  Only the lse rows are needed: with a workspace that holds just these
+ * (n_q_heads * chunk_len floats, rounded up to 256 bytes), or with none if lse is given, the call
+ * runs such problems in their unshared form, slower and with sums in another order.            */
 size_t reform_chunk_attend_score_workspace(const reform_attn_desc *desc);
 
 reform_status reform_chunk_attend_score(const reform_attn_desc *desc,

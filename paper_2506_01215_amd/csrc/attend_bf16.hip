@@ -504,9 +504,9 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2) void attn_fwd_bf16(AttnParams p)
     if constexpr (SPLIT) {
         const int rwg = kFwdWaves / p.gp * 32;
         const int share = bid / p.Hkv;
-        const long begin = share * p.tiles / p.shares, end = (share + 1) * p.tiles / p.shares;
+        const int begin = share * p.tiles / p.shares, end = (share + 1) * p.tiles / p.shares;
         int rb = 0, hs = 0;
-        long pos = 0;                                    // list position of (rb, hs)'s first tile
+        int pos = 0;                                     // list position of (rb, hs)'s first tile
         int nt = fwd_row_block_tiles(p, rwg, 0);
         while (pos + nt <= begin) {
             pos += nt;
@@ -514,7 +514,7 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2) void attn_fwd_bf16(AttnParams p)
         }
         bool first = true;
         while (pos < end) {
-            const int t0 = (int)max(begin - pos, 0L), t1 = (int)min(end - pos, (long)nt);
+            const int t0 = max(begin - pos, 0), t1 = min(end - pos, nt);
             // a workgroup leaves at most two pieces: the end of a row block it begins in, and the
             // beginning of the one it ends in
             const long slot = t0 == 0 && t1 == nt ? -1 : (long)bid * 2 + (t0 == 0 ? 1 : 0);
@@ -531,50 +531,72 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2) void attn_fwd_bf16(AttnParams p)
     }
 }
 
-// Merges the pieces of the row blocks that several workgroups share: a group of D/4 lanes per
-// query row, four output columns per lane.  grid (row groups of a row block, row block x subgroup, KV head).
-template <int D>
+// Merges the pieces of the row blocks that several workgroups share: a group of D/4 lanes adds up
+// pieces of one query row, four output columns per lane.  Each piece is a dependent load and an
+// exponential, so with many pieces per row (MANY: a token's row has as many as its KV head has
+// shares) all groups of a workgroup take one row together, and their sums meet in LDS: 33 pieces
+// of one row 8 us with one group, 3 us with eight.  grid (rows of a row block / rows per
+// workgroup, row block x subgroup, KV head).
+template <int D, bool MANY>
 __global__ __launch_bounds__(256) void attn_fwd_merge(AttnParams p)
 {
-    constexpr int L = D / 4;
+    constexpr int L = D / 4, GROUPS = 256 / L;
+    __shared__ f32x4 so[MANY ? GROUPS : 1][L];
+    __shared__ float2 sml[GROUPS];
     const int nsub = p.G / p.gp;
     const int rb = blockIdx.y / nsub, hs = blockIdx.y % nsub, kvh = blockIdx.z;
     const int rwg = kFwdWaves / p.gp * 32;
     // list position of the row block: rwg is a multiple of 64, so every whole row block adds rwg/64 tiles
     const int k64 = rwg / 64, base = fwd_row_block_tiles(p, rwg, 0);
     const int nt = fwd_row_block_tiles(p, rwg, rb);
-    long pos = (long)hs * nt;
-    if (rb > 0) pos += nsub * ((long)rb * base + (long)k64 * ((long)rb * (rb - 1) / 2));
+    const int pos = hs * nt + (rb > 0 ? nsub * (rb * base + k64 * (rb * (rb - 1) / 2)) : 0);
     // shares that hold a tile of [pos, pos + nt): share j holds [j*tiles/shares, (j+1)*tiles/shares)
-    const int j0 = (int)(((pos + 1) * p.shares - 1) / p.tiles), j1 = (int)(((pos + nt) * p.shares - 1) / p.tiles);
+    const unsigned T = p.tiles, S = p.shares;
+    const int j0 = (int)(((unsigned)(pos + 1) * S - 1) / T), j1 = (int)(((unsigned)(pos + nt) * S - 1) / T);
     if (j0 == j1) return;                                // finished by one workgroup
-    const int pr = blockIdx.x * (256 / L) + threadIdx.x / L;
+    const int grp = threadIdx.x / L, c4 = (threadIdx.x % L) * 4;
+    const int pr = MANY ? blockIdx.x : blockIdx.x * GROUPS + grp;
     if (pr >= p.part_rows) return;
     const int rows = p.part_rows / p.gp;
     const int row = rb * rwg + pr % rows, head = kvh * p.G + hs * p.gp + pr / rows;
     if (row >= p.Ct) return;
-    const int c4 = (threadIdx.x % L) * 4;
-    // pieces: share j0's is its end of a row block (slot 0) unless the row block begins the share,
-    // the later shares begin inside the row block (slot 0)
-    auto slot_of = [&](int j) -> long {
-        const long wg = (long)j * p.Hkv + kvh;
-        const bool begins = j == j0 && j * p.tiles / p.shares <= pos;
-        return wg * 2 + (begins ? 1 : 0);
+    // share j0's piece is the end of a row block (slot 0) unless this one begins inside the share
+    // (slot 1); the later shares begin inside this one (slot 0)
+    const bool begins = (int)((unsigned)j0 * T / S) <= pos;
+    auto piece = [&](int j) -> size_t {
+        return ((size_t)(j * p.Hkv + kvh) * 2 + (begins && j == j0 ? 1 : 0)) * p.part_rows + pr;
     };
-    float m = -INFINITY;
-#pragma unroll 8
-    for (int j = j0; j <= j1; ++j) m = fmaxf(m, p.part_ml[(size_t)slot_of(j) * p.part_rows + pr].x);
-    float l = 0.f;
+    const int first = MANY ? j0 + grp : j0, step = MANY ? GROUPS : 1;
+    float m = -INFINITY, l = 0.f;
     f32x4 o = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-    for (int j = j0; j <= j1; ++j) {
-        const size_t at = (size_t)slot_of(j) * p.part_rows + pr;
-        const float2 ml = p.part_ml[at];
-        const f32x4 x = *(const f32x4 *)(p.part_o + at * D + c4);
-        const float w = __builtin_amdgcn_exp2f(ml.x - m);    // 0 for a piece without a visible key
-        l = fmaf(w, ml.y, l);
+    auto add = [&](float pm, float pl, f32x4 x) {        // pm = -inf: a piece without a visible key
+        const float m_new = fmaxf(m, pm);
+        const float a = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - m_new);
+        const float w = m_new == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(pm - m_new);
+        m = m_new;
+        l = fmaf(l, a, w * pl);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = fmaf(w, x[e], o[e]);
+        for (int e = 0; e < 4; ++e) o[e] = fmaf(o[e], a, w * x[e]);
+    };
+    for (int j = first; j <= j1; j += 4 * step) {        // four pieces in flight
+        float2 ml[4];
+        f32x4 x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const size_t at = piece(min(j + u * step, j1));
+            ml[u] = p.part_ml[at];
+            x[u] = *(const f32x4 *)(p.part_o + at * D + c4);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (j + u * step <= j1) add(ml[u].x, ml[u].y, x[u]);
+    }
+    if constexpr (MANY) {
+        so[grp][c4 / 4] = o;
+        if (c4 == 0) sml[grp] = make_float2(m, l);
+        __syncthreads();
+        if (grp) return;
+        for (int g = 1; g < GROUPS; ++g) add(sml[g].x, sml[g].y, so[g][c4 / 4]);
     }
     const float inv = 1.0f / l;
     v2u w;
@@ -677,9 +699,19 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_score_bf16(AttnParams p)
     const int lg = lane >> 4;
 
     const int kvh = blockIdx.x % p.Hkv;
-    const int kt = blockIdx.x / p.Hkv;
+    const int nkt = (p.n + NW * WKEYS - 1) / (NW * WKEYS);
+    const int slice = p.slices - 1 - blockIdx.x / p.Hkv / nkt;
+    const int kt = blockIdx.x / p.Hkv % nkt;
     const int j_wg = kt * (NW * WKEYS);
     const int jw = j_wg + wave * WKEYS;
+
+    const int i_lo = p.Ct - p.W;                         // first observing row
+    const int i_first = max(i_lo, max(j_wg - p.M, 0));   // first row that both observes and sees j_wg
+    // query tiles of this slice: slices are counted from the first observing tile for every key block
+    const int s_lo = i_lo / QT + slice * p.slice_tiles;
+    const int qt0 = max(i_first / QT, s_lo);
+    const int ntq = min((p.Ct + QT - 1) / QT, s_lo + p.slice_tiles) - qt0;   // per head
+    if (ntq <= 0) return;                                // the whole slice lies before the diagonal
 
     const u16 *Kg = (const u16 *)p.k + (size_t)kvh * p.cap * D;
     v4u kreg[KB][KS];
@@ -696,10 +728,6 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_score_bf16(AttnParams p)
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) col[kb] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
-    const int i_lo = p.Ct - p.W;                         // first observing row
-    const int i_first = max(i_lo, max(j_wg - p.M, 0));   // first row that both observes and sees j_wg
-    const int qt0 = i_first / QT;
-    const int ntq = (p.Ct + QT - 1) / QT - qt0;          // q tiles per head (>= 1 since j_wg < n)
     const int iters = p.G * ntq;
     const float c = p.scale * kLog2e;
     const int q_frag0 = ln * QROW + 8 * lg;
@@ -831,7 +859,9 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_score_bf16(AttnParams p)
     accumulate2(sB, lsB0, lsB1);               // flush the last pending unit
 
     if (jw >= p.n) return;
-    float *dst = p.score + (size_t)kvh * p.cap;
+    const bool partial = p.slices > 1;
+    float *dst = partial ? p.part_score + ((size_t)slice * p.Hkv + kvh) * p.n : p.score + (size_t)kvh * p.cap;
+    const bool add = p.accumulate && !partial;
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
@@ -840,7 +870,121 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_score_bf16(AttnParams p)
 #pragma unroll
             for (int off = 8; off >= 1; off >>= 1) x += __shfl_xor(x, off);    // over the 16 query lanes
             const int j = jw + kb * 16 + 4 * lg + e;
-            if (ln == 0 && j < p.n) dst[j] = p.accumulate ? dst[j] + x : x;
+            if (ln == 0 && j < p.n) dst[j] = add ? dst[j] + x : x;
+        }
+}
+
+// Adds up the slices of every key, in order; slices that lie before a key block's diagonal were
+// not written.  keys: keys of one workgroup of the score pass.
+__global__ __launch_bounds__(256) void attn_score_sum(AttnParams p, int keys)
+{
+    const int j = blockIdx.x * 256 + threadIdx.x, kvh = blockIdx.y;
+    if (j >= p.n) return;
+    const int i_lo = p.Ct - p.W, i_first = max(i_lo, max(j / keys * keys - p.M, 0));
+    float x = 0.f;
+#pragma unroll 4
+    for (int s = (i_first / 64 - i_lo / 64) / p.slice_tiles; s < p.slices; ++s)
+        x += p.part_score[((size_t)s * p.Hkv + kvh) * p.n + j];
+    float *dst = p.score + (size_t)kvh * p.cap + j;
+    *dst = p.accumulate ? *dst + x : x;
+}
+
+// Score of few observing rows (a ragged last chunk, or the observation window of 128 rows): the keys
+// are read once and hardly anything is done with each, so nothing is staged.  A wave owns 16*KB
+// keys as the A operand, as above, and takes the query rows 16 at a time straight from global
+// memory (the waves of a compute unit walk the same rows, so all but the first find them in the
+// cache), two blocks ahead of their use: no LDS, no barrier, and four times as many workgroups.
+// Row blocks are counted from the first observing row, so all cache keys see the same blocks in
+// the same order (identical keys, identical scores).
+template <int D, int KB>
+__global__ __launch_bounds__(256) void attn_score_few(AttnParams p)
+{
+    constexpr int KS = D / 32;
+    constexpr int WKEYS = 16 * KB;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int ln = lane & 15, lg = lane >> 4;
+    const int kvh = blockIdx.x % p.Hkv;
+    const int jw = ((blockIdx.x / p.Hkv) * 4 + wave) * WKEYS;
+    if (jw >= p.n) return;
+
+    const u16 *Kg = (const u16 *)p.k + (size_t)kvh * p.cap * D;
+    v4u kreg[KB][KS];
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+        const u16 *src = Kg + (size_t)min(jw + kb * 16 + ln, p.n - 1) * D + 8 * lg;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) kreg[kb][ks] = *(const v4u *)(src + ks * 32);
+    }
+    f32x4 col[KB];
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) col[kb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+
+    const int i_lo = p.Ct - p.W;                         // first observing row
+    const int b0 = max(jw - p.M - i_lo, 0) / 16;         // first row block with a row that sees key jw
+    const int nb = (p.W + 15) / 16 - b0;                 // row blocks per head (>= 1 since jw < n)
+    const int iters = p.G * nb;
+    const float c = p.scale * kLog2e;
+
+    struct Block { v4u q[KS]; float lse; };
+    auto load = [&](Block &b, int it) {
+        it = min(it, iters - 1);
+        const int head = kvh * p.G + it / nb;
+        const int row = i_lo + (b0 + it % nb) * 16 + ln, r = min(row, p.Ct - 1);
+        const u16 *src = (const u16 *)p.q + (size_t)head * p.q_hs + (size_t)r * p.q_rs + 8 * lg;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) b.q[ks] = *(const v4u *)(src + ks * 32);
+        b.lse = p.lse[(size_t)head * p.Ct + r];
+    };
+    auto use = [&](const Block &b, int it) {
+        if (it >= iters) return;
+        const int r0 = i_lo + (b0 + it % nb) * 16;
+        f32x4 s[KB];
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) s[kb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) s[kb] = mfma16(kreg[kb][ks], b.q[ks], s[kb]);
+        const float ls = r0 + ln < p.Ct ? b.lse * kLog2e : INFINITY;
+        const int lim = p.M + r0 + ln - jw;              // key offset <= lim is visible
+        if (p.M + r0 >= jw + WKEYS - 1) {
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) col[kb][e] += __builtin_amdgcn_exp2f(fmaf(s[kb][e], c, -ls));
+        } else {
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float pv = __builtin_amdgcn_exp2f(fmaf(s[kb][e], c, -ls));
+                    col[kb][e] += kb * 16 + 4 * lg + e > lim ? 0.f : pv;
+                }
+        }
+    };
+    Block x, y;
+    load(x, 0);
+    load(y, 1);
+    for (int it = 0; it < iters; it += 2) {
+        Block z;
+        load(z, it + 2);
+        use(x, it);
+        x = z;
+        load(z, it + 3);
+        use(y, it + 1);
+        y = z;
+    }
+
+    float *dst = p.score + (size_t)kvh * p.cap;
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            float t = col[kb][e];
+#pragma unroll
+            for (int off = 8; off >= 1; off >>= 1) t += __shfl_xor(t, off);
+            const int j = jw + kb * 16 + 4 * lg + e;
+            if (ln == 0 && j < p.n) dst[j] = p.accumulate ? dst[j] + t : t;
         }
 }
 
@@ -860,21 +1004,28 @@ static void fwd_plan(AttnParams &p)
     if (whole > 4l * cus || p.Hkv > cus) return;         // at least four well-filled rounds
     // rwg is a multiple of 64: every row block but the last has rwg/64 tiles more than the one before
     const long first = (p.M + rwg - 1) / 64 + 1, nrb = p.n_row_blocks, longest = (p.M + p.Ct - 1) / 64 + 1;
-    p.tiles = nsub * ((nrb - 1) * first + (nrb - 1) * (nrb - 2) / 2 * (rwg / 64) + longest);
+    const long tiles = nsub * ((nrb - 1) * first + (nrb - 1) * (nrb - 2) / 2 * (rwg / 64) + longest);
     // Time of either form, in key tiles of one workgroup (one workgroup is resident per compute unit):
-    // whole row blocks run in rounds; equal shares add their partial results, about 24 tiles' time
-    // for a full slot of 256 x 128 written and read back, and a launch that merges them.
+    // whole row blocks run in rounds; equal shares add their partial results, about 28 tiles' time
+    // for full slots of 256 x 128 on every compute unit, written and read back, and a launch that
+    // merges them.  Measured, whole -> split: one token over 16640 keys (32/8 heads, head_dim 128)
+    // 290 -> 21 us; 17 rows over 4096 keys of 8 heads 70 -> 13 us; 512 rows over 8192 keys 202 -> 83
+    // us; 3001 rows over 8192 keys (24/8 heads, head_dim 64: 288 row blocks) 306 -> 214 us; 16000
+    // over 500 keys of 8 heads (504 row blocks) 537 -> 468 us; 3000 rows, no cache (16/4 heads: 188
+    // row blocks of up to 47 tiles) 83 -> 87 us, so left whole.
     const long per_head = cus / p.Hkv;
-    long shares = p.tiles / 2 < per_head ? p.tiles / 2 : per_head;
-    if (shares < 2) return;
+    const long shares = tiles / 2 < per_head ? tiles / 2 : per_head;
+    if (shares < 2 || tiles * (shares + 1) >= (1l << 31)) return;
     const double rounds = (double)((whole + cus - 1) / cus);
-    const double t_whole = whole <= cus ? (double)longest : rounds * (double)p.tiles * p.Hkv / (double)whole;
+    const double t_whole = whole <= cus ? (double)longest : rounds * (double)tiles * p.Hkv / (double)whole;
     const double slot = p.part_rows * p.D / (256.0 * 128.0), busy = (double)shares * p.Hkv / cus;
-    const double t_split = (double)p.tiles / shares + 4.0 + slot * (4.0 + 20.0 * busy);
-    if (t_split < t_whole) p.shares = (int)shares;
+    const double t_split = (double)tiles / shares + 4.0 + slot * (4.0 + 24.0 * busy);
+    if (t_split >= t_whole) return;
+    p.shares = (int)shares;
+    p.tiles = (int)tiles;
 }
 
-size_t attend_bf16_split_bytes(AttnParams p)
+static size_t fwd_split_bytes(AttnParams p)
 {
     fwd_plan(p);
     return (size_t)p.shares * p.Hkv * 2 * p.part_rows * (p.D * sizeof(float) + sizeof(float2));
@@ -905,24 +1056,112 @@ static hipError_t launch_fwd(AttnParams p, void *part, size_t part_bytes, hipStr
 {
     fwd_plan(p);
     const int nsub = p.G / p.gp;
-    if (!p.shares || !part || part_bytes < attend_bf16_split_bytes(p))
+    if (!p.shares || !part || part_bytes < fwd_split_bytes(p))
         return launch_fwd_form<D, false>(p, p.Hkv * nsub * p.n_row_blocks, st);
     p.part_o = (float *)part;
     p.part_ml = (float2 *)(p.part_o + (size_t)p.shares * p.Hkv * 2 * p.part_rows * D);
     hipError_t e = launch_fwd_form<D, true>(p, p.shares * p.Hkv, st);
     if (e != hipSuccess) return e;
-    const dim3 grid((p.part_rows * (D / 4) + 255) / 256, p.n_row_blocks * nsub, p.Hkv);
-    hipLaunchKernelGGL(attn_fwd_merge<D>, grid, dim3(256), 0, st, p);
+    // pieces of the longest row block: two or three where row blocks are many, a head's shares for a token
+    const long pieces = ((long)((p.M + p.Ct - 1) / 64 + 1) * p.shares) / p.tiles + 1;
+    const int groups = 256 / (D / 4);
+    if (pieces > 6) {
+        const dim3 grid(p.part_rows, p.n_row_blocks * nsub, p.Hkv);
+        hipLaunchKernelGGL((attn_fwd_merge<D, true>), grid, dim3(256), 0, st, p);
+    } else {
+        const dim3 grid((p.part_rows + groups - 1) / groups, p.n_row_blocks * nsub, p.Hkv);
+        hipLaunchKernelGGL((attn_fwd_merge<D, false>), grid, dim3(256), 0, st, p);
+    }
     return hipGetLastError();
 }
 
-template <int D, int KB, int NW>
-static hipError_t launch_score(AttnParams p, hipStream_t st)
+// How the score pass of a problem is cut into workgroups: waves per workgroup (returned), slices and
+// slice_tiles.  Time is estimated in query tiles that a compute unit takes against 512 keys (2.1 us
+// at head_dim 128); at most two workgroups of four waves or one of eight are resident on it.
+//   - Eight waves, uncut: the fewest Q bytes per key, the best form where its workgroups fill the chip
+//     evenly.  Keys of the cache (and of the chunk before the window) cost the same each; those of
+//     the window itself are triangular and fill up what the others leave.
+//   - Four waves, cut: half the keys and 1/slices of the rows per workgroup, at the price of a start-up
+//     of about 1.5 tiles each and of a launch that adds the slices up (2 tiles).
+// Measured with 32/8 heads, head_dim 128: 8192 rows over 8192 keys 974 -> 828 us with 8 slices (256
+// uncut workgroups, half of them triangular); 512 rows over 8192 keys 77 -> 63 us with 4; 32768
+// over 32768 12.1 ms uncut, 12.3 ms in 4 or 8 slices; 700 over 30000 207 us uncut, 223 us in 4;
+// 128 rows over 8192 keys 23 us uncut, 28 us with four waves.
+static int score_plan(AttnParams &p)
 {
-    const int keys_wg = NW * 16 * KB;
-    const int grid = p.Hkv * ((p.n + keys_wg - 1) / keys_wg);
+    const int cus = device_compute_units() > 0 ? device_compute_units() : 256;
+    const int tiles = (p.Ct + 63) / 64 - (p.Ct - p.W) / 64;
+    const double iters = (double)p.G * tiles;
+    const long full = (long)p.Hkv * ((p.n - p.W + 511) / 512), all = (long)p.Hkv * ((p.n + 511) / 512);
+    const double total = (full + 0.5 * (double)(all - full)) * iters / cus;       // per compute unit
+    const double rounds = (double)((full + cus - 1) / cus) * iters;
+    double best = rounds > total ? rounds : total;
+    if (best < iters) best = iters;
+    int waves = 8;
+    p.slices = 1;
+    p.slice_tiles = tiles;
+    for (int want = 1; want <= 16; want *= 2) {
+        const int per = (tiles + want - 1) / want, slices = (tiles + per - 1) / per;
+        const double item = (double)p.G * per, items = 2.0 * total * cus / item;
+        double t = total + 0.5 * item;
+        if (t < item) t = item;
+        t += 1.5 * items / (2.0 * cus) + (slices > 1 ? 2.0 : 0.0);
+        if (t < best) { best = t; waves = 4; p.slices = slices; p.slice_tiles = per; }
+    }
+    return waves;
+}
+
+// Few observing rows over not too many keys: the register-only form.  Its waves fetch every query
+// row themselves, so it loses its lead as rows or waves grow: 17 rows over 4113 keys of 8 heads
+// 10 -> 6 us, 4 x 32 rows over 4128 keys 16.5 -> 12.3 us, 64 rows over 16064 keys 12 -> 18 us.
+static bool score_few(const AttnParams &p)
+{
+    const long blocks = (long)p.G * ((p.W + 15) / 16);
+    return blocks <= 2 || (blocks <= 8 && (long)p.Hkv * p.n <= 65536);
+}
+
+template <int D, int NW>
+static hipError_t launch_score_tiled(const AttnParams &p, hipStream_t st)
+{
+    constexpr int KB = 4, keys_wg = NW * 16 * KB;
+    const int grid = p.Hkv * ((p.n + keys_wg - 1) / keys_wg) * p.slices;
     hipLaunchKernelGGL((attn_score_bf16<D, KB, NW>), dim3(grid), dim3(NW * 64), 0, st, p);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || p.slices == 1) return e;
+    hipLaunchKernelGGL(attn_score_sum, dim3((p.n + 255) / 256, p.Hkv), dim3(256), 0, st, p, keys_wg);
     return hipGetLastError();
+}
+
+template <int D>
+static hipError_t launch_score(AttnParams p, void *part, size_t part_bytes, hipStream_t st)
+{
+    if (score_few(p)) {
+        constexpr int KB = 2;
+        const int grid = p.Hkv * ((p.n + 64 * KB - 1) / (64 * KB));
+        hipLaunchKernelGGL((attn_score_few<D, KB>), dim3(grid), dim3(256), 0, st, p);
+        return hipGetLastError();
+    }
+    int waves = score_plan(p);
+    if (p.slices > 1 && (!part || part_bytes < (size_t)p.slices * p.Hkv * p.n * sizeof(float))) {
+        p.slice_tiles *= p.slices;                       // no room for partial sums: uncut
+        p.slices = 1;
+        waves = 8;
+    }
+    p.part_score = (float *)part;
+    return waves == 8 ? launch_score_tiled<D, 8>(p, st) : launch_score_tiled<D, 4>(p, st);
+}
+
+// Scratch of either pass (they run one after the other and share it).
+size_t attend_bf16_scratch_bytes(const AttnParams &sizes)
+{
+    AttnParams p = sizes;
+    size_t score = 0;
+    if (!score_few(p)) {
+        score_plan(p);
+        if (p.slices > 1) score = (size_t)p.slices * p.Hkv * p.n * sizeof(float);
+    }
+    const size_t fwd = fwd_split_bytes(sizes);
+    return fwd > score ? fwd : score;
 }
 
 hipError_t attend_bf16_forward(const AttnParams &p, void *part, size_t part_bytes, hipStream_t st)
@@ -931,10 +1170,10 @@ hipError_t attend_bf16_forward(const AttnParams &p, void *part, size_t part_byte
     return launch_fwd<64>(p, part, part_bytes, st);
 }
 
-hipError_t attend_bf16_score(const AttnParams &p, hipStream_t st)
+hipError_t attend_bf16_score(const AttnParams &p, void *part, size_t part_bytes, hipStream_t st)
 {
-    if (p.D == 128) return launch_score<128, 4, 8>(p, st);
-    return launch_score<64, 4, 4>(p, st);
+    if (p.D == 128) return launch_score<128>(p, part, part_bytes, st);
+    return launch_score<64>(p, part, part_bytes, st);
 }
 
 }  // namespace reform

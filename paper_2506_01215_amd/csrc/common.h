@@ -32,10 +32,13 @@ struct AttnParams {
     int n_row_blocks;
     // forward pass with the key range split over workgroups (see attn_fwd_bf16); shares == 0: whole
     int shares;      // workgroups per KV head, each an equal share of the head's key tiles
-    long tiles;      // key tiles of one KV head, over its row blocks and head subgroups
+    int tiles;       // key tiles of one KV head, over its row blocks and head subgroups (tiles * shares < 2^31)
     int part_rows;   // query rows (heads x chunk rows) of one partial result
     float *part_o;   // [workgroup][2][part_rows][D] unnormalised outputs
     float2 *part_ml; // [workgroup][2][part_rows] reference maximum (log2 units) and running sum
+    // score pass with the observing rows cut into slices (see attn_score_bf16)
+    int slices, slice_tiles;   // number of slices (1: uncut), query tiles of 64 rows in each
+    float *part_score;         // [slice][KV head][n] column sums of one slice, when there are several
 };
 
 #ifndef RF_MOVE_TILE

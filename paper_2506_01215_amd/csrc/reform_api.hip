@@ -9,8 +9,8 @@
 
 namespace reform {
 hipError_t attend_bf16_forward(const AttnParams &p, void *part, size_t part_bytes, hipStream_t st);
-size_t attend_bf16_split_bytes(AttnParams p);
-hipError_t attend_bf16_score(const AttnParams &p, hipStream_t st);
+size_t attend_bf16_scratch_bytes(const AttnParams &sizes);
+hipError_t attend_bf16_score(const AttnParams &p, void *part, size_t part_bytes, hipStream_t st);
 hipError_t attend_f32_forward(const AttnParams &p, hipStream_t st);
 hipError_t attend_f32_score(const AttnParams &p, hipStream_t st);
 
@@ -227,7 +227,7 @@ size_t reform_chunk_attend_score_workspace(const reform_attn_desc *d)
 {
     if (check_attn(d) != REFORM_OK) return 0;
     size_t bytes = attn_lse_bytes(d);
-    if (d->dtype == REFORM_BF16) bytes += align_up(attend_bf16_split_bytes(attn_sizes(d)));
+    if (d->dtype == REFORM_BF16) bytes += align_up(attend_bf16_scratch_bytes(attn_sizes(d)));
     return bytes;
 }
 
@@ -252,7 +252,7 @@ reform_status reform_chunk_attend_score(const reform_attn_desc *d, const void *q
     hipError_t e = hipSuccess;
     if (d->dtype == REFORM_BF16) {
         if (do_attn) e = attend_bf16_forward(p, part, part_bytes, st);
-        if (e == hipSuccess && do_score) e = attend_bf16_score(p, st);
+        if (e == hipSuccess && do_score) e = attend_bf16_score(p, part, part_bytes, st);
     } else {
         if (do_attn) e = attend_f32_forward(p, st);
         if (e == hipSuccess && do_score) e = attend_f32_score(p, st);

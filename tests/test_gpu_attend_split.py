@@ -1,7 +1,12 @@
-"""Forward attention with the key range split over workgroups (few row blocks, or a last round of
+"""Attention of problems too small or too uneven for one workgroup per row block or key block.
+
+Forward attention with the key range split over workgroups (few row blocks, or a last round of
 workgroups that would be nearly empty), against the fp64 oracle: ranges cut inside the causal
 diagonal, row blocks shared by many workgroups or by two, heads and chunk ends that leave a
-workgroup partly idle; and the same call with a workspace too small for the partial results."""
+workgroup partly idle; and the same call with a workspace too small for the partial results.
+
+The eviction score with the observing rows cut into slices, and its form for few rows: windows that
+begin inside a query tile, key blocks on the diagonal, accumulation, identical keys."""
 import math
 
 import pytest
@@ -58,10 +63,47 @@ def test_split_forward_matches_oracle(shape):
     assert torch.equal(results[0][0], results[1][0]) and torch.equal(results[0][1], results[1][1])
 
 
+@pytest.mark.parametrize("shape", [
+    (16, 4, 128, 100, 700, 0),      # slices of one tile, the last of 60 rows
+    (2, 2, 64, 0, 1500, 0),         # every key block on the diagonal
+    (8, 2, 128, 1000, 600, 301),    # window begins inside a tile
+    (4, 4, 128, 515, 2048, 2048),
+    (8, 8, 128, 300, 17, 0),        # few rows: two row blocks, the second of one row
+    (3, 1, 64, 5, 20, 9),           # few rows, fewer keys than a workgroup holds
+    (16, 2, 64, 700, 1, 0),         # eight row blocks of one row
+], ids=lambda s: "x".join(map(str, s)))
+def test_score_slices_match_oracle(shape):
+    Hq, Hkv, d, M, Ct, W = shape
+    q, k, v = inputs(Hq, Hkv, d, M, Ct, seed=3 + M + Ct)
+    if M > 10:
+        k[:, 9] = k[:, 2]
+        k[:, M - 1] = k[:, 2]
+    scale = 1.0 / math.sqrt(d)
+    n = M + Ct
+    _, _, s_ref = oracle.attend_score(to_np(q), to_np(k), to_np(v), M, scale, W=W)
+    need = binding.attend_workspace_bytes(binding.attn_desc(q, k, q, M, scale, W))
+    for nbytes in (need, (Hq * Ct * 4 + 255) // 256 * 256):
+        ws = torch.full((nbytes + 256,), 0xff, dtype=torch.uint8, device=DEV)
+        _, _, score = binding.reform_chunk_attend_score(q, k, v, M, scale, obs_window=W, workspace=ws)
+        twice = score.clone()
+        binding.reform_chunk_attend_score(q, k, v, M, scale, obs_window=W, workspace=ws, score=twice, accumulate=True)
+        torch.cuda.synchronize()
+        # rtol 1e-5: logits and sums are fp32 (the wider bf16 bound concerns P and the output)
+        assert_scores_close(to_np(score)[:, :n], s_ref[:, :n], 1e-5, "score")
+        assert torch.equal(twice[:, :n], 2 * score[:, :n])
+        assert not score[:, n:].any()
+        if M > 10:
+            assert torch.equal(score[:, 2], score[:, 9]) and torch.equal(score[:, 2], score[:, M - 1])
+
+
 def test_the_shapes_split():
-    """Every shape but the two-tile one asks for more workspace than the lse rows."""
+    """Every shape but the two-tile one asks for more workspace than the lse rows, and so do the
+    score shapes that are cut into slices."""
     for Hq, Hkv, d, M, Ct, W in SHAPES:
         q, k, _ = inputs(Hq, Hkv, d, M, Ct, seed=1)
         need = binding.attend_workspace_bytes(binding.attn_desc(q, k, q, M, 0.1, W))
         whole = (Hq * Ct * 4 + 255) // 256 * 256
         assert (need > whole) == (M + Ct > 128), (Hq, Hkv, d, M, Ct, need, whole)
+    for Hq, Hkv, d, M, Ct, W in [(16, 4, 128, 100, 700, 0), (2, 2, 64, 0, 1500, 0), (8, 2, 128, 1000, 600, 301)]:
+        q, k, _ = inputs(Hq, Hkv, d, M, Ct, seed=1)
+        assert binding.attend_workspace_bytes(binding.attn_desc(q, k, q, M, 0.1, W)) > (Hq * Ct * 4 + 255) // 256 * 256
