@@ -1,9 +1,11 @@
 // fp32 chunk attention + eviction score (Sec. 3.1 / Fig. 1 step 1 of arXiv 2506.01215).
 //
-// The fp32 configuration is the small verification workload; gfx950 has no fast fp32 matrix
-// path worth tiling for it, so these kernels favour a short, exact formulation: one wave per
-// attention row (two passes: row maximum, then probabilities and P.V), and one wave per key for
-// the column sums.  Accurate expf/logf, fixed summation order, no atomics.
+// The fp32 configuration is the small verification workload: few rows, a few hundred keys, so what
+// bounds it is latency, not arithmetic.  head_dim 32, 64 and 128 run on v_mfma_f32_16x16x4f32 (fp32
+// operands and sums) with a row block's keys spread over the waves of a workgroup; any other
+// head_dim takes the short formulation with one wave per attention row (two passes: row maximum,
+// then probabilities and P.V) and one wave per key for the column sums.  Accurate expf/logf,
+// fixed summation order, no atomics.
 #include "common.h"
 
 namespace reform {
@@ -105,14 +107,254 @@ __global__ __launch_bounds__(64) void attn_score_f32(AttnParams p)
     }
 }
 
+// ------------------------------------------------------------------------------------------
+// Matrix-core forms.  v_mfma_f32_16x16x4f32: A[m][k] lane l holds m = l%16, k = l/16; B[k][n]: n = l%16,
+// k = l/16; C[m][n]: n = l%16, m = 4*(l/16) + e.  As in the bf16 kernels the transposed tile
+// S^T = K Q^T is formed, so a lane owns one query (ln) and the keys 4*lg + e of a 16-key block, and
+// its probabilities are the B operands of O^T = V^T P^T as they stand (k-step e contracts the
+// keys 4*lg + e).  Contraction and output order are free, so they are permuted to make every
+// global load 16 bytes: k-step (j, i) of Q.K contracts the dims 16*j + 4*lg + i, and row m of
+// output block db is dim D/16 * m + db.
+template <int D>
+__device__ __forceinline__ void f32_load_row(float (&dst)[D / 4], const float *row, int lg)
+{
+#pragma unroll
+    for (int j = 0; j < D / 16; ++j) *(f32x4 *)&dst[4 * j] = *(const f32x4 *)(row + 16 * j + 4 * lg);
+}
+
+template <int D>
+__device__ __forceinline__ f32x4 f32_logits(const float (&a)[D / 4], const float (&b)[D / 4])
+{
+    f32x4 s[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};    // two chains: an MFMA waits for its addend
+#pragma unroll
+    for (int i = 0; i < D / 4; ++i) s[i & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[i], s[i & 1], 0, 0, 0);
+    return s[0] + s[1];
+}
+
+// Forward.  A workgroup owns 16 rows of one head; its NW waves take the 16-key blocks in turn, each
+// with a running maximum of its own, and meet in LDS once at the end.  With one wave per row the
+// keys of a row were a chain of dependent steps: 4 heads, 128 rows over 384 keys, head_dim 64
+// 81 -> 7 us.
+constexpr int kF32FwdWaves = 8;
+
+template <int D>
+__global__ __launch_bounds__(kF32FwdWaves * 64) void attn_fwd_f32_mfma(AttnParams p)
+{
+    constexpr int NW = kF32FwdWaves, DB = D / 16, PITCH = D + 4;
+    __shared__ __attribute__((aligned(16))) float so[NW / 2][16][PITCH];
+    __shared__ float sm[NW][16], sl[NW][16];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int ln = lane & 15, lg = lane >> 4;
+    const int nrb = (p.Ct + 15) / 16;
+    const int h = blockIdx.x % p.Hq, i0 = (nrb - 1 - blockIdx.x / p.Hq) * 16;   // late row blocks first
+    const int g = h / p.G;
+    const float *K = (const float *)p.k + (size_t)g * p.cap * D;
+    const float *V = (const float *)p.v + (size_t)g * p.cap * D;
+    const int lim = p.M + i0 + ln;                       // last key this lane's row sees
+    const int nblk = (p.M + min(i0 + 16, p.Ct) - 1) / 16 + 1;
+
+    float q[D / 4], k[D / 4], v[4][DB];
+    auto load_v = [&](int b) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float *src = V + (size_t)min(b * 16 + 4 * lg + e, p.n - 1) * D + DB * ln;
+            if constexpr (DB % 4 == 0) {
+#pragma unroll
+                for (int c = 0; c < DB; c += 4) *(f32x4 *)&v[e][c] = *(const f32x4 *)(src + c);
+            } else {
+                *(float2 *)&v[e][0] = *(const float2 *)src;
+            }
+        }
+    };
+    auto key_row = [&](int b) { return K + (size_t)min(b * 16 + ln, p.n - 1) * D; };
+    f32_load_row<D>(q, (const float *)p.q + (size_t)h * p.q_hs + (size_t)min(i0 + ln, p.Ct - 1) * p.q_rs, lg);
+    f32_load_row<D>(k, key_row(wave), lg);
+    load_v(wave);
+
+    f32x4 o[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db) o[db] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    float m = -INFINITY, l = 0.f;
+    for (int b = wave; b < nblk; b += NW) {
+        const int j0 = b * 16;
+        f32x4 s = f32_logits<D>(k, q);
+        f32_load_row<D>(k, key_row(b + NW), lg);         // past the end: the last key again
+        float x[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = j0 + 4 * lg + e > lim ? -INFINITY : p.scale * s[e];
+        float mx = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
+        mx = fmaxf(mx, __shfl_xor(mx, 16));
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float m_new = fmaxf(m, mx);
+        if (m_new != -INFINITY) {                        // else: the row sees no key of this wave yet
+            const float alpha = expf(m - m_new);
+            m = m_new;
+            l *= alpha;
+#pragma unroll
+            for (int db = 0; db < DB; ++db) o[db] *= alpha;
+        }
+        float pr[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            pr[e] = x[e] == -INFINITY ? 0.f : expf(x[e] - m);
+            l += pr[e];
+        }
+        bool finite = true;
+        if (j0 + 15 > p.M + i0) {                        // some row does not see some key of the block:
+#pragma unroll
+            for (int e = 0; e < 4; ++e)                  // 0 * inf must not reach its sum
+#pragma unroll
+                for (int c = 0; c < DB; ++c) finite = finite && __builtin_isfinite(v[e][c]);
+        }
+        if (__all(finite)) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int db = 0; db < DB; ++db)
+                    o[db] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[e][db], pr[e], o[db], 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                for (int u = 0; u < 4; ++u) {
+                    const float w = __shfl(pr[e], ln + 16 * u);
+                    const int j = j0 + 4 * u + e;
+                    if (j > lim || j >= p.n) continue;
+#pragma unroll
+                    for (int db = 0; db < DB; ++db)
+#pragma unroll
+                        for (int c = 0; c < 4; ++c)
+                            o[db][c] = fmaf(w, V[(size_t)j * D + DB * (4 * lg + c) + db], o[db][c]);
+                }
+        }
+        load_v(b + NW);
+    }
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    if (lg == 0) { sm[wave][ln] = m; sl[wave][ln] = l; }
+    __syncthreads();
+    float m_tot = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) m_tot = fmaxf(m_tot, sm[w][ln]);
+    const float f = m == -INFINITY ? 0.f : expf(m - m_tot);
+#pragma unroll
+    for (int db = 0; db < DB; ++db) o[db] *= f;
+    // the upper half of the waves hands its sums to the lower half, and that to the output
+    float *mine = &so[wave % (NW / 2)][ln][DB * 4 * lg];
+    if (wave >= NW / 2) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int db = 0; db < DB; ++db) mine[DB * c + db] = o[db][c];
+    }
+    __syncthreads();
+    if (wave < NW / 2) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int db = 0; db < DB; ++db) mine[DB * c + db] += o[db][c];
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < 16 * D; t += NW * 64) {
+        const int r = t / D, c = t % D;
+        if (i0 + r >= p.Ct) break;
+        float mt = -INFINITY, lt = 0.f, x = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) mt = fmaxf(mt, sm[w][r]);
+#pragma unroll
+        for (int w = 0; w < NW; ++w) lt += sm[w][r] == -INFINITY ? 0.f : sl[w][r] * expf(sm[w][r] - mt);
+#pragma unroll
+        for (int w = 0; w < NW / 2; ++w) x += so[w][r][c];
+        ((float *)p.out)[(size_t)h * p.o_hs + (size_t)(i0 + r) * p.o_rs + c] = x / lt;
+        if (c == 0) p.lse[(size_t)h * p.Ct + i0 + r] = mt + logf(lt);
+    }
+}
+
+// Score.  A workgroup owns 16 keys of one KV head as the A operand; its waves take the (head, 16-row
+// block) items of the observing rows in turn and add up their columns in wave order.  Row blocks
+// are counted from the first observing row, so all cache keys see the same items in the same
+// order (identical keys, identical scores).  4 heads, 128 rows over 384 keys 7.8 -> 4 us.
+constexpr int kF32ScoreWaves = 8;
+
+template <int D>
+__global__ __launch_bounds__(kF32ScoreWaves * 64) void attn_score_f32_mfma(AttnParams p)
+{
+    constexpr int NW = kF32ScoreWaves;
+    __shared__ float part[NW][16];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int ln = lane & 15, lg = lane >> 4;
+    const int g = blockIdx.x % p.Hkv, j0 = blockIdx.x / p.Hkv * 16;
+    float k[D / 4], q[D / 4];
+    f32_load_row<D>(k, (const float *)p.k + ((size_t)g * p.cap + min(j0 + ln, p.n - 1)) * D, lg);
+    const int i_first = max(p.Ct - p.W, max(j0 - p.M, 0));     // first row that observes and sees key j0
+    const int nb = (p.Ct - i_first + 15) / 16;                 // row blocks per head (>= 1 since j0 < n)
+    const int items = p.G * nb;
+    float lse = 0.f;
+    auto load_q = [&](int it) {
+        it = min(it, items - 1);
+        const int h = g * p.G + it / nb, i = min(i_first + it % nb * 16 + ln, p.Ct - 1);
+        f32_load_row<D>(q, (const float *)p.q + (size_t)h * p.q_hs + (size_t)i * p.q_rs, lg);
+        lse = p.lse[(size_t)h * p.Ct + i];
+    };
+    load_q(wave);
+    f32x4 col = {0.f, 0.f, 0.f, 0.f};
+    for (int it = wave; it < items; it += NW) {
+        const int i = i_first + it % nb * 16 + ln, lim = i < p.Ct ? p.M + i : -1;
+        const f32x4 s = f32_logits<D>(k, q);
+        const float ls = lse;
+        load_q(it + NW);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float pv = expf(p.scale * s[e] - ls);
+            col[e] += j0 + 4 * lg + e > lim ? 0.f : pv;
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        float x = col[e];
+#pragma unroll
+        for (int off = 8; off >= 1; off >>= 1) x += __shfl_xor(x, off);
+        if (ln == 0) part[wave][4 * lg + e] = x;
+    }
+    __syncthreads();
+    const int j = j0 + threadIdx.x;
+    if (threadIdx.x >= 16 || j >= p.n) return;
+    float x = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) x += part[w][threadIdx.x];
+    float *dst = p.score + (size_t)g * p.cap + j;
+    *dst = p.accumulate ? *dst + x : x;
+}
+
+template <int D>
+static hipError_t launch_fwd_f32(const AttnParams &p, hipStream_t st)
+{
+    const unsigned grid = (unsigned)p.Hq * ((p.Ct + 15) / 16);
+    hipLaunchKernelGGL(attn_fwd_f32_mfma<D>, dim3(grid), dim3(kF32FwdWaves * 64), 0, st, p);
+    return hipGetLastError();
+}
+
+template <int D>
+static hipError_t launch_score_f32(const AttnParams &p, hipStream_t st)
+{
+    const unsigned grid = (unsigned)p.Hkv * ((p.n + 15) / 16);
+    hipLaunchKernelGGL(attn_score_f32_mfma<D>, dim3(grid), dim3(kF32ScoreWaves * 64), 0, st, p);
+    return hipGetLastError();
+}
+
 hipError_t attend_f32_forward(const AttnParams &p, hipStream_t st)
 {
+    if (p.D == 32) return launch_fwd_f32<32>(p, st);
+    if (p.D == 64) return launch_fwd_f32<64>(p, st);
+    if (p.D == 128) return launch_fwd_f32<128>(p, st);
     hipLaunchKernelGGL(attn_fwd_f32, dim3((unsigned)p.Hq * p.Ct), dim3(64), 0, st, p);
     return hipGetLastError();
 }
 
 hipError_t attend_f32_score(const AttnParams &p, hipStream_t st)
 {
+    if (p.D == 32) return launch_score_f32<32>(p, st);
+    if (p.D == 64) return launch_score_f32<64>(p, st);
+    if (p.D == 128) return launch_score_f32<128>(p, st);
     hipLaunchKernelGGL(attn_score_f32, dim3((unsigned)p.Hkv * p.n), dim3(64), 0, st, p);
     return hipGetLastError();
 }
