@@ -120,11 +120,11 @@ struct EmbedParams {
 };
 
 struct PoolParams {
-    const float *sim;    // [nq][ld]
+    const float *best;   // [N] largest similarity over the query tokens
     float *pooled;       // [N]
     SelParams sel;       // budget selection over pooled (one row)
-    long N, ld;
-    int nq, window;      // window odd, <= the kernel's maximum
+    long N;
+    int window;          // odd, <= the kernel's maximum
 };
 
 struct GatherParams {
@@ -142,7 +142,7 @@ struct GatherParams {
     int D, nq, k, radius, n_head, n_tail;
     int nwords;          // bitmap words
     float eps;
-    int q0, nq_grp;      // query group handled by this similarity launch
+    int q0, nq_grp;      // first query and number of queries of this similarity launch
 };
 
 // Compute units of the current device (reform_api.hip; cached per device, 0 if it cannot be told).

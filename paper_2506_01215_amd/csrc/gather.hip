@@ -2,10 +2,10 @@
 // of arXiv 2506.01215): cosine similarity of query embeddings with every context embedding,
 // per-query top-k with lowest-index ties, union with a +-radius neighbourhood, sorted unique.
 //
-//   sim_bf16_mfma   streams the [N][D] bf16 store once; 16 rows x up to 16 queries per
-//                   v_mfma_f32_16x16x32_bf16; the row norms come from a second MFMA of the row
+//   sim_bf16_mfma   streams the [N][D] bf16 store once for up to 64 queries; 16 rows x 16 queries
+//                   per v_mfma_f32_16x16x32_bf16; the row norms come from a second MFMA of the row
 //                   tile with itself (Gram diagonal), so the VALU does no per-element work and
-//                   the kernel stays HBM-bound for 16 queries.
+//                   the kernel stays HBM-bound.
 //   sim_generic     fp32 (or odd-shaped bf16) inputs: one wave per row, fp32 FMA.
 //   select_topk     (select.hip) 3-pass radix select of the k-th largest per query, then an
 //                   ordered two-kernel compaction.
@@ -25,7 +25,18 @@ hipError_t select_topk(const SelParams &p, hipStream_t st);
 // The kernel is a pure HBM stream (1 flop/byte for the dot products of one query, 16 for 16), so
 // what matters is bytes in flight: 8 waves per workgroup share one LDS copy of the queries, and
 // every wave keeps two chunks of kChunk 16-byte loads per lane outstanding (2 x 8 KB per wave,
-// about 260 KB per CU) while the MFMAs of the previous chunk run.
+// 128 KB per CU: the prefetch registers leave room for one workgroup) while the MFMAs of the
+// previous chunk run.  128 registers, so that two workgroups or sixteen waves fit, spill: 37
+// queries over 262144 x 1024 167 -> 257 and 219 us.
+//
+// NG: blocks of 16 queries that share the pass, as many as fit the LDS (up to 4).  A store row costs
+// its HBM time once for all of them; they add one LDS read and one MFMA per 16 x 32 tile each, which
+// at NG = 4 is still less than half of either unit's time.  37 queries over 262144 x 1024: three passes
+// of 108 us -> one of 119 us; with everything behind it the call takes 407 -> 167 us.
+//
+// MAX: the pooled gather only needs the maximum over the queries, so the row's largest similarity is
+// stored instead of all of them (one value per row, the maximum with what an earlier pass over
+// further queries left there): 39 MB less written and read back in that example.
 constexpr int kSimThreads = 512;
 constexpr int kChunk = 8;            // MFMA k-steps (of 32 elements) per prefetch chunk
 
@@ -37,42 +48,40 @@ __device__ __forceinline__ int sim_qrow(int D)   // LDS row pitch in elements: p
 
 // FULL: dim is a multiple of 32 * kChunk, so every prefetch chunk is whole and the loads and MFMAs of
 // a loop trip are unconditional (the compiler can then count the loads in flight exactly).
-template <bool FULL>
+template <bool FULL, int NG, bool MAX>
 __global__ __launch_bounds__(kSimThreads) void sim_bf16_mfma(GatherParams p)
 {
-    extern __shared__ __attribute__((aligned(16))) u16 qs[];   // [16][QROW]
-    __shared__ float qnorm[16];
+    extern __shared__ __attribute__((aligned(16))) u16 qs[];   // [16 * NG][QROW]
+    __shared__ float qnorm[16 * NG];
     const int D = p.D, QROW = sim_qrow(D);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int ln = lane & 15, lg = lane >> 4;
     if (p.sel.pre_zeroed && p.q0 == 0)        // the selection that follows finds its histograms cleared
         sel_clear(p.sel, (long)blockIdx.x * kSimThreads + tid, (long)gridDim.x * kSimThreads);
 
-    // stage the (up to 16) queries of this group, zero-padded, and their norms
+    // stage the queries of this pass, zero-padded, and their norms
     const u16 *Q = (const u16 *)p.qry + (size_t)p.q0 * D;
-    for (int idx = tid; idx < 16 * (D / 8); idx += kSimThreads) {
+    for (int idx = tid; idx < 16 * NG * (D / 8); idx += kSimThreads) {
         const int r = idx / (D / 8), c8 = idx % (D / 8);
         v4u v = {0u, 0u, 0u, 0u};
         if (r < p.nq_grp) v = *(const v4u *)(Q + (size_t)r * D + c8 * 8);
         *(v4u *)(qs + r * QROW + c8 * 8) = v;
     }
     __syncthreads();
-    {
-        // two queries per wave, 64 lanes per query, fixed order
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int qi = 2 * wave + h;
-            float s = 0.f;
-            for (int c = lane; c < D; c += 64) {
-                const float x = bf16_bits_to_f32(qs[qi * QROW + c]);
-                s = fmaf(x, x, s);
-            }
-            s = wave_sum(s);
-            if (lane == 0) qnorm[qi] = sqrtf(s);
+    // 64 lanes per query, fixed order
+    for (int qi = wave; qi < 16 * NG; qi += kSimThreads / 64) {
+        float s = 0.f;
+        for (int c = lane; c < D; c += 64) {
+            const float x = bf16_bits_to_f32(qs[qi * QROW + c]);
+            s = fmaf(x, x, s);
         }
+        s = wave_sum(s);
+        if (lane == 0) qnorm[qi] = sqrtf(s);
     }
     __syncthreads();
-    const float un = qnorm[ln];
+    float un[NG];
+#pragma unroll
+    for (int y = 0; y < NG; ++y) un[y] = qnorm[16 * y + ln];
 
     const long ngroups_all = (p.N + 15) / 16;
     // A workgroup streams one contiguous range of row groups (its eight waves interleaved group
@@ -129,8 +138,12 @@ __global__ __launch_bounds__(kSimThreads) void sim_bf16_mfma(GatherParams p)
     };
     load_next(cur);
     load_next(nx1);
-    f32x4 dot = {0.f, 0.f, 0.f, 0.f}, gram = {0.f, 0.f, 0.f, 0.f};
-    float held[4] = {0.f, 0.f, 0.f, 0.f};
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    f32x4 dot[NG], gram = zero;
+#pragma unroll
+    for (int y = 0; y < NG; ++y) dot[y] = zero;
+    constexpr int NOUT = MAX ? 1 : NG;                     // result quads of a group of rows
+    f32x4 held[NOUT];
     int ch = 0;                        // compute cursor
     while (grp < ngroups) {
         load_next(nx2);
@@ -140,8 +153,11 @@ __global__ __launch_bounds__(kSimThreads) void sim_bf16_mfma(GatherParams p)
             const int ks = ch * kChunk + i;
             if (FULL || ks < nks) {
                 const bf16x8 a = as_bf16x8(cur[i]);
-                const bf16x8 b = as_bf16x8(*(const v4u *)(qsrc + ks * 32));
-                dot = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, dot, 0, 0, 0);
+#pragma unroll
+                for (int y = 0; y < NG; ++y) {
+                    const bf16x8 b = as_bf16x8(*(const v4u *)(qsrc + 16 * y * QROW + ks * 32));
+                    dot[y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, dot[y], 0, 0, 0);
+                }
                 gram = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, a, gram, 0, 0, 0);
             }
         }
@@ -150,38 +166,60 @@ __global__ __launch_bounds__(kSimThreads) void sim_bf16_mfma(GatherParams p)
             // accumulator element r%4.  Lane (ln, lg) needs rows 4*lg + e.
             const long row0 = grp * 16;
             const float diag = (ln >> 2) == lg ? gram[ln & 3] : 0.f;
-            float out[4];
+            f32x4 out[NOUT];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int r = 4 * lg + e;                 // row inside the group
                 const float en2 = __shfl(diag, r + 16 * (r >> 2));
-                float den = sqrtf(en2) * un;
-                den = den < p.eps ? p.eps : den;
-                out[e] = dot[e] / den;
+                float best = NAN;                         // fmaxf passes over NaN: padding takes no part
+#pragma unroll
+                for (int y = 0; y < NG; ++y) {
+                    float den = sqrtf(en2) * un[y];
+                    den = den < p.eps ? p.eps : den;
+                    const float x = dot[y][e] / den;
+                    if constexpr (MAX) best = 16 * y + ln < p.nq_grp ? fmaxf(best, x) : best;
+                    else out[y][e] = x;
+                }
+                if constexpr (MAX) {
+#pragma unroll
+                    for (int o = 1; o < 16; o <<= 1) best = fmaxf(best, __shfl_xor(best, o));
+                    out[0][e] = best;
+                }
             }
             // The results of an even group wait for its odd neighbour, so that the wave writes the
             // 128 contiguous bytes of each query row back to back (whole cache lines).
-            auto store_group = [&](long r0, const float (&o)[4]) {
-                float *dst = p.sim + (size_t)(p.q0 + ln) * p.sim_ld + r0 + 4 * lg;
-                if (r0 + 16 <= p.N && ((p.sim_ld & 3) == 0) && ((((uintptr_t)p.sim) & 15) == 0)) {
-                    // one 16-byte store per lane (r0 and 4*lg are multiples of 4); four 4-byte
-                    // stores cost the kernel 15 % of its time
-                    *(f32x4 *)dst = (f32x4){o[0], o[1], o[2], o[3]};
-                } else {
+            auto store_group = [&](long r0, const f32x4 (&o)[NOUT]) {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (r0 + 4 * lg + e < p.N) dst[e] = o[e];
+                for (int y = 0; y < NOUT; ++y) {
+                    if (MAX ? ln > 0 : 16 * y + ln >= p.nq_grp) continue;
+                    float *dst = (MAX ? p.sim : p.sim + (size_t)(p.q0 + 16 * y + ln) * p.sim_ld) + r0 + 4 * lg;
+                    f32x4 x = o[y];
+                    if (MAX && p.q0 > 0) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (r0 + 4 * lg + e < p.N) x[e] = fmaxf(dst[e], x[e]);
+                    }
+                    if (r0 + 16 <= p.N && ((p.sim_ld & 3) == 0) && ((((uintptr_t)p.sim) & 15) == 0)) {
+                        // one 16-byte store per lane (r0 and 4*lg are multiples of 4); four 4-byte
+                        // stores cost the kernel 15 % of its time
+                        *(f32x4 *)dst = x;
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (r0 + 4 * lg + e < p.N) dst[e] = x[e];
+                    }
                 }
             };
             if (!(grp & 1) && grp + 1 < ngroups) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) held[e] = out[e];
-            } else if (ln < p.nq_grp) {
+                for (int y = 0; y < NOUT; ++y) held[y] = out[y];
+            } else {
                 if (grp & 1) store_group(row0 - 16, held);
                 store_group(row0, out);
             }
-            dot = (f32x4){0.f, 0.f, 0.f, 0.f};
-            gram = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int y = 0; y < NG; ++y) dot[y] = zero;
+            gram = zero;
         }
 #pragma unroll
         for (int i = 0; i < kChunk; ++i) { cur[i] = nx1[i]; nx1[i] = nx2[i]; }
@@ -189,8 +227,8 @@ __global__ __launch_bounds__(kSimThreads) void sim_bf16_mfma(GatherParams p)
     }
 }
 
-// One wave per context row; up to 16 queries of the group in LDS as fp32.
-template <typename T>
+// One wave per context row; up to 16 queries of the group in LDS as fp32.  MAX as above.
+template <typename T, bool MAX>
 __global__ __launch_bounds__(256) void sim_generic(GatherParams p)
 {
     extern __shared__ __attribute__((aligned(16))) float qf[];   // [nq_grp][D]
@@ -227,15 +265,18 @@ __global__ __launch_bounds__(256) void sim_generic(GatherParams p)
                 if (qi < p.nq_grp) dot[qi] = fmaf(x, qf[qi * D + c], dot[qi]);
         }
         en2 = wave_sum(en2);
+        float best = NAN;
 #pragma unroll
         for (int qi = 0; qi < 16; ++qi) {
             if (qi < p.nq_grp) {
                 const float dsum = wave_sum(dot[qi]);
                 float den = sqrtf(en2) * qnorm[qi];
                 den = den < p.eps ? p.eps : den;
-                if (lane == 0) p.sim[(size_t)(p.q0 + qi) * p.sim_ld + row] = dsum / den;
+                if constexpr (MAX) best = fmaxf(best, dsum / den);
+                else if (lane == 0) p.sim[(size_t)(p.q0 + qi) * p.sim_ld + row] = dsum / den;
             }
         }
+        if (MAX && lane == 0) p.sim[row] = p.q0 > 0 ? fmaxf(p.sim[row], best) : best;
     }
 }
 
@@ -325,47 +366,64 @@ __global__ __launch_bounds__(256) void union_emit(GatherParams p)
         if (e_ != hipSuccess) return e_;      \
     } while (0)
 
-hipError_t gather_similarity(GatherParams p, int dtype_is_bf16, hipStream_t st)
+template <bool MAX, int NG>
+static auto sim_kernel(bool full) -> void (*)(GatherParams)
 {
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) {
-        int v = 0;
-        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) cus = v;
-    }
-    for (int q0 = 0; q0 < p.nq; q0 += 16) {
+    return full ? sim_bf16_mfma<true, NG, MAX> : sim_bf16_mfma<false, NG, MAX>;
+}
+
+template <bool MAX>
+static hipError_t similarity_passes(GatherParams p, bool bf16, hipStream_t st)
+{
+    const int cus = device_compute_units() > 0 ? device_compute_units() : 256;
+    const size_t lds = 160 * 1024, block = (size_t)16 * (p.D + ((32 - 2 * p.D) & 255) / 2) * sizeof(u16);
+    const bool mfma = bf16 && p.D % 32 == 0 && (size_t)16 * (p.D + 128) * 2 <= 150 * 1024;
+    // blocks of 16 queries: as few passes over the store as the LDS allows, evenly filled
+    const int blocks = (p.nq + 15) / 16;
+    const int fit = mfma ? (int)min((size_t)4, (lds - 1024) / block) : 1;
+    const int passes = (blocks + fit - 1) / fit, ng = (blocks + passes - 1) / passes;
+    // One workgroup is resident per compute unit.  A second round evens out a long stream and costs a
+    // second start (staging the queries): one round / two, 16 queries or fewer, rows x dim: 131072 x
+    // 1024 87.2 / 91.6 us, 262144 x 2048 248 / 260 us; 500000 x 1024 225 / 220 us, 1048576 x 2048
+    // 877 / 873 us (whole gather).
+    const long rounds = (p.N + 15) / 16 >= 96l * cus ? 2 : 1;
+    for (int q0 = 0; q0 < p.nq; q0 += 16 * ng) {
         p.q0 = q0;
-        p.nq_grp = p.nq - q0 < 16 ? p.nq - q0 : 16;
-        if (dtype_is_bf16 && p.D % 32 == 0 && (size_t)16 * (p.D + 128) * 2 <= 150 * 1024) {
-            const int rem = (2 * p.D) & 255;
-            const size_t smem = (size_t)16 * (p.D + (((32 - rem) & 255) >> 1)) * sizeof(u16);
-            const long ngroups = (p.N + 15) / 16;
-            long grid = (ngroups + 7) / 8;
-            const long cap = (long)cus * 2;
-            if (grid > cap) grid = cap;
-            auto kern = p.D % (32 * kChunk) == 0 ? sim_bf16_mfma<true> : sim_bf16_mfma<false>;
-            hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-            if (e != hipSuccess) return e;
-            hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kSimThreads), smem, st, p);
+        p.nq_grp = min(p.nq - q0, 16 * ng);
+        void (*kern)(GatherParams);
+        size_t smem;
+        long grid;
+        int threads;
+        if (mfma) {
+            smem = block * ng;
+            threads = kSimThreads;
+            grid = min(((p.N + 15) / 16 + kSimThreads / 64 - 1) / (kSimThreads / 64), cus * rounds);
+            const bool full = p.D % (32 * kChunk) == 0;
+            kern = ng == 1 ? sim_kernel<MAX, 1>(full) : ng == 2 ? sim_kernel<MAX, 2>(full)
+                 : ng == 3 ? sim_kernel<MAX, 3>(full) : sim_kernel<MAX, 4>(full);
         } else {
-            const size_t smem = (size_t)p.nq_grp * p.D * sizeof(float);
-            long grid = (p.N + 3) / 4;
-            const long cap = (long)cus * 16;
-            if (grid > cap) grid = cap;
-            if (dtype_is_bf16) {
-                hipError_t e = hipFuncSetAttribute((const void *)sim_generic<u16>,
-                                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-                if (e != hipSuccess) return e;
-                hipLaunchKernelGGL(sim_generic<u16>, dim3((unsigned)grid), dim3(256), smem, st, p);
-            } else {
-                hipError_t e = hipFuncSetAttribute((const void *)sim_generic<float>,
-                                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-                if (e != hipSuccess) return e;
-                hipLaunchKernelGGL(sim_generic<float>, dim3((unsigned)grid), dim3(256), smem, st, p);
-            }
+            smem = (size_t)p.nq_grp * p.D * sizeof(float);
+            threads = 256;
+            grid = min((p.N + 3) / 4, (long)cus * 16);
+            kern = bf16 ? sim_generic<u16, MAX> : sim_generic<float, MAX>;
         }
+        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), smem, st, p);
         RF_CHECK_LAUNCH();
     }
     return hipSuccess;
+}
+
+hipError_t gather_similarity(const GatherParams &p, bool bf16, hipStream_t st)
+{
+    return similarity_passes<false>(p, bf16, st);
+}
+
+// The largest similarity of every row over all queries, into p.sim[N].
+hipError_t gather_similarity_max(const GatherParams &p, bool bf16, hipStream_t st)
+{
+    return similarity_passes<true>(p, bf16, st);
 }
 
 hipError_t gather_select_union(GatherParams p, hipStream_t st)

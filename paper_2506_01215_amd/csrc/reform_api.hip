@@ -17,7 +17,8 @@ hipError_t attend_f32_score(const AttnParams &p, hipStream_t st);
 hipError_t evict_run(const EvictParams &p, hipStream_t st);
 hipError_t evict_fill_identity(int32_t *kept, int Hkv, int B, int n, hipStream_t st);
 
-hipError_t gather_similarity(GatherParams p, int dtype_is_bf16, hipStream_t st);
+hipError_t gather_similarity(const GatherParams &p, bool bf16, hipStream_t st);
+hipError_t gather_similarity_max(const GatherParams &p, bool bf16, hipStream_t st);
 hipError_t gather_select_union(GatherParams p, hipStream_t st);
 hipError_t gather_pool_select(const PoolParams &p, hipStream_t st);
 int gather_pool_max_window();
@@ -164,7 +165,7 @@ reform_status check_pooled(const reform_pooled_desc *d)
 }
 
 struct PooledLayout {
-    size_t status, sim, pooled, hist, prefix, krem, blk, total;
+    size_t status, best, pooled, hist, prefix, krem, blk, total;
     int nblk;
 };
 
@@ -174,7 +175,7 @@ PooledLayout pooled_layout(const reform_pooled_desc *d)
     L.nblk = (int)((d->n_ctx + 4095) / 4096);
     size_t off = 0;
     L.status = off; off += align_up(sizeof(int));
-    L.sim = off;    off += align_up((size_t)d->n_query * sim_pitch(d->n_ctx) * sizeof(float));
+    L.best = off;   off += align_up((size_t)sim_pitch(d->n_ctx) * sizeof(float));
     L.pooled = off; off += align_up((size_t)d->n_ctx * sizeof(float));
     L.hist = off;   off += align_up((size_t)3 * 2048 * sizeof(int));
     L.prefix = off; off += align_up((size_t)3 * sizeof(uint32_t));
@@ -490,16 +491,11 @@ reform_status reform_gather_pooled(const reform_pooled_desc *d, const void *emb,
     char *ws = (char *)workspace;
     hipStream_t st = (hipStream_t)hip_stream;
     const reform_gather_desc g = pooled_as_gather(d);
-    GatherParams gp;
-    fill_gather(gp, &g, emb, qry);
-    gp.sim = (float *)(ws + L.sim);
-    gp.sim_ld = sim_pitch(d->n_ctx);
-    if (gather_similarity(gp, d->dtype == REFORM_BF16, st) != hipSuccess) return REFORM_ERR_RUNTIME;
     PoolParams p;
     std::memset(&p, 0, sizeof(p));
-    p.sim = gp.sim;
+    p.best = (float *)(ws + L.best);
     p.pooled = pooled ? pooled : (float *)(ws + L.pooled);
-    p.N = d->n_ctx; p.ld = gp.sim_ld; p.nq = d->n_query; p.window = d->pool_window;
+    p.N = d->n_ctx; p.window = d->pool_window;
     p.sel.vals = p.pooled; p.sel.ld = d->n_ctx; p.sel.N = d->n_ctx;
     p.sel.nq = 1; p.sel.k = d->budget;
     p.sel.n_sink = d->n_head_keep; p.sel.n_recent = d->n_tail_keep;
@@ -512,6 +508,13 @@ reform_status reform_gather_pooled(const reform_pooled_desc *d, const void *emb,
     p.sel.multi_ok = 1;
     p.sel.err = (int *)(ws + L.status);
     p.sel.spin_limit = g_move_spin_limit.load(std::memory_order_relaxed);
+    p.sel.pre_zeroed = 1;                     // by the first similarity launch
+    GatherParams gp;
+    fill_gather(gp, &g, emb, qry);
+    gp.sim = (float *)(ws + L.best);
+    gp.sim_ld = sim_pitch(d->n_ctx);
+    gp.sel = p.sel;
+    if (gather_similarity_max(gp, d->dtype == REFORM_BF16, st) != hipSuccess) return REFORM_ERR_RUNTIME;
     return gather_pool_select(p, st) == hipSuccess ? REFORM_OK : REFORM_ERR_RUNTIME;
 }
 
