@@ -130,7 +130,7 @@ reform_status reform_chunk_attend_score(const reform_attn_desc *desc,
  * work keeps part of this call's workgroups off the device for seconds; if it does, the call
  * still ends, the cache content is then undefined, and the first int32 of the workspace, which
  * such a call clears when it starts, is set to 1.  A caller that wants to know reads that word
- * once the stream has finished.  Rows of more than 32768 candidates are selected by several
+ * once the stream has finished.  Rows of more than 8192 candidates are selected by several
  * workgroups per row that wait for each other inside one launch (at most 128 workgroups, half of
  * what the chip holds at once); the same bounded wait and status word cover it, and more than two
  * such calls overlapping on one GPU from different streams are the one way to make it expire.
@@ -198,7 +198,12 @@ reform_status reform_evict_topk_compact_static(const reform_evict_desc *desc,
  *     topk_score  [n_query][k] fp32 out (sim of the selected rows), may be NULL
  *     union_idx   [n_ctx] int32 out (first union_count entries), may be NULL (then no union)
  *     union_count one int32 in device memory, out, required iff union_idx != NULL
- * Supported: n_ctx <= 2^31 - 65536; dim % 8 == 0; any n_query >= 1 (processed 16 at a time).
+ * Supported: n_ctx <= 2^31 - 65536; dim % 8 == 0; any n_query >= 1 (up to 64 per pass over emb).
+ * Device-side status: rows of more than 8192 similarities are selected, where at most 64 workgroups
+ * suffice for all of them, by several workgroups per row that wait for each other inside one
+ * launch, with the bounded wait described for reform_evict_topk_compact; the first int32 of the
+ * workspace is cleared by the call and set to 1 if such a wait expired (the outputs are then
+ * undefined).
  */
 typedef struct {
     uint32_t struct_size;
@@ -242,7 +247,7 @@ reform_status reform_gather_similarity(const reform_gather_desc *desc,
  *     pooled   [n_ctx] fp32 out, may be NULL (then it lives in the workspace only)
  * Supported: as reform_gather_topk; pool_window odd, 1 <= pool_window <= 1025;
  * n_head_keep + n_tail_keep <= budget <= n_ctx.
- * Device-side status: the one row of pooled scores is selected, when it has more than 32768
+ * Device-side status: the one row of pooled scores is selected, when it has more than 8192
  * entries and at most 4 million, by up to 128 workgroups that wait for each other inside one
  * launch, with the bounded wait described for reform_evict_topk_compact; the first int32 of the
  * workspace is cleared by the call and set to 1 if such a wait expired (sel_idx is then undefined).

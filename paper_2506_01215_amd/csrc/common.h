@@ -45,6 +45,7 @@ struct AttnParams {
 #define RF_MOVE_TILE 16384
 #endif
 constexpr int kMoveTileBytes = RF_MOVE_TILE;   // bytes of destination rows per workgroup of the in-place move
+constexpr int kMultiMaxGroups = 128;        // see select_row
 constexpr int kUnionWordsPerBlock = 256;   // bitmap words per workgroup of the union kernels
 
 // Top-k selection problem: nq rows of N candidates (row stride ld), k winners per row.
@@ -64,12 +65,14 @@ struct SelParams {
     int32_t *out_rank;       // nullable [nq][ld]: rank[t] = number of selected candidates below t
     const int32_t *side_src; // nullable [nq][ld]: a 4-byte companion of every candidate ...
     int32_t *side_dst;       // ... copied to [nq][out_ld] for the selected ones (same order as out_idx)
+    uint32_t *mark;          // nullable: bitmap over the candidates (shared by the rows, cleared before) in which
+    long mark_radius;        // ... every selected one and its neighbours up to this distance are marked
     int *zero_extra;         // nullable: zero_extra_n more ints cleared by the histogram-clearing launch
     int zero_extra_n;
     int pre_zeroed;          // hist and zero_extra were cleared by an earlier kernel of the same call
-    int multi_ok;            // rows too long for one workgroup may be selected in one launch by several
-                             // workgroups that wait for each other (needs hist, blk_cnt and err to be usable
-                             // for that: the eviction sets it)
+    int multi_groups;        // rows too long for one workgroup may be selected in one launch by several
+                             // workgroups that wait for each other, at most this many in all (0: never;
+                             // needs hist, blk_cnt and err to be usable for that)
     int *err;                // nullable: set to 1 if a bounded wait between workgroups expired
     int spin_limit;          // polls of such a wait
 };
@@ -199,7 +202,7 @@ __device__ __forceinline__ void sel_clear(const SelParams &p, long i0, long stri
     const long nh = (long)p.nq * 3 * 2048;
     for (long i = i0; i < nh; i += stride) p.hist[i] = 0;
     for (long i = i0; i < p.zero_extra_n; i += stride) p.zero_extra[i] = 0;
-    if (p.multi_ok)
+    if (p.multi_groups)
         for (long i = i0; i < (long)p.nq * p.nblk * 2; i += stride) p.blk_cnt[i] = 0;
     if (p.err && i0 == 0) *p.err = 0;
 }

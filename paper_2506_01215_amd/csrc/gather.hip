@@ -7,9 +7,9 @@
 //                   tile with itself (Gram diagonal), so the VALU does no per-element work and
 //                   the kernel stays HBM-bound.
 //   sim_generic     fp32 (or odd-shaped bf16) inputs: one wave per row, fp32 FMA.
-//   select_topk     (select.hip) 3-pass radix select of the k-th largest per query, then an
-//                   ordered two-kernel compaction.
-//   union_*         bitmap of N bits: mark dilated hits, count, emit ascending.
+//   select_topk     (select.hip) radix select of the k-th largest per query and ordered emission,
+//                   which also marks the dilated hits in a bitmap of N bits.
+//   union_*         count and emit the bitmap's rows ascending.
 #include "common.h"
 
 namespace reform {
@@ -281,38 +281,16 @@ __global__ __launch_bounds__(256) void sim_generic(GatherParams p)
 }
 
 // ------------------------------------------------------------------------------------------
-// Zero the bitmap of one call.
-// ------------------------------------------------------------------------------------------
-// Union with dilation through a bitmap of N bits.
-__device__ __forceinline__ void set_bits(uint32_t *bm, long lo, long hi)   // inclusive range
-{
-    for (long w = lo >> 5; w <= (hi >> 5); ++w) {
-        const long b0 = w << 5;
-        const int a = (int)max(lo - b0, 0L), b = (int)min(hi - b0, 31L);
-        const uint32_t mask = (b - a == 31) ? 0xffffffffu : (((1u << (b - a + 1)) - 1u) << a);
-        atomicOr(&bm[w], mask);
-    }
-}
+// Union through a bitmap of N bits, in which the selection marks its winners and their
+// neighbourhoods as it writes them.  union_word: a word with the forced first / last rows added.
+__device__ __forceinline__ uint32_t low_bits(long n) { return n >= 32 ? 0xffffffffu : n <= 0 ? 0u : (1u << n) - 1u; }
 
-__global__ __launch_bounds__(256) void union_mark(GatherParams p)
+__device__ __forceinline__ uint32_t union_word(const GatherParams &p, long w)
 {
-    const long i = (long)blockIdx.x * 256 + threadIdx.x;
-    const long total = (long)p.nq * p.k;
-    if (i < total) {
-        const long t = p.topk_idx[i];
-        if (t >= 0 && t < p.N)
-            set_bits(p.bitmap, max(t - p.radius, 0L), min(t + (long)p.radius, p.N - 1));
-    }
-    // forced first / last rows: one thread per word of each range
-    if (i < p.nwords) {
-        const long b0 = i << 5;
-        uint32_t mask = 0u;
-        for (int b = 0; b < 32; ++b) {
-            const long t = b0 + b;
-            if (t < p.N && (t < p.n_head || t >= p.N - p.n_tail)) mask |= 1u << b;
-        }
-        if (mask) atomicOr(&p.bitmap[i], mask);
-    }
+    if (w >= p.nwords) return 0u;
+    const long b0 = w << 5;
+    const uint32_t forced = low_bits(p.n_head - b0) | ~low_bits(p.N - p.n_tail - b0);
+    return p.bitmap[w] | (forced & low_bits(p.N - b0));
 }
 
 // One bitmap word per thread, kUnionWordsPerBlock = 256 words (8192 rows) per workgroup.
@@ -320,8 +298,7 @@ __global__ __launch_bounds__(256) void union_count_words(GatherParams p)
 {
     __shared__ int red[4];
     const int tid = threadIdx.x;
-    const long w = (long)blockIdx.x * kUnionWordsPerBlock + tid;
-    int c = w < p.nwords ? __popc(p.bitmap[w]) : 0;
+    int c = __popc(union_word(p, (long)blockIdx.x * kUnionWordsPerBlock + tid));
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) c += __shfl_xor(c, o);
     if ((tid & 63) == 0) red[tid >> 6] = c;
@@ -330,7 +307,9 @@ __global__ __launch_bounds__(256) void union_count_words(GatherParams p)
 }
 
 // The set bits of the workgroup's words are expanded into an LDS staging array in ascending
-// order and copied out as one contiguous, coalesced block of indices.
+// order and copied out as one contiguous, coalesced block of indices.  COUNTED: union_count_words
+// has left the counts of the workgroups before this one; otherwise it counts their words itself.
+template <bool COUNTED>
 __global__ __launch_bounds__(256) void union_emit(GatherParams p)
 {
     __shared__ int32_t stage[kUnionWordsPerBlock * 32];
@@ -338,14 +317,18 @@ __global__ __launch_bounds__(256) void union_emit(GatherParams p)
     __shared__ int sh_base;
     const int tid = threadIdx.x, blk = blockIdx.x;
     int before = 0;
-    for (int b = tid; b < blk; b += 256) before += p.word_cnt[b];
+    if (COUNTED)
+        for (int b = tid; b < blk; b += 256) before += p.word_cnt[b];
+    else
+#pragma unroll 8
+        for (int b = 0; b < blk; ++b) before += __popc(union_word(p, (long)b * kUnionWordsPerBlock + tid));
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) before += __shfl_xor(before, o);
     if (tid == 0) sh_base = 0;
     __syncthreads();
     if ((tid & 63) == 0) atomicAdd(&sh_base, before);
     const long w = (long)blk * kUnionWordsPerBlock + tid;
-    uint32_t m = w < p.nwords ? p.bitmap[w] : 0u;
+    uint32_t m = union_word(p, w);
     int tot;
     int pos = block256_excl_scan(__popc(m), tmp, tot);          // synchronises: sh_base is complete after it
     const int32_t first = (int32_t)(w << 5);
@@ -426,18 +409,24 @@ hipError_t gather_similarity_max(const GatherParams &p, bool bf16, hipStream_t s
     return similarity_passes<true>(p, bf16, st);
 }
 
+constexpr int kUnionSelfCount = 4;
+
 hipError_t gather_select_union(GatherParams p, hipStream_t st)
 {
     hipError_t es = select_topk(p.sel, st);
     if (es != hipSuccess) return es;
     if (p.union_idx) {
-        const long total = max((long)p.nq * p.k, (long)p.nwords);
-        hipLaunchKernelGGL(union_mark, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, p);
-        RF_CHECK_LAUNCH();
+        // Counting the words before its own costs a workgroup more as they grow; for a few workgroups that
+        // is less than the launch it saves: 2048 rows 18.2 instead of 20.4 us for the whole call, 20000
+        // rows 42.8 and 44.0 us, 100000 rows 66.4 and 65.8 us, 250000 rows 97.7 and 92.7 us.
         const int ub = (p.nwords + kUnionWordsPerBlock - 1) / kUnionWordsPerBlock;
-        hipLaunchKernelGGL(union_count_words, dim3(ub), dim3(256), 0, st, p);
-        RF_CHECK_LAUNCH();
-        hipLaunchKernelGGL(union_emit, dim3(ub), dim3(256), 0, st, p);
+        if (ub > kUnionSelfCount) {
+            hipLaunchKernelGGL(union_count_words, dim3(ub), dim3(256), 0, st, p);
+            RF_CHECK_LAUNCH();
+            hipLaunchKernelGGL(union_emit<true>, dim3(ub), dim3(256), 0, st, p);
+        } else {
+            hipLaunchKernelGGL(union_emit<false>, dim3(ub), dim3(256), 0, st, p);
+        }
         RF_CHECK_LAUNCH();
     }
     return hipSuccess;

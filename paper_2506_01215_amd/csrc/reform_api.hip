@@ -117,6 +117,14 @@ reform_status check_gather(const reform_gather_desc *d)
 // to 64 KB measured alike).
 long sim_pitch(int64_t n_ctx) { return (long)((n_ctx + 63) / 64 * 64 + 1088); }
 
+// Workgroups that may wait for each other in the selection of a gather call.  The calls of several
+// streams may overlap, so fewer than an eviction's: eight such launches fit the chip together.
+constexpr int kGatherMultiGroups = 64;
+
+// The gather's similarities begin this many floats into their region (the last row ends at least 1088
+// floats before its end): the first word of the workspace is the status word of the selection.
+constexpr int kSimSkip = 64;
+
 struct GatherLayout {
     size_t sim, hist, prefix, krem, blk, bitmap, words, total;
     int nblk, nwords, nublk;
@@ -348,7 +356,7 @@ reform_status reform_evict_topk_compact(const reform_evict_desc *d, void *k, voi
     p.sel.nblk = L.nblk;
     p.sel.out_idx = p.kept; p.sel.out_val = nullptr; p.sel.out_ld = d->budget;
     p.sel.out_rank = L.inplace ? (int32_t *)(ws + L.rank) : nullptr;
-    p.sel.multi_ok = 1;
+    p.sel.multi_groups = kMultiMaxGroups;
     p.sel.spin_limit = g_move_spin_limit.load(std::memory_order_relaxed);
     p.sync = L.inplace ? (int *)(ws + L.sync) : nullptr;
     p.ntile = L.ntile;
@@ -445,7 +453,7 @@ reform_status reform_gather_topk(const reform_gather_desc *d, const void *emb, c
     char *ws = (char *)workspace;
     GatherParams p;
     fill_gather(p, d, emb, qry);
-    p.sim = (float *)(ws + L.sim);
+    p.sim = (float *)(ws + L.sim) + kSimSkip;
     p.sim_ld = sim_pitch(d->n_ctx);
     p.topk_idx = topk_idx; p.topk_score = topk_score;
     p.union_idx = union_idx; p.union_count = union_count;
@@ -464,7 +472,12 @@ reform_status reform_gather_topk(const reform_gather_desc *d, const void *emb, c
     if (union_idx) {                          // the bitmap is cleared together with the histograms ...
         p.sel.zero_extra = (int *)p.bitmap;
         p.sel.zero_extra_n = L.nwords;
+        p.sel.mark = p.bitmap;
+        p.sel.mark_radius = d->radius;
     }
+    p.sel.multi_groups = kGatherMultiGroups;
+    p.sel.err = (int *)ws;                    // status word, in the 256 bytes before the similarities
+    p.sel.spin_limit = g_move_spin_limit.load(std::memory_order_relaxed);
     p.sel.pre_zeroed = 1;                     // ... by the first similarity launch
     hipStream_t st = (hipStream_t)hip_stream;
     if (gather_similarity(p, d->dtype == REFORM_BF16, st) != hipSuccess) return REFORM_ERR_RUNTIME;
@@ -505,7 +518,7 @@ reform_status reform_gather_pooled(const reform_pooled_desc *d, const void *emb,
     p.sel.blk_cnt = (int *)(ws + L.blk);
     p.sel.nblk = L.nblk;
     p.sel.out_idx = sel_idx; p.sel.out_val = nullptr; p.sel.out_ld = d->budget;
-    p.sel.multi_ok = 1;
+    p.sel.multi_groups = kMultiMaxGroups;
     p.sel.err = (int *)(ws + L.status);
     p.sel.spin_limit = g_move_spin_limit.load(std::memory_order_relaxed);
     p.sel.pre_zeroed = 1;                     // by the first similarity launch

@@ -10,12 +10,13 @@
 //   select_count  final pick, then per workgroup the number of candidates above / equal to the
 //                 threshold key
 //   select_write  ordered emission: everything above the threshold, then the lowest-index ties
-//   select_fused  rows of at most 32768 candidates: all of the above in one launch, one workgroup
-//                 per row, keys held in registers
-//   select_multi  longer rows, when every workgroup of the launch fits on the chip at once: one
-//                 launch, several workgroups per row that wait for each other (keys in registers)
+//   select_row    all of the above in one launch, keys held in LDS: one workgroup per row for rows
+//                 of at most kFusedMaxN candidates; for longer ones, when every workgroup of the
+//                 launch fits on the chip at once, several per row that wait for each other
 // Candidates in the first n_sink or last n_recent slots get the maximal key (always selected).
 #include "common.h"
+
+#include <atomic>
 
 namespace reform {
 
@@ -45,7 +46,7 @@ __global__ void sel_zero(SelParams p)
     const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < (long)p.nq * 3 * 2048) p.hist[i] = 0;
     if (i < p.zero_extra_n) p.zero_extra[i] = 0;
-    if (p.multi_ok && i < (long)p.nq * p.nblk * 2) p.blk_cnt[i] = 0;
+    if (p.multi_groups && i < (long)p.nq * p.nblk * 2) p.blk_cnt[i] = 0;
     if (p.err && i == 0) *p.err = 0;
 }
 
@@ -194,169 +195,181 @@ __global__ __launch_bounds__(256) void select_count(SelParams p)
 
 // ------------------------------------------------------------------------------------------
 // Building blocks shared by the ordered emission of the multi-launch path and by the
-// single-launch selection of short rows.  A wave owns a contiguous range of NIT * 256
-// candidates starting at w_lo; in step `it` lane l holds the four consecutive candidates
-// w_lo + it * 256 + 4 * l + (0..3).  Every global access of a step is then one contiguous block
-// per wave, and positions in index order follow from wave ballots (no cross-lane data movement)
-// plus the running counts of the wave.  `FULL` marks a wave whose whole range lies inside the row
-// (no per-candidate bounds test).
+// single-launch selection.  A wave owns a contiguous range of nit * 256 candidates starting at
+// w_lo; in step `it` lane l holds the four consecutive candidates w_lo + it * 256 + 4 * l + (0..3).
+// Every global access of a step is then one contiguous block per wave, and positions in index
+// order follow from wave ballots (no cross-lane data movement) plus the running counts of the wave.
+//
+// The keys lie in LDS and every step is a trip of a short loop, so the code has one size for all
+// rows (10 KB; with the keys in registers and every step unrolled up to 59 KB).
 __device__ __forceinline__ int lanes_below(unsigned long long m)
 {
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-// Keys of the wave's range; slots at or beyond N hold 0 and are masked by the users.
-template <int NIT>
-__device__ __forceinline__ void range_keys(const SelParams &p, const float *s, int N, int w_lo, uint32_t (&u)[NIT][4])
+// Keys of the wave's range into LDS, in batches whose loads are in flight together; slots at or
+// beyond N get 0 and are masked by the users.
+__device__ __forceinline__ void load_keys(const SelParams &p, const float *s, int N, int w_lo, int nit, v4u *keys)
 {
-    const int t_lane = w_lo + (threadIdx.x & 63) * 4;
-    const int w_hi = w_lo + NIT * 256;
-    const bool forced = w_lo < p.n_sink || w_hi > N - p.n_recent;     // some slot of the range may be forced in
-    if (w_hi <= N && !forced && sel_rows_aligned(p)) {
+    const int lane = threadIdx.x & 63;
+    const bool quads = sel_rows_aligned(p);
+    const int tail = N - p.n_recent;
+#pragma unroll 1
+    for (int it0 = 0; it0 < nit; it0 += 4) {
+        float v[4][4];
 #pragma unroll
-        for (int it = 0; it < NIT; ++it) {
-            const float4 v = *(const float4 *)(s + t_lane + it * 256);
-            u[it][0] = ordered_key(v.x);
-            u[it][1] = ordered_key(v.y);
-            u[it][2] = ordered_key(v.z);
-            u[it][3] = ordered_key(v.w);
-        }
-    } else {
+        for (int b = 0; b < 4; ++b) {
+            if (it0 + b >= nit) continue;
+            const int t = min(w_lo + (it0 + b) * 256 + 4 * lane, (N - 1) & ~3);
+            if (quads) {                                      // a quad that begins inside the row ends inside its pitch
+                *(f32x4 *)v[b] = *(const f32x4 *)(s + t);
+            } else {
 #pragma unroll
-        for (int it = 0; it < NIT; ++it)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int t = t_lane + it * 256 + j;
-                const uint32_t key = sel_key(p, s, min(t, N - 1));
-                u[it][j] = t < N ? key : 0u;
+                for (int j = 0; j < 4; ++j) v[b][j] = s[min(t + j, N - 1)];
             }
+        }
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            if (it0 + b >= nit) continue;
+            const int t = w_lo + (it0 + b) * 256 + 4 * lane;
+            v4u u;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                u[j] = t + j >= N ? 0u : t + j < p.n_sink || t + j >= tail ? 0xffffffffu : ordered_key(v[b][j]);
+            keys[(it0 + b) * 64 + lane] = u;
+        }
     }
 }
 
 // Candidates of the wave's range above / equal to the threshold key (wave-uniform results).
-template <int NIT, bool FULL>
-__device__ __forceinline__ void range_count(const uint32_t (&u)[NIT][4], int N, int w_lo, uint32_t T, int &gt, int &eq)
+__device__ __forceinline__ void range_count(const v4u *keys, int N, int w_lo, int nit, uint32_t T, int &gt, int &eq)
 {
-    const int t_lane = w_lo + (threadIdx.x & 63) * 4;
+    const int lane = threadIdx.x & 63;
     gt = 0;
     eq = 0;
-#pragma unroll
-    for (int it = 0; it < NIT; ++it)
+#pragma unroll 1
+    for (int it = 0; it < nit; ++it) {
+        const v4u u = keys[it * 64 + lane];
+        const int t = w_lo + it * 256 + 4 * lane;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const bool valid = FULL || t_lane + it * 256 + j < N;
-            gt += __popcll(__ballot(valid && u[it][j] > T));
-            eq += __popcll(__ballot(valid && u[it][j] == T));
+            gt += __popcll(__ballot(t + j < N && u[j] > T));
+            eq += __popcll(__ballot(t + j < N && u[j] == T));
         }
+    }
 }
 
-// Four consecutive 4-byte entries src[t..t+3] (those at or beyond N come back as 0).
-template <bool FULL>
-__device__ __forceinline__ int4 load_quad(const int32_t *src, bool quads, int t, int N)
+__device__ __forceinline__ void mark_range(uint32_t *bitmap, long lo, long hi)   // inclusive
 {
-    if (quads && (FULL || t + 4 <= N)) return *(const int4 *)(src + t);
-    int4 r;
-    r.x = t < N ? src[t] : 0;
-    r.y = t + 1 < N ? src[t + 1] : 0;
-    r.z = t + 2 < N ? src[t + 2] : 0;
-    r.w = t + 3 < N ? src[t + 3] : 0;
-    return r;
+    for (long w = lo >> 5; w <= (hi >> 5); ++w) {
+        const uint32_t from_lo = lo > (w << 5) ? ~0u << (lo & 31) : ~0u;
+        const uint32_t to_hi = hi < (w << 5) + 31 ? ~(~1u << (hi & 31)) : ~0u;
+        atomicOr(&bitmap[w], from_lo & to_hi);
+    }
 }
 
 // Ordered emission of the wave's range: dest_run = selected candidates before the range,
-// eq_run = candidates equal to T before it (both wave-uniform).  The values and the companion
-// entries of a step are fetched as whole quads one step ahead, never per selected candidate
-// (a load feeding a store inside the per-candidate branch costs a memory round trip each).
-template <int NIT, bool FULL>
-__device__ __forceinline__ void range_emit(const SelParams &p, int q, const uint32_t (&u)[NIT][4], int N, int w_lo,
+// eq_run = candidates equal to T before it (both wave-uniform).  A first loop replaces the keys by
+// the indices of the kept candidates, dense (a step's keys are read before its indices are written,
+// and those end before the next step's keys).  A second one writes them out, coalesced, together
+// with their values, companion entries and marks, several loads in flight: inside the first loop
+// every step would wait for the stores of the one before (5.6 us of a row's 11.6 us at 4113
+// candidates, now 2.9 us).
+__device__ __forceinline__ void range_emit(const SelParams &p, int q, v4u *keys, int N, int w_lo, int nit,
                                            uint32_t T, int need_eq, int dest_run, int eq_run)
 {
-    const int t_lane = w_lo + (threadIdx.x & 63) * 4;
-    const int32_t *sv = (const int32_t *)(p.vals + (size_t)q * p.ld);
+    const int lane = threadIdx.x & 63;
     int32_t *orank = p.out_rank ? p.out_rank + (size_t)q * p.ld : nullptr;
     const bool rank_quads = ((p.ld & 3) == 0) && ((((uintptr_t)p.out_rank) & 15) == 0);
-    const bool val_quads = sel_rows_aligned(p);
-    const bool side_quads = ((p.ld & 3) == 0) && ((((uintptr_t)p.side_src) & 15) == 0);
-    int32_t *oi = p.out_idx + (size_t)q * p.out_ld;
-    int32_t *os = p.out_val ? (int32_t *)(p.out_val + (size_t)q * p.out_ld) : nullptr;
-    const int32_t *ss = p.side_src ? p.side_src + (size_t)q * p.ld : nullptr;
-    int32_t *sd = p.side_src ? p.side_dst + (size_t)q * p.out_ld : nullptr;
-    int4 val_nx = make_int4(0, 0, 0, 0), side_nx = make_int4(0, 0, 0, 0);
-    if (os) val_nx = load_quad<FULL>(sv, val_quads, t_lane, N);
-    if (ss) side_nx = load_quad<FULL>(ss, side_quads, t_lane, N);
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-        const int t = t_lane + it * 256;
-        const int4 val4 = val_nx, side4 = side_nx;
-        if (it + 1 < NIT) {
-            if (os) val_nx = load_quad<FULL>(sv, val_quads, t + 256, N);
-            if (ss) side_nx = load_quad<FULL>(ss, side_quads, t + 256, N);
-        }
-        const int val[4] = {val4.x, val4.y, val4.z, val4.w};
-        const int side[4] = {side4.x, side4.y, side4.z, side4.w};
+    int *found = (int *)keys;
+    int n_found = 0;
+#pragma unroll 1
+    for (int it = 0; it < nit; ++it) {
+        const int t = w_lo + it * 256 + 4 * lane;
+        const v4u u = keys[it * 64 + lane];
         bool keep[4];
-        unsigned long long me[4];
-        unsigned long long any_eq = 0;
+        int eq_seen = eq_run;                                 // ties: lowest index first
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            me[j] = __ballot((FULL || t + j < N) && u[it][j] == T);
-            any_eq |= me[j];
+            const unsigned long long me = __ballot(t + j < N && u[j] == T);
+            eq_seen += lanes_below(me);
+            eq_run += __popcll(me);
         }
-        if (any_eq) {                                         // ties inside these 256 candidates: lowest index first
-            int eq_seen = eq_run;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) eq_seen += lanes_below(me[j]);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const bool is_eq = (FULL || t + j < N) && u[it][j] == T;
-                keep[j] = (FULL || t + j < N) && (u[it][j] > T || (is_eq && eq_seen < need_eq));
-                eq_seen += is_eq;
-                eq_run += __popcll(me[j]);
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) keep[j] = (FULL || t + j < N) && u[it][j] > T;
-        }
-        int dest = dest_run;
+        int at = n_found;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
+            const bool is_eq = t + j < N && u[j] == T;
+            keep[j] = t + j < N && (u[j] > T || (is_eq && eq_seen < need_eq));
+            eq_seen += is_eq;
             const unsigned long long mk = __ballot(keep[j]);
-            dest += lanes_below(mk);
-            dest_run += __popcll(mk);
+            at += lanes_below(mk);
+            n_found += __popcll(mk);
         }
         if (orank) {
-            const int r1 = dest + keep[0], r2 = r1 + keep[1], r3 = r2 + keep[2];
-            if (rank_quads && (FULL || t + 4 <= N)) {
-                *(int4 *)(orank + t) = make_int4(dest, r1, r2, r3);
+            const int r0 = dest_run + at, r1 = r0 + keep[0], r2 = r1 + keep[1], r3 = r2 + keep[2];
+            if (rank_quads && t + 4 <= N) {
+                *(int4 *)(orank + t) = make_int4(r0, r1, r2, r3);
             } else {
-                if (t < N) orank[t] = dest;
+                if (t < N) orank[t] = r0;
                 if (t + 1 < N) orank[t + 1] = r1;
                 if (t + 2 < N) orank[t + 2] = r2;
                 if (t + 3 < N) orank[t + 3] = r3;
             }
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (keep[j] && (unsigned)dest < (unsigned)p.k) {
-                oi[dest] = (int32_t)(t + j);
-                if (os) os[dest] = val[j];
-                if (ss) sd[dest] = side[j];
-            }
-            dest += keep[j];
+        for (int j = 0; j < 4; ++j)
+            if (keep[j]) found[at++] = t + j;
+    }
+    // dest_run and k bound the output whatever the keys were (see the bounded waits below)
+    const int n_out = min(n_found, max(p.k - dest_run, 0));
+    const int32_t *sv = (const int32_t *)(p.vals + (size_t)q * p.ld);
+    int32_t *oi = p.out_idx + (size_t)q * p.out_ld + dest_run;
+    int32_t *os = p.out_val ? (int32_t *)(p.out_val + (size_t)q * p.out_ld) + dest_run : nullptr;
+    const int32_t *ss = p.side_src ? p.side_src + (size_t)q * p.ld : nullptr;
+    int32_t *sd = p.side_src ? p.side_dst + (size_t)q * p.out_ld + dest_run : nullptr;
+    constexpr int B = 4;
+#pragma unroll 1
+    for (int i0 = lane; i0 < n_out; i0 += 64 * B) {
+        int t[B], val[B], side[B];
+#pragma unroll
+        for (int b = 0; b < B; ++b) t[b] = found[min(i0 + 64 * b, n_out - 1)];
+        if (os) {
+#pragma unroll
+            for (int b = 0; b < B; ++b) val[b] = sv[t[b]];
+        }
+        if (ss) {
+#pragma unroll
+            for (int b = 0; b < B; ++b) side[b] = ss[t[b]];
+        }
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            const int i = i0 + 64 * b;
+            if (i >= n_out) continue;
+            oi[i] = t[b];
+            if (os) os[i] = val[b];
+            if (ss) sd[i] = side[b];
         }
     }
+    if (p.mark)
+        for (int i = lane; i < n_out; i += 64)
+            mark_range(p.mark, max((long)found[i] - p.mark_radius, 0L), min((long)found[i] + p.mark_radius, N - 1L));
 }
 
 // grid (nblk, nq): ordered emission of the selected indices (ascending), lowest-index ties.
 // A workgroup covers 4096 candidates, a wave 1024 of them.
 __global__ __launch_bounds__(256) void select_write(SelParams p)
 {
+    __shared__ v4u keys[kSelBlock / 4];
     __shared__ int wtot[2][4];
     __shared__ int sh_gt, sh_eq;
     const int q = blockIdx.y, tid = threadIdx.x, blk = blockIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const uint32_t T = p.sel_prefix[2 * p.nq + q];
     const int need_eq = p.sel_krem[2 * p.nq + q];
+    const int N = (int)p.N;
+    const int w_lo = blk * kSelBlock + wave * 1024;
+    v4u *mine = keys + wave * 256;
+    load_keys(p, p.vals + (size_t)q * p.ld, N, w_lo, 4, mine);
     // candidates above / equal to T in the blocks before this one
     const int *c = p.blk_cnt + (size_t)q * p.nblk * 2;
     int gt_b = 0, eq_b = 0;
@@ -366,70 +379,85 @@ __global__ __launch_bounds__(256) void select_write(SelParams p)
     if (tid == 0) { sh_gt = 0; sh_eq = 0; }
     __syncthreads();
     if (lane == 0) { atomicAdd(&sh_gt, gt_b); atomicAdd(&sh_eq, eq_b); }
-
-    const float *s = p.vals + (size_t)q * p.ld;
-    const int N = (int)p.N;
-    const int w_lo = blk * kSelBlock + wave * 1024;
-    const bool full = w_lo + 1024 <= N;
-    uint32_t u[4][4];
-    range_keys<4>(p, s, N, w_lo, u);
     int gt_w, eq_w;
-    if (full) range_count<4, true>(u, N, w_lo, T, gt_w, eq_w);
-    else range_count<4, false>(u, N, w_lo, T, gt_w, eq_w);
+    range_count(mine, N, w_lo, 4, T, gt_w, eq_w);
     if (lane == 0) { wtot[0][wave] = gt_w; wtot[1][wave] = eq_w; }
     __syncthreads();
     int base_gt = sh_gt, base_eq = sh_eq;                         // above / equal to T before this wave's range
 #pragma unroll
     for (int w = 0; w < 4; ++w)
         if (w < wave) { base_gt += wtot[0][w]; base_eq += wtot[1][w]; }
-    const int dest_run = base_gt + min(base_eq, need_eq);
-    if (full) range_emit<4, true>(p, q, u, N, w_lo, T, need_eq, dest_run, base_eq);
-    else range_emit<4, false>(p, q, u, N, w_lo, T, need_eq, dest_run, base_eq);
+    range_emit(p, q, mine, N, w_lo, 4, T, need_eq, base_gt + min(base_eq, need_eq), base_eq);
 }
 
 // ------------------------------------------------------------------------------------------
-// Rows of at most 32768 candidates: the whole selection of a row in ONE launch by one workgroup
-// of 1024 threads (16 waves, each owning NIT * 256 candidates).  The row is read once; its keys
-// stay in registers through the three radix passes (LDS histogram, pick by a workgroup scan) and
-// the ordered emission.  Results are identical to the multi-launch path; the per-pass selection
-// state is not written back.  One compute unit does all the work of a row, so beyond this size
-// the multi-launch path, which spreads a row over many, is faster.
-constexpr int kFusedMaxN = 32768;
+// The whole selection of a row in ONE launch, by `parts` workgroups of 1024 threads (16 waves, each
+// owning nit * 256 candidates, nit <= 8).  The row is read once; its keys stay in LDS through the
+// radix passes (LDS histogram, pick by a workgroup scan) and the ordered emission.  As soon as the
+// digits picked so far are shared by at most kSelList candidates (nearly always after two passes:
+// the rest is ties) these go into a list, and the k-th largest is found by counting for each of them
+// how many are larger.  Results are identical to the multi-launch path; the per-pass selection state
+// is not written back.
+//
+// One workgroup per row (MULTI = false) serves rows of at most kFusedMaxN candidates: its compute unit
+// does all the work of a row, so beyond this size more of them are faster.
+//
+// MULTI: several workgroups per row, when the whole grid can be resident at once.  Per radix pass
+// a workgroup merges its LDS histogram into the row's
+// global histogram (cleared by the launch before) with integer atomics and then polls that
+// histogram until its total equals the number of candidates the pass must see -- all N in the
+// first pass, afterwards the count of the bin picked by the pass before -- so the merged histogram
+// is its own completion signal and no separate barrier is paid.  Every workgroup of a row takes
+// the same pick from the same numbers.  The list is a global one of (key, index) words, polled for in
+// the same way, and goes out together with the workgroups' counts of the candidates beyond it
+// (published as count + 1 into cleared words, which the later workgroups of the row poll for); from
+// both each workgroup derives where its share of the ascending output starts.  Without a list (more
+// ties than fit) a third pass and the counts above / equal to the threshold take its place.
+//
+// Everything that crosses workgroups inside the launch goes through agent-scope atomics (adds,
+// loads, stores), which are performed beyond the per-XCD L2s.  The waits are bounded: the host
+// launches this kernel only with at most kMultiMaxGroups workgroups, half of what the chip's 256
+// compute units hold at once even at one such workgroup each, so every workgroup that is waited
+// for is running or will be dispatched as soon as unrelated work drains; if a limit is reached
+// all the same (more than two such launches overlapping on different streams could do that), the
+// kernel still ends, sets *err and leaves undefined output.
+constexpr int kSelList = 256;
 
-// Histogram of digit PASS over the keys a thread holds (candidates matching the prefix only).
-template <int NIT, int PASS, bool FULL>
-__device__ __forceinline__ void fused_hist(const uint32_t (&u)[NIT][4], int N, int w_lo, uint32_t prefix, int *h)
+// Histogram of the digit at `shift` over the wave's keys whose higher bits equal the prefix.
+__device__ __forceinline__ void radix_hist(const v4u *keys, int N, int w_lo, int nit, int shift, int bits,
+                                           uint32_t prefix, int *h)
 {
     const int lane = threadIdx.x & 63;
-    const int t_lane = w_lo + lane * 4;
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-        const int t = t_lane + it * 256;
+#pragma unroll 1
+    for (int it = 0; it < nit; ++it) {
+        const v4u u = keys[it * 64 + lane];
+        const int t = w_lo + it * 256 + 4 * lane;
         bool m[4];
         bool same = true;                                     // all four count and share one digit
-        const int d0 = digit_of(u[it][0], PASS);
+        const uint32_t low = (1u << bits) - 1u, d0 = (u[0] >> shift) & low;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            m[j] = (FULL || t + j < N) && prefix_match(u[it][j], prefix, PASS);
-            same = same && m[j] && digit_of(u[it][j], PASS) == d0;
+            m[j] = t + j < N && (u[j] >> shift) >> bits == prefix;
+            same = same && m[j] && ((u[j] >> shift) & low) == d0;
         }
         // a wave whose 256 candidates all fall into one bin adds them at once (constant or
         // narrowly spread rows would otherwise serialise 64 lanes on one LDS address)
-        const int dref = __builtin_amdgcn_readfirstlane(d0);
+        const uint32_t dref = __builtin_amdgcn_readfirstlane(d0);
         if (__all(same && d0 == dref)) {
             if (lane == 0) atomicAdd(&h[dref], 256);
         } else {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                if (m[j]) atomicAdd(&h[digit_of(u[it][j], PASS)], 1);
+                if (m[j]) atomicAdd(&h[(u[j] >> shift) & low], 1);
         }
     }
 }
 
 // Executed by all 1024 threads: pick the digit of the histogram that holds the krem-th largest
-// key (thread t owns digits 2t and 2t+1) and extend the prefix by it.
-template <int PASS>
-__device__ __forceinline__ void fused_pick(uint32_t &prefix, int &krem, const int *h, int *wtot, int *sel)
+// key (thread t owns digits 2t and 2t+1), extend the prefix by it and report how many candidates
+// the digit holds.
+__device__ __forceinline__ void bin_pick(int bits, uint32_t &prefix, int &krem, int &in_bin, const int *h, int *wtot,
+                                         int *sel)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l0 = h[2 * tid], l1 = h[2 * tid + 1], sum = l0 + l1;
@@ -449,81 +477,36 @@ __device__ __forceinline__ void fused_pick(uint32_t &prefix, int &krem, const in
         total += x;
     }
     const int above = total - below - sum;                    // candidates with a digit above 2t+1
-    if (above < krem && krem <= above + l1) { sel[0] = 2 * tid + 1; sel[1] = krem - above; }
-    else if (above + l1 < krem && krem <= above + sum) { sel[0] = 2 * tid; sel[1] = krem - above - l1; }
+    if (above < krem && krem <= above + l1) { sel[0] = 2 * tid + 1; sel[1] = krem - above; sel[2] = l1; }
+    else if (above + l1 < krem && krem <= above + sum) { sel[0] = 2 * tid; sel[1] = krem - above - l1; sel[2] = l0; }
     __syncthreads();
-    prefix = (prefix << (PASS == 2 ? 10 : 11)) | (uint32_t)sel[0];
+    prefix = (prefix << bits) | (uint32_t)sel[0];
     krem = sel[1];
+    in_bin = sel[2];
     __syncthreads();
 }
 
-template <int NIT>
-__global__ __launch_bounds__(1024) void select_fused(SelParams p)
+// All 1024 threads: the krem-th largest of the m <= kSelList keys in `list` (padded with zeros).
+__device__ __forceinline__ void list_pick(const v4u *list, int m, int krem, uint32_t &T, int &need_eq, int *sel)
 {
-    __shared__ int h[2048];
-    __shared__ int wtot[2][16];
-    __shared__ int sel[2];
-    const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (long i = (long)q * 1024 + tid; i < p.zero_extra_n; i += (long)gridDim.x * 1024) p.zero_extra[i] = 0;
-
-    const float *s = p.vals + (size_t)q * p.ld;
-    const int N = (int)p.N;
-    const int w_lo = wave * (NIT * 256);
-    const bool full = w_lo + NIT * 256 <= N;
-    uint32_t u[NIT][4];
-    range_keys<NIT>(p, s, N, w_lo, u);
-
-    uint32_t prefix = 0u;
-    int krem = p.k;
-#define RF_FUSED_PASS(PASS)                                                           \
-    for (int i = tid; i < 2048; i += 1024) h[i] = 0;                                  \
-    __syncthreads();                                                                  \
-    if (full) fused_hist<NIT, PASS, true>(u, N, w_lo, prefix, h);                     \
-    else fused_hist<NIT, PASS, false>(u, N, w_lo, prefix, h);                         \
-    __syncthreads();                                                                  \
-    fused_pick<PASS>(prefix, krem, h, wtot[0], sel);
-    RF_FUSED_PASS(0)
-    RF_FUSED_PASS(1)
-    RF_FUSED_PASS(2)
-#undef RF_FUSED_PASS
-    const uint32_t T = prefix;                                    // key of the k-th largest candidate
-    const int need_eq = krem;                                     // how many candidates equal to it are taken
-
-    int gt_w, eq_w;
-    if (full) range_count<NIT, true>(u, N, w_lo, T, gt_w, eq_w);
-    else range_count<NIT, false>(u, N, w_lo, T, gt_w, eq_w);
-    if (lane == 0) { wtot[0][wave] = gt_w; wtot[1][wave] = eq_w; }
-    __syncthreads();
-    int base_gt = 0, base_eq = 0;                                 // above / equal to T in the waves before this one
+    const int at = threadIdx.x >> 2;                          // four threads per key
+    const uint32_t mine = ((const uint32_t *)list)[at];
+    int gt = 0, eq = 0;
+#pragma unroll 4
+    for (int i = threadIdx.x & 3; i < (m + 3) / 4; i += 4) {
+        const v4u x = list[i];
 #pragma unroll
-    for (int w = 0; w < 16; ++w)
-        if (w < wave) { base_gt += wtot[0][w]; base_eq += wtot[1][w]; }
-    const int dest_run = base_gt + min(base_eq, need_eq);
-    if (full) range_emit<NIT, true>(p, q, u, N, w_lo, T, need_eq, dest_run, base_eq);
-    else range_emit<NIT, false>(p, q, u, N, w_lo, T, need_eq, dest_run, base_eq);
+        for (int j = 0; j < 4; ++j) { gt += x[j] > mine; eq += x[j] == mine; }
+    }
+    gt += __shfl_xor(gt, 1);
+    gt += __shfl_xor(gt, 2);
+    eq += __shfl_xor(eq, 1);
+    eq += __shfl_xor(eq, 2);
+    if (at < m && gt < krem && krem <= gt + eq) { sel[0] = (int)mine; sel[1] = krem - gt; }   // equal keys write the same
+    __syncthreads();
+    T = (uint32_t)sel[0];
+    need_eq = sel[1];
 }
-
-// ------------------------------------------------------------------------------------------
-// Rows longer than that, in ONE launch when the whole grid can be resident at once: `parts`
-// workgroups of 1024 threads share a row, each holding NIT * 4096 of its candidates in registers
-// for the whole selection.  Per radix pass a workgroup merges its LDS histogram into the row's
-// global histogram (cleared by the launch before) with integer atomics and then polls that
-// histogram until its total equals the number of candidates the pass must see -- all N in the
-// first pass, afterwards the count of the bin picked by the pass before -- so the merged histogram
-// is its own completion signal and no separate barrier is paid.  Every workgroup of a row takes
-// the same pick from the same numbers.  The per-workgroup counts of candidates above / equal to
-// the threshold are published as count + 1 into cleared words, which the later workgroups of the
-// row poll for; from them each workgroup derives where its share of the ascending output starts.
-// Results are identical to the other two paths.
-//
-// Everything that crosses workgroups inside the launch goes through agent-scope atomics (adds,
-// loads, stores), which are performed beyond the per-XCD L2s.  The waits are bounded: the host
-// launches this kernel only with at most kMultiMaxGroups workgroups, half of what the chip's 256
-// compute units hold at once even at one such workgroup each, so every workgroup that is waited
-// for is running or will be dispatched as soon as unrelated work drains; if a limit is reached
-// all the same (more than two such launches overlapping on different streams could do that), the
-// kernel still ends, sets *err and leaves undefined output.
-constexpr int kMultiMaxGroups = 128;
 
 // All 1024 threads: poll the row's histogram of a pass (thread t owns digits 2t, 2t+1) until it
 // holds `expected` candidates, then leave that snapshot in h.
@@ -558,115 +541,142 @@ __device__ __forceinline__ void multi_wait_hist(const int *gh, int ndigits, int 
     __syncthreads();
 }
 
-// fused_pick that also reports how many candidates the picked digit holds (sel[2]).
-template <int PASS>
-__device__ __forceinline__ void multi_pick(uint32_t &prefix, int &krem, int &in_bin, const int *h, int *wtot, int *sel)
+// Bounded wait for a word that another workgroup sets to a value other than 0 (0 if it expires).
+template <typename T>
+__device__ __forceinline__ T multi_wait_word(const T *word, int spin_limit, int *err)
 {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int l0 = h[2 * tid], l1 = h[2 * tid + 1], sum = l0 + l1;
-    int incl = sum;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(incl, o);
-        if (lane >= o) incl += y;
+    for (int spins = 0;; ++spins) {
+        const T v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (v != 0) return v;
+        if (spins >= spin_limit) {
+            if (err) atomicExch(err, 1);
+            return v;
+        }
+        __builtin_amdgcn_s_sleep(1);
     }
-    if (lane == 63) wtot[wave] = incl;
-    __syncthreads();
-    int below = incl - sum, total = 0;
-#pragma unroll
-    for (int w = 0; w < 16; ++w) {
-        const int x = wtot[w];
-        if (w < wave) below += x;
-        total += x;
-    }
-    const int above = total - below - sum;                    // candidates with a digit above 2t+1
-    if (above < krem && krem <= above + l1) { sel[0] = 2 * tid + 1; sel[1] = krem - above; sel[2] = l1; }
-    else if (above + l1 < krem && krem <= above + sum) { sel[0] = 2 * tid; sel[1] = krem - above - l1; sel[2] = l0; }
-    __syncthreads();
-    prefix = (prefix << (PASS == 2 ? 10 : 11)) | (uint32_t)sel[0];
-    krem = sel[1];
-    in_bin = sel[2];
-    __syncthreads();
 }
 
-template <int NIT>
-__global__ __launch_bounds__(1024) void select_multi(SelParams p, int parts)
+template <bool MULTI>
+__global__ __launch_bounds__(1024) void select_row(SelParams p, int parts, int nit)
 {
+    extern __shared__ v4u keys[];                                 // [nit * 1024]
     __shared__ int h[2048];
+    __shared__ v4u list[kSelList / 4];
     __shared__ int wtot[2][16];
-    __shared__ int sel[3];
-    __shared__ int before[2];
+    __shared__ int sel[3], before[2], list_n;
     const int q = blockIdx.x / parts, part = blockIdx.x % parts;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int N = (int)p.N;
+    const int wg_lo = part * (nit * 4096), w_lo = wg_lo + wave * (nit * 256);
+    v4u *mine = keys + wave * (nit * 64);
+    h[tid] = 0;
+    h[tid + 1024] = 0;
     if (tid < 3) sel[tid] = 0;
     if (tid < 2) before[tid] = 0;
-
-    const float *s = p.vals + (size_t)q * p.ld;
-    const int N = (int)p.N;
-    const int w_lo = part * (NIT * 4096) + wave * (NIT * 256);
-    const bool full = w_lo + NIT * 256 <= N;
-    uint32_t u[NIT][4];
-    range_keys<NIT>(p, s, N, w_lo, u);
+    if (tid == 2) list_n = 0;
+    if (tid < kSelList / 4) list[tid] = (v4u){0u, 0u, 0u, 0u};
+    __syncthreads();
+    load_keys(p, p.vals + (size_t)q * p.ld, N, w_lo, nit, mine);
+    if (!MULTI && !p.pre_zeroed)
+        for (long i = (long)q * 1024 + tid; i < p.zero_extra_n; i += (long)gridDim.x * 1024) p.zero_extra[i] = 0;
 
     uint32_t prefix = 0u;
-    int krem = p.k;
-    int expected = N;                                             // candidates the coming pass counts
-#define RF_MULTI_PASS(PASS)                                                                  \
-    {                                                                                        \
-        for (int i = tid; i < 2048; i += 1024) h[i] = 0;                                     \
-        __syncthreads();                                                                     \
-        if (full) fused_hist<NIT, PASS, true>(u, N, w_lo, prefix, h);                        \
-        else fused_hist<NIT, PASS, false>(u, N, w_lo, prefix, h);                            \
-        __syncthreads();                                                                     \
-        int *gh = p.hist + ((size_t)q * 3 + PASS) * 2048;                                    \
-        for (int i = tid; i < 2048; i += 1024)                                               \
-            if (h[i]) atomicAdd(&gh[i], h[i]);                                               \
-        __syncthreads();                                                                     \
-        multi_wait_hist(gh, PASS == 2 ? 1024 : 2048, expected, h, wtot[0], p.spin_limit, p.err); \
-        multi_pick<PASS>(prefix, krem, expected, h, wtot[0], sel);                           \
+    int krem = p.k, in_bin = N, shift = 21;
+#pragma unroll 1
+    for (int pass = 0; pass < 3; ++pass) {
+        const int bits = pass == 2 ? 10 : 11;
+        shift = pass == 0 ? 21 : pass == 1 ? 10 : 0;
+        if (pass) {
+            h[tid] = 0;
+            h[tid + 1024] = 0;
+            __syncthreads();
+        }
+        radix_hist(mine, N, w_lo, nit, shift, bits, prefix, h);
+        __syncthreads();
+        if constexpr (MULTI) {
+            int *gh = p.hist + ((size_t)q * 3 + pass) * 2048;
+            for (int i = tid; i < 2048; i += 1024)
+                if (h[i]) atomicAdd(&gh[i], h[i]);
+            __syncthreads();
+            multi_wait_hist(gh, 1 << bits, in_bin, h, wtot[0], p.spin_limit, p.err);
+        }
+        bin_pick(bits, prefix, krem, in_bin, h, wtot[0], sel);
+        if (in_bin <= kSelList) break;
     }
-    RF_MULTI_PASS(0)
-    RF_MULTI_PASS(1)
-    RF_MULTI_PASS(2)
-#undef RF_MULTI_PASS
-    const uint32_t T = prefix;
-    const int need_eq = max(krem, 0);
-
+    // here prefix holds the threshold's bits from `shift` up, shared by in_bin candidates
+    uint32_t T = prefix;
+    int need_eq = max(krem, 0);
+    const bool listed = shift > 0;
+    int *c = p.blk_cnt + (size_t)q * parts * 2;                   // MULTI: cleared words, 0 = not published yet
+    if (listed) {
+        unsigned long long *glist = (unsigned long long *)(p.hist + ((size_t)q * 3 + 2) * 2048);
+        int *gcount = p.hist + ((size_t)q * 3 + 2) * 2048 + 2047; // the third pass's histogram is still clear
+        int gt = 0;
+#pragma unroll 1
+        for (int it = 0; it < nit; ++it) {
+            const v4u u = mine[it * 64 + lane];
+            const int t = w_lo + it * 256 + 4 * lane;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (MULTI) gt += __popcll(__ballot(t + j < N && u[j] >> shift > prefix));
+                if (t + j < N && u[j] >> shift == prefix) {
+                    const unsigned at = MULTI ? atomicAdd(gcount, 1) : atomicAdd(&list_n, 1);
+                    if (at >= kSelList) continue;
+                    if (MULTI)
+                        __hip_atomic_store(&glist[at], (unsigned long long)u[j] << 32 | (unsigned)(t + j + 1),
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    else
+                        ((uint32_t *)list)[at] = u[j];
+                }
+            }
+        }
+        int at = N;
+        uint32_t key = 0u;
+        if constexpr (MULTI) {
+            if (lane == 0) wtot[0][wave] = gt;
+            __syncthreads();
+            if (tid == 0) {
+                int tot = 0;
+#pragma unroll
+                for (int w = 0; w < 16; ++w) tot += wtot[0][w];
+                __hip_atomic_store(&c[2 * part], tot + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            if (tid < in_bin) {
+                const unsigned long long e = multi_wait_word(&glist[tid], p.spin_limit, p.err);
+                key = (uint32_t)(e >> 32);
+                at = (int)(uint32_t)e - 1;
+                ((uint32_t *)list)[tid] = key;
+            } else if (tid >= 512 && tid - 512 < part) {          // part < 128
+                atomicAdd(&before[0], max(multi_wait_word(&c[2 * (tid - 512)], p.spin_limit, p.err) - 1, 0));
+            }
+        }
+        __syncthreads();
+        list_pick(list, in_bin, krem, T, need_eq, sel);
+        if (MULTI && at < wg_lo) {
+            if (key > T) atomicAdd(&before[0], 1);
+            if (key == T) atomicAdd(&before[1], 1);
+        }
+    }
     int gt_w, eq_w;
-    if (full) range_count<NIT, true>(u, N, w_lo, T, gt_w, eq_w);
-    else range_count<NIT, false>(u, N, w_lo, T, gt_w, eq_w);
+    range_count(mine, N, w_lo, nit, T, gt_w, eq_w);
     if (lane == 0) { wtot[0][wave] = gt_w; wtot[1][wave] = eq_w; }
     __syncthreads();
-    int *c = p.blk_cnt + (size_t)q * parts * 2;                   // cleared words: 0 = not published yet
-    if (tid < 2) {
-        int tot = 0;
+    if (MULTI && !listed) {
+        if (tid < 2) {
+            int tot = 0;
 #pragma unroll
-        for (int w = 0; w < 16; ++w) tot += wtot[tid][w];
-        __hip_atomic_store(&c[2 * part + tid], tot + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    // candidates above / equal to T in the workgroups before this one (2 * parts <= 256 < 1024 threads)
-    if (tid < 2 * part) {
-        int v = 0;
-        for (int spins = 0;; ++spins) {
-            v = __hip_atomic_load(&c[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (v != 0) break;
-            if (spins >= p.spin_limit) {
-                if (p.err) atomicExch(p.err, 1);
-                v = 1;
-                break;
-            }
-            __builtin_amdgcn_s_sleep(1);
+            for (int w = 0; w < 16; ++w) tot += wtot[tid][w];
+            __hip_atomic_store(&c[2 * part + tid], tot + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        atomicAdd(&before[tid & 1], v - 1);
+        // candidates above / equal to T in the workgroups before this one (2 * parts <= 256 < 1024 threads)
+        if (tid < 2 * part) atomicAdd(&before[tid & 1], max(multi_wait_word(&c[tid], p.spin_limit, p.err) - 1, 0));
+        __syncthreads();
     }
-    __syncthreads();
-    int base_gt = before[0], base_eq = before[1];
+    int base_gt = before[0], base_eq = before[1];                 // above / equal to T before this wave's range
 #pragma unroll
     for (int w = 0; w < 16; ++w)
         if (w < wave) { base_gt += wtot[0][w]; base_eq += wtot[1][w]; }
-    const int dest_run = base_gt + min(base_eq, need_eq);
-    if (full) range_emit<NIT, true>(p, q, u, N, w_lo, T, need_eq, dest_run, base_eq);
-    else range_emit<NIT, false>(p, q, u, N, w_lo, T, need_eq, dest_run, base_eq);
+    range_emit(p, q, mine, N, w_lo, nit, T, need_eq, base_gt + min(base_eq, need_eq), base_eq);
 }
 
 #define RF_CHECK_LAUNCH()                     \
@@ -675,15 +685,37 @@ __global__ __launch_bounds__(1024) void select_multi(SelParams p, int parts)
         if (e_ != hipSuccess) return e_;      \
     } while (0)
 
+template <bool MULTI>
+static hipError_t launch_select_row(const SelParams &p, long parts, int nit, hipStream_t st)
+{
+    auto kern = select_row<MULTI>;
+    // the keys of nit = 8 need more than the default 64 KB of LDS: raised once per device, not per launch
+    static std::atomic<bool> lds_raised[64];
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= 64 || !lds_raised[dev].load(std::memory_order_acquire)) {
+        e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 8 * 4096 * 4);
+        if (e != hipSuccess) return e;
+        if (dev >= 0 && dev < 64) lds_raised[dev].store(true, std::memory_order_release);
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)(p.nq * parts)), dim3(1024), (size_t)nit * 4096 * 4, st, p, (int)parts, nit);
+    return hipGetLastError();
+}
+
+// A compute unit takes about 1 us per 4096 candidates and step of the selection, three exchanges
+// between workgroups about 6 us in all, and an eviction pays a launch that clears the histograms.
+// One workgroup per row / several, whole calls: gather of one row of 6000 27.6 / 30.4 us, of 12000 32.4 /
+// 29.2 us, of 30000 74.5 / 58.5 us, 16 rows of 30000 55.4 / 43.7 us; eviction, 8 rows of 4113 37.2 / 40.9
+// us, of 32000 82.0 / 64.8 us.
+constexpr int kFusedMaxN = 8192;
+
 hipError_t select_topk(const SelParams &p, hipStream_t st)
 {
     if (p.N <= kFusedMaxN) {
-        if (p.N <= 4096) hipLaunchKernelGGL(select_fused<1>, dim3(p.nq), dim3(1024), 0, st, p);
-        else if (p.N <= 8192) hipLaunchKernelGGL(select_fused<2>, dim3(p.nq), dim3(1024), 0, st, p);
-        else if (p.N <= 16384) hipLaunchKernelGGL(select_fused<4>, dim3(p.nq), dim3(1024), 0, st, p);
-        else hipLaunchKernelGGL(select_fused<8>, dim3(p.nq), dim3(1024), 0, st, p);
-        RF_CHECK_LAUNCH();
-        return hipSuccess;
+        int nit = 1;
+        while (nit * 4096 < p.N) nit *= 2;
+        return launch_select_row<false>(p, 1, nit, st);
     }
     if (!p.pre_zeroed) {
         const long nz = max((long)p.nq * 3 * 2048, (long)p.zero_extra_n);
@@ -691,19 +723,12 @@ hipError_t select_topk(const SelParams &p, hipStream_t st)
         RF_CHECK_LAUNCH();
     }
     // one launch for the rest when the row's workgroups can all be resident together
-    if (p.multi_ok) {
+    if (p.multi_groups) {
         // at most half of the compute units (a partitioned device has fewer than 256)
-        const long max_groups = min((long)kMultiMaxGroups, (long)device_compute_units() / 2);
+        const long max_groups = min((long)p.multi_groups, (long)device_compute_units() / 2);
         for (int nit = 1; nit <= 8; nit *= 2) {
             const long parts = (p.N + (long)nit * 4096 - 1) / ((long)nit * 4096);
-            if ((long)p.nq * parts > max_groups) continue;
-            const dim3 grid((unsigned)(p.nq * parts));
-            if (nit == 1) hipLaunchKernelGGL(select_multi<1>, grid, dim3(1024), 0, st, p, (int)parts);
-            else if (nit == 2) hipLaunchKernelGGL(select_multi<2>, grid, dim3(1024), 0, st, p, (int)parts);
-            else if (nit == 4) hipLaunchKernelGGL(select_multi<4>, grid, dim3(1024), 0, st, p, (int)parts);
-            else hipLaunchKernelGGL(select_multi<8>, grid, dim3(1024), 0, st, p, (int)parts);
-            RF_CHECK_LAUNCH();
-            return hipSuccess;
+            if ((long)p.nq * parts <= max_groups) return launch_select_row<true>(p, parts, nit, st);
         }
     }
     const dim3 sgrid(p.nblk, p.nq);
