@@ -18,6 +18,7 @@
 // C[m][n]: lane l holds n = l%16 and, in accumulator element e, m = 4*(l/16) + e).
 #include "common.h"
 
+#include <algorithm>
 #include <atomic>
 
 namespace reform {
@@ -131,9 +132,14 @@ __device__ __forceinline__ float softmax_row(const f32x4 (&s)[4], float c, float
     return rs;
 }
 
-// Forward: out, lse.  One workgroup = 8 waves; a wave owns 32 chunk rows of one query head.  The
-// waves of a workgroup cover `gp` query heads of one KV group times 8/gp row slabs, so the K/V
-// tiles staged in LDS (two K slots, three V slots, one barrier per 64-key tile) serve every wave.
+// Forward: out, lse.  One workgroup = 8 waves; a wave owns 32 query rows.  The query rows of a KV head
+// are counted over its chunk rows and the G heads of its group together (row r is chunk row r / G
+// of head r % G), and a workgroup takes 256 of them, so the K/V tiles staged in LDS (two K slots,
+// three V slots, one barrier per 64-key tile) serve every wave and every head whatever G is, and
+// only the last row block of a KV head is padded.  With one, two or four heads per row block, whichever
+// divides G, and each head's chunk rows padded by themselves: four tokens over 60000 keys with 24/8
+// heads 108 us, now 41; one over 20000 with 14/2 heads of 64 24 us, now 13.6; 300 rows over 1500 keys
+// with 24/8 heads 66 us, now 56 (with the score).
 //
 // MFMA shape: v_mfma_f32_16x16x32_bf16 (A[m][k]: lane l holds m = l%16, k = 8*(l/16)..+7; B[k][n]:
 // n = l%16, same k; C[m][n]: n = l%16, m = 4*(l/16) + e).  Measured on gfx950 with random bf16
@@ -157,6 +163,7 @@ __device__ __forceinline__ float softmax_row(const f32x4 (&s)[4], float c, float
 //   - tile addresses are a uniform base plus per-thread constants computed once.
 constexpr float kBigSum = 65536.0f;
 constexpr int kFwdWaves = 8;
+constexpr int kFwdRows = kFwdWaves * 32;                       // query rows of a row block
 
 template <int D>
 constexpr size_t fwd_lds_bytes()
@@ -164,18 +171,20 @@ constexpr size_t fwd_lds_bytes()
     return sizeof(u16) * (size_t)(5 * 64 * (D + 16));      // two K slots, three V slots
 }
 
-// Key tiles of row block rb (64-key tiles up to the last key its last row sees).
-__device__ __forceinline__ int fwd_row_block_tiles(const AttnParams &p, int rwg, int rb)
+// Key tiles of row block rb (64-key tiles up to the last key its last row sees):
+// (M + (last row) / G) / 64 + 1.  For a full row block that is (a + rows / 64 * rb) / G + 1 with
+// a = (M G + rows - 1) / 64, rows = kFwdRows being a multiple of 64.
+__host__ __device__ __forceinline__ int fwd_row_block_tiles(const AttnParams &p, int rb)
 {
-    return (p.M + min(rb * rwg + rwg, p.Ct) - 1) / 64 + 1;
+    const int last = min((rb + 1) * kFwdRows, p.G * p.Ct) - 1;
+    return (p.M + last / p.G) / 64 + 1;
 }
 
-// One workgroup's pass of row block rb of head subgroup hs over the key tiles [t0, t1).  With
+// One workgroup's pass of row block rb over the key tiles [t0, t1).  With
 // SPLIT the result is either final (the range covers the whole row block) or goes, unnormalised,
 // to partial slot `slot`; without it the range is the whole row block.
 template <int D, bool SPLIT>
-__device__ __forceinline__ void fwd_segment(const AttnParams &p, u16 *smem, int kvh, int hs, int rb, int t0, int t1,
-                                            long slot)
+__device__ __forceinline__ void fwd_segment(const AttnParams &p, u16 *smem, int kvh, int rb, int t0, int t1, long slot)
 {
     constexpr int NW = kFwdWaves;
     constexpr int NT = NW * 64;
@@ -197,10 +206,21 @@ __device__ __forceinline__ void fwd_segment(const AttnParams &p, u16 *smem, int 
     const int ln = lane & 15;
     const int lg = lane >> 4;
 
-    const int slabs = NW / p.gp;
-    const int head = kvh * p.G + hs * p.gp + (wave % p.gp);
-    const int rwg = slabs * 32;
-    const int w0 = rb * rwg + (wave / p.gp) * 32;
+    const int rows = p.G * p.Ct;
+    // Which 32 of the row block's rows the wave has: lane's row in 16-row block nb is row0 + rstep * (16 nb
+    // + ln).  p.by_head (G divides the waves, so a full row block is kFwdRows / G chunk rows of every head): consecutive
+    // chunk rows of one head; otherwise consecutive rows.
+    const int slab = p.by_head ? wave / p.G : wave, rstep = p.by_head ? p.G : 1;
+    const int row0 = rb * kFwdRows + slab * 32 * rstep + (p.by_head ? wave % p.G : 0);
+    // Chunk row and head of this lane's row.  Formed where needed, from a G the compiler cannot relate to
+    // the other uses: kept, the four values cost registers in the main loop.
+    auto locate = [&](int nb, int &chunk_row, size_t &head) {
+        int G = p.G;
+        asm volatile("" : "+s"(G));
+        const int r = min(row0 + rstep * (16 * nb + ln), rows - 1);
+        chunk_row = r / G;
+        head = kvh * G + r % G;
+    };
 
     const int jbase = SPLIT ? t0 * BN : 0;               // first key of the range; tiles below count from it
     const u16 *Kg = (const u16 *)p.k + ((size_t)kvh * p.cap + jbase) * D;
@@ -210,19 +230,20 @@ __device__ __forceinline__ void fwd_segment(const AttnParams &p, u16 *smem, int 
     // Q^T operands of the wave's two 16-row query blocks stay in registers for the whole pass
     v4u qreg[2][KS];
     {
-        const u16 *Qh = (const u16 *)p.q + (size_t)head * p.q_hs;
 #pragma unroll
         for (int nb = 0; nb < 2; ++nb) {
-            int row = w0 + 16 * nb + ln;
-            row = row < p.Ct ? row : p.Ct - 1;
-            const u16 *src = Qh + (size_t)row * p.q_rs + 8 * lg;
+            int row;
+            size_t head;
+            locate(nb, row, head);
+            const u16 *src = (const u16 *)p.q + head * p.q_hs + (size_t)row * p.q_rs + 8 * lg;
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) qreg[nb][ks] = *(const v4u *)(src + ks * 32);
         }
     }
 
-    const int ntiles = SPLIT ? t1 - t0 : fwd_row_block_tiles(p, rwg, rb);
-    const int wave_last_key = (w0 < p.Ct) ? M + min(w0 + 32, p.Ct) - 1 : -1;
+    const int ntiles = SPLIT ? t1 - t0 : fwd_row_block_tiles(p, rb);
+    const int wave_first_row = row0 / p.G;
+    const int wave_last_key = (row0 < rows) ? M + min(row0 + 31 * rstep, rows - 1) / p.G : -1;
 
     f32x4 o[2][DB];
     float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
@@ -256,11 +277,14 @@ __device__ __forceinline__ void fwd_segment(const AttnParams &p, u16 *smem, int 
     int vslot = 0;                                                    // t mod 3
 
     auto mask_tile = [&](f32x4 (&s)[2][4], int j0) {
-        if (j0 + BN - 1 > M + w0) {
+        if (j0 + BN - 1 > M + wave_first_row) {
             asm volatile("; mask path" ::: "memory");      // diagonal tiles only: keep out of line
 #pragma unroll
             for (int nb = 0; nb < 2; ++nb) {
-                const int lim = M + w0 + 16 * nb + ln - j0;   // key offset <= lim is visible
+                int row;
+                size_t head;
+                locate(nb, row, head);
+                const int lim = M + row - j0;                 // key offset <= lim is visible
 #pragma unroll
                 for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
@@ -452,14 +476,13 @@ __device__ __forceinline__ void fwd_segment(const AttnParams &p, u16 *smem, int 
         // a partial result: every row of the slot is written (a wave that saw no key leaves m = -inf, l = 0)
         float *po = p.part_o + (size_t)slot * p.part_rows * D;
         float2 *pml = p.part_ml + (size_t)slot * p.part_rows;
-        const int rows = p.part_rows / p.gp;             // chunk rows per head in the slot
 #pragma unroll
         for (int nb = 0; nb < 2; ++nb) {
-            const int row = w0 + 16 * nb + ln;
+            const int row = row0 + rstep * (16 * nb + ln);
             float l_tot = l_run[nb] + __shfl_xor(l_run[nb], 16);
             l_tot += __shfl_xor(l_tot, 32);
-            if (row >= p.Ct) continue;
-            const int pr = (wave % p.gp) * rows + (row - rb * rwg);
+            if (row >= rows) continue;
+            const int pr = row - rb * kFwdRows;
 #pragma unroll
             for (int db = 0; db < DB; ++db)
                 *(f32x4 *)(po + (size_t)pr * D + db * 16 + 4 * lg) = o[nb][db];
@@ -468,15 +491,17 @@ __device__ __forceinline__ void fwd_segment(const AttnParams &p, u16 *smem, int 
         return;
     }
     if (!SPLIT && wave_last_key < 0) return;
-    u16 *Oh = (u16 *)p.out + (size_t)head * p.o_hs;
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) {
-        const int row = w0 + 16 * nb + ln;
+        const int row = row0 + rstep * (16 * nb + ln);
         float l_tot = l_run[nb] + __shfl_xor(l_run[nb], 16);
         l_tot += __shfl_xor(l_tot, 32);
-        if (row >= p.Ct) continue;
+        if (row >= rows) continue;
+        int chunk_row;
+        size_t head;
+        locate(nb, chunk_row, head);
         const float inv = 1.0f / l_tot;
-        u16 *dst = Oh + (size_t)row * p.o_rs;
+        u16 *dst = (u16 *)p.out + head * p.o_hs + (size_t)chunk_row * p.o_rs;
 #pragma unroll
         for (int db = 0; db < DB; ++db) {
             v2u w;
@@ -484,14 +509,16 @@ __device__ __forceinline__ void fwd_segment(const AttnParams &p, u16 *smem, int 
             w.y = pack_bf16x2(o[nb][db][2] * inv, o[nb][db][3] * inv);
             *(v2u *)(dst + db * 16 + 4 * lg) = w;
         }
-        if (lg == 0) p.lse[(size_t)head * p.Ct + row] = (m_run[nb] * c + __builtin_amdgcn_logf(l_tot)) * kLn2;
+        if (lg == 0) p.lse[head * p.Ct + chunk_row] = (m_run[nb] * c + __builtin_amdgcn_logf(l_tot)) * kLn2;
     }
 }
 
 // SPLIT: for problems with few row blocks (a generated token has one per KV head) or a number of them
 // that fills the last round of workgroups badly.  A KV head's key tiles, over all its row
-// blocks, form one list; `shares` workgroups take equal parts of it, whatever row blocks these cut
-// through.  A row block that one workgroup covers alone is finished there, the pieces of the
+// blocks, form one list, with p.start empty places before each row block's tiles for the time it
+// takes to begin one (without a cache the first ones have a tile or two: 5000 rows, 14/2 heads, with the
+// score 263 us without the empty places, 212 with four); `shares` workgroups take equal parts of it, whatever row
+// blocks these cut through.  A row block that one workgroup covers alone is finished there, the pieces of the
 // others are merged by attn_fwd_merge.  blockIdx % Hkv is the KV head in both forms, so with
 // eight of them an XCD's L2 sees one head's K/V.
 template <int D, bool SPLIT>
@@ -500,34 +527,36 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2) void attn_fwd_bf16(AttnParams p)
     extern __shared__ __attribute__((aligned(16))) u16 smem[];
     const int bid = blockIdx.x;
     const int kvh = bid % p.Hkv;
-    const int nsub = p.G / p.gp;
     if constexpr (SPLIT) {
-        const int rwg = kFwdWaves / p.gp * 32;
         const int share = bid / p.Hkv;
         const int begin = share * p.tiles / p.shares, end = (share + 1) * p.tiles / p.shares;
-        int rb = 0, hs = 0;
-        int pos = 0;                                     // list position of (rb, hs)'s first tile
-        int nt = fwd_row_block_tiles(p, rwg, 0);
-        while (pos + nt <= begin) {
-            pos += nt;
-            if (++hs == nsub) { hs = 0; nt = fwd_row_block_tiles(p, rwg, ++rb); }
-        }
+        // walk to the row block of the first tile; q and r: quotient and remainder of a + rows / 64 * rb by G
+        int rb = 0, pos = p.start, nt;                   // pos: list position of rb's first tile
+        const int a = (p.M * p.G + kFwdRows - 1) / 64;
+        int q = a / p.G, r = a % p.G;
+        auto tiles = [&]() { return rb + 1 < p.n_row_blocks ? q + 1 : (p.M + p.Ct - 1) / 64 + 1; };
+        auto next = [&]() {
+            pos += nt + p.start;
+            ++rb;
+            for (r += kFwdRows / 64; r >= p.G; r -= p.G) ++q;
+            nt = tiles();
+        };
+        nt = tiles();
+        while (pos + nt <= begin) next();
         bool first = true;
         while (pos < end) {
-            const int t0 = max(begin - pos, 0), t1 = min(end - pos, nt);
+            const int t0 = max(begin - pos, 0), t1 = min(end - pos, nt);      // t0 < nt, t1 > 0
             // a workgroup leaves at most two pieces: the end of a row block it begins in, and the
             // beginning of the one it ends in
             const long slot = t0 == 0 && t1 == nt ? -1 : (long)bid * 2 + (t0 == 0 ? 1 : 0);
             if (!first) __syncthreads();                 // lagging waves still read the last V tile
             first = false;
-            fwd_segment<D, true>(p, smem, kvh, hs, rb, t0, t1, slot);
-            pos += nt;
-            if (++hs == nsub) { hs = 0; if (pos < end) nt = fwd_row_block_tiles(p, rwg, ++rb); }
+            fwd_segment<D, true>(p, smem, kvh, rb, t0, t1, slot);
+            next();
         }
     } else {
-        // block -> (kv head, head subgroup, row block); heavy (late) row blocks first
-        const int rest = bid / p.Hkv;
-        fwd_segment<D, false>(p, smem, kvh, rest % nsub, p.n_row_blocks - 1 - rest / nsub, 0, 0, -1);
+        // block -> (kv head, row block); heavy (late) row blocks first
+        fwd_segment<D, false>(p, smem, kvh, p.n_row_blocks - 1 - bid / p.Hkv, 0, 0, -1);
     }
 }
 
@@ -536,20 +565,20 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2) void attn_fwd_bf16(AttnParams p)
 // exponential, so with many pieces per row (MANY: a token's row has as many as its KV head has
 // shares) all groups of a workgroup take one row together, and their sums meet in LDS: 33 pieces
 // of one row 8 us with one group, 3 us with eight.  grid (rows of a row block / rows per
-// workgroup, row block x subgroup, KV head).
+// workgroup, row block, KV head).
 template <int D, bool MANY>
 __global__ __launch_bounds__(256) void attn_fwd_merge(AttnParams p)
 {
     constexpr int L = D / 4, GROUPS = 256 / L;
     __shared__ f32x4 so[MANY ? GROUPS : 1][L];
     __shared__ float2 sml[GROUPS];
-    const int nsub = p.G / p.gp;
-    const int rb = blockIdx.y / nsub, hs = blockIdx.y % nsub, kvh = blockIdx.z;
-    const int rwg = kFwdWaves / p.gp * 32;
-    // list position of the row block: rwg is a multiple of 64, so every whole row block adds rwg/64 tiles
-    const int k64 = rwg / 64, base = fwd_row_block_tiles(p, rwg, 0);
-    const int nt = fwd_row_block_tiles(p, rwg, rb);
-    const int pos = hs * nt + (rb > 0 ? nsub * (rb * base + k64 * (rb * (rb - 1) / 2)) : 0);
+    const int rb = blockIdx.y, kvh = blockIdx.z;
+    int pos = 0;                                         // list position of the row block's first tile
+    for (int b = threadIdx.x & 63; b < rb; b += 64) pos += p.start + fwd_row_block_tiles(p, b);
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) pos += __shfl_xor(pos, o);
+    pos += p.start;
+    const int nt = fwd_row_block_tiles(p, rb);
     // shares that hold a tile of [pos, pos + nt): share j holds [j*tiles/shares, (j+1)*tiles/shares)
     const unsigned T = p.tiles, S = p.shares;
     const int j0 = (int)(((unsigned)(pos + 1) * S - 1) / T), j1 = (int)(((unsigned)(pos + nt) * S - 1) / T);
@@ -557,9 +586,8 @@ __global__ __launch_bounds__(256) void attn_fwd_merge(AttnParams p)
     const int grp = threadIdx.x / L, c4 = (threadIdx.x % L) * 4;
     const int pr = MANY ? blockIdx.x : blockIdx.x * GROUPS + grp;
     if (pr >= p.part_rows) return;
-    const int rows = p.part_rows / p.gp;
-    const int row = rb * rwg + pr % rows, head = kvh * p.G + hs * p.gp + pr / rows;
-    if (row >= p.Ct) return;
+    if (rb * kFwdRows + pr >= p.G * p.Ct) return;
+    const int row = (rb * kFwdRows + pr) / p.G, head = kvh * p.G + (rb * kFwdRows + pr) % p.G;
     // share j0's piece is the end of a row block (slot 0) unless this one begins inside the share
     // (slot 1); the later shares begin inside this one (slot 0)
     const bool begins = (int)((unsigned)j0 * T / S) <= pos;
@@ -701,6 +729,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_score_bf16(AttnParams p)
     const int kvh = blockIdx.x % p.Hkv;
     const int nkt = (p.n + NW * WKEYS - 1) / (NW * WKEYS);
     const int slice = p.slices - 1 - blockIdx.x / p.Hkv / nkt;
+    const int tile_slice = slice / p.head_slices;
+    const int g0 = slice % p.head_slices * p.slice_heads, heads = min(p.slice_heads, p.G - g0);
     const int kt = blockIdx.x / p.Hkv % nkt;
     const int j_wg = kt * (NW * WKEYS);
     const int jw = j_wg + wave * WKEYS;
@@ -708,7 +738,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_score_bf16(AttnParams p)
     const int i_lo = p.Ct - p.W;                         // first observing row
     const int i_first = max(i_lo, max(j_wg - p.M, 0));   // first row that both observes and sees j_wg
     // query tiles of this slice: slices are counted from the first observing tile for every key block
-    const int s_lo = i_lo / QT + slice * p.slice_tiles;
+    const int s_lo = i_lo / QT + tile_slice * p.slice_tiles;
     const int qt0 = max(i_first / QT, s_lo);
     const int ntq = min((p.Ct + QT - 1) / QT, s_lo + p.slice_tiles) - qt0;   // per head
     if (ntq <= 0) return;                                // the whole slice lies before the diagonal
@@ -728,14 +758,14 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_score_bf16(AttnParams p)
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) col[kb] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
-    const int iters = p.G * ntq;
+    const int iters = heads * ntq;
     const float c = p.scale * kLog2e;
     const int q_frag0 = ln * QROW + 8 * lg;
 
     Stage st;
     st.init(tid, p.q_rs);
     auto load_q = [&](int it) {
-        const int head = kvh * p.G + it / ntq;
+        const int head = kvh * p.G + g0 + it / ntq;
         const int i0 = (qt0 + it % ntq) * QT;
         st.load((const u16 *)p.q + (size_t)head * p.q_hs + (size_t)i0 * p.q_rs,
                 p.lse + (size_t)head * p.Ct + i0, p.Ct - i0, i_lo - i0, p.q_rs, tid);
@@ -883,7 +913,7 @@ __global__ __launch_bounds__(256) void attn_score_sum(AttnParams p, int keys)
     const int i_lo = p.Ct - p.W, i_first = max(i_lo, max(j / keys * keys - p.M, 0));
     float x = 0.f;
 #pragma unroll 4
-    for (int s = (i_first / 64 - i_lo / 64) / p.slice_tiles; s < p.slices; ++s)
+    for (int s = (i_first / 64 - i_lo / 64) / p.slice_tiles * p.head_slices; s < p.slices; ++s)
         x += p.part_score[((size_t)s * p.Hkv + kvh) * p.n + j];
     float *dst = p.score + (size_t)kvh * p.cap + j;
     *dst = p.accumulate ? *dst + x : x;
@@ -990,44 +1020,48 @@ __global__ __launch_bounds__(256) void attn_score_few(AttnParams p)
 
 // ------------------------------------------------------------------------------------------
 // Host-side launchers (called from the C-ABI file).
-// How the forward pass of a problem is cut into workgroups: gp, n_row_blocks and, if the key range
-// is to be split, shares, tiles and part_rows.
+// How the forward pass of a problem is cut into workgroups: n_row_blocks and, if the key range is to be
+// split, shares, tiles and part_rows.
 static void fwd_plan(AttnParams &p)
 {
-    p.gp = p.G % 4 == 0 ? 4 : p.G % 2 == 0 ? 2 : 1;
-    const int rwg = kFwdWaves / p.gp * 32, nsub = p.G / p.gp;
-    p.n_row_blocks = (p.Ct + rwg - 1) / rwg;
+    const int rows = p.G * p.Ct;
+    p.n_row_blocks = (rows + kFwdRows - 1) / kFwdRows;
     p.shares = 0;
-    p.part_rows = p.gp * (p.Ct < rwg ? p.Ct : rwg);
+    p.part_rows = std::min(rows, kFwdRows);
+    // Waves of one head are 0.6 % to 1.3 % faster where they are full (8192 rows over 8192 keys, 32768 over
+    // 32768, 32/8 heads); with few chunk rows they would be nearly empty (one token: 20.6 instead of 18.3 us).
+    p.by_head = kFwdWaves % p.G == 0 && p.Ct >= 32;
     const int cus = device_compute_units() > 0 ? device_compute_units() : 256;
-    const long whole = (long)p.Hkv * nsub * p.n_row_blocks;
+    const long whole = (long)p.Hkv * p.n_row_blocks;
     if (whole > 4l * cus || p.Hkv > cus) return;         // at least four well-filled rounds
-    // rwg is a multiple of 64: every row block but the last has rwg/64 tiles more than the one before
-    const long first = (p.M + rwg - 1) / 64 + 1, nrb = p.n_row_blocks, longest = (p.M + p.Ct - 1) / 64 + 1;
-    const long tiles = nsub * ((nrb - 1) * first + (nrb - 1) * (nrb - 2) / 2 * (rwg / 64) + longest);
-    // Time of either form, in key tiles of one workgroup (one workgroup is resident per compute unit):
-    // whole row blocks run in rounds; equal shares add their partial results, about 28 tiles' time
-    // for full slots of 256 x 128 on every compute unit, written and read back, and a launch that
-    // merges them.  Measured, whole -> split: one token over 16640 keys (32/8 heads, head_dim 128)
-    // 290 -> 21 us; 17 rows over 4096 keys of 8 heads 70 -> 13 us; 512 rows over 8192 keys 202 -> 83
-    // us; 3001 rows over 8192 keys (24/8 heads, head_dim 64: 288 row blocks) 306 -> 214 us; 16000
-    // over 500 keys of 8 heads (504 row blocks) 537 -> 468 us; 3000 rows, no cache (16/4 heads: 188
-    // row blocks of up to 47 tiles) 83 -> 87 us, so left whole.
-    const long per_head = cus / p.Hkv;
-    const long shares = tiles / 2 < per_head ? tiles / 2 : per_head;
-    if (shares < 2 || tiles * (shares + 1) >= (1l << 31)) return;
+    const long longest = (p.M + p.Ct - 1) / 64 + 1;
+    p.start = p.n_row_blocks > 1 ? 4 : 0;
+    long tiles = 0;
+    for (int rb = 0; rb < p.n_row_blocks; ++rb) tiles += p.start + fwd_row_block_tiles(p, rb);
+    // Time of either form, in key tiles of one workgroup (1.45 us at head_dim 128, 1.1 us at 64; one
+    // workgroup is resident per compute unit).  Whole row blocks run in rounds.  Equal shares pay the
+    // launch that merges them and the partial results, written and read back, which grow with their
+    // size, with the number of shares, and double where a share can begin and end inside row blocks.
+    // Fitted to (us; whole, then with the number of shares per KV head): 60 rows over 8000 keys, 32/8
+    // heads 183, 38 (8), 29 (16), 26 (32); 300 over 1500, 24/8 heads 48, 45 (8), 37 (13), 43 (32); 2000
+    // over 4000, 8 heads 138, 95 (13), 66 (24), 61 (32); 60 over 8000, 14/2 heads, head_dim 64 136, 28
+    // (16), 18.6 (64), 20.6 (128).  One token over 16640 keys (32/8 heads) 290 -> 18 us.
     const double rounds = (double)((whole + cus - 1) / cus);
-    const double t_whole = whole <= cus ? (double)longest : rounds * (double)tiles * p.Hkv / (double)whole;
-    const double slot = p.part_rows * p.D / (256.0 * 128.0), busy = (double)shares * p.Hkv / cus;
-    const double t_split = (double)tiles / shares + 4.0 + slot * (4.0 + 24.0 * busy);
-    if (t_split >= t_whole) return;
+    double best = whole <= cus ? 4.0 + (double)longest : rounds * (double)tiles * p.Hkv / (double)whole;
+    const double slot = p.part_rows * p.D / (256.0 * 128.0) * (p.n_row_blocks > 1 ? 2.0 : 1.0);
+    long shares = 0;
+    for (long s = std::min(tiles / 2, (long)cus / p.Hkv); s >= 2; s -= (s + 7) / 8) {
+        const double t = (double)tiles / s + 4.0 + slot * (4.5 + 5.5 * (double)s * p.Hkv / cus);
+        if (t < best) { best = t; shares = s; }
+    }
+    if (!shares || tiles * (shares + 1) >= (1l << 31)) return;
     p.shares = (int)shares;
     p.tiles = (int)tiles;
 }
 
-static size_t fwd_split_bytes(AttnParams p)
+// Bytes of the partial results of a planned problem.
+static size_t fwd_split_bytes(const AttnParams &p)
 {
-    fwd_plan(p);
     return (size_t)p.shares * p.Hkv * 2 * p.part_rows * (p.D * sizeof(float) + sizeof(float2));
 }
 
@@ -1055,9 +1089,8 @@ template <int D>
 static hipError_t launch_fwd(AttnParams p, void *part, size_t part_bytes, hipStream_t st)
 {
     fwd_plan(p);
-    const int nsub = p.G / p.gp;
     if (!p.shares || !part || part_bytes < fwd_split_bytes(p))
-        return launch_fwd_form<D, false>(p, p.Hkv * nsub * p.n_row_blocks, st);
+        return launch_fwd_form<D, false>(p, p.Hkv * p.n_row_blocks, st);
     p.part_o = (float *)part;
     p.part_ml = (float2 *)(p.part_o + (size_t)p.shares * p.Hkv * 2 * p.part_rows * D);
     hipError_t e = launch_fwd_form<D, true>(p, p.shares * p.Hkv, st);
@@ -1065,18 +1098,20 @@ static hipError_t launch_fwd(AttnParams p, void *part, size_t part_bytes, hipStr
     // pieces of the longest row block: two or three where row blocks are many, a head's shares for a token
     const long pieces = ((long)((p.M + p.Ct - 1) / 64 + 1) * p.shares) / p.tiles + 1;
     const int groups = 256 / (D / 4);
-    if (pieces > 6) {
-        const dim3 grid(p.part_rows, p.n_row_blocks * nsub, p.Hkv);
+    // (11200 rows of up to 8 pieces at head_dim 64: 19 us with a workgroup per row, 6 us without)
+    const long merged_rows = (long)p.Hkv * p.n_row_blocks * p.part_rows;
+    if (pieces > 12 || (pieces > 6 && merged_rows <= 2048)) {
+        const dim3 grid(p.part_rows, p.n_row_blocks, p.Hkv);
         hipLaunchKernelGGL((attn_fwd_merge<D, true>), grid, dim3(256), 0, st, p);
     } else {
-        const dim3 grid((p.part_rows + groups - 1) / groups, p.n_row_blocks * nsub, p.Hkv);
+        const dim3 grid((p.part_rows + groups - 1) / groups, p.n_row_blocks, p.Hkv);
         hipLaunchKernelGGL((attn_fwd_merge<D, false>), grid, dim3(256), 0, st, p);
     }
     return hipGetLastError();
 }
 
-// How the score pass of a problem is cut into workgroups: waves per workgroup (returned), slices and
-// slice_tiles.  Time is estimated in query tiles that a compute unit takes against 512 keys (2.1 us
+// How the score pass of a problem is cut into workgroups: waves per workgroup (returned), slices,
+// slice_tiles, head_slices and slice_heads.  Time is estimated in query tiles that a compute unit takes against 512 keys (2.1 us
 // at head_dim 128); at most two workgroups of four waves or one of eight are resident on it.
 //   - Eight waves, uncut: the fewest Q bytes per key, the best form where its workgroups fill the chip
 //     evenly.  Keys of the cache (and of the chunk before the window) cost the same each; those of
@@ -1098,16 +1133,30 @@ static int score_plan(AttnParams &p)
     double best = rounds > total ? rounds : total;
     if (best < iters) best = iters;
     int waves = 8;
-    p.slices = 1;
+    p.slices = p.head_slices = 1;
     p.slice_tiles = tiles;
-    for (int want = 1; want <= 16; want *= 2) {
-        const int per = (tiles + want - 1) / want, slices = (tiles + per - 1) / per;
-        const double item = (double)p.G * per, items = 2.0 * total * cus / item;
+    p.slice_heads = p.G;
+    auto consider = [&](int per, int heads) {            // slices of `per` tiles of `heads` heads
+        const int hs = (p.G + heads - 1) / heads, slices = (tiles + per - 1) / per * hs;
+        const double item = (double)heads * per, items = 2.0 * total * cus / item;
         double t = total + 0.5 * item;
         if (t < item) t = item;
         t += 1.5 * items / (2.0 * cus) + (slices > 1 ? 2.0 : 0.0);
-        if (t < best) { best = t; waves = 4; p.slices = slices; p.slice_tiles = per; }
-    }
+        if (t >= best) return;
+        best = t;
+        waves = 4;
+        p.slices = slices;
+        p.slice_tiles = per;
+        p.head_slices = hs;
+        p.slice_heads = heads;
+    };
+    for (int want = 1; want <= 16; want *= 2) consider((tiles + want - 1) / want, p.G);
+    // Where that leaves compute units without a workgroup the heads are cut as well: 60 rows over 8000 keys
+    // with 14/2 heads of 64 (32 workgroups of 7 tiles) 38 -> 31 us for the call, 30 over 1000 with 14/2 of
+    // 128 38 -> 28 us.  (On a chip that is busy it gives nothing: 2000 rows over 1000 keys, 32/8 heads, 18.9
+    // -> 19.8 us.)
+    if ((waves == 8 ? all : (long)p.Hkv * ((p.n + 255) / 256) * p.slices) < cus)
+        for (int heads = (p.G + 1) / 2; heads >= 1; heads = heads > 1 ? (heads + 1) / 2 : 0) consider(1, heads);
     return waves;
 }
 
@@ -1144,7 +1193,8 @@ static hipError_t launch_score(AttnParams p, void *part, size_t part_bytes, hipS
     int waves = score_plan(p);
     if (p.slices > 1 && (!part || part_bytes < (size_t)p.slices * p.Hkv * p.n * sizeof(float))) {
         p.slice_tiles *= p.slices;                       // no room for partial sums: uncut
-        p.slices = 1;
+        p.slice_heads = p.G;
+        p.slices = p.head_slices = 1;
         waves = 8;
     }
     p.part_score = (float *)part;
@@ -1160,7 +1210,8 @@ size_t attend_bf16_scratch_bytes(const AttnParams &sizes)
         score_plan(p);
         if (p.slices > 1) score = (size_t)p.slices * p.Hkv * p.n * sizeof(float);
     }
-    const size_t fwd = fwd_split_bytes(sizes);
+    fwd_plan(p);
+    const size_t fwd = fwd_split_bytes(p);
     return fwd > score ? fwd : score;
 }
 

@@ -28,16 +28,18 @@ struct AttnParams {
     float scale;
     int W;           // resolved observation window, 1..Ct
     int accumulate;
-    int gp;          // query heads of one group that share a workgroup (1, 2 or 4)
     int n_row_blocks;
+    int by_head;     // how a row block's rows are dealt to the waves (see fwd_segment)
     // forward pass with the key range split over workgroups (see attn_fwd_bf16); shares == 0: whole
-    int shares;      // workgroups per KV head, each an equal share of the head's key tiles
-    int tiles;       // key tiles of one KV head, over its row blocks and head subgroups (tiles * shares < 2^31)
-    int part_rows;   // query rows (heads x chunk rows) of one partial result
+    int shares;      // workgroups per KV head, each an equal share of the list of the head's key tiles
+    int start;       // places of that list left empty before each row block's tiles
+    int tiles;       // length of the list: key tiles of one KV head and empty places (tiles * shares < 2^31)
+    int part_rows;   // query rows (over the heads of a group and the chunk rows) of one partial result
     float *part_o;   // [workgroup][2][part_rows][D] unnormalised outputs
     float2 *part_ml; // [workgroup][2][part_rows] reference maximum (log2 units) and running sum
     // score pass with the observing rows cut into slices (see attn_score_bf16)
-    int slices, slice_tiles;   // number of slices (1: uncut), query tiles of 64 rows in each
+    int slices;                // number of slices (1: uncut), = slices of the tiles x head_slices
+    int slice_tiles, head_slices, slice_heads;   // query tiles of 64 rows and heads of the group in each
     float *part_score;         // [slice][KV head][n] column sums of one slice, when there are several
 };
 
