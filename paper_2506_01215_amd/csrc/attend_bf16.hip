@@ -560,6 +560,139 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2) void attn_fwd_bf16(AttnParams p)
     }
 }
 
+// The split pass of at most 16 query rows (a generated token), which is bound by reading K and V and,
+// when they are short, by the time to start.  Nothing is shared between the waves: each takes every
+// eighth 32-key tile of the share, K as A operands straight from global memory and V through LDS of
+// its own (for the transposing loads), the next tile's loads in flight over this one's work, and no
+// barrier until the waves' sums meet at the end.  In the general form all eight waves stage every
+// tile and one of them computes: one token, 32/8 heads over 16640 keys (68 MB) 16.0 -> 13.5 us (5.0
+// TB/s), 2048 keys 8.2 -> 5.9 us; with the merge, 16/4 heads of 64 over 65000 keys 21.3 -> 16.7 us.
+// A form of 32 rows was slower than the general one (8 rows of 32/8 heads over 30000 keys 25.7 -> 27.4).
+template <int D>
+__global__ __launch_bounds__(kFwdWaves * 64) void attn_fwd_few(AttnParams p)
+{
+    constexpr int NW = kFwdWaves, KS = D / 32, DB = D / 16, C8 = D / 8, VP = D / 16;
+    constexpr int VROW = D + 16, OROW = D + 4, R = 16;
+    __shared__ __attribute__((aligned(16))) union { u16 v[NW][32 * VROW]; float o[NW / 2][R][OROW]; } sh;
+    __shared__ float sm[NW][R], sl[NW][R];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int ln = lane & 15, lg = lane >> 4;
+    const int kvh = blockIdx.x % p.Hkv, share = blockIdx.x / p.Hkv;
+    const int begin = share * p.tiles / p.shares, end = (share + 1) * p.tiles / p.shares;
+    const int s1 = min(2 * end, (p.n + 31) / 32);
+    const int rows = p.G * p.Ct;
+    const u16 *Kg = (const u16 *)p.k + (size_t)kvh * p.cap * D;
+    const u16 *Vg = (const u16 *)p.v + (size_t)kvh * p.cap * D;
+
+    v4u kreg[2][KS], vreg[VP];
+    auto load = [&](int s) {
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+            const u16 *src = Kg + (size_t)min(s * 32 + kb * 16 + ln, p.n - 1) * D + 8 * lg;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) kreg[kb][ks] = *(const v4u *)(src + ks * 32);
+        }
+#pragma unroll
+        for (int i = 0; i < VP; ++i)
+            vreg[i] = *(const v4u *)(Vg + (size_t)min(s * 32 + lane / C8 + i * (64 / C8), p.n - 1) * D + lane % C8 * 8);
+    };
+    int s = 2 * begin + wave;
+    if (s < s1) load(s);
+    v4u qreg[KS];
+        const int row = min(ln, rows - 1), chunk_row = row / p.G, lim = p.M + chunk_row;   // last key the row sees
+    {
+        const u16 *src = (const u16 *)p.q + (size_t)(kvh * p.G + row % p.G) * p.q_hs + (size_t)chunk_row * p.q_rs + 8 * lg;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) qreg[ks] = *(const v4u *)(src + ks * 32);
+    }
+    f32x4 o[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db) o[db] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    float m = -INFINITY, l = 0.f;
+    const float c = p.scale * kLog2e;
+    u16 *sv = sh.v[wave];
+    for (; s < s1; s += NW) {
+        const int j0 = s * 32;
+#pragma unroll
+        for (int i = 0; i < VP; ++i) *(v4u *)(sv + (lane / C8 + i * (64 / C8)) * VROW + lane % C8 * 8) = vreg[i];
+        f32x4 x[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) x[kb] = mfma16(kreg[kb][ks], qreg[ks], x[kb]);
+        if (s + NW < s1) load(s + NW);
+        float mx = -INFINITY;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            if (j0 + (e >> 2) * 16 + 4 * lg + (e & 3) > lim) x[e >> 2][e & 3] = -INFINITY;
+            mx = fmaxf(mx, x[e >> 2][e & 3]);
+        }
+        mx = fmaxf(mx, __shfl_xor(mx, 16));
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float m_new = fmaxf(m, mx);
+        const float ref = m_new == -INFINITY ? 0.f : m_new * c;         // -inf: the row sees no key yet
+        const float alpha = __builtin_amdgcn_exp2f(fmaf(m, c, -ref));
+        m = m_new;
+        float pv[8], sum = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            pv[e] = __builtin_amdgcn_exp2f(fmaf(x[e >> 2][e & 3], c, -ref));
+            sum += pv[e];
+        }
+        l = fmaf(l, alpha, sum);
+#pragma unroll
+        for (int db = 0; db < DB; ++db) o[db] *= alpha;
+        const v4u pb = {pack_bf16x2(pv[0], pv[1]), pack_bf16x2(pv[2], pv[3]), pack_bf16x2(pv[4], pv[5]),
+                        pack_bf16x2(pv[6], pv[7])};
+        const u16 *vf = sv + (4 * lg + (ln >> 2)) * VROW + 4 * (ln & 3);      // see lds_read_tr16
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+            const v2u lo = lds_read_tr16(vf + 16 * db), hi = lds_read_tr16(vf + 16 * VROW + 16 * db);
+            o[db] = mfma16((v4u){lo.x, lo.y, hi.x, hi.y}, pb, o[db]);
+        }
+    }
+    // the waves' sums: scaled to the common maximum, the upper half's handed to the lower half's, and
+    // those added up on the way out
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    if (lg == 0) { sm[wave][ln] = m; sl[wave][ln] = l; }
+    __syncthreads();                                     // also: the last V tiles have been read
+    float m_all = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) m_all = fmaxf(m_all, sm[w][ln]);
+    const float f = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m - m_all) * c);
+#pragma unroll
+    for (int db = 0; db < DB; ++db) {
+        o[db] *= f;
+        if (wave >= NW / 2) *(f32x4 *)&sh.o[wave - NW / 2][ln][db * 16 + 4 * lg] = o[db];
+    }
+    __syncthreads();
+    if (wave < NW / 2) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db) *(f32x4 *)&sh.o[wave][ln][db * 16 + 4 * lg] += o[db];
+    }
+    __syncthreads();
+    const size_t slot = (size_t)blockIdx.x * 2 + (begin == 0 ? 1 : 0);      // as in attn_fwd_bf16
+    float *po = p.part_o + slot * p.part_rows * D;
+    float2 *pml = p.part_ml + slot * p.part_rows;
+    for (int t = threadIdx.x; t < rows * (D / 4); t += NW * 64) {
+        const int r = t / (D / 4), c4 = t % (D / 4) * 4;
+        f32x4 y = *(const f32x4 *)&sh.o[0][r][c4];
+#pragma unroll
+        for (int w = 1; w < NW / 2; ++w) y += *(const f32x4 *)&sh.o[w][r][c4];
+        *(f32x4 *)(po + (size_t)r * D + c4) = y;
+        if (c4 == 0) {
+            float m_row = -INFINITY, l_row = 0.f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) m_row = fmaxf(m_row, sm[w][r]);
+#pragma unroll
+            for (int w = 0; w < NW; ++w)
+                l_row += sm[w][r] == -INFINITY ? 0.f : sl[w][r] * __builtin_amdgcn_exp2f((sm[w][r] - m_row) * c);
+            pml[r] = make_float2(m_row * c, l_row);
+        }
+    }
+}
+
 // Merges the pieces of the row blocks that several workgroups share: a group of D/4 lanes adds up
 // pieces of one query row, four output columns per lane.  Each piece is a dependent load and an
 // exponential, so with many pieces per row (MANY: a token's row has as many as its KV head has
@@ -1093,7 +1226,11 @@ static hipError_t launch_fwd(AttnParams p, void *part, size_t part_bytes, hipStr
         return launch_fwd_form<D, false>(p, p.Hkv * p.n_row_blocks, st);
     p.part_o = (float *)part;
     p.part_ml = (float2 *)(p.part_o + (size_t)p.shares * p.Hkv * 2 * p.part_rows * D);
-    hipError_t e = launch_fwd_form<D, true>(p, p.shares * p.Hkv, st);
+    const int grid = p.shares * p.Hkv, rows = p.G * p.Ct;
+    hipError_t e = hipSuccess;
+    if (rows <= 16) hipLaunchKernelGGL(attn_fwd_few<D>, dim3(grid), dim3(kFwdWaves * 64), 0, st, p);
+    else e = launch_fwd_form<D, true>(p, grid, st);
+    if (e == hipSuccess) e = hipGetLastError();
     if (e != hipSuccess) return e;
     // pieces of the longest row block: two or three where row blocks are many, a head's shares for a token
     const long pieces = ((long)((p.M + p.Ct - 1) / 64 + 1) * p.shares) / p.tiles + 1;
@@ -1101,11 +1238,11 @@ static hipError_t launch_fwd(AttnParams p, void *part, size_t part_bytes, hipStr
     // (11200 rows of up to 8 pieces at head_dim 64: 19 us with a workgroup per row, 6 us without)
     const long merged_rows = (long)p.Hkv * p.n_row_blocks * p.part_rows;
     if (pieces > 12 || (pieces > 6 && merged_rows <= 2048)) {
-        const dim3 grid(p.part_rows, p.n_row_blocks, p.Hkv);
-        hipLaunchKernelGGL((attn_fwd_merge<D, true>), grid, dim3(256), 0, st, p);
+        const dim3 mgrid(p.part_rows, p.n_row_blocks, p.Hkv);
+        hipLaunchKernelGGL((attn_fwd_merge<D, true>), mgrid, dim3(256), 0, st, p);
     } else {
-        const dim3 grid((p.part_rows + groups - 1) / groups, p.n_row_blocks, p.Hkv);
-        hipLaunchKernelGGL((attn_fwd_merge<D, false>), grid, dim3(256), 0, st, p);
+        const dim3 mgrid((p.part_rows + groups - 1) / groups, p.n_row_blocks, p.Hkv);
+        hipLaunchKernelGGL((attn_fwd_merge<D, false>), mgrid, dim3(256), 0, st, p);
     }
     return hipGetLastError();
 }

@@ -49,3 +49,20 @@ def test_rows_match_oracle(Hq, Hkv, d, M, Ct):
         assert_close(to_np(out), o_ref, 2e-2, "out", row_floor=True)
         assert_close(to_np(lse), l_ref, 1e-5, "lse")
         assert_scores_close(to_np(score)[:, :n], s_ref[:, :n], 1e-5, "score")
+
+
+@pytest.mark.parametrize("sign", [-1.0, 1.0])
+@pytest.mark.parametrize("Hq,Hkv,d,M,Ct", [(4, 1, 128, 5000, 1), (2, 2, 64, 700, 16), (3, 1, 64, 300, 6)])
+def test_few_rows_far_from_zero(Hq, Hkv, d, M, Ct, sign):
+    """All logits of a row near +-1400 (natural units): a sum that begins relative to zero overflows."""
+    g = torch.Generator().manual_seed(M)
+    q = torch.ones((Hq, Ct, d)).to(torch.bfloat16)
+    k = (sign * 40.0 + 0.25 * torch.randn((Hkv, M + Ct, d), generator=g)).to(torch.bfloat16)
+    v = torch.randn((Hkv, M + Ct, d), generator=g).to(torch.bfloat16)
+    scale = 35.0 / d
+    out, lse, _ = binding.reform_chunk_attend_score(q.to(DEV), k.to(DEV), v.to(DEV), M, scale, want_score=False)
+    torch.cuda.synchronize()
+    o_ref, l_ref, _ = oracle.attend_score(to_np(q), to_np(k), to_np(v), M, scale)
+    # fp32 logits of size 1400 carry an error of 1e-4: exp() of them 1e-4, within the bf16 bound
+    assert_close(to_np(out), o_ref, 2e-2, "out", row_floor=True)
+    assert_close(to_np(lse), l_ref, 1e-5, "lse")
