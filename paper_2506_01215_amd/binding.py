@@ -151,28 +151,34 @@ def _dtype_code(t):
     raise TypeError(f"unsupported dtype {t.dtype}")
 
 
+# A call on a short problem is bound by what happens on the host before its launches: pointers go to
+# ctypes as plain integers (the argument types are declared), and a workspace that the caller keeps is
+# neither sliced nor measured here, since the library checks its size.
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    if stream is None:      # the handle alone: building the Stream object takes 2 us
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
-def _workspace(nbytes, device, workspace, stream=None):
-    if nbytes == 0:
-        return None
+def _workspace(query, desc, device, workspace, stream=None):
+    """(address, bytes) of the 256-byte aligned part of the workspace; query(desc) gives the bytes a
+    temporary one needs when the caller has none."""
     if workspace is None:
+        nbytes = query(desc)
+        if nbytes == 0:
+            return None, 0
         workspace = torch.empty(nbytes + 256, dtype=torch.uint8, device=device)
         if stream is not None:
             # a temporary that is dropped on return while the kernels are only enqueued: tell the
             # caching allocator which stream still uses the block
             workspace.record_stream(stream)
-    off = (-workspace.data_ptr()) % 256
-    ws = workspace[off:]
-    return ws
+    base = workspace.data_ptr()
+    off = -base % 256
+    return base + off, max(workspace.numel() - off, 0)
 
 
 def debug_set_move_spin_limit(polls):
@@ -219,11 +225,10 @@ def reform_chunk_attend_score(q, k, v, cache_len, scale, obs_window=0, accumulat
             raise ValueError("accumulate needs the previous score tensor")
         score = torch.zeros(k.shape[:2], dtype=torch.float32, device=q.device)
     desc = attn_desc(q, k, out, cache_len, scale, obs_window, accumulate, phases)
-    need = lib.reform_chunk_attend_score_workspace(ctypes.byref(desc))
-    ws = _workspace(need, q.device, workspace, stream)
+    ws, ws_bytes = _workspace(lib.reform_chunk_attend_score_workspace, ctypes.byref(desc), q.device, workspace, stream)
     rc = lib.reform_chunk_attend_score(ctypes.byref(desc), _ptr(q), _ptr(k), _ptr(v), _ptr(out),
-                                       _ptr(lse), _ptr(score), _ptr(ws),
-                                       0 if ws is None else ws.numel(), _stream(stream))
+                                       _ptr(lse), _ptr(score), ws,
+                                       ws_bytes, _stream(stream))
     _check(rc, "reform_chunk_attend_score")
     return out, lse, score
 
@@ -246,10 +251,9 @@ def reform_evict_topk_compact(k, v, score, n_valid, budget, n_sink=0, n_recent=0
         assert kept_idx.dtype == torch.int32 and kept_idx.is_contiguous()
         assert kept_idx.shape == (k.shape[0], budget)
     desc = evict_desc(k, n_valid, budget, n_sink, n_recent)
-    need = lib.reform_evict_topk_compact_workspace(ctypes.byref(desc))
-    ws = _workspace(need, k.device, workspace, stream)
+    ws, ws_bytes = _workspace(lib.reform_evict_topk_compact_workspace, ctypes.byref(desc), k.device, workspace, stream)
     rc = lib.reform_evict_topk_compact(ctypes.byref(desc), _ptr(k), _ptr(v), _ptr(score), _ptr(pos),
-                                       _ptr(kept_idx), _ptr(ws), 0 if ws is None else ws.numel(),
+                                       _ptr(kept_idx), ws, ws_bytes,
                                        _stream(stream))
     _check(rc, "reform_evict_topk_compact")
     return min(int(n_valid), int(budget))
@@ -298,11 +302,10 @@ def reform_gather_topk(emb, qry, k, radius=0, n_head_keep=0, n_tail_keep=0, eps=
         if union_count is None:
             union_count = torch.zeros((1,), dtype=torch.int32, device=dev)
     desc = gather_desc(emb, qry, k, radius, n_head_keep, n_tail_keep, eps)
-    need = lib.reform_gather_topk_workspace(ctypes.byref(desc))
-    ws = _workspace(need, dev, workspace, stream)
+    ws, ws_bytes = _workspace(lib.reform_gather_topk_workspace, ctypes.byref(desc), dev, workspace, stream)
     rc = lib.reform_gather_topk(ctypes.byref(desc), _ptr(emb), _ptr(qry), _ptr(topk_idx),
-                                _ptr(topk_score), _ptr(union_idx), _ptr(union_count), _ptr(ws),
-                                0 if ws is None else ws.numel(), _stream(stream))
+                                _ptr(topk_score), _ptr(union_idx), _ptr(union_count), ws,
+                                ws_bytes, _stream(stream))
     _check(rc, "reform_gather_topk")
     return topk_idx, topk_score, union_idx, union_count
 
@@ -383,10 +386,9 @@ def reform_gather_pooled(emb, qry, budget, pool_window=129, n_head_keep=0, n_tai
     if pooled is None:
         pooled = torch.empty((emb.shape[0],), dtype=torch.float32, device=dev)
     desc = pooled_desc(emb, qry, budget, pool_window, n_head_keep, n_tail_keep, eps)
-    need = lib.reform_gather_pooled_workspace(ctypes.byref(desc))
-    ws = _workspace(need, dev, workspace, stream)
+    ws, ws_bytes = _workspace(lib.reform_gather_pooled_workspace, ctypes.byref(desc), dev, workspace, stream)
     rc = lib.reform_gather_pooled(ctypes.byref(desc), _ptr(emb), _ptr(qry), _ptr(sel_idx), _ptr(pooled),
-                                  _ptr(ws), 0 if ws is None else ws.numel(), _stream(stream))
+                                  ws, ws_bytes, _stream(stream))
     _check(rc, "reform_gather_pooled")
     return sel_idx, pooled
 
