@@ -11,7 +11,7 @@
 // Bound: HBM, as long as the arithmetic per pair stays short.  A frequency per pair in fp64 (exp2)
 // and the library's sincosf took more time than the stream, so a workgroup forms the rot/2
 // frequencies once into LDS and the sine and cosine come from sin_cos_quarter: 8 heads x 32768
-// rows x 128 bf16 37 -> 23 us (134 MB), 8 x 4096 rows 9.2 -> 7.9 us.
+// rows x 128 bf16 37 -> 22 us (134 MB), 8 x 4096 rows 9.2 -> 6.2 us.
 #include "common.h"
 
 namespace reform {
@@ -56,23 +56,28 @@ __global__ __launch_bounds__(256) void rope_rerotate(RopeParams p)
 {
     __shared__ double table[kRopeTable];
     constexpr int E = BF16 ? 8 : 4;                      // elements per 16-byte piece
+    const int tpr = p.rot / (2 * E);                     // threads per row
+    const long gid = (long)blockIdx.x * 256 + threadIdx.x;
+    // 32-bit division where it suffices: the 64-bit one is some hundred instructions
+    const long row = gid < (1l << 31) ? (long)((unsigned)gid / (unsigned)tpr) : gid / tpr;
+    const int piece = (int)(gid - row * tpr);
+    const int g = blockIdx.y;
+    // the loads are under way while the frequencies are formed
+    const int delta = row < p.n_rows ? (int)row - p.kept[(size_t)g * p.kept_ld + row] : 0;
+    char *base = (char *)p.k + ((size_t)g * p.cap + row) * p.row_bytes;
+    v4u *plo = (v4u *)(base + piece * 16);
+    v4u *phi = (v4u *)(base + (p.rot / 2) * (BF16 ? 2 : 4) + piece * 16);
+    v4u lo = {0u, 0u, 0u, 0u}, hi = lo;
+    if (delta != 0) {
+        lo = *plo;
+        hi = *phi;
+    }
     const bool tabulated = p.rot <= 2 * kRopeTable;
     if (tabulated) {
         for (int c = threadIdx.x; c < p.rot / 2; c += 256) table[c] = rope_quarters(p, c);
         __syncthreads();
     }
-    const int tpr = p.rot / (2 * E);                     // threads per row
-    const long gid = (long)blockIdx.x * 256 + threadIdx.x;
-    const long row = gid / tpr;
-    const int piece = (int)(gid % tpr);
-    const int g = blockIdx.y;
-    if (row >= p.n_rows) return;
-    const int delta = (int)row - p.kept[(size_t)g * p.kept_ld + row];
     if (delta == 0) return;
-    char *base = (char *)p.k + ((size_t)g * p.cap + row) * p.row_bytes;
-    v4u *plo = (v4u *)(base + piece * 16);
-    v4u *phi = (v4u *)(base + (p.rot / 2) * (BF16 ? 2 : 4) + piece * 16);
-    const v4u lo = *plo, hi = *phi;
     float x0[E], x1[E];
     if (BF16) {
         const uint32_t a[4] = {lo.x, lo.y, lo.z, lo.w}, b[4] = {hi.x, hi.y, hi.z, hi.w};
