@@ -350,9 +350,13 @@ __device__ __forceinline__ void range_emit(const SelParams &p, int q, v4u *keys,
             if (ss) sd[i] = side[b];
         }
     }
+    // Neighbourhoods overlap where winners are dense, and atomics on one word queue: each winner marks only
+    // what the one before it in the wave has not (16 rows of 8849, 1106 winners of radius 64 each: TBD).
     if (p.mark)
-        for (int i = lane; i < n_out; i += 64)
-            mark_range(p.mark, max((long)found[i] - p.mark_radius, 0L), min((long)found[i] + p.mark_radius, N - 1L));
+        for (int i = lane; i < n_out; i += 64) {
+            const long t = found[i], before = i > 0 ? found[i - 1] + p.mark_radius + 1 : 0;
+            mark_range(p.mark, max(t - p.mark_radius, before), min(t + p.mark_radius, N - 1L));
+        }
 }
 
 // grid (nblk, nq): ordered emission of the selected indices (ascending), lowest-index ties.
