@@ -17,8 +17,8 @@
 // A[m][k]: lane l holds m = l%16, k = 8*(l/16)..+7;  B[k][n]: n = l%16, same k;
 // C[m][n]: lane l holds n = l%16 and, in accumulator element e, m = 4*(l/16) + e).
 #include "common.h"
+#include "attend_plan.h"
 
-#include <algorithm>
 #include <atomic>
 
 namespace reform {
@@ -162,22 +162,11 @@ __device__ __forceinline__ float softmax_row(const f32x4 (&s)[4], float c, float
 //   - scale*log2(e) folded into one v_fma per logit, v_exp_f32 directly, packed bf16 converts;
 //   - tile addresses are a uniform base plus per-thread constants computed once.
 constexpr float kBigSum = 65536.0f;
-constexpr int kFwdWaves = 8;
-constexpr int kFwdRows = kFwdWaves * 32;                       // query rows of a row block
 
 template <int D>
 constexpr size_t fwd_lds_bytes()
 {
     return sizeof(u16) * (size_t)(5 * 64 * (D + 16));      // two K slots, three V slots
-}
-
-// Key tiles of row block rb (64-key tiles up to the last key its last row sees):
-// (M + (last row) / G) / 64 + 1.  For a full row block that is (a + rows / 64 * rb) / G + 1 with
-// a = (M G + rows - 1) / 64, rows = kFwdRows being a multiple of 64.
-__host__ __device__ __forceinline__ int fwd_row_block_tiles(const AttnParams &p, int rb)
-{
-    const int last = min((rb + 1) * kFwdRows, p.G * p.Ct) - 1;
-    return (p.M + last / p.G) / 64 + 1;
 }
 
 // One workgroup's pass of row block rb over the key tiles [t0, t1).  With
@@ -529,30 +518,16 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2) void attn_fwd_bf16(AttnParams p)
     const int kvh = bid % p.Hkv;
     if constexpr (SPLIT) {
         const int share = bid / p.Hkv;
-        const int begin = share * p.tiles / p.shares, end = (share + 1) * p.tiles / p.shares;
-        // walk to the row block of the first tile; q and r: quotient and remainder of a + rows / 64 * rb by G
-        int rb = 0, pos = p.start, nt;                   // pos: list position of rb's first tile
-        const int a = (p.M * p.G + kFwdRows - 1) / 64;
-        int q = a / p.G, r = a % p.G;
-        auto tiles = [&]() { return rb + 1 < p.n_row_blocks ? q + 1 : (p.M + p.Ct - 1) / 64 + 1; };
-        auto next = [&]() {
-            pos += nt + p.start;
-            ++rb;
-            for (r += kFwdRows / 64; r >= p.G; r -= p.G) ++q;
-            nt = tiles();
-        };
-        nt = tiles();
-        while (pos + nt <= begin) next();
+        const int begin = fwd_share_begin(p, share), end = fwd_share_begin(p, share + 1);
+        FwdWalk<AttnParams> w(p);
+        while (w.pos + w.nt <= begin) w.next(p);
         bool first = true;
-        while (pos < end) {
-            const int t0 = max(begin - pos, 0), t1 = min(end - pos, nt);      // t0 < nt, t1 > 0
-            // a workgroup leaves at most two pieces: the end of a row block it begins in, and the
-            // beginning of the one it ends in
-            const long slot = t0 == 0 && t1 == nt ? -1 : (long)bid * 2 + (t0 == 0 ? 1 : 0);
+        while (w.pos < end) {
+            const int t0 = max(begin - w.pos, 0), t1 = min(end - w.pos, w.nt);      // t0 < nt, t1 > 0
             if (!first) __syncthreads();                 // lagging waves still read the last V tile
             first = false;
-            fwd_segment<D, true>(p, smem, kvh, rb, t0, t1, slot);
-            next();
+            fwd_segment<D, true>(p, smem, kvh, w.rb, t0, t1, fwd_slot(p, share, kvh, t0, t1, w.nt));
+            w.next(p);
         }
     } else {
         // block -> (kv head, row block); heavy (late) row blocks first
@@ -578,7 +553,7 @@ __global__ __launch_bounds__(kFwdWaves * 64) void attn_fwd_few(AttnParams p)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int ln = lane & 15, lg = lane >> 4;
     const int kvh = blockIdx.x % p.Hkv, share = blockIdx.x / p.Hkv;
-    const int begin = share * p.tiles / p.shares, end = (share + 1) * p.tiles / p.shares;
+    const int begin = fwd_share_begin(p, share), end = fwd_share_begin(p, share + 1);
     const int s1 = min(2 * end, (p.n + 31) / 32);
     const int rows = p.G * p.Ct;
     const u16 *Kg = (const u16 *)p.k + (size_t)kvh * p.cap * D;
@@ -712,21 +687,15 @@ __global__ __launch_bounds__(256) void attn_fwd_merge(AttnParams p)
     for (int o = 32; o >= 1; o >>= 1) pos += __shfl_xor(pos, o);
     pos += p.start;
     const int nt = fwd_row_block_tiles(p, rb);
-    // shares that hold a tile of [pos, pos + nt): share j holds [j*tiles/shares, (j+1)*tiles/shares)
-    const unsigned T = p.tiles, S = p.shares;
-    const int j0 = (int)(((unsigned)(pos + 1) * S - 1) / T), j1 = (int)(((unsigned)(pos + nt) * S - 1) / T);
+    const FwdPieces<AttnParams> pieces(p, pos, nt);
+    const int j0 = pieces.j0, j1 = pieces.j1;
     if (j0 == j1) return;                                // finished by one workgroup
     const int grp = threadIdx.x / L, c4 = (threadIdx.x % L) * 4;
     const int pr = MANY ? blockIdx.x : blockIdx.x * GROUPS + grp;
     if (pr >= p.part_rows) return;
     if (rb * kFwdRows + pr >= p.G * p.Ct) return;
     const int row = (rb * kFwdRows + pr) / p.G, head = kvh * p.G + (rb * kFwdRows + pr) % p.G;
-    // share j0's piece is the end of a row block (slot 0) unless this one begins inside the share
-    // (slot 1); the later shares begin inside this one (slot 0)
-    const bool begins = (int)((unsigned)j0 * T / S) <= pos;
-    auto piece = [&](int j) -> size_t {
-        return ((size_t)(j * p.Hkv + kvh) * 2 + (begins && j == j0 ? 1 : 0)) * p.part_rows + pr;
-    };
+    auto piece = [&](int j) -> size_t { return (size_t)pieces.slot(p, j, kvh) * p.part_rows + pr; };
     const int first = MANY ? j0 + grp : j0, step = MANY ? GROUPS : 1;
     float m = -INFINITY, l = 0.f;
     f32x4 o = {0.f, 0.f, 0.f, 0.f};
@@ -1153,44 +1122,7 @@ __global__ __launch_bounds__(256) void attn_score_few(AttnParams p)
 
 // ------------------------------------------------------------------------------------------
 // Host-side launchers (called from the C-ABI file).
-// How the forward pass of a problem is cut into workgroups: n_row_blocks and, if the key range is to be
-// split, shares, tiles and part_rows.
-static void fwd_plan(AttnParams &p)
-{
-    const int rows = p.G * p.Ct;
-    p.n_row_blocks = (rows + kFwdRows - 1) / kFwdRows;
-    p.shares = 0;
-    p.part_rows = std::min(rows, kFwdRows);
-    // Waves of one head are 0.6 % to 1.3 % faster where they are full (8192 rows over 8192 keys, 32768 over
-    // 32768, 32/8 heads); with few chunk rows they would be nearly empty (one token: 20.6 instead of 18.3 us).
-    p.by_head = kFwdWaves % p.G == 0 && p.Ct >= 32;
-    const int cus = device_compute_units() > 0 ? device_compute_units() : 256;
-    const long whole = (long)p.Hkv * p.n_row_blocks;
-    if (whole > 4l * cus || p.Hkv > cus) return;         // at least four well-filled rounds
-    const long longest = (p.M + p.Ct - 1) / 64 + 1;
-    p.start = p.n_row_blocks > 1 ? 4 : 0;
-    long tiles = 0;
-    for (int rb = 0; rb < p.n_row_blocks; ++rb) tiles += p.start + fwd_row_block_tiles(p, rb);
-    // Time of either form, in key tiles of one workgroup (1.45 us at head_dim 128, 1.1 us at 64; one
-    // workgroup is resident per compute unit).  Whole row blocks run in rounds.  Equal shares pay the
-    // launch that merges them and the partial results, written and read back, which grow with their
-    // size, with the number of shares, and double where a share can begin and end inside row blocks.
-    // Fitted to (us; whole, then with the number of shares per KV head): 60 rows over 8000 keys, 32/8
-    // heads 183, 38 (8), 29 (16), 26 (32); 300 over 1500, 24/8 heads 48, 45 (8), 37 (13), 43 (32); 2000
-    // over 4000, 8 heads 138, 95 (13), 66 (24), 61 (32); 60 over 8000, 14/2 heads, head_dim 64 136, 28
-    // (16), 18.6 (64), 20.6 (128).  One token over 16640 keys (32/8 heads) 290 -> 18 us.
-    const double rounds = (double)((whole + cus - 1) / cus);
-    double best = whole <= cus ? 4.0 + (double)longest : rounds * (double)tiles * p.Hkv / (double)whole;
-    const double slot = p.part_rows * p.D / (256.0 * 128.0) * (p.n_row_blocks > 1 ? 2.0 : 1.0);
-    long shares = 0;
-    for (long s = std::min(tiles / 2, (long)cus / p.Hkv); s >= 2; s -= (s + 7) / 8) {
-        const double t = (double)tiles / s + 4.0 + slot * (4.5 + 5.5 * (double)s * p.Hkv / cus);
-        if (t < best) { best = t; shares = s; }
-    }
-    if (!shares || tiles * (shares + 1) >= (1l << 31)) return;
-    p.shares = (int)shares;
-    p.tiles = (int)tiles;
-}
+static int compute_units() { return device_compute_units() > 0 ? device_compute_units() : 256; }
 
 // Bytes of the partial results of a planned problem.
 static size_t fwd_split_bytes(const AttnParams &p)
@@ -1221,7 +1153,7 @@ static hipError_t launch_fwd_form(const AttnParams &p, int grid, hipStream_t st)
 template <int D>
 static hipError_t launch_fwd(AttnParams p, void *part, size_t part_bytes, hipStream_t st)
 {
-    fwd_plan(p);
+    fwd_plan(p, compute_units());
     if (!p.shares || !part || part_bytes < fwd_split_bytes(p))
         return launch_fwd_form<D, false>(p, p.Hkv * p.n_row_blocks, st);
     p.part_o = (float *)part;
@@ -1261,7 +1193,7 @@ static hipError_t launch_fwd(AttnParams p, void *part, size_t part_bytes, hipStr
 // 128 rows over 8192 keys 23 us uncut, 28 us with four waves.
 static int score_plan(AttnParams &p)
 {
-    const int cus = device_compute_units() > 0 ? device_compute_units() : 256;
+    const int cus = compute_units();
     const int tiles = (p.Ct + 63) / 64 - (p.Ct - p.W) / 64;
     const double iters = (double)p.G * tiles;
     const long full = (long)p.Hkv * ((p.n - p.W + 511) / 512), all = (long)p.Hkv * ((p.n + 511) / 512);
@@ -1347,7 +1279,7 @@ size_t attend_bf16_scratch_bytes(const AttnParams &sizes)
         score_plan(p);
         if (p.slices > 1) score = (size_t)p.slices * p.Hkv * p.n * sizeof(float);
     }
-    fwd_plan(p);
+    fwd_plan(p, compute_units());
     const size_t fwd = fwd_split_bytes(p);
     return fwd > score ? fwd : score;
 }

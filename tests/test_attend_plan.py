@@ -1,0 +1,46 @@
+"""The cut of the split forward pass, replayed on the CPU: every key tile of every row block of a problem
+belongs to exactly one workgroup, and the merge reads the slots that were written.  The header that the
+kernels use is compiled as host code (attend_plan_replay.cpp)."""
+import ctypes
+import os
+import random
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(HERE, "..", "paper_2506_01215_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def replay(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("plan") / "replay.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-fsanitize=undefined",
+                    "-fno-sanitize-recover=undefined", "-static-libubsan", "-shared", "-fPIC", "-I", CSRC,
+                    os.path.join(HERE, "attend_plan_replay.cpp"), "-o", lib], check=True)
+    return ctypes.CDLL(lib).replay
+
+
+@pytest.mark.parametrize("G", range(1, 33))
+def test_every_tile_has_one_workgroup(replay, G):
+    rng = random.Random(G)
+    split = 0
+    for _ in range(300):
+        Hkv = rng.choice([1, 2, 4, 8, 32])
+        M = rng.choice([0, rng.randint(0, 300), rng.randint(0, 70000)])
+        Ct = rng.choice([1, rng.randint(1, 40), rng.randint(1, 6000)])
+        rc = replay(Hkv, G, rng.choice([64, 128]), M, Ct, rng.choice([256, 256, 32, 304]))
+        assert rc in (0, 1), (Hkv, G, M, Ct, rc)
+        split += rc == 0
+    assert split > 50
+
+
+@pytest.mark.parametrize("Hkv,G", [(1, 16), (1, 32), (2, 16), (1, 71), (8, 4), (1, 128)])
+def test_caches_whose_keys_times_heads_pass_32_bits(replay, Hkv, G):
+    """K and V of 2^30 keys of 64 bf16 elements fill the card: G * keys reaches 2^37 for G = 128."""
+    rng = random.Random(G)
+    for M in [(1 << 31) // G - 300, (1 << 31) // G + 300, (1 << 32) // G + 77, (1 << 30) - 65]:
+        if Hkv * M > (1 << 30):
+            continue
+        for Ct in (1, 256 // G + 1, 16, 33, 700):
+            assert replay(Hkv, G, 64, M + rng.randint(0, 63), Ct, 256) in (0, 1), (Hkv, G, M, Ct)
