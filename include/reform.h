@@ -130,10 +130,12 @@ reform_status reform_chunk_attend_score(const reform_attn_desc *desc,
  * work keeps part of this call's workgroups off the device for seconds; if it does, the call
  * still ends, the cache content is then undefined, and the first int32 of the workspace, which
  * such a call clears when it starts, is set to 1.  A caller that wants to know reads that word
- * once the stream has finished.  Rows of more than 8192 candidates are selected by several
- * workgroups per row that wait for each other inside one launch (at most 128 workgroups, half of
- * what the chip holds at once); the same bounded wait and status word cover it, and more than two
- * such calls overlapping on one GPU from different streams are the one way to make it expire.
+ * once the stream has finished.
+ * Rows of more than 8192 candidates are selected by several workgroups per row that wait for each
+ * other inside one launch, at most 128 in all, one on a compute unit.  The waiting workgroups of
+ * all evictions, gathers (64 at most) and pooled gathers (128) that overlap on one GPU from
+ * different streams share its 256 compute units.  If they do not fit, such a wait expires after
+ * some seconds and the workgroup selects by itself: the results are the same, only late.
  */
 typedef struct {
     uint32_t struct_size;
@@ -151,12 +153,12 @@ reform_status reform_evict_topk_compact(const reform_evict_desc *desc,
                                         void *workspace, size_t workspace_bytes,
                                         void *hip_stream);
 
-/* Testing aid for the device-side status word above.  Sets, for later calls in this process, how
- * many times a workgroup of the in-place move polls another workgroup's flag before it gives up
- * (default 2^22; a negative value restores the default).  0 switches publishing off as well, so
- * every wait on another workgroup expires on its first poll and the status word is set whenever
- * the kept set makes one tile depend on another: the error path can then be observed while every
- * kernel still runs to its end.  The cache content after such a call is undefined.            */
+/* Testing aid for the bounded waits above.  Sets, for later calls in this process, how many times a
+ * workgroup polls for another one before it gives up (default 2^22; a negative value restores the
+ * default).  0: every wait expires on its first poll.  In the in-place move publishing is off as
+ * well, so the status word is set whenever the kept set makes one tile depend on another, and the
+ * cache content after such a call is undefined; a selection stays exact.  Every kernel still runs
+ * to its end.                                                                                   */
 void reform_debug_set_move_spin_limit(int32_t polls);
 
 /* reform_evict_topk_compact_static -- the same operation for callers that cannot allocate device
@@ -199,11 +201,10 @@ reform_status reform_evict_topk_compact_static(const reform_evict_desc *desc,
  *     union_idx   [n_ctx] int32 out (first union_count entries), may be NULL (then no union)
  *     union_count one int32 in device memory, out, required iff union_idx != NULL
  * Supported: n_ctx <= 2^31 - 65536; dim % 8 == 0; any n_query >= 1 (up to 64 per pass over emb).
- * Device-side status: rows of more than 8192 similarities are selected, where at most 64 workgroups
- * suffice for all of them, by several workgroups per row that wait for each other inside one
- * launch, with the bounded wait described for reform_evict_topk_compact; the first int32 of the
- * workspace is cleared by the call and set to 1 if such a wait expired (the outputs are then
- * undefined).
+ * Rows of more than 8192 similarities are selected, where at most 64 workgroups suffice for all of
+ * them, by several workgroups per row that wait for each other inside one launch (see
+ * reform_evict_topk_compact).  The first int32 of the workspace is cleared by the call and set to
+ * 1 if such a wait expired; the outputs are exact all the same.
  */
 typedef struct {
     uint32_t struct_size;
@@ -247,10 +248,10 @@ reform_status reform_gather_similarity(const reform_gather_desc *desc,
  *     pooled   [n_ctx] fp32 out, may be NULL (then it lives in the workspace only)
  * Supported: as reform_gather_topk; pool_window odd, 1 <= pool_window <= 1025;
  * n_head_keep + n_tail_keep <= budget <= n_ctx.
- * Device-side status: the one row of pooled scores is selected, when it has more than 8192
- * entries and at most 4 million, by up to 128 workgroups that wait for each other inside one
- * launch, with the bounded wait described for reform_evict_topk_compact; the first int32 of the
- * workspace is cleared by the call and set to 1 if such a wait expired (sel_idx is then undefined).
+ * The one row of pooled scores is selected, when it has more than 8192 entries and at most 4
+ * million, by up to 128 workgroups that wait for each other inside one launch (see
+ * reform_evict_topk_compact).  The first int32 of the workspace is cleared by the call and set to
+ * 1 if such a wait expired; the outputs are exact all the same.
  */
 typedef struct {
     uint32_t struct_size;

@@ -182,8 +182,8 @@ def _workspace(query, desc, device, workspace, stream=None):
 
 
 def debug_set_move_spin_limit(polls):
-    """Testing aid, see include/reform.h: polls of the in-place move's bounded wait (0 forces the
-    give-up branch, a negative value restores the default)."""
+    """Testing aid, see include/reform.h: polls of the bounded waits between workgroups (0 forces the
+    give-up branches, a negative value restores the default)."""
     load_library().reform_debug_set_move_spin_limit(int(polls))
 
 

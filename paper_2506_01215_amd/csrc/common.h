@@ -74,9 +74,10 @@ struct SelParams {
     int pre_zeroed;          // hist and zero_extra were cleared by an earlier kernel of the same call
     int multi_groups;        // rows too long for one workgroup may be selected in one launch by several
                              // workgroups that wait for each other, at most this many in all (0: never;
-                             // needs hist, blk_cnt and err to be usable for that)
-    int *err;                // nullable: set to 1 if a bounded wait between workgroups expired
-    int spin_limit;          // polls of such a wait
+                             // needs hist, blk_cnt and gave_up)
+    int *gave_up;            // nullable: cleared with them, set to 1 if a wait between workgroups expired (the
+                             // selection is exact all the same)
+    int spin_limit;          // polls of such a wait (0: it expires at once)
 };
 
 struct EvictParams {
@@ -206,7 +207,7 @@ __device__ __forceinline__ void sel_clear(const SelParams &p, long i0, long stri
     for (long i = i0; i < p.zero_extra_n; i += stride) p.zero_extra[i] = 0;
     if (p.multi_groups)
         for (long i = i0; i < (long)p.nq * p.nblk * 2; i += stride) p.blk_cnt[i] = 0;
-    if (p.err && i0 == 0) *p.err = 0;
+    if (p.gave_up && i0 == 0) *p.gave_up = 0;
 }
 
 // Exclusive scan of one int per thread over a 256-thread workgroup (tmp: 4 ints of LDS);

@@ -118,11 +118,12 @@ reform_status check_gather(const reform_gather_desc *d)
 long sim_pitch(int64_t n_ctx) { return (long)((n_ctx + 63) / 64 * 64 + 1088); }
 
 // Workgroups that may wait for each other in the selection of a gather call.  The calls of several
-// streams may overlap, so fewer than an eviction's: eight such launches fit the chip together.
+// streams may overlap, so fewer than an eviction's: one workgroup is resident on a compute unit
+// (registers, and LDS where it holds the most keys), so four such launches fit the 256 together.
 constexpr int kGatherMultiGroups = 64;
 
 // The gather's similarities begin this many floats into their region (the last row ends at least 1088
-// floats before its end): the first word of the workspace is the status word of the selection.
+// floats before its end): the first word of the workspace tells whether a wait of the selection expired.
 constexpr int kSimSkip = 64;
 
 struct GatherLayout {
@@ -358,6 +359,7 @@ reform_status reform_evict_topk_compact(const reform_evict_desc *d, void *k, voi
     p.sel.out_rank = L.inplace ? (int32_t *)(ws + L.rank) : nullptr;
     p.sel.multi_groups = kMultiMaxGroups;
     p.sel.spin_limit = g_move_spin_limit.load(std::memory_order_relaxed);
+    p.sel.gave_up = (int *)(ws + L.sync) + 1; // the word behind the status word
     p.sync = L.inplace ? (int *)(ws + L.sync) : nullptr;
     p.ntile = L.ntile;
     p.spin_limit = g_move_spin_limit.load(std::memory_order_relaxed);
@@ -476,7 +478,7 @@ reform_status reform_gather_topk(const reform_gather_desc *d, const void *emb, c
         p.sel.mark_radius = d->radius;
     }
     p.sel.multi_groups = kGatherMultiGroups;
-    p.sel.err = (int *)ws;                    // status word, in the 256 bytes before the similarities
+    p.sel.gave_up = (int *)ws;                // in the 256 bytes before the similarities
     p.sel.spin_limit = g_move_spin_limit.load(std::memory_order_relaxed);
     p.sel.pre_zeroed = 1;                     // ... by the first similarity launch
     hipStream_t st = (hipStream_t)hip_stream;
@@ -519,7 +521,7 @@ reform_status reform_gather_pooled(const reform_pooled_desc *d, const void *emb,
     p.sel.nblk = L.nblk;
     p.sel.out_idx = sel_idx; p.sel.out_val = nullptr; p.sel.out_ld = d->budget;
     p.sel.multi_groups = kMultiMaxGroups;
-    p.sel.err = (int *)(ws + L.status);
+    p.sel.gave_up = (int *)(ws + L.status);
     p.sel.spin_limit = g_move_spin_limit.load(std::memory_order_relaxed);
     p.sel.pre_zeroed = 1;                     // by the first similarity launch
     GatherParams gp;

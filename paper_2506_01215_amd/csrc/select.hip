@@ -47,7 +47,7 @@ __global__ void sel_zero(SelParams p)
     if (i < (long)p.nq * 3 * 2048) p.hist[i] = 0;
     if (i < p.zero_extra_n) p.zero_extra[i] = 0;
     if (p.multi_groups && i < (long)p.nq * p.nblk * 2) p.blk_cnt[i] = 0;
-    if (p.err && i == 0) *p.err = 0;
+    if (p.gave_up && i == 0) *p.gave_up = 0;
 }
 
 __device__ __forceinline__ int digit_of(uint32_t u, int pass)
@@ -320,7 +320,7 @@ __device__ __forceinline__ void range_emit(const SelParams &p, int q, v4u *keys,
         for (int j = 0; j < 4; ++j)
             if (keep[j]) found[at++] = t + j;
     }
-    // dest_run and k bound the output whatever the keys were (see the bounded waits below)
+    // dest_run and k bound the output whatever the keys were
     const int n_out = min(n_found, max(p.k - dest_run, 0));
     const int32_t *sv = (const int32_t *)(p.vals + (size_t)q * p.ld);
     int32_t *oi = p.out_idx + (size_t)q * p.out_ld + dest_run;
@@ -420,12 +420,15 @@ __global__ __launch_bounds__(256) void select_write(SelParams p)
 // ties than fit) a third pass and the counts above / equal to the threshold take its place.
 //
 // Everything that crosses workgroups inside the launch goes through agent-scope atomics (adds,
-// loads, stores), which are performed beyond the per-XCD L2s.  The waits are bounded: the host
-// launches this kernel only with at most kMultiMaxGroups workgroups, half of what the chip's 256
-// compute units hold at once even at one such workgroup each, so every workgroup that is waited
-// for is running or will be dispatched as soon as unrelated work drains; if a limit is reached
-// all the same (more than two such launches overlapping on different streams could do that), the
-// kernel still ends, sets *err and leaves undefined output.
+// loads, stores), which are performed beyond the per-XCD L2s.  The host launches this kernel with at
+// most kMultiMaxGroups workgroups, which fit the chip's 256 compute units together even where
+// the keys leave room for one on each (nit = 8), so every workgroup that is waited for is running or will be
+// dispatched as soon as unrelated work drains.  Several such launches on different streams may fill the
+// chip with workgroups that wait for others which find no room; so may other programs.  The
+// waits are therefore bounded, and a workgroup whose wait expires goes on alone: the row lies in memory
+// as the launch before left it, so it selects from the whole row by itself (select_alone) and then
+// emits its own part like the others.  The outcome is the same, only late.  It also sets *gave_up, on which
+// the other waits of the call end as well: what they wait for will not come.
 constexpr int kSelList = 256;
 
 // Histogram of the digit at `shift` over the wave's keys whose higher bits equal the prefix.
@@ -513,10 +516,20 @@ __device__ __forceinline__ void list_pick(const v4u *list, int m, int krem, uint
     need_eq = sel[1];
 }
 
+// Whether a wait of this call has to end: after spin_limit polls, or soon after another one has.
+__device__ __forceinline__ bool multi_give_up(const SelParams &p, int spins)
+{
+    const bool over = spins >= p.spin_limit ||
+        ((spins & 63) == 63 && __hip_atomic_load(p.gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0);
+    if (over) atomicExch(p.gave_up, 1);
+    return over;
+}
+
 // All 1024 threads: poll the row's histogram of a pass (thread t owns digits 2t, 2t+1) until it
-// holds `expected` candidates, then leave that snapshot in h.
-__device__ __forceinline__ void multi_wait_hist(const int *gh, int ndigits, int expected, int *h, int *wtot,
-                                                int spin_limit, int *err)
+// holds `expected` candidates, then leave that snapshot in h.  False (for all of them) if the wait
+// had to end; a spin_limit of 0 ends every wait.
+__device__ __forceinline__ bool multi_wait_hist(const SelParams &p, const int *gh, int ndigits, int expected, int *h,
+                                                int *wtot, int *stop)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int v0 = 0, v1 = 0;
@@ -533,32 +546,70 @@ __device__ __forceinline__ void multi_wait_hist(const int *gh, int ndigits, int 
         int total = 0;
 #pragma unroll
         for (int w = 0; w < 16; ++w) total += wtot[w];
-        __syncthreads();                                  // wtot is rewritten by the next poll
-        if (total == expected) break;
-        if (spins >= spin_limit) {                        // uniform: every thread saw the same total
-            if (tid == 0 && err) atomicExch(err, 1);
-            break;
-        }
+        if (total == expected && p.spin_limit > 0) break;     // uniform: every thread saw the same total
+        if (tid == 0) *stop = multi_give_up(p, spins);
+        __syncthreads();                                      // also: wtot is rewritten by the next poll
+        if (*stop) return false;
         __builtin_amdgcn_s_sleep(1);
     }
     h[2 * tid] = v0;
     h[2 * tid + 1] = v1;
     __syncthreads();
+    return true;
 }
 
-// Bounded wait for a word that another workgroup sets to a value other than 0 (0 if it expires).
+// Wait for a word that another workgroup sets to a value other than 0; 0, and *stop set, if the wait had to end.
 template <typename T>
-__device__ __forceinline__ T multi_wait_word(const T *word, int spin_limit, int *err)
+__device__ __forceinline__ T multi_wait_word(const SelParams &p, const T *word, int *stop)
 {
     for (int spins = 0;; ++spins) {
         const T v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (v != 0) return v;
-        if (spins >= spin_limit) {
-            if (err) atomicExch(err, 1);
-            return v;
+        if (v != 0 && p.spin_limit > 0) return v;
+        if (multi_give_up(p, spins)) {
+            *stop = 1;
+            return 0;
         }
         __builtin_amdgcn_s_sleep(1);
     }
+}
+
+// All 1024 threads, without the other workgroups: the threshold key of row s, how many candidates equal
+// to it are selected, and how many above / equal to it lie before index `lo`.
+__device__ __forceinline__ void select_alone(const SelParams &p, const float *s, int N, int lo, int *h, int *wtot,
+                                             int *sel, int *before, uint32_t &T, int &need_eq)
+{
+    const int tid = threadIdx.x;
+    uint32_t prefix = 0u;
+    int krem = p.k, in_bin;
+#pragma unroll 1
+    for (int pass = 0; pass < 3; ++pass) {
+        const int bits = pass == 2 ? 10 : 11, shift = pass == 0 ? 21 : pass == 1 ? 10 : 0;
+        __syncthreads();
+        h[tid] = 0;
+        h[tid + 1024] = 0;
+        __syncthreads();
+#pragma unroll 1
+        for (long t = tid; t < N; t += 1024) {
+            const uint32_t u = sel_key(p, s, t);
+            if ((u >> shift) >> bits == prefix) atomicAdd(&h[(u >> shift) & ((1u << bits) - 1u)], 1);
+        }
+        __syncthreads();
+        bin_pick(bits, prefix, krem, in_bin, h, wtot, sel);
+    }
+    T = prefix;
+    need_eq = krem;
+    if (tid < 2) before[tid] = 0;
+    __syncthreads();
+    int gt = 0, eq = 0;
+#pragma unroll 1
+    for (int t = tid; t < lo; t += 1024) {
+        const uint32_t u = sel_key(p, s, t);
+        gt += u > T;
+        eq += u == T;
+    }
+    if (gt) atomicAdd(&before[0], gt);
+    if (eq) atomicAdd(&before[1], eq);
+    __syncthreads();
 }
 
 template <bool MULTI>
@@ -568,7 +619,7 @@ __global__ __launch_bounds__(1024) void select_row(SelParams p, int parts, int n
     __shared__ int h[2048];
     __shared__ v4u list[kSelList / 4];
     __shared__ int wtot[2][16];
-    __shared__ int sel[3], before[2], list_n;
+    __shared__ int sel[3], before[2], list_n, stop;
     const int q = blockIdx.x / parts, part = blockIdx.x % parts;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int N = (int)p.N;
@@ -579,6 +630,7 @@ __global__ __launch_bounds__(1024) void select_row(SelParams p, int parts, int n
     if (tid < 3) sel[tid] = 0;
     if (tid < 2) before[tid] = 0;
     if (tid == 2) list_n = 0;
+    if (tid == 3) stop = 0;
     if (tid < kSelList / 4) list[tid] = (v4u){0u, 0u, 0u, 0u};
     __syncthreads();
     load_keys(p, p.vals + (size_t)q * p.ld, N, w_lo, nit, mine);
@@ -587,6 +639,7 @@ __global__ __launch_bounds__(1024) void select_row(SelParams p, int parts, int n
 
     uint32_t prefix = 0u;
     int krem = p.k, in_bin = N, shift = 21;
+    bool alone = false;                                           // MULTI: this workgroup waits no more
 #pragma unroll 1
     for (int pass = 0; pass < 3; ++pass) {
         const int bits = pass == 2 ? 10 : 11;
@@ -603,7 +656,8 @@ __global__ __launch_bounds__(1024) void select_row(SelParams p, int parts, int n
             for (int i = tid; i < 2048; i += 1024)
                 if (h[i]) atomicAdd(&gh[i], h[i]);
             __syncthreads();
-            multi_wait_hist(gh, 1 << bits, in_bin, h, wtot[0], p.spin_limit, p.err);
+            alone = !multi_wait_hist(p, gh, 1 << bits, in_bin, h, wtot[0], &stop);
+            if (alone) break;
         }
         bin_pick(bits, prefix, krem, in_bin, h, wtot[0], sel);
         if (in_bin <= kSelList) break;
@@ -611,7 +665,7 @@ __global__ __launch_bounds__(1024) void select_row(SelParams p, int parts, int n
     // here prefix holds the threshold's bits from `shift` up, shared by in_bin candidates
     uint32_t T = prefix;
     int need_eq = max(krem, 0);
-    const bool listed = shift > 0;
+    const bool listed = shift > 0 && !alone;
     int *c = p.blk_cnt + (size_t)q * parts * 2;                   // MULTI: cleared words, 0 = not published yet
     if (listed) {
         unsigned long long *glist = (unsigned long long *)(p.hist + ((size_t)q * 3 + 2) * 2048);
@@ -647,34 +701,44 @@ __global__ __launch_bounds__(1024) void select_row(SelParams p, int parts, int n
                 __hip_atomic_store(&c[2 * part], tot + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             if (tid < in_bin) {
-                const unsigned long long e = multi_wait_word(&glist[tid], p.spin_limit, p.err);
+                const unsigned long long e = multi_wait_word(p, &glist[tid], &stop);
                 key = (uint32_t)(e >> 32);
                 at = (int)(uint32_t)e - 1;
                 ((uint32_t *)list)[tid] = key;
             } else if (tid >= 512 && tid - 512 < part) {          // part < 128
-                atomicAdd(&before[0], max(multi_wait_word(&c[2 * (tid - 512)], p.spin_limit, p.err) - 1, 0));
+                atomicAdd(&before[0], max(multi_wait_word(p, &c[2 * (tid - 512)], &stop) - 1, 0));
             }
         }
         __syncthreads();
-        list_pick(list, in_bin, krem, T, need_eq, sel);
-        if (MULTI && at < wg_lo) {
+        alone = MULTI && stop;
+        if (!alone) list_pick(list, in_bin, krem, T, need_eq, sel);
+        if (MULTI && !alone && at < wg_lo) {
             if (key > T) atomicAdd(&before[0], 1);
             if (key == T) atomicAdd(&before[1], 1);
         }
     }
     int gt_w, eq_w;
-    range_count(mine, N, w_lo, nit, T, gt_w, eq_w);
-    if (lane == 0) { wtot[0][wave] = gt_w; wtot[1][wave] = eq_w; }
-    __syncthreads();
-    if (MULTI && !listed) {
-        if (tid < 2) {
-            int tot = 0;
+    if (!alone) {
+        range_count(mine, N, w_lo, nit, T, gt_w, eq_w);
+        if (lane == 0) { wtot[0][wave] = gt_w; wtot[1][wave] = eq_w; }
+        __syncthreads();
+        if (MULTI && !listed) {
+            if (tid < 2) {
+                int tot = 0;
 #pragma unroll
-            for (int w = 0; w < 16; ++w) tot += wtot[tid][w];
-            __hip_atomic_store(&c[2 * part + tid], tot + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                for (int w = 0; w < 16; ++w) tot += wtot[tid][w];
+                __hip_atomic_store(&c[2 * part + tid], tot + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            // candidates above / equal to T in the workgroups before this one (2 * parts <= 256 < 1024 threads)
+            if (tid < 2 * part) atomicAdd(&before[tid & 1], max(multi_wait_word(p, &c[tid], &stop) - 1, 0));
+            __syncthreads();
+            alone = stop;
         }
-        // candidates above / equal to T in the workgroups before this one (2 * parts <= 256 < 1024 threads)
-        if (tid < 2 * part) atomicAdd(&before[tid & 1], max(multi_wait_word(&c[tid], p.spin_limit, p.err) - 1, 0));
+    }
+    if (MULTI && alone) {
+        select_alone(p, p.vals + (size_t)q * p.ld, N, wg_lo, h, wtot[0], sel, before, T, need_eq);
+        range_count(mine, N, w_lo, nit, T, gt_w, eq_w);
+        if (lane == 0) { wtot[0][wave] = gt_w; wtot[1][wave] = eq_w; }
         __syncthreads();
     }
     int base_gt = before[0], base_eq = before[1];                 // above / equal to T before this wave's range
@@ -728,7 +792,7 @@ hipError_t select_topk(const SelParams &p, hipStream_t st)
         RF_CHECK_LAUNCH();
     }
     // one launch for the rest when the row's workgroups can all be resident together
-    if (p.multi_groups) {
+    if (p.multi_groups && p.gave_up) {
         // at most half of the compute units (a partitioned device has fewer than 256)
         const long max_groups = min((long)p.multi_groups, (long)device_compute_units() / 2);
         for (int nit = 1; nit <= 8; nit *= 2) {
