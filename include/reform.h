@@ -130,7 +130,7 @@ reform_status reform_chunk_attend_score(const reform_attn_desc *desc,
  * work keeps part of this call's workgroups off the device for seconds; if it does, the call
  * still ends, the cache content is then undefined, and the first int32 of the workspace, which
  * such a call clears when it starts, is set to 1.  A caller that wants to know reads that word
- * once the stream has finished.
+ * once the stream has finished (other row sizes clear it too and never set it).
  * Rows of more than 8192 candidates are selected by several workgroups per row that wait for each
  * other inside one launch, at most 128 in all, one on a compute unit.  The waiting workgroups of
  * all evictions, gathers (64 at most) and pooled gathers (128) that overlap on one GPU from

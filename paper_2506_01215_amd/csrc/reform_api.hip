@@ -359,7 +359,9 @@ reform_status reform_evict_topk_compact(const reform_evict_desc *d, void *k, voi
     p.sel.out_rank = L.inplace ? (int32_t *)(ws + L.rank) : nullptr;
     p.sel.multi_groups = kMultiMaxGroups;
     p.sel.spin_limit = g_move_spin_limit.load(std::memory_order_relaxed);
-    p.sel.gave_up = (int *)(ws + L.sync) + 1; // the word behind the status word
+    p.sel.zero_extra = (int *)(ws + L.sync);  // the status word, which only the in-place move sets, and ...
+    p.sel.zero_extra_n = 2;
+    p.sel.gave_up = (int *)(ws + L.sync) + 1; // ... the selection's own word behind it
     p.sync = L.inplace ? (int *)(ws + L.sync) : nullptr;
     p.ntile = L.ntile;
     p.spin_limit = g_move_spin_limit.load(std::memory_order_relaxed);

@@ -48,11 +48,20 @@ def test_staged_eviction_is_exact_whatever_expires(Hkv, n, B, sink, recent, kind
         ws = filled(binding.evict_workspace_bytes(binding.evict_desc(kd, n, B, sink, recent)))
         binding.reform_evict_topk_compact(kd, vd, sd, n, B, sink, recent, kept_idx=kept, workspace=ws)
         torch.cuda.synchronize()
+        assert binding.evict_status_word(ws) == 0
         for h in range(Hkv):
             np.testing.assert_array_equal(kept[h].cpu().numpy(), want[h])
             src = torch.from_numpy(want[h]).long()
             assert torch.equal(kd[h, :B].cpu(), k[h][src]) and torch.equal(vd[h, :B].cpu(), -k[h][src])
             assert torch.equal(sd[h, :B].cpu(), s[h][src])
+
+
+def test_status_word_of_the_staged_eviction_of_short_rows():
+    g = torch.Generator().manual_seed(3)
+    k = torch.randn((2, 500, 12), generator=g).to(DEV)
+    ws = filled(binding.evict_workspace_bytes(binding.evict_desc(k, 500, 200)))
+    binding.reform_evict_topk_compact(k, k.clone(), torch.rand((2, 500), device=DEV), 500, 200, workspace=ws)
+    assert binding.evict_status_word(ws) == 0
 
 
 def test_in_place_eviction_keeps_the_right_slots():
