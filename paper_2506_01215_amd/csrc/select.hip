@@ -10,9 +10,8 @@
 //   select_count  final pick, then per workgroup the number of candidates above / equal to the
 //                 threshold key
 //   select_write  ordered emission: everything above the threshold, then the lowest-index ties
-//   select_row    all of the above in one launch, keys held in LDS: one workgroup per row for rows
-//                 of at most kFusedMaxN candidates; for longer ones, when every workgroup of the
-//                 launch fits on the chip at once, several per row that wait for each other
+//   select_row    all of the above in one launch, keys held in LDS: one workgroup per row, or several that
+//                 wait for each other where every workgroup of the launch fits on the chip at once
 // Candidates in the first n_sink or last n_recent slots get the maximal key (always selected).
 #include "common.h"
 
@@ -404,8 +403,8 @@ __global__ __launch_bounds__(256) void select_write(SelParams p)
 // how many are larger.  Results are identical to the multi-launch path; the per-pass selection state
 // is not written back.
 //
-// One workgroup per row (MULTI = false) serves rows of at most kFusedMaxN candidates: its compute unit
-// does all the work of a row, so beyond this size more of them are faster.
+// One workgroup per row (MULTI = false) serves short rows and many rows: its compute unit does all the
+// work of a row, so a few long ones are faster with more of them.
 //
 // MULTI: several workgroups per row, when the whole grid can be resident at once.  Per radix pass
 // a workgroup merges its LDS histogram into the row's
@@ -778,12 +777,30 @@ static hipError_t launch_select_row(const SelParams &p, long parts, int nit, hip
 // 29.2 us, of 30000 74.5 / 58.5 us, 16 rows of 30000 55.4 / 43.7 us; eviction, 8 rows of 4113 37.2 / 40.9
 // us, of 32000 82.0 / 64.8 us.
 constexpr int kFusedMaxN = 8192;
+// Longer rows of up to kRowMaxN candidates (what the LDS holds) that are too many for that still take one
+// workgroup each rather than five launches (five / one): gather of 65 rows of 8300 64 / 48 us, of 100 rows of
+// 30000 100 / 94 us, of 1000 rows of 32768 440 / 386 us; eviction, 130 rows of 9192 233 / 214 us, 600 rows
+// of 16384 938 / 909 us.
+constexpr int kRowMaxN = 8 * 4096;
 
 hipError_t select_topk(const SelParams &p, hipStream_t st)
 {
-    if (p.N <= kFusedMaxN) {
-        int nit = 1;
-        while (nit * 4096 < p.N) nit *= 2;
+    int nit = 0, parts = 1;
+    if (p.N > kFusedMaxN && p.multi_groups && p.gave_up) {
+        // several workgroups per row when they can all be resident together: at most half of the
+        // compute units (a partitioned device has fewer than 256)
+        const long max_groups = min((long)p.multi_groups, (long)device_compute_units() / 2);
+        for (int n = 1; n <= 8 && !nit; n *= 2) {
+            const long w = (p.N + (long)n * 4096 - 1) / ((long)n * 4096);
+            if ((long)p.nq * w <= max_groups) {
+                nit = n;
+                parts = (int)w;
+            }
+        }
+    }
+    const bool multi = nit > 0;
+    if (!multi && p.N <= kRowMaxN) {
+        for (nit = 1; nit * 4096 < p.N;) nit *= 2;
         return launch_select_row<false>(p, 1, nit, st);
     }
     if (!p.pre_zeroed) {
@@ -791,15 +808,7 @@ hipError_t select_topk(const SelParams &p, hipStream_t st)
         hipLaunchKernelGGL(sel_zero, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, st, p);
         RF_CHECK_LAUNCH();
     }
-    // one launch for the rest when the row's workgroups can all be resident together
-    if (p.multi_groups && p.gave_up) {
-        // at most half of the compute units (a partitioned device has fewer than 256)
-        const long max_groups = min((long)p.multi_groups, (long)device_compute_units() / 2);
-        for (int nit = 1; nit <= 8; nit *= 2) {
-            const long parts = (p.N + (long)nit * 4096 - 1) / ((long)nit * 4096);
-            if ((long)p.nq * parts <= max_groups) return launch_select_row<true>(p, parts, nit, st);
-        }
-    }
+    if (multi) return launch_select_row<true>(p, parts, nit, st);
     const dim3 sgrid(p.nblk, p.nq);
     const int hblk = max(1, kHistWorkgroups / p.nq);       // workgroups per row of the histogram passes
     const dim3 hgrid(min(p.nblk, hblk), p.nq);

@@ -79,3 +79,34 @@ def test_gather_is_exact_and_its_union_complete(N, nq, radius, head, tail):
             np.testing.assert_array_equal(val[q].cpu().numpy(), sim[q][want])
         got = union.cpu().numpy()[:int(count.item())]
         np.testing.assert_array_equal(got, numpy_union(idx, N, radius, head, tail))
+
+
+@pytest.mark.parametrize("N", [8193, 16385, 32768, 32769])
+def test_many_long_rows_are_exact(N):
+    """More rows than workgroups may wait for each other: one workgroup per row up to 32768 candidates, several
+    launches above."""
+    g = torch.Generator().manual_seed(N)
+    rows_e, B = 129, N // 3
+    x = torch.randint(0, 4000, (rows_e, N), generator=g).float()                    # ties
+    k = torch.randint(-9, 9, (rows_e, N, 8), generator=g).to(torch.bfloat16)
+    kd, vd, sd = k.to(DEV), k.neg().to(DEV), x.to(DEV)
+    kept = torch.full((rows_e, B), -1, dtype=torch.int32, device=DEV)
+    binding.reform_evict_topk_compact(kd, vd, sd, N, B, 3, 5, kept_idx=kept)
+    torch.cuda.synchronize()
+    for h in range(0, rows_e, 16):
+        want = oracle.evict_select(x[h].numpy().astype(np.float64), N, B, 3, 5)
+        np.testing.assert_array_equal(kept[h].cpu().numpy(), want)
+        src = torch.from_numpy(want).long()
+        assert torch.equal(kd[h, :B].cpu(), k[h][src]) and torch.equal(vd[h, :B].cpu(), -k[h][src])
+    emb = torch.randint(-2, 3, (N, 32), generator=g).to(torch.bfloat16).to(DEV)
+    qry = torch.randint(-2, 3, (65, 32), generator=g).to(torch.bfloat16).to(DEV)
+    emb[:, 0] = 3
+    sim = binding.reform_gather_similarity(emb, qry).cpu().numpy()
+    idx, val, union, count = binding.reform_gather_topk(emb, qry, 60, 2, 1, 9)
+    torch.cuda.synchronize()
+    idx = idx.cpu().numpy()
+    for q in range(65):
+        want = np.sort(np.lexsort((np.arange(N), -sim[q].astype(np.float64)))[:60])
+        np.testing.assert_array_equal(idx[q], want)
+        np.testing.assert_array_equal(val[q].cpu().numpy(), sim[q][want])
+    np.testing.assert_array_equal(union.cpu().numpy()[:int(count.item())], numpy_union(idx, N, 2, 1, 9))
