@@ -67,8 +67,9 @@ struct SelParams {
     int32_t *out_rank;       // nullable [nq][ld]: rank[t] = number of selected candidates below t
     const int32_t *side_src; // nullable [nq][ld]: a 4-byte companion of every candidate ...
     int32_t *side_dst;       // ... copied to [nq][out_ld] for the selected ones (same order as out_idx)
-    uint32_t *mark;          // nullable: bitmap over the candidates (shared by the rows, cleared before) in which
-    long mark_radius;        // ... every selected one and its neighbours up to this distance are marked
+    uint32_t *mark;          // nullable: bitmap over the candidates (shared by the rows; cleared by an earlier kernel of
+    long mark_radius;        // ... the call, see pre_zeroed) in which every selected one and its neighbours up to this
+                             // distance are marked
     int *zero_extra;         // nullable: zero_extra_n more ints cleared by the histogram-clearing launch
     int zero_extra_n;
     int pre_zeroed;          // hist and zero_extra were cleared by an earlier kernel of the same call

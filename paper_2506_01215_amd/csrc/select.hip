@@ -800,6 +800,8 @@ hipError_t select_topk(const SelParams &p, hipStream_t st)
     }
     const bool multi = nit > 0;
     if (!multi && p.N <= kRowMaxN) {
+        // this launch would clear the bitmap of a call that has not, while its other workgroups mark in it
+        if (p.mark && !p.pre_zeroed) return hipErrorInvalidValue;
         for (nit = 1; nit * 4096 < p.N;) nit *= 2;
         return launch_select_row<false>(p, 1, nit, st);
     }
