@@ -12,6 +12,7 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libreform_hip.so")
 _LIB = None
+_RAW_STREAM = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 REFORM_F32, REFORM_BF16 = 0, 1
 STATUS = {0: "REFORM_OK", 1: "REFORM_ERR_INVALID_ARG", 2: "REFORM_ERR_UNSUPPORTED",
@@ -159,8 +160,10 @@ def _ptr(t):
 
 
 def _stream(stream):
-    if stream is None:      # the handle alone: building the Stream object takes 2 us
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if stream is None:      # the handle alone where this torch gives it: building the Stream object takes 2 us
+        if _RAW_STREAM is not None:
+            return _RAW_STREAM(torch.cuda.current_device())
+        stream = torch.cuda.current_stream()
     return stream.cuda_stream
 
 

@@ -191,3 +191,13 @@ def test_gather_rows_rejects_bad_arguments():
     assert call(mk(row_bytes=100)) == 2
     assert call(mk(n_table=1 << 31)) == 2
     assert call(mk(), fake, fake, ctypes.c_void_p(0x1008)) == 2
+
+
+def test_stream_handle_without_the_raw_stream_call(monkeypatch):
+    """A torch without the call that gives the current stream's handle alone: the Stream object is asked."""
+    import torch
+    from types import SimpleNamespace
+    monkeypatch.setattr(binding, "_RAW_STREAM", None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: SimpleNamespace(cuda_stream=0x7000))
+    assert binding._stream(None) == 0x7000
+    assert binding._stream(SimpleNamespace(cuda_stream=0x8000)) == 0x8000
