@@ -540,7 +540,7 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2) void attn_fwd_bf16(AttnParams p)
 // eighth 32-key tile of the share, K as A operands straight from global memory and V through LDS of
 // its own (for the transposing loads), the next tile's loads in flight over this one's work, and no
 // barrier until the waves' sums meet at the end.  In the general form all eight waves stage every
-// tile and one of them computes: one token, 32/8 heads over 16640 keys (68 MB) 16.0 -> 13.5 us (5.0
+// tile and one of them computes: one token, 32/8 heads over 16640 keys (68 MB) 16.0 -> 13.8 us (4.9
 // TB/s), 2048 keys 8.2 -> 5.9 us; with the merge, 16/4 heads of 64 over 65000 keys 21.3 -> 16.7 us.
 // A form of 32 rows was slower than the general one (8 rows of 32/8 heads over 30000 keys 25.7 -> 27.4).
 template <int D>
@@ -574,7 +574,7 @@ __global__ __launch_bounds__(kFwdWaves * 64) void attn_fwd_few(AttnParams p)
     int s = 2 * begin + wave;
     if (s < s1) load(s);
     v4u qreg[KS];
-        const int row = min(ln, rows - 1), chunk_row = row / p.G, lim = p.M + chunk_row;   // last key the row sees
+    const int row = min(ln, rows - 1), chunk_row = row / p.G, lim = p.M + chunk_row;   // last key the row sees
     {
         const u16 *src = (const u16 *)p.q + (size_t)(kvh * p.G + row % p.G) * p.q_hs + (size_t)chunk_row * p.q_rs + 8 * lg;
 #pragma unroll
@@ -1229,8 +1229,8 @@ static int score_plan(AttnParams &p)
     return waves;
 }
 
-// Few observing rows over not too many keys: the register-only form.  Its waves fetch every query
-// row themselves, so it loses its lead as rows or waves grow: 17 rows over 4113 keys of 8 heads
+// Few observing rows over not too many keys: the register-only form.  Its waves (one per 32 keys of a KV
+// head) fetch every query row themselves, so it loses its lead as rows or waves grow: 17 rows over 4113 keys of 8 heads
 // 10 -> 6 us, 4 x 32 rows over 4128 keys 16.5 -> 12.3 us, 64 rows over 16064 keys 12 -> 18 us.
 static bool score_few(const AttnParams &p)
 {

@@ -106,7 +106,8 @@ inline void fwd_plan(P &p, int cus)
     long tiles = 0;
     for (int rb = 0; rb < p.n_row_blocks; ++rb) tiles += p.start + fwd_row_block_tiles(p, rb);
     // Time of either form, in key tiles of one workgroup (1.45 us at head_dim 128, 1.1 us at 64; one
-    // workgroup is resident per compute unit).  Whole row blocks run in rounds.  Equal shares pay the
+    // workgroup is resident per compute unit).  Only ratios decide, and of these only the launches' would differ
+    // (4 tiles are 5.8 us at 128 and 4.4 us at 64), so one set of constants serves both.  Whole row blocks run in rounds.  Equal shares pay the
     // launch that merges them and the partial results, written and read back, which grow with their
     // size, with the number of shares, and double where a share can begin and end inside row blocks.
     // Fitted to (us; whole, then with the number of shares per KV head): 60 rows over 8000 keys, 32/8

@@ -16,8 +16,6 @@ namespace reform {
 
 hipError_t select_topk(const SelParams &p, hipStream_t st);
 
-
-
 // ------------------------------------------------------------------------------------------
 // 16x16x32 operand layout (wave64): A[m][k]: lane l holds m = l%16, k = 8*(l/16)..+7;
 // B[k][n]: lane l holds n = l%16, same k;  C[m][n]: lane l holds n = l%16, m = 4*(l/16) + e.
@@ -91,7 +89,8 @@ __global__ __launch_bounds__(kSimThreads) void sim_bf16_mfma(GatherParams p)
     // Where a wave has no more than one group (short stores) it takes single ones, not pairs.  Ranges are
     // whole pairs and no more: rounded to a pair for every wave they left up to half of the workgroups
     // without any.  Whole gathers, before and after: 4000 x 512 26.7 -> 18.8 us, 8000 x 2048 with 16
-    // queries 57 -> 32 us, 30000 x 2048 58 -> 48 us, 70000 x 1024 58 -> 54 us, 131072 x 1024 unchanged.
+    // queries 57 -> 32 us, 30000 x 2048 58 -> 48 us, 70000 x 1024 58 -> 54 us, 131072 x 1024 unchanged; against that,
+    // 100000 x 512 with 16 queries 63.7 -> 64.9 us.
     constexpr int NWAVES = kSimThreads / 64;
     const long share = (ngroups_all + gridDim.x - 1) / gridDim.x;
     const bool single = share <= NWAVES;

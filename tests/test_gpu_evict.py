@@ -70,14 +70,14 @@ def test_matches_oracle(Hkv, d, n, B, dtype, ties):
 
 
 @pytest.mark.parametrize("Hkv,n,B,pad,ties,sink,recent", [
-    (2, 4096, 2000, 0, True, 0, 0),         # one step per lane, aligned rows
-    (2, 4097, 4000, 3, True, 5, 9),         # first size of the four-step variant, unaligned pitch
+    (2, 4096, 2000, 0, True, 0, 0),         # one step per wave, aligned rows
+    (2, 4097, 4000, 3, True, 5, 9),         # first size of two steps, unaligned pitch
     (2, 16384, 8000, 0, False, 0, 0),
-    (1, 16385, 100, 2, True, 0, 3),         # first size of the sixteen-step variant
-    (2, 65535, 32768, 1, True, 0, 0),       # ragged last quad at the largest single-launch size
+    (1, 16385, 100, 2, True, 0, 3),         # five workgroups, the last with one candidate
+    (2, 65535, 32768, 1, True, 0, 0),       # ragged last quad
     (1, 65536, 65535, 0, True, 0, 0),       # evict exactly one of 65536
     (2, 65536, 30000, 0, True, 256, 256),
-    (2, 65537, 30000, 3, True, 0, 0),       # first size of the multi-launch selection
+    (2, 65537, 30000, 3, True, 0, 0),       # 17 workgroups, the last with one candidate
     (2, 70001, 30000, 3, True, 256, 256),
     (1, 131072, 1000, 0, False, 0, 0),
     (8, 65536, 32768, 0, True, 0, 0),       # 16 workgroups per row in the one-launch selection of long rows
@@ -87,7 +87,7 @@ def test_matches_oracle(Hkv, d, n, B, dtype, ties):
     (1, 3000000, 1000, 0, False, 0, 0),     # 32768 keys per workgroup, 92 workgroups for the one row
 ])
 def test_selection_paths(Hkv, n, B, pad, ties, sink, recent):
-    """Sizes on both sides of every switch inside the selection (registers per lane, one workgroup
+    """Sizes on both sides of every switch inside the selection (steps per wave, one workgroup
     per row, several workgroups per row in one launch, several launches), with ties, forced slots
     and rows that cannot be read as aligned quads."""
     cap = n + pad
