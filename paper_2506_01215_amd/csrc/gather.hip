@@ -32,6 +32,12 @@ hipError_t select_topk(const SelParams &p, hipStream_t st);
 // at NG = 4 is still less than half of either unit's time.  37 queries over 262144 x 1024: three passes
 // of 108 us -> one of 119 us; with everything behind it the call takes 407 -> 167 us.
 //
+// A pass begins and ends without the stream, so both ends are kept short: several query loads in flight and
+// the first store chunks right behind them (before: one load, one LDS store at a time, the norms read
+// back from LDS, then the first chunk), and idle loads at the end that cost no traffic (33 MB over all
+// waves before).  Whole calls: 131072 x 1024, one query 76.5 -> 72.4 us; 262144 x 1024, 37 queries 170 -> 162
+// us; 1048576 x 2048, 16 queries 874 -> 861 us; 50000 x 2048, 64 queries 147 -> 124 us.
+//
 // MAX: the pooled gather only needs the maximum over the queries, so the row's largest similarity is
 // stored instead of all of them (one value per row, the maximum with what an earlier pass over
 // further queries left there): 39 MB less written and read back in that example.
@@ -56,30 +62,6 @@ __global__ __launch_bounds__(kSimThreads) void sim_bf16_mfma(GatherParams p)
     const int ln = lane & 15, lg = lane >> 4;
     if (p.sel.pre_zeroed && p.q0 == 0)        // the selection that follows finds its histograms cleared
         sel_clear(p.sel, (long)blockIdx.x * kSimThreads + tid, (long)gridDim.x * kSimThreads);
-
-    // stage the queries of this pass, zero-padded, and their norms
-    const u16 *Q = (const u16 *)p.qry + (size_t)p.q0 * D;
-    for (int idx = tid; idx < 16 * NG * (D / 8); idx += kSimThreads) {
-        const int r = idx / (D / 8), c8 = idx % (D / 8);
-        v4u v = {0u, 0u, 0u, 0u};
-        if (r < p.nq_grp) v = *(const v4u *)(Q + (size_t)r * D + c8 * 8);
-        *(v4u *)(qs + r * QROW + c8 * 8) = v;
-    }
-    __syncthreads();
-    // 64 lanes per query, fixed order
-    for (int qi = wave; qi < 16 * NG; qi += kSimThreads / 64) {
-        float s = 0.f;
-        for (int c = lane; c < D; c += 64) {
-            const float x = bf16_bits_to_f32(qs[qi * QROW + c]);
-            s = fmaf(x, x, s);
-        }
-        s = wave_sum(s);
-        if (lane == 0) qnorm[qi] = sqrtf(s);
-    }
-    __syncthreads();
-    float un[NG];
-#pragma unroll
-    for (int y = 0; y < NG; ++y) un[y] = qnorm[16 * y + ln];
 
     const long ngroups_all = (p.N + 15) / 16;
     // A workgroup streams one contiguous range of row groups (its eight waves interleaved group
@@ -106,7 +88,6 @@ __global__ __launch_bounds__(kSimThreads) void sim_bf16_mfma(GatherParams p)
     const u16 *qsrc = qs + ln * QROW + 8 * lg;
 
     long grp = (long)blockIdx.x * per_wg + (single ? wave : 2 * wave);
-    if (grp >= ngroups) return;
     auto row_ptr = [&](long g) -> const u16 * {
         long row = g * 16 + ln;
         row = row < p.N ? row : p.N - 1;
@@ -118,17 +99,19 @@ __global__ __launch_bounds__(kSimThreads) void sim_bf16_mfma(GatherParams p)
     v4u cur[kChunk], nx1[kChunk], nx2[kChunk];
     long l_grp = grp;                  // load cursor
     int l_ch = 0;
-    const u16 *l_base = row_ptr(grp);
+    // Past the wave's last group the cursor stays on one line of the store, so that the unconditional loads
+    // there cost no traffic.
+    const u16 *const idle = E + 8 * lg;
+    const u16 *l_base = grp < ngroups ? row_ptr(grp) : idle;
     auto load_next = [&](v4u (&dst)[kChunk]) {
         if (FULL) {
-            // past the wave's last group the cursor stays on it: a few redundant loads instead of a branch
 #pragma unroll
             for (int i = 0; i < kChunk; ++i) dst[i] = *(const v4u *)(l_base + (l_ch * kChunk + i) * 32);
             if (l_grp < ngroups && ++l_ch == nchunks) {
                 const long g = next_grp(l_grp);
                 l_grp = g;
-                if (g < ngroups) { l_ch = 0; l_base = row_ptr(g); }
-                else l_ch = nchunks - 1;
+                l_ch = 0;
+                l_base = g < ngroups ? row_ptr(g) : idle;
             }
             return;
         }
@@ -144,8 +127,64 @@ __global__ __launch_bounds__(kSimThreads) void sim_bf16_mfma(GatherParams p)
             if (l_grp < ngroups) l_base = row_ptr(l_grp);
         }
     };
-    load_next(cur);
-    load_next(nx1);
+    // Stage the queries of this pass, zero-padded, and their norms: a wave takes every eighth query, NQ * U
+    // loads in flight, and forms the norms from the registers on the way.  The first chunks of the store
+    // are asked for behind the last of these loads (loads return in order), so they arrive meanwhile.
+    {
+        constexpr int NQ = (16 * NG + NWAVES - 1) / NWAVES, U = NG == 1 ? 4 : 2;
+        const u16 *Q = (const u16 *)p.qry + (size_t)p.q0 * D;
+        const int pieces = D / 8;
+        v4u v[NQ][U];
+        float ss[NQ];
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) ss[i] = 0.f;
+        auto fetch = [&](int c0) {
+#pragma unroll
+            for (int i = 0; i < NQ; ++i) {
+                const int r = wave + NWAVES * i;
+#pragma unroll
+                for (int u = 0; u < U; ++u) v[i][u] = (v4u){0u, 0u, 0u, 0u};
+                if (r >= p.nq_grp) continue;
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    v[i][u] = *(const v4u *)(Q + (size_t)r * D + min(c0 + 64 * u + lane, pieces - 1) * 8);
+            }
+        };
+        auto keep = [&](int c0) {
+#pragma unroll
+            for (int i = 0; i < NQ; ++i)
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int c8 = c0 + 64 * u + lane;
+                    if (c8 >= pieces || wave + NWAVES * i >= 16 * NG) continue;
+                    *(v4u *)(qs + (wave + NWAVES * i) * QROW + c8 * 8) = v[i][u];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float lo = __uint_as_float(v[i][u][e] << 16), hi = __uint_as_float(v[i][u][e] & 0xffff0000u);
+                        ss[i] = fmaf(hi, hi, fmaf(lo, lo, ss[i]));
+                    }
+                }
+        };
+        int c0 = 0;
+        for (; c0 + 64 * U < pieces; c0 += 64 * U) {
+            fetch(c0);
+            keep(c0);
+        }
+        fetch(c0);
+        load_next(cur);
+        load_next(nx1);
+        keep(c0);
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) {
+            const float t = wave_sum(ss[i]);
+            if (lane == 0 && wave + NWAVES * i < 16 * NG) qnorm[wave + NWAVES * i] = sqrtf(t);
+        }
+    }
+    __syncthreads();
+    float un[NG];
+#pragma unroll
+    for (int y = 0; y < NG; ++y) un[y] = qnorm[16 * y + ln];
+    if (grp >= ngroups) return;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
     f32x4 dot[NG], gram = zero;
 #pragma unroll
@@ -375,8 +414,8 @@ static hipError_t similarity_passes(GatherParams p, bool bf16, hipStream_t st)
     const int passes = (blocks + fit - 1) / fit, ng = (blocks + passes - 1) / passes;
     // One workgroup is resident per compute unit.  A second round evens out a long stream and costs a
     // second start (staging the queries): one round / two, 16 queries or fewer, rows x dim: 131072 x
-    // 1024 87.2 / 91.6 us, 262144 x 2048 248 / 260 us; 500000 x 1024 225 / 220 us, 1048576 x 2048
-    // 877 / 873 us (whole gather).
+    // 1024 67.0 / 68.7 us, 262144 x 2048 240 / 254 us; 500000 x 1024 210 / 207 us, 1048576 x 2048
+    // 868 / 857 us (whole gather, the same store again and again).
     const long rounds = (p.N + 15) / 16 >= 96l * cus ? 2 : 1;
     for (int q0 = 0; q0 < p.nq; q0 += 16 * ng) {
         p.q0 = q0;
