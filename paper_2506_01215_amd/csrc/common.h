@@ -43,10 +43,8 @@ struct AttnParams {
     float *part_score;         // [slice][KV head][n] column sums of one slice, when there are several
 };
 
-#ifndef RF_MOVE_TILE
-#define RF_MOVE_TILE 16384
-#endif
-constexpr int kMoveTileBytes = RF_MOVE_TILE;   // bytes of destination rows per workgroup of the in-place move
+constexpr int kMoveTileBytes = 32768;  // bytes of destination rows per workgroup of the in-place move
+constexpr int kMoveRowBytes = 16384;    // rows whose size divides this move in place
 constexpr int kMultiMaxGroups = 128;        // see select_row
 constexpr int kUnionWordsPerBlock = 256;   // bitmap words per workgroup of the union kernels
 
@@ -93,6 +91,7 @@ struct EvictParams {
     int *sync;                 // in-place move: error word, per-stream tickets, per-tile flags; null = staged move
     int ntile;                 // tiles per stream of the in-place move
     int spin_limit;            // polls a tile spends on another tile's flag before giving up (0: see the kernel)
+    int poll_delay;            // units of 1024 clocks before the first of them
     int Hkv, n, B, cap, n_sink, n_recent;
     int row_bytes;      // head_dim * sizeof(element), multiple of 16
 };

@@ -65,7 +65,7 @@ __global__ __launch_bounds__(256) void evict_move(EvictParams p)
 // kept[r] >= r, so a workgroup that writes dest rows [a, b) may destroy sources that other
 // workgroups still have to read.  Who reads the rows [a, b)?  The dest rows rank(a)..rank(b)-1
 // (rank(x) = number of kept slots below x), which lie in at most two tiles, both at or before the
-// writer's own tile.  Protocol per tile of 16 KB:
+// writer's own tile.  Protocol per tile of 32 KB:
 //   1. take a ticket from the stream's atomic counter (stream = (head, K|V)): tiles of a stream are
 //      handed out in ascending order, so every lower tile of the stream is already running when a
 //      tile starts, whatever order the hardware dispatches workgroups in;
@@ -79,11 +79,20 @@ __global__ __launch_bounds__(256) void evict_move(EvictParams p)
 //      an error word.  The stores of step 5 are issued after the poll returned;
 //   5. store the registers to rows [a, b).
 // Traffic: every moved row is read once and written once.
+//
+// Bound: the bytes, and the chain of a tile: ticket, slots, rows, flag, poll.  Each link is a memory round
+// trip, two or three microseconds behind the bulk traffic of a busy chip, so what does not depend on each
+// other is asked for together, and the first poll waits for about as long as a neighbour that
+// started with this tile needs to publish: a poll that comes too early costs a whole round trip more.
+// Tiles of 32 KB by 512 threads halve the tickets, flags and polls of 16 KB ones.  Whole eviction with
+// rotation and saving of states, us: 8 heads, 32768 of 65536 rows of 256 bytes 126.3 -> 115.0; 4096 of 4113 35.8 -> 32.0;
+// 12000 of 12300 59.3 -> 52.1; 64-wide heads, 30000 of 30100 66.3 -> 57.8; 8192 of 16384 47.4 -> 43.8.
 constexpr int kTileBytes = kMoveTileBytes;
-constexpr int kTilePieces = kTileBytes / 16 / 256;   // 16-byte pieces per thread
+constexpr int kMoveThreads = 512;
+constexpr int kTilePieces = kTileBytes / 16 / kMoveThreads;   // 16-byte pieces per thread
 constexpr int kSyncLine = 32;        // ints per 128-byte line
 
-__global__ __launch_bounds__(256) void evict_move_inplace(EvictParams p)
+__global__ __launch_bounds__(kMoveThreads, 8) void evict_move_inplace(EvictParams p)
 {
     __shared__ int sh[4];
     const int tid = threadIdx.x;
@@ -92,8 +101,8 @@ __global__ __launch_bounds__(256) void evict_move_inplace(EvictParams p)
         // trailing workgroups: the 4-byte score / pos entries come back from their staging rows
         // (filled by the selection's emission pass, which has finished before this kernel starts)
         const int sb = blockIdx.x - nstreams * p.ntile;
-        const int per_head = (p.B + 255) / 256;
-        const int g = sb / per_head, r = (sb % per_head) * 256 + tid;
+        const int per_head = (p.B + kMoveThreads - 1) / kMoveThreads;
+        const int g = sb / per_head, r = (sb % per_head) * kMoveThreads + tid;
         if (r >= p.B) return;
         const int src = p.kept[(size_t)g * p.B + r];
         if (src == r || (unsigned)src >= (unsigned)p.n) return;
@@ -118,57 +127,65 @@ __global__ __launch_bounds__(256) void evict_move_inplace(EvictParams p)
     int *flag = flags + (size_t)stream * p.ntile;
     char *base = (char *)((stream & 1) ? p.v : p.k) + (size_t)g * p.cap * p.row_bytes;
 
+    // everything that hangs on the tile number alone is asked for at once: the slots of this thread's rows, the
+    // last one (does anything move?) and, for the wait below, which dest rows read rows [a, b)
+    int rows[kTilePieces], src[kTilePieces];
+#pragma unroll
+    for (int i = 0; i < kTilePieces; ++i) {
+        const int r = a + (tid + kMoveThreads * i) / pieces;
+        rows[i] = r < b ? r : -1;
+        src[i] = kept[min(r, b - 1)];
+    }
+    const int last = kept[b - 1];
+    const int32_t *rank = p.sel.out_rank + (size_t)g * p.cap;
+    int lo = 0, hi = 0;
+    if (tid < 64) {
+        lo = rank[a];
+        hi = rank[b];                                     // b <= B < n: inside the candidate range
+    }
     // spin_limit 0 is the host's way to exercise the give-up branch: no tile publishes and every
     // wait on another tile expires on its first poll, so the kernel still runs to its end
     const bool publish = p.spin_limit > 0;
-    if (kept[b - 1] == b - 1) {                           // kept[r] == r for every r < b: nothing moves
+    if (last == b - 1) {                                  // kept[r] == r for every r < b: nothing moves
         if (tid == 0 && publish) __hip_atomic_store(&flag[tile], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;
     }
     v4u data[kTilePieces];
-    int rows[kTilePieces];
 #pragma unroll
     for (int i = 0; i < kTilePieces; ++i) {
-        const int q = tid + 256 * i;
-        const int r = a + q / pieces, c = q % pieces;
-        rows[i] = r < b ? r : -1;
-        if (r < b) {
-            int src = kept[r];
-            src = (unsigned)src < (unsigned)p.n ? src : r;
-            data[i] = *(const v4u *)(base + (size_t)src * p.row_bytes + (size_t)c * 16);
-        }
+        if (rows[i] < 0) continue;
+        const int c = (tid + kMoveThreads * i) % pieces;
+        const int at = (unsigned)src[i] < (unsigned)p.n ? src[i] : rows[i];
+        data[i] = *(const v4u *)(base + (size_t)at * p.row_bytes + (size_t)c * 16);
     }
     __builtin_amdgcn_s_waitcnt(0);                        // all loads of this wave have returned
     asm volatile("" ::: "memory");
     __syncthreads();                                      // ... and of every wave of the tile
-    if (tid == 0) {
-        if (publish) __hip_atomic_store(&flag[tile], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        // readers of rows [a, b): dest rows lo .. hi-1 with lo = rank(a), hi = rank(b)
-        const int32_t *rank = p.sel.out_rank + (size_t)g * p.cap;
-        const int lo = rank[a], hi = rank[b];             // b <= B < n: inside the candidate range
-        if (hi > lo) {
-            for (int t2 = lo / tr; t2 <= (hi - 1) / tr; ++t2) {
-                if (t2 == tile) continue;
-                int spins = 0;
-                while (__hip_atomic_load(&flag[t2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) {
-                    if (++spins > p.spin_limit) { atomicExch(p.sync, 1); break; }
-                    __builtin_amdgcn_s_sleep(4);
-                }
+    if (tid == 0 && publish) __hip_atomic_store(&flag[tile], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // readers of rows [a, b): dest rows rank(a) .. rank(b)-1, at most tr of them, so at most two tiles: a lane each
+    if (tid < 2 && hi > lo) {
+        const int t2 = lo / tr + tid;
+        if (t2 <= (hi - 1) / tr && t2 != tile) {
+            int spins = 0;
+            for (int w = 0; w < p.poll_delay; ++w) __builtin_amdgcn_s_sleep(16);
+            while (__hip_atomic_load(&flag[t2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) {
+                if (++spins > p.spin_limit) { atomicExch(p.sync, 1); break; }
+                __builtin_amdgcn_s_sleep(4);
             }
         }
-        asm volatile("" ::: "memory");
     }
+    asm volatile("" ::: "memory");
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < kTilePieces; ++i) {
         if (rows[i] >= 0) {
-            const int c = (tid + 256 * i) % pieces;
+            const int c = (tid + kMoveThreads * i) % pieces;
             *(v4u *)(base + (size_t)rows[i] * p.row_bytes + (size_t)c * 16) = data[i];
         }
     }
 }
 
-hipError_t evict_run(const EvictParams &p, hipStream_t st)
+hipError_t evict_run(EvictParams p, hipStream_t st)
 {
     const int pieces = p.row_bytes >> 4;
     if (p.sync) {
@@ -183,8 +200,15 @@ hipError_t evict_run(const EvictParams &p, hipStream_t st)
         sel.zero_extra_n = kSyncLine * (1 + p.Hkv * 2) + p.Hkv * 2 * p.ntile;
         hipError_t e = select_topk(sel, st);
         if (e != hipSuccess) return e;
-        const int side_blocks = p.Hkv * ((p.B + 255) / 256);
-        hipLaunchKernelGGL(evict_move_inplace, dim3(p.Hkv * 2 * p.ntile + side_blocks), dim3(256), 0, st, p);
+        // tiles per compute unit tell how long the round trips are: none is waited for up front where there is
+        // less than one (2 heads, 600 of 20600 rows: 28.2 -> 27.2 us, with four units 29.8), two units for two
+        // tiles (8 heads, 4096 rows: 32.0 us, with six 33.4), six from five on (12000 rows: 57.6 us with two
+        // and tiles of 16 KB, 52.8 with six; with eight nothing more)
+        const int cus = device_compute_units() > 0 ? device_compute_units() : 256;
+        const long delay = (long)p.Hkv * 2 * p.ntile * 5 / (4 * cus);
+        p.poll_delay = (int)(delay < 6 ? delay : 6);
+        const int side_blocks = p.Hkv * ((p.B + kMoveThreads - 1) / kMoveThreads);
+        hipLaunchKernelGGL(evict_move_inplace, dim3(p.Hkv * 2 * p.ntile + side_blocks), dim3(kMoveThreads), 0, st, p);
         return hipGetLastError();
     }
     hipError_t e = select_topk(p.sel, st);

@@ -14,7 +14,7 @@ hipError_t attend_bf16_score(const AttnParams &p, void *part, size_t part_bytes,
 hipError_t attend_f32_forward(const AttnParams &p, hipStream_t st);
 hipError_t attend_f32_score(const AttnParams &p, hipStream_t st);
 
-hipError_t evict_run(const EvictParams &p, hipStream_t st);
+hipError_t evict_run(EvictParams p, hipStream_t st);
 hipError_t evict_fill_identity(int32_t *kept, int Hkv, int B, int n, hipStream_t st);
 
 hipError_t gather_similarity(const GatherParams &p, bool bf16, hipStream_t st);
@@ -293,7 +293,7 @@ static EvictLayout evict_layout(const reform_evict_desc *d)
     L.nblk = (d->n_valid + 4095) / 4096;
     size_t off = 0;
     // rows whose size divides 16 KB move in place; other sizes go through K/V staging
-    L.inplace = row_bytes <= (size_t)kMoveTileBytes && ((size_t)kMoveTileBytes % row_bytes) == 0;
+    L.inplace = row_bytes <= (size_t)kMoveRowBytes && ((size_t)kMoveRowBytes % row_bytes) == 0;
     L.ntile = L.inplace ? (int)(((size_t)d->budget * row_bytes + kMoveTileBytes - 1) / kMoveTileBytes) : 0;
     // the synchronisation words of the in-place move come first: word 0 of the workspace is its
     // error word (documented in the header), then the per-stream tickets and the per-tile flags
