@@ -134,7 +134,9 @@ __device__ __forceinline__ f32x4 f32_logits(const float (&a)[D / 4], const float
 // Forward.  A workgroup owns 16 rows of one head; its NW waves take the 16-key blocks in turn, each
 // with a running maximum of its own, and meet in LDS once at the end.  With one wave per row the
 // keys of a row were a chain of dependent steps: 4 heads, 128 rows over 384 keys, head_dim 64
-// 81 -> 7 us.
+// 81 -> 11 us, and with the waves' factors formed once per row at the end, not per output element, 10 us.  Batches of
+// two or three blocks that share the maximum and overlap their MFMA chains give nothing: the fp32 matrix pipe of the
+// 32 busy compute units is what a block waits for (2048 of the 2900 clocks of a step).
 constexpr int kF32FwdWaves = 8;
 
 template <int D>
@@ -230,12 +232,13 @@ __global__ __launch_bounds__(kF32FwdWaves * 64) void attn_fwd_f32_mfma(AttnParam
     }
     l += __shfl_xor(l, 16);
     l += __shfl_xor(l, 32);
-    if (lg == 0) { sm[wave][ln] = m; sl[wave][ln] = l; }
+    if (lg == 0) sm[wave][ln] = m;
     __syncthreads();
     float m_tot = -INFINITY;
 #pragma unroll
     for (int w = 0; w < NW; ++w) m_tot = fmaxf(m_tot, sm[w][ln]);
     const float f = m == -INFINITY ? 0.f : expf(m - m_tot);
+    if (lg == 0) sl[wave][ln] = l * f;                   // scaled once, not for every output element
 #pragma unroll
     for (int db = 0; db < DB; ++db) o[db] *= f;
     // the upper half of the waves hands its sums to the lower half, and that to the output
@@ -254,18 +257,22 @@ __global__ __launch_bounds__(kF32FwdWaves * 64) void attn_fwd_f32_mfma(AttnParam
             for (int db = 0; db < DB; ++db) mine[DB * c + db] += o[db][c];
     }
     __syncthreads();
-    for (int t = threadIdx.x; t < 16 * D; t += NW * 64) {
-        const int r = t / D, c = t % D;
+    for (int t = threadIdx.x; t < 16 * (D / 4); t += NW * 64) {
+        const int r = t / (D / 4), c = t % (D / 4) * 4;
         if (i0 + r >= p.Ct) break;
-        float mt = -INFINITY, lt = 0.f, x = 0.f;
+        float lt = 0.f;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) mt = fmaxf(mt, sm[w][r]);
+        for (int w = 0; w < NW; ++w) lt += sl[w][r];
+        f32x4 x = *(const f32x4 *)&so[0][r][c];
 #pragma unroll
-        for (int w = 0; w < NW; ++w) lt += sm[w][r] == -INFINITY ? 0.f : sl[w][r] * expf(sm[w][r] - mt);
+        for (int w = 1; w < NW / 2; ++w) x += *(const f32x4 *)&so[w][r][c];
+        *(f32x4 *)((float *)p.out + (size_t)h * p.o_hs + (size_t)(i0 + r) * p.o_rs + c) = x / lt;
+        if (c == 0) {
+            float mt = -INFINITY;
 #pragma unroll
-        for (int w = 0; w < NW / 2; ++w) x += so[w][r][c];
-        ((float *)p.out)[(size_t)h * p.o_hs + (size_t)(i0 + r) * p.o_rs + c] = x / lt;
-        if (c == 0) p.lse[(size_t)h * p.Ct + i0 + r] = mt + logf(lt);
+            for (int w = 0; w < NW; ++w) mt = fmaxf(mt, sm[w][r]);
+            p.lse[(size_t)h * p.Ct + i0 + r] = mt + logf(lt);
+        }
     }
 }
 
