@@ -674,24 +674,29 @@ __global__ __launch_bounds__(kFwdWaves * 64) void attn_fwd_few(AttnParams p)
 // shares) all groups of a workgroup take one row together, and their sums meet in LDS: 33 pieces
 // of one row 8 us with one group, 3 us with eight.  grid (rows of a row block / rows per
 // workgroup, row block, KV head).
+// List position of row block rb's first tile, by the 64 lanes of a wave.
+__device__ __forceinline__ int fwd_row_block_pos(const AttnParams &p, int rb)
+{
+    int pos = 0;
+    for (int b = threadIdx.x & 63; b < rb; b += 64) pos += p.start + fwd_row_block_tiles(p, b);
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) pos += __shfl_xor(pos, o);
+    return pos + p.start;
+}
+
 template <int D, bool MANY>
-__global__ __launch_bounds__(256) void attn_fwd_merge(AttnParams p)
+__device__ __forceinline__ void fwd_merge(const AttnParams &p, int bx, int rb, int kvh)
 {
     constexpr int L = D / 4, GROUPS = 256 / L;
     __shared__ f32x4 so[MANY ? GROUPS : 1][L];
     __shared__ float2 sml[GROUPS];
-    const int rb = blockIdx.y, kvh = blockIdx.z;
-    int pos = 0;                                         // list position of the row block's first tile
-    for (int b = threadIdx.x & 63; b < rb; b += 64) pos += p.start + fwd_row_block_tiles(p, b);
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) pos += __shfl_xor(pos, o);
-    pos += p.start;
+    const int pos = fwd_row_block_pos(p, rb);
     const int nt = fwd_row_block_tiles(p, rb);
     const FwdPieces<AttnParams> pieces(p, pos, nt);
     const int j0 = pieces.j0, j1 = pieces.j1;
     if (j0 == j1) return;                                // finished by one workgroup
     const int grp = threadIdx.x / L, c4 = (threadIdx.x % L) * 4;
-    const int pr = MANY ? blockIdx.x : blockIdx.x * GROUPS + grp;
+    const int pr = MANY ? bx : bx * GROUPS + grp;
     if (pr >= p.part_rows) return;
     if (rb * kFwdRows + pr >= p.G * p.Ct) return;
     const int row = (rb * kFwdRows + pr) / p.G, head = kvh * p.G + (rb * kFwdRows + pr) % p.G;
@@ -734,6 +739,12 @@ __global__ __launch_bounds__(256) void attn_fwd_merge(AttnParams p)
     w.y = pack_bf16x2(o[2] * inv, o[3] * inv);
     *(v2u *)((u16 *)p.out + (size_t)head * p.o_hs + (size_t)row * p.o_rs + c4) = w;
     if (c4 == 0) p.lse[(size_t)head * p.Ct + row] = (m + __builtin_amdgcn_logf(l)) * kLn2;
+}
+
+template <int D, bool MANY>
+__global__ __launch_bounds__(256) void attn_fwd_merge(AttnParams p)
+{
+    fwd_merge<D, MANY>(p, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1028,16 +1039,23 @@ __global__ __launch_bounds__(256) void attn_score_sum(AttnParams p, int keys)
 // cache), two blocks ahead of their use: no LDS, no barrier, and four times as many workgroups.
 // Row blocks are counted from the first observing row, so all cache keys see the same blocks in
 // the same order (identical keys, identical scores).
-template <int D, int KB>
-__global__ __launch_bounds__(256) void attn_score_few(AttnParams p)
+//
+// PIECES: the attention of the same call left pieces that are not merged yet; the workgroup forms the rows'
+// normalisers from the pieces' maxima and sums itself, in LDS (see attn_merge_score).
+constexpr int kFewBlocks = 8;                            // row blocks over all heads of a group, at most
+
+template <int D, int KB, bool PIECES>
+__device__ __forceinline__ void score_few_keys(const AttnParams &p, int bid)
 {
+    __shared__ float slse[PIECES ? kFewBlocks * 16 : 1];
+    const int w16 = (p.W + 15) / 16 * 16;                // rows of a head, filled up to whole blocks
     constexpr int KS = D / 32;
     constexpr int WKEYS = 16 * KB;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int ln = lane & 15, lg = lane >> 4;
-    const int kvh = blockIdx.x % p.Hkv;
-    const int jw = ((blockIdx.x / p.Hkv) * 4 + wave) * WKEYS;
-    if (jw >= p.n) return;
+    const int kvh = bid % p.Hkv;
+    const int jw = ((bid / p.Hkv) * 4 + wave) * WKEYS;
+    if (!PIECES && jw >= p.n) return;
 
     const u16 *Kg = (const u16 *)p.k + (size_t)kvh * p.cap * D;
     v4u kreg[KB][KS];
@@ -1052,8 +1070,8 @@ __global__ __launch_bounds__(256) void attn_score_few(AttnParams p)
     for (int kb = 0; kb < KB; ++kb) col[kb] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
     const int i_lo = p.Ct - p.W;                         // first observing row
-    const int b0 = max(jw - p.M - i_lo, 0) / 16;         // first row block with a row that sees key jw
-    const int nb = (p.W + 15) / 16 - b0;                 // row blocks per head (>= 1 since jw < n)
+    // first row block with a row that sees key jw; row blocks per head (a wave behind the last key: one)
+    const int b0 = min(max(jw - p.M - i_lo, 0) / 16, (p.W + 15) / 16 - 1), nb = (p.W + 15) / 16 - b0;
     const int iters = p.G * nb;
     const float c = p.scale * kLog2e;
 
@@ -1065,7 +1083,7 @@ __global__ __launch_bounds__(256) void attn_score_few(AttnParams p)
         const u16 *src = (const u16 *)p.q + (size_t)head * p.q_hs + (size_t)r * p.q_rs + 8 * lg;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) b.q[ks] = *(const v4u *)(src + ks * 32);
-        b.lse = p.lse[(size_t)head * p.Ct + r];
+        if (!PIECES) b.lse = p.lse[(size_t)head * p.Ct + r];
     };
     auto use = [&](const Block &b, int it) {
         if (it >= iters) return;
@@ -1077,7 +1095,8 @@ __global__ __launch_bounds__(256) void attn_score_few(AttnParams p)
         for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb) s[kb] = mfma16(kreg[kb][ks], b.q[ks], s[kb]);
-        const float ls = r0 + ln < p.Ct ? b.lse * kLog2e : INFINITY;
+        const float ls = r0 + ln >= p.Ct ? INFINITY
+                       : PIECES ? slse[it / nb * w16 + (b0 + it % nb) * 16 + ln] : b.lse * kLog2e;
         const int lim = p.M + r0 + ln - jw;              // key offset <= lim is visible
         if (p.M + r0 >= jw + WKEYS - 1) {
 #pragma unroll
@@ -1097,6 +1116,54 @@ __global__ __launch_bounds__(256) void attn_score_few(AttnParams p)
     Block x, y;
     load(x, 0);
     load(y, 1);
+    if constexpr (PIECES) {                              // while the keys and the first rows are on their way
+        const int rows = p.G * p.Ct, r_first = (p.Ct - p.W) * p.G, rb0 = r_first / kFwdRows;
+        const int pos0 = fwd_row_block_pos(p, rb0), nt0 = fwd_row_block_tiles(p, rb0);
+        // the rows lie in row block rb0 and at most the next one
+        const int rb1 = min(rb0 + 1, p.n_row_blocks - 1);
+        const int pos1 = rb1 > rb0 ? pos0 + nt0 + p.start : pos0;
+        const FwdPieces<AttnParams> pc0(p, pos0, nt0), pc1(p, pos1, fwd_row_block_tiles(p, rb1));
+        // T threads to a row, each over every T-th piece
+        const int entries = p.G * w16;
+        int T = 256;
+        while (T * entries > 256) T >>= 1;
+        const int e = threadIdx.x / T, sub = threadIdx.x % T;
+        if (e < entries) {                               // the same for all T lanes of a row
+            const int row = min(p.Ct - p.W + e % w16, p.Ct - 1), gi = e / w16, r = min(row * p.G + gi, rows - 1);
+            const bool second = r / kFwdRows > rb0;
+            const int j0 = second ? pc1.j0 : pc0.j0, j1 = second ? pc1.j1 : pc0.j1, pr = r % kFwdRows;
+            float m = -INFINITY, l = 0.f;
+            if (j0 < j1)
+                for (int j = j0 + sub; j <= j1; j += 4 * T) {        // four pieces in flight
+                    float2 x[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        x[u] = p.part_ml[(size_t)(second ? pc1 : pc0).slot(p, min(j + u * T, j1), kvh) * p.part_rows + pr];
+                        if (j + u * T > j1) x[u] = make_float2(-INFINITY, 0.f);
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const float m_new = fmaxf(m, x[u].x);        // -inf: a piece without a visible key
+                        const float a = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - m_new);
+                        const float w = m_new == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(x[u].x - m_new);
+                        m = m_new;
+                        l = fmaf(l, a, w * x[u].y);
+                    }
+                }
+            for (int o = 1; o < T && o < 64; o <<= 1) {
+                const float om = __shfl_xor(m, o), ol = __shfl_xor(l, o);
+                const float m_new = fmaxf(m, om);
+                const float a = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - m_new);
+                const float w = m_new == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(om - m_new);
+                m = m_new;
+                l = fmaf(l, a, w * ol);
+            }
+            if (sub == 0)
+                slse[e] = j0 < j1 ? m + __builtin_amdgcn_logf(l) : p.lse[(size_t)(kvh * p.G + gi) * p.Ct + row] * kLog2e;
+        }
+        __syncthreads();
+        if (jw >= p.n) return;
+    }
     for (int it = 0; it < iters; it += 2) {
         Block z;
         load(z, it + 2);
@@ -1118,6 +1185,26 @@ __global__ __launch_bounds__(256) void attn_score_few(AttnParams p)
             const int j = jw + kb * 16 + 4 * lg + e;
             if (ln == 0 && j < p.n) dst[j] = p.accumulate ? dst[j] + t : t;
         }
+}
+
+template <int D, int KB>
+__global__ __launch_bounds__(256) void attn_score_few(AttnParams p)
+{
+    score_few_keys<D, KB, false>(p, blockIdx.x);
+}
+
+// The merge of a split forward pass and the score of few rows in one launch: a ragged last chunk is a chain of
+// short launches of 3 us and more, and the score only needs the pieces' maxima and sums, a few KB.
+// The first n_score workgroups are the score's, the others merge as attn_fwd_merge<D, true> does, one row
+// each.  Whole calls: 17 rows over 4113 keys of 8 heads 17.7 -> 16.0 us, 25 rows over 5025, 32/8 heads 29.0 -> 25.6
+// us, 200 rows (128 observe) over 6200, 8 heads 37.9 -> 34.0 us, 30 over 30030, 8 heads 51.2 -> 50.8 us; with the
+// normalisers formed before the keys are asked for, 30 over 30030 55.5 us.
+template <int D, int KB>
+__global__ __launch_bounds__(256) void attn_merge_score(AttnParams p, int n_score)
+{
+    const int bid = blockIdx.x - n_score;
+    if (bid < 0) score_few_keys<D, KB, true>(p, blockIdx.x);
+    else fwd_merge<D, true>(p, bid % p.part_rows, bid / p.part_rows % p.n_row_blocks, bid / p.part_rows / p.n_row_blocks);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1149,20 +1236,32 @@ static hipError_t launch_fwd_form(const AttnParams &p, int grid, hipStream_t st)
     return hipGetLastError();
 }
 
-// `part` (part_bytes): scratch for partial results; the key range is only split if they fit.
+// `part` (part_bytes): scratch for partial results; the key range is only split if they fit (true).
+template <int D>
+static bool fwd_place(AttnParams &p, void *part, size_t part_bytes)
+{
+    fwd_plan(p, compute_units());
+    if (!p.shares || !part || part_bytes < fwd_split_bytes(p)) return false;
+    p.part_o = (float *)part;
+    p.part_ml = (float2 *)(p.part_o + (size_t)p.shares * p.Hkv * 2 * p.part_rows * D);
+    return true;
+}
+
+// The split pass itself.
+template <int D>
+static hipError_t launch_fwd_pieces(const AttnParams &p, hipStream_t st)
+{
+    const int grid = p.shares * p.Hkv;
+    if (p.G * p.Ct > 16) return launch_fwd_form<D, true>(p, grid, st);
+    hipLaunchKernelGGL(attn_fwd_few<D>, dim3(grid), dim3(kFwdWaves * 64), 0, st, p);
+    return hipGetLastError();
+}
+
 template <int D>
 static hipError_t launch_fwd(AttnParams p, void *part, size_t part_bytes, hipStream_t st)
 {
-    fwd_plan(p, compute_units());
-    if (!p.shares || !part || part_bytes < fwd_split_bytes(p))
-        return launch_fwd_form<D, false>(p, p.Hkv * p.n_row_blocks, st);
-    p.part_o = (float *)part;
-    p.part_ml = (float2 *)(p.part_o + (size_t)p.shares * p.Hkv * 2 * p.part_rows * D);
-    const int grid = p.shares * p.Hkv, rows = p.G * p.Ct;
-    hipError_t e = hipSuccess;
-    if (rows <= 16) hipLaunchKernelGGL(attn_fwd_few<D>, dim3(grid), dim3(kFwdWaves * 64), 0, st, p);
-    else e = launch_fwd_form<D, true>(p, grid, st);
-    if (e == hipSuccess) e = hipGetLastError();
+    if (!fwd_place<D>(p, part, part_bytes)) return launch_fwd_form<D, false>(p, p.Hkv * p.n_row_blocks, st);
+    const hipError_t e = launch_fwd_pieces<D>(p, st);
     if (e != hipSuccess) return e;
     // pieces of the longest row block: two or three where row blocks are many, a head's shares for a token
     const long pieces = ((long)((p.M + p.Ct - 1) / 64 + 1) * p.shares) / p.tiles + 1;
@@ -1235,7 +1334,7 @@ static int score_plan(AttnParams &p)
 static bool score_few(const AttnParams &p)
 {
     const long blocks = (long)p.G * ((p.W + 15) / 16);
-    return blocks <= 2 || (blocks <= 8 && (long)p.Hkv * p.n <= 65536);
+    return blocks <= 2 || (blocks <= kFewBlocks && (long)p.Hkv * p.n <= 65536);
 }
 
 template <int D, int NW>
@@ -1250,11 +1349,29 @@ static hipError_t launch_score_tiled(const AttnParams &p, hipStream_t st)
     return hipGetLastError();
 }
 
+constexpr int kFewKB = 2;                               // 16-key blocks of a wave of the register-only form
+
+// Both passes where the first is split and the second takes few rows.  Merging is then a workgroup per row, so
+// there must not be many (a window of a longer chunk).
+template <int D>
+static bool launch_both(AttnParams p, void *part, size_t part_bytes, hipStream_t st, hipError_t &e)
+{
+    if (!score_few(p) || !fwd_place<D>(p, part, part_bytes) || (long)p.Hkv * p.n_row_blocks * p.part_rows > 2048)
+        return false;
+    e = launch_fwd_pieces<D>(p, st);
+    if (e != hipSuccess) return true;
+    const int n_score = p.Hkv * ((p.n + 64 * kFewKB - 1) / (64 * kFewKB));
+    const int n_merge = p.part_rows * p.n_row_blocks * p.Hkv;
+    hipLaunchKernelGGL((attn_merge_score<D, kFewKB>), dim3(n_score + n_merge), dim3(256), 0, st, p, n_score);
+    e = hipGetLastError();
+    return true;
+}
+
 template <int D>
 static hipError_t launch_score(AttnParams p, void *part, size_t part_bytes, hipStream_t st)
 {
     if (score_few(p)) {
-        constexpr int KB = 2;
+        constexpr int KB = kFewKB;
         const int grid = p.Hkv * ((p.n + 64 * KB - 1) / (64 * KB));
         hipLaunchKernelGGL((attn_score_few<D, KB>), dim3(grid), dim3(256), 0, st, p);
         return hipGetLastError();
@@ -1288,6 +1405,17 @@ hipError_t attend_bf16_forward(const AttnParams &p, void *part, size_t part_byte
 {
     if (p.D == 128) return launch_fwd<128>(p, part, part_bytes, st);
     return launch_fwd<64>(p, part, part_bytes, st);
+}
+
+hipError_t attend_bf16_score(const AttnParams &p, void *part, size_t part_bytes, hipStream_t st);
+
+// Attention and score of one call.
+hipError_t attend_bf16_both(const AttnParams &p, void *part, size_t part_bytes, hipStream_t st)
+{
+    hipError_t e = hipSuccess;
+    if (p.D == 128 ? launch_both<128>(p, part, part_bytes, st, e) : launch_both<64>(p, part, part_bytes, st, e)) return e;
+    e = attend_bf16_forward(p, part, part_bytes, st);
+    return e == hipSuccess ? attend_bf16_score(p, part, part_bytes, st) : e;
 }
 
 hipError_t attend_bf16_score(const AttnParams &p, void *part, size_t part_bytes, hipStream_t st)

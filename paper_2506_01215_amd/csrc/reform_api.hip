@@ -10,6 +10,7 @@
 namespace reform {
 hipError_t attend_bf16_forward(const AttnParams &p, void *part, size_t part_bytes, hipStream_t st);
 size_t attend_bf16_scratch_bytes(const AttnParams &sizes);
+hipError_t attend_bf16_both(const AttnParams &p, void *part, size_t part_bytes, hipStream_t st);
 hipError_t attend_bf16_score(const AttnParams &p, void *part, size_t part_bytes, hipStream_t st);
 hipError_t attend_f32_forward(const AttnParams &p, hipStream_t st);
 hipError_t attend_f32_score(const AttnParams &p, hipStream_t st);
@@ -261,8 +262,9 @@ reform_status reform_chunk_attend_score(const reform_attn_desc *d, const void *q
     hipStream_t st = (hipStream_t)hip_stream;
     hipError_t e = hipSuccess;
     if (d->dtype == REFORM_BF16) {
-        if (do_attn) e = attend_bf16_forward(p, part, part_bytes, st);
-        if (e == hipSuccess && do_score) e = attend_bf16_score(p, part, part_bytes, st);
+        if (do_attn && do_score) e = attend_bf16_both(p, part, part_bytes, st);
+        else if (do_attn) e = attend_bf16_forward(p, part, part_bytes, st);
+        else if (do_score) e = attend_bf16_score(p, part, part_bytes, st);
     } else {
         if (do_attn) e = attend_f32_forward(p, st);
         if (e == hipSuccess && do_score) e = attend_f32_score(p, st);
