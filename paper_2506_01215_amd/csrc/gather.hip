@@ -332,12 +332,16 @@ __global__ __launch_bounds__(256) void sim_generic(GatherParams p)
 // neighbourhoods as it writes them.  union_word: a word with the forced first / last rows added.
 __device__ __forceinline__ uint32_t low_bits(long n) { return n >= 32 ? 0xffffffffu : n <= 0 ? 0u : (1u << n) - 1u; }
 
-__device__ __forceinline__ uint32_t union_word(const GatherParams &p, long w)
+__device__ __forceinline__ uint32_t union_bits(const GatherParams &p, long w, uint32_t marked)
 {
-    if (w >= p.nwords) return 0u;
     const long b0 = w << 5;
     const uint32_t forced = low_bits(p.n_head - b0) | ~low_bits(p.N - p.n_tail - b0);
-    return p.bitmap[w] | (forced & low_bits(p.N - b0));
+    return marked | (forced & low_bits(p.N - b0));
+}
+
+__device__ __forceinline__ uint32_t union_word(const GatherParams &p, long w)
+{
+    return w < p.nwords ? union_bits(p, w, p.bitmap[w]) : 0u;
 }
 
 // One bitmap word per thread, kUnionWordsPerBlock = 256 words (8192 rows) per workgroup.
@@ -368,7 +372,11 @@ __global__ __launch_bounds__(256) void union_emit(GatherParams p)
         for (int b = tid; b < blk; b += 256) before += p.word_cnt[b];
     else
 #pragma unroll 8
-        for (int b = 0; b < blk; ++b) before += __popc(union_word(p, (long)b * kUnionWordsPerBlock + tid));
+        for (int w = 4 * tid; w < blk * kUnionWordsPerBlock; w += 4 * 256) {
+            const v4u m = *(const v4u *)(p.bitmap + w);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) before += __popc(union_bits(p, w + j, m[j]));
+        }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) before += __shfl_xor(before, o);
     if (tid == 0) sh_base = 0;
@@ -456,16 +464,16 @@ hipError_t gather_similarity_max(const GatherParams &p, bool bf16, hipStream_t s
     return similarity_passes<true>(p, bf16, st);
 }
 
-constexpr int kUnionSelfCount = 4;
+constexpr int kUnionSelfCount = 16;
 
 hipError_t gather_select_union(GatherParams p, hipStream_t st)
 {
     hipError_t es = select_topk(p.sel, st);
     if (es != hipSuccess) return es;
     if (p.union_idx) {
-        // Counting the words before its own costs a workgroup more as they grow; for a few workgroups that
-        // is less than the launch it saves: 2048 rows 18.2 instead of 20.4 us for the whole call, 20000
-        // rows 42.8 and 44.0 us, 100000 rows 66.4 and 65.8 us, 250000 rows 97.7 and 92.7 us.
+        // Counting the words before its own costs a workgroup more as they grow; up to 16 workgroups that is
+        // less than the launch it saves.  Whole calls, counted by themselves / by a launch of their own: 131072
+        // rows 71.0 / 72.5 us, 262144 rows 95.1 / 94.6 us, 500000 rows 86.7 / 84.7 us, 1048576 rows 867 / 858 us.
         const int ub = (p.nwords + kUnionWordsPerBlock - 1) / kUnionWordsPerBlock;
         if (ub > kUnionSelfCount) {
             hipLaunchKernelGGL(union_count_words, dim3(ub), dim3(256), 0, st, p);
