@@ -68,6 +68,8 @@ struct SelParams {
     uint32_t *mark;          // nullable: bitmap over the candidates (shared by the rows; cleared by an earlier kernel of
     long mark_radius;        // ... the call, see pre_zeroed) in which every selected one and its neighbours up to this
                              // distance are marked
+    int32_t *union_idx;      // nullable (one row): the winners a second time, and how many they are: the union of one
+    int32_t *union_count;    // ... query's winners without neighbours
     int *zero_extra;         // nullable: zero_extra_n more ints cleared by the histogram-clearing launch
     int zero_extra_n;
     int pre_zeroed;          // hist and zero_extra were cleared by an earlier kernel of the same call

@@ -321,6 +321,7 @@ __device__ __forceinline__ void range_emit(const SelParams &p, int q, v4u *keys,
     }
     // dest_run and k bound the output whatever the keys were
     const int n_out = min(n_found, max(p.k - dest_run, 0));
+    if (p.union_count && w_lo == 0 && lane == 0) *p.union_count = p.k;
     const int32_t *sv = (const int32_t *)(p.vals + (size_t)q * p.ld);
     int32_t *oi = p.out_idx + (size_t)q * p.out_ld + dest_run;
     int32_t *os = p.out_val ? (int32_t *)(p.out_val + (size_t)q * p.out_ld) + dest_run : nullptr;
@@ -345,6 +346,7 @@ __device__ __forceinline__ void range_emit(const SelParams &p, int q, v4u *keys,
             const int i = i0 + 64 * b;
             if (i >= n_out) continue;
             oi[i] = t[b];
+            if (p.union_idx) p.union_idx[dest_run + i] = t[b];
             if (os) os[i] = val[b];
             if (ss) sd[i] = side[b];
         }
