@@ -1297,9 +1297,16 @@ static int score_plan(AttnParams &p)
     const double iters = (double)p.G * tiles;
     const long full = (long)p.Hkv * ((p.n - p.W + 511) / 512), all = (long)p.Hkv * ((p.n + 511) / 512);
     const double total = (full + 0.5 * (double)(all - full)) * iters / cus;       // per compute unit
-    const double rounds = (double)((full + cus - 1) / cus) * iters;
-    double best = rounds > total ? rounds : total;
-    if (best < iters) best = iters;
+    // Uncut workgroups in the order they are dispatched: `whole` rounds of full ones, then on the units that a last,
+    // partly filled round leaves (`room`) the triangular ones, the longest of which is a full one as well, and
+    // with more than there is room for the longest left over behind the shortest.
+    const long whole = full / cus, room = cus - full % cus, tri = all - full;
+    double best = (double)(whole + (room < cus || tri > 0)) * iters;
+    if (tri > room) {
+        const double pair = (2.0 - 2.0 * (double)room / (double)tri) * iters;
+        if (best < (double)whole * iters + pair) best = (double)whole * iters + pair;
+    }
+    if (best < total) best = total;
     int waves = 8;
     p.slices = p.head_slices = 1;
     p.slice_tiles = tiles;
