@@ -1040,22 +1040,28 @@ __global__ __launch_bounds__(256) void attn_score_sum(AttnParams p, int keys)
 // Row blocks are counted from the first observing row, so all cache keys see the same blocks in
 // the same order (identical keys, identical scores).
 //
+// RW: waves of a workgroup that share their keys and divide the row blocks among themselves; their sums meet in LDS, in
+// wave order.  One where the blocks are few; four where there are more of them, which then need no slices
+// and no launch that adds them up.
+//
 // PIECES: the attention of the same call left pieces that are not merged yet; the workgroup forms the rows'
 // normalisers from the pieces' maxima and sums itself, in LDS (see attn_merge_score).
-constexpr int kFewBlocks = 8;                            // row blocks over all heads of a group, at most
+constexpr int kFewBlocks = 8;                            // row blocks over all heads of a group, at most (RW = 1)
 
-template <int D, int KB, bool PIECES>
+template <int D, int KB, int RW, bool PIECES>
 __device__ __forceinline__ void score_few_keys(const AttnParams &p, int bid)
 {
+    static_assert(RW == 1 || (RW == 4 && !PIECES), "one wave or all waves of the workgroup to a set of keys");
     __shared__ float slse[PIECES ? kFewBlocks * 16 : 1];
+    __shared__ float part[RW > 1 ? 4 : 1][16 * KB];
     const int w16 = (p.W + 15) / 16 * 16;                // rows of a head, filled up to whole blocks
     constexpr int KS = D / 32;
     constexpr int WKEYS = 16 * KB;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int ln = lane & 15, lg = lane >> 4;
     const int kvh = bid % p.Hkv;
-    const int jw = ((bid / p.Hkv) * 4 + wave) * WKEYS;
-    if (!PIECES && jw >= p.n) return;
+    const int jw = ((bid / p.Hkv) * (4 / RW) + wave / RW) * WKEYS, rw = wave % RW;
+    if (!PIECES && jw >= p.n) return;                    // with RW = 4 no workgroup
 
     const u16 *Kg = (const u16 *)p.k + (size_t)kvh * p.cap * D;
     v4u kreg[KB][KS];
@@ -1114,8 +1120,8 @@ __device__ __forceinline__ void score_few_keys(const AttnParams &p, int bid)
         }
     };
     Block x, y;
-    load(x, 0);
-    load(y, 1);
+    load(x, rw);
+    load(y, rw + RW);
     if constexpr (PIECES) {                              // while the keys and the first rows are on their way
         const int rows = p.G * p.Ct, r_first = (p.Ct - p.W) * p.G, rb0 = r_first / kFwdRows;
         const int pos0 = fwd_row_block_pos(p, rb0), nt0 = fwd_row_block_tiles(p, rb0);
@@ -1164,13 +1170,13 @@ __device__ __forceinline__ void score_few_keys(const AttnParams &p, int bid)
         __syncthreads();
         if (jw >= p.n) return;
     }
-    for (int it = 0; it < iters; it += 2) {
+    for (int it = rw; it < iters; it += 2 * RW) {
         Block z;
-        load(z, it + 2);
+        load(z, it + 2 * RW);
         use(x, it);
         x = z;
-        load(z, it + 3);
-        use(y, it + 1);
+        load(z, it + 3 * RW);
+        use(y, it + RW);
         y = z;
     }
 
@@ -1183,14 +1189,23 @@ __device__ __forceinline__ void score_few_keys(const AttnParams &p, int bid)
 #pragma unroll
             for (int off = 8; off >= 1; off >>= 1) t += __shfl_xor(t, off);
             const int j = jw + kb * 16 + 4 * lg + e;
-            if (ln == 0 && j < p.n) dst[j] = p.accumulate ? dst[j] + t : t;
+            if (ln != 0) continue;
+            if (RW > 1) part[wave][j - jw] = t;
+            else if (j < p.n) dst[j] = p.accumulate ? dst[j] + t : t;
         }
+    if constexpr (RW > 1) {
+        __syncthreads();
+        const int at = threadIdx.x, j = jw + at;
+        if (at >= WKEYS || j >= p.n) return;
+        const float t = (part[0][at] + part[1][at]) + (part[2][at] + part[3][at]);
+        dst[j] = p.accumulate ? dst[j] + t : t;
+    }
 }
 
-template <int D, int KB>
+template <int D, int KB, int RW>
 __global__ __launch_bounds__(256) void attn_score_few(AttnParams p)
 {
-    score_few_keys<D, KB, false>(p, blockIdx.x);
+    score_few_keys<D, KB, RW, false>(p, blockIdx.x);
 }
 
 // The merge of a split forward pass and the score of few rows in one launch: a ragged last chunk is a chain of
@@ -1203,7 +1218,7 @@ template <int D, int KB>
 __global__ __launch_bounds__(256) void attn_merge_score(AttnParams p, int n_score)
 {
     const int bid = blockIdx.x - n_score;
-    if (bid < 0) score_few_keys<D, KB, true>(p, blockIdx.x);
+    if (bid < 0) score_few_keys<D, KB, 1, true>(p, blockIdx.x);
     else fwd_merge<D, true>(p, bid % p.part_rows, bid / p.part_rows % p.n_row_blocks, bid / p.part_rows / p.n_row_blocks);
 }
 
@@ -1335,13 +1350,22 @@ static int score_plan(AttnParams &p)
     return waves;
 }
 
+constexpr int kFewKB = 2;                               // 16-key blocks of a wave of the register-only form
+
 // Few observing rows over not too many keys: the register-only form.  Its waves (one per 32 keys of a KV
 // head) fetch every query row themselves, so it loses its lead as rows or waves grow: 17 rows over 4113 keys of 8 heads
 // 10 -> 6 us, 4 x 32 rows over 4128 keys 16.5 -> 12.3 us, 64 rows over 16064 keys 12 -> 18 us.
-static bool score_few(const AttnParams &p)
+// Returns how many waves share their keys (RW above), 0 where this is not the form to take.  Four of them: also for
+// more row blocks, as long as the keys are not so many that each workgroup's walk over all rows tells.  Whole
+// calls, tiled / four waves: 88 rows over 1234 keys, 16/4 heads 32.1 -> 27.4 us, 201 over 1407 36.8 -> 32.5 us, 128
+// of 3039 over 4057, 14/2 heads 91.1 -> 85.9 us, 47 over 14688, 14/2 heads of 64 31.9 -> 30.4 us (19 thousand workgroups
+// times blocks), 327 over 327, 32/8 heads 31.2 -> 29.9 us (84 blocks); but 447 over 447, 16/4 heads (112 blocks) 32.6 ->
+// 35.9 us, and with few blocks over many keys 12 rows over 18878, 32/8 heads 54.7 -> 69.9 us.
+static int score_few(const AttnParams &p)
 {
     const long blocks = (long)p.G * ((p.W + 15) / 16);
-    return blocks <= 2 || (blocks <= kFewBlocks && (long)p.Hkv * p.n <= 65536);
+    if (blocks <= 2 || (blocks <= kFewBlocks && (long)p.Hkv * p.n <= 65536)) return 1;
+    return blocks > kFewBlocks && blocks <= 96 && p.Hkv * ((p.n + 16l * kFewKB - 1) / (16 * kFewKB)) * blocks <= 20000 ? 4 : 0;
 }
 
 template <int D, int NW>
@@ -1356,14 +1380,12 @@ static hipError_t launch_score_tiled(const AttnParams &p, hipStream_t st)
     return hipGetLastError();
 }
 
-constexpr int kFewKB = 2;                               // 16-key blocks of a wave of the register-only form
-
 // Both passes where the first is split and the second takes few rows.  Merging is then a workgroup per row, so
 // there must not be many (a window of a longer chunk).
 template <int D>
 static bool launch_both(AttnParams p, void *part, size_t part_bytes, hipStream_t st, hipError_t &e)
 {
-    if (!score_few(p) || !fwd_place<D>(p, part, part_bytes) || (long)p.Hkv * p.n_row_blocks * p.part_rows > 2048)
+    if (score_few(p) != 1 || !fwd_place<D>(p, part, part_bytes) || (long)p.Hkv * p.n_row_blocks * p.part_rows > 2048)
         return false;
     e = launch_fwd_pieces<D>(p, st);
     if (e != hipSuccess) return true;
@@ -1377,10 +1399,11 @@ static bool launch_both(AttnParams p, void *part, size_t part_bytes, hipStream_t
 template <int D>
 static hipError_t launch_score(AttnParams p, void *part, size_t part_bytes, hipStream_t st)
 {
-    if (score_few(p)) {
+    if (const int rw = score_few(p)) {
         constexpr int KB = kFewKB;
-        const int grid = p.Hkv * ((p.n + 64 * KB - 1) / (64 * KB));
-        hipLaunchKernelGGL((attn_score_few<D, KB>), dim3(grid), dim3(256), 0, st, p);
+        const int keys = rw == 1 ? 64 * KB : 16 * KB, grid = p.Hkv * ((p.n + keys - 1) / keys);
+        if (rw == 1) hipLaunchKernelGGL((attn_score_few<D, KB, 1>), dim3(grid), dim3(256), 0, st, p);
+        else hipLaunchKernelGGL((attn_score_few<D, KB, 4>), dim3(grid), dim3(256), 0, st, p);
         return hipGetLastError();
     }
     int waves = score_plan(p);
