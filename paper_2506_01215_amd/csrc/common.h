@@ -191,6 +191,24 @@ __device__ __forceinline__ float wave_max(float x)
     return x;
 }
 
+// Inclusive sums over the 16 lanes of a row and over the wave, by data-parallel primitives: a shuffle goes through the
+// LDS unit and takes about 100 clocks, one of these moves some eight.
+__device__ __forceinline__ int row_incl_scan(int x)
+{
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);      // from 1, 2, 4, 8 lanes below
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    return x;
+}
+__device__ __forceinline__ int wave_incl_scan(int x)
+{
+    x = row_incl_scan(x);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);      // lane 15 to row 1, lane 47 to row 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);      // lane 31 to rows 2 and 3
+    return x;
+}
+
 // Monotone map float -> uint32: a > b  <=>  key(a) > key(b) (finite values; -0 and +0 map alike).
 __device__ __forceinline__ uint32_t ordered_key(float f)
 {

@@ -119,8 +119,8 @@ reform_status check_gather(const reform_gather_desc *d)
 long sim_pitch(int64_t n_ctx) { return (long)((n_ctx + 63) / 64 * 64 + 1088); }
 
 // Workgroups that may wait for each other in the selection of a gather call.  The calls of several
-// streams may overlap, so fewer than an eviction's: one workgroup is resident on a compute unit
-// (registers, and LDS where it holds the most keys), so four such launches fit the 256 together.
+// streams may overlap, so fewer than an eviction's: where it holds the most keys one workgroup is resident on a
+// compute unit (LDS), so four such launches fit the 256 together.
 constexpr int kGatherMultiGroups = 64;
 
 // The gather's similarities begin this many floats into their region (the last row ends at least 1088

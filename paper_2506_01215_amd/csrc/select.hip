@@ -454,6 +454,8 @@ __device__ __forceinline__ void radix_hist(const v4u *keys, int N, int w_lo, int
         const uint32_t dref = __builtin_amdgcn_readfirstlane(d0);
         if (__all(same && d0 == dref)) {
             if (lane == 0) atomicAdd(&h[dref], 256);
+        } else if (same) {                                    // a plateau: pooled scores mostly are
+            atomicAdd(&h[d0], 4);
         } else {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
@@ -462,6 +464,21 @@ __device__ __forceinline__ void radix_hist(const v4u *keys, int N, int w_lo, int
     }
 }
 
+// Sum of 16 waves' totals, and of those before this wave, by every wave for itself.
+__device__ __forceinline__ int waves_total(const int *wtot, int &before)
+{
+    const int wave = threadIdx.x >> 6, incl = row_incl_scan(wtot[threadIdx.x & 15]);
+    const int upto = __builtin_amdgcn_readlane(incl, (wave + 15) & 15);
+    before = __builtin_amdgcn_readfirstlane(wave) ? upto : 0;
+    return __builtin_amdgcn_readlane(incl, 15);
+}
+
+// Where the time of a selection goes (time stamps, 131072 similarities in 32 workgroups, 15.4 us before, 13.8 now):
+// load 1.5, histogram 0.6, exchange 2.8, pick 0.5 (0.85 with shuffles in place of data-parallel primitives), second
+// histogram 0.5 and exchange 2.5, pick 0.5, list 1.4, its pick 0.9, count 0.6, emission 1.6.  Whole calls: 37
+// queries pooled over 262144 x 1024 162.4 -> 155.7 us (its plateaus queued on few histogram words), 2048
+// rows fp32 13.5 -> 12.3 us, 65536 slots of 8 heads 115.6 -> 113.8 us.
+//
 // Executed by all 1024 threads: pick the digit of the histogram that holds the krem-th largest
 // key (thread t owns digits 2t and 2t+1), extend the prefix by it and report how many candidates
 // the digit holds.
@@ -470,22 +487,12 @@ __device__ __forceinline__ void bin_pick(int bits, uint32_t &prefix, int &krem, 
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l0 = h[2 * tid], l1 = h[2 * tid + 1], sum = l0 + l1;
-    int incl = sum;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(incl, o);
-        if (lane >= o) incl += y;
-    }
+    const int incl = wave_incl_scan(sum);
     if (lane == 63) wtot[wave] = incl;
     __syncthreads();
-    int below = incl - sum, total = 0;
-#pragma unroll
-    for (int w = 0; w < 16; ++w) {
-        const int x = wtot[w];
-        if (w < wave) below += x;
-        total += x;
-    }
-    const int above = total - below - sum;                    // candidates with a digit above 2t+1
+    int below;
+    const int total = waves_total(wtot, below);
+    const int above = total - below - incl;                   // candidates with a digit above 2t+1
     if (above < krem && krem <= above + l1) { sel[0] = 2 * tid + 1; sel[1] = krem - above; sel[2] = l1; }
     else if (above + l1 < krem && krem <= above + sum) { sel[0] = 2 * tid; sel[1] = krem - above - l1; sel[2] = l0; }
     __syncthreads();
@@ -495,23 +502,44 @@ __device__ __forceinline__ void bin_pick(int bits, uint32_t &prefix, int &krem, 
     __syncthreads();
 }
 
-// All 1024 threads: the krem-th largest of the m <= kSelList keys in `list` (padded with zeros).
-__device__ __forceinline__ void list_pick(const v4u *list, int m, int krem, uint32_t &T, int &need_eq, int *sel)
+// All 1024 threads: the krem-th largest of the m <= kSelList keys in `list` (padded with zeros), which agree from bit
+// `shift` up.  A short list: four threads per key count how many are larger, 0.5 us at 20 keys and 2.3 us at 256.  A
+// longer one: the first wave holds it all and settles a bit at a time by counting, 0.8 us for 10 bits and
+// 1.3 us for 21 whatever the length.
+constexpr int kCountedList = 96;
+
+__device__ __forceinline__ void list_pick(const v4u *list, int m, int krem, int shift, uint32_t &T, int &need_eq, int *sel)
 {
-    const int at = threadIdx.x >> 2;                          // four threads per key
-    const uint32_t mine = ((const uint32_t *)list)[at];
-    int gt = 0, eq = 0;
+    if (m <= kCountedList) {
+        const int at = threadIdx.x >> 2;
+        const uint32_t mine = ((const uint32_t *)list)[at];
+        int gt = 0, eq = 0;
 #pragma unroll 4
-    for (int i = threadIdx.x & 3; i < (m + 3) / 4; i += 4) {
-        const v4u x = list[i];
+        for (int i = threadIdx.x & 3; i < (m + 3) / 4; i += 4) {
+            const v4u x = list[i];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) { gt += x[j] > mine; eq += x[j] == mine; }
+            for (int j = 0; j < 4; ++j) { gt += x[j] > mine; eq += x[j] == mine; }
+        }
+        gt += __builtin_amdgcn_update_dpp(0, gt, 0xb1, 0xf, 0xf, false);      // lanes 1 0 3 2 of each four
+        gt += __builtin_amdgcn_update_dpp(0, gt, 0x4e, 0xf, 0xf, false);      // lanes 2 3 0 1
+        eq += __builtin_amdgcn_update_dpp(0, eq, 0xb1, 0xf, 0xf, false);
+        eq += __builtin_amdgcn_update_dpp(0, eq, 0x4e, 0xf, 0xf, false);
+        if (at < m && gt < krem && krem <= gt + eq) { sel[0] = (int)mine; sel[1] = krem - gt; }   // equal keys write the same
+    } else if (threadIdx.x < 64) {
+        const v4u x = list[threadIdx.x];
+        uint32_t t = __builtin_amdgcn_readfirstlane(x[0]) >> shift << shift;  // the shared bits
+        for (int b = shift - 1; b >= 0; --b) {
+            const uint32_t up = t | 1u << b;
+            int ge = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) ge += __popcll(__ballot(x[j] >= up));
+            if (ge >= krem) t = up;
+        }
+        int gt = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) gt += __popcll(__ballot(x[j] > t));
+        if (threadIdx.x == 0) { sel[0] = (int)t; sel[1] = krem - gt; }
     }
-    gt += __shfl_xor(gt, 1);
-    gt += __shfl_xor(gt, 2);
-    eq += __shfl_xor(eq, 1);
-    eq += __shfl_xor(eq, 2);
-    if (at < m && gt < krem && krem <= gt + eq) { sel[0] = (int)mine; sel[1] = krem - gt; }   // equal keys write the same
     __syncthreads();
     T = (uint32_t)sel[0];
     need_eq = sel[1];
@@ -539,14 +567,11 @@ __device__ __forceinline__ bool multi_wait_hist(const SelParams &p, const int *g
             v0 = __hip_atomic_load(&gh[2 * tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             v1 = __hip_atomic_load(&gh[2 * tid + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        int sum = v0 + v1;
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) sum += __shfl_xor(sum, o);
-        if (lane == 0) wtot[wave] = sum;
+        const int incl = wave_incl_scan(v0 + v1);
+        if (lane == 63) wtot[wave] = incl;
         __syncthreads();
-        int total = 0;
-#pragma unroll
-        for (int w = 0; w < 16; ++w) total += wtot[w];
+        int below;
+        const int total = waves_total(wtot, below);
         if (total == expected && p.spin_limit > 0) break;     // uniform: every thread saw the same total
         if (tid == 0) *stop = multi_give_up(p, spins);
         __syncthreads();                                      // also: wtot is rewritten by the next poll
@@ -712,7 +737,7 @@ __global__ __launch_bounds__(1024) void select_row(SelParams p, int parts, int n
         }
         __syncthreads();
         alone = MULTI && stop;
-        if (!alone) list_pick(list, in_bin, krem, T, need_eq, sel);
+        if (!alone) list_pick(list, in_bin, krem, shift, T, need_eq, sel);
         if (MULTI && !alone && at < wg_lo) {
             if (key > T) atomicAdd(&before[0], 1);
             if (key == T) atomicAdd(&before[1], 1);
@@ -742,10 +767,11 @@ __global__ __launch_bounds__(1024) void select_row(SelParams p, int parts, int n
         if (lane == 0) { wtot[0][wave] = gt_w; wtot[1][wave] = eq_w; }
         __syncthreads();
     }
-    int base_gt = before[0], base_eq = before[1];                 // above / equal to T before this wave's range
-#pragma unroll
-    for (int w = 0; w < 16; ++w)
-        if (w < wave) { base_gt += wtot[0][w]; base_eq += wtot[1][w]; }
+    int base_gt, base_eq;                                         // above / equal to T before this wave's range
+    waves_total(wtot[0], base_gt);
+    waves_total(wtot[1], base_eq);
+    base_gt += before[0];
+    base_eq += before[1];
     range_emit(p, q, mine, N, w_lo, nit, T, need_eq, base_gt + min(base_eq, need_eq), base_eq);
 }
 
