@@ -72,6 +72,7 @@ struct SelParams {
     int32_t *union_count;    // ... query's winners without neighbours
     int *zero_extra;         // nullable: zero_extra_n more ints cleared by the histogram-clearing launch
     int zero_extra_n;
+    int own_vals;            // vals is scratch of the call: the rows may be compacted in place
     int pre_zeroed;          // hist and zero_extra were cleared by an earlier kernel of the same call
     int multi_groups;        // rows too long for one workgroup may be selected in one launch by several
                              // workgroups that wait for each other, at most this many in all (0: never;

@@ -488,6 +488,7 @@ reform_status reform_gather_topk(const reform_gather_desc *d, const void *emb, c
         p.sel.mark = p.bitmap;
         p.sel.mark_radius = d->radius;
     }
+    p.sel.own_vals = 1;
     p.sel.multi_groups = kGatherMultiGroups;
     p.sel.gave_up = (int *)ws;                // in the 256 bytes before the similarities
     p.sel.spin_limit = g_move_spin_limit.load(std::memory_order_relaxed);

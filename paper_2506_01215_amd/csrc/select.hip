@@ -10,6 +10,8 @@
 //   select_count  final pick, then per workgroup the number of candidates above / equal to the
 //                 threshold key
 //   select_write  ordered emission: everything above the threshold, then the lowest-index ties
+//   select_compact, select_*_rest
+//                 the second pass and those behind it for rows that may be compacted in place
 //   select_row    all of the above in one launch, keys held in LDS: one workgroup per row, or several that
 //                 wait for each other where every workgroup of the launch fits on the chip at once
 // Candidates in the first n_sink or last n_recent slots get the maximal key (always selected).
@@ -20,6 +22,7 @@
 namespace reform {
 
 constexpr int kSelBlock = 4096;      // candidates per selection workgroup (256 threads x 16)
+constexpr int kRestWorkgroups = 1024; // the passes over what remains of compacted rows
 constexpr int kHistWorkgroups = 2048; // the histogram passes use about this many workgroups at most
 
 __device__ __forceinline__ uint32_t sel_key(const SelParams &p, const float *row, long t)
@@ -394,6 +397,213 @@ __global__ __launch_bounds__(256) void select_write(SelParams p)
     for (int w = 0; w < 4; ++w)
         if (w < wave) { base_gt += wtot[0][w]; base_eq += wtot[1][w]; }
     range_emit(p, q, mine, N, w_lo, 4, T, need_eq, base_gt + min(base_eq, need_eq), base_eq);
+}
+
+// ------------------------------------------------------------------------------------------
+// Rows that are the call's own scratch and of which at most 1/16 is selected: the second pass leaves of each block
+// of 4096 candidates only those with at least the first pass's digit (2 to 4 % where 1/64 is selected),
+// ascending, at the block's own place: their values and behind them their places in the block (16 bits
+// each).  A block of which more than two thirds remain stays as it is.  blk_cnt[0] of a block holds 1 + the number that
+// remain, shifted by 16, or 0 there.  The passes that follow read a few percent of the row.  16 rows of
+// 2^20 of which 1/64 is selected: passes of 18 + 20 + 17 + 15 + 28 us -> 18 + 21 + 5 + 5 + 9 us, the whole gather
+// 860 -> 817 us; 600000 x 512, 16 queries, 1/64 225 -> 190 us, five queries, 1/33 170 -> 162 us; 150000 x 256, 23
+// queries, 1/37 73.5 -> 67.0 us; but where 1/8 is selected 200000 x 512, 16 queries 115 -> 122 us.
+constexpr int kCompactShare = 16;
+
+struct Remaining {
+    const float *val;
+    const u16 *at;           // null: nothing was left out
+    int n;
+    __device__ __forceinline__ Remaining(const SelParams &p, int q, int blk, int word)
+    {
+        const long t0 = (long)blk * kSelBlock;
+        val = p.vals + (size_t)q * p.ld + t0;
+        n = (word >> 16) - 1;
+        at = n < 0 ? nullptr : (const u16 *)(val + n);
+        if (n < 0) n = (int)min((long)kSelBlock, p.N - t0);
+    }
+    __device__ __forceinline__ int place(int i) const { return at ? at[i] : i; }
+};
+
+// grid (<= nblk, nq): histogram of the second digit, as select_hist, and the compaction.
+__global__ __launch_bounds__(256) void select_compact(SelParams p)
+{
+    __shared__ int h[2048];
+    __shared__ int part[4];
+    __shared__ int sel[2];
+    __shared__ int wtot[4];
+    const int q = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int i = tid; i < 2048; i += 256) h[i] = 0;
+    uint32_t prefix;
+    int krem;
+    select_pick(p, q, 0, prefix, krem, part, sel);
+    if (blockIdx.x == 0 && tid == 0) {
+        p.sel_prefix[q] = prefix;
+        p.sel_krem[q] = krem;
+    }
+    float *row = const_cast<float *>(p.vals) + (size_t)q * p.ld;
+    for (int blk = blockIdx.x; blk < p.nblk; blk += gridDim.x) {
+        const long t0 = (long)blk * kSelBlock;
+        const int have = (int)min((long)kSelBlock, p.N - t0), w_lo = wave * 1024;
+        float v[4][4];
+#pragma unroll
+        for (int it = 0; it < 4; ++it)                   // a quad that begins inside the row ends inside its pitch
+            *(f32x4 *)v[it] = *(const f32x4 *)(row + t0 + min(w_lo + it * 256 + 4 * lane, (have - 1) & ~3));
+        unsigned kept = 0;                               // bit 4 * it + j
+        int mine = 0;
+#pragma unroll
+        for (int it = 0; it < 4; ++it)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t u = ordered_key(v[it][j]);
+                const bool in = w_lo + it * 256 + 4 * lane + j < have && (u >> 21) >= prefix;
+                if (in && (u >> 21) == prefix) atomicAdd(&h[digit_of(u, 1)], 1);
+                kept |= in ? 1u << (4 * it + j) : 0u;
+                mine += __popcll(__ballot(in));
+            }
+        if (lane == 0) wtot[wave] = mine;
+        __syncthreads();                                 // also: every value of the block has been read
+        int base = 0, c = 0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            base += w < wave ? wtot[w] : 0;
+            c += wtot[w];
+        }
+        const bool fits = 3 * c <= 2 * have;             // values and places within the block's own bytes
+        if (fits) {
+            u16 *at = (u16 *)(row + t0 + c);
+#pragma unroll
+            for (int it = 0; it < 4; ++it) {
+                int to = base;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const unsigned long long m = __ballot(kept >> (4 * it + j) & 1u);
+                    to += lanes_below(m);
+                    base += __popcll(m);
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (kept >> (4 * it + j) & 1u) {
+                        row[t0 + to] = v[it][j];
+                        at[to++] = (u16)(w_lo + it * 256 + 4 * lane + j);
+                    }
+            }
+        }
+        if (tid == 0) p.blk_cnt[((size_t)q * p.nblk + blk) * 2] = fits ? (c + 1) << 16 : 0;
+        __syncthreads();                                 // wtot is rewritten by the next block
+    }
+    int *gh = p.hist + ((size_t)q * 3 + 1) * 2048;
+    for (int i = tid; i < 2048; i += 256)
+        if (h[i]) atomicAdd(&gh[i], h[i]);
+}
+
+// grid (workgroups, nq), a wave per block of candidates: histogram of the last digit of what remains.
+__global__ __launch_bounds__(256) void select_hist_rest(SelParams p)
+{
+    __shared__ int h[1024];
+    __shared__ int part[4];
+    __shared__ int sel[2];
+    const int q = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+    for (int i = tid; i < 1024; i += 256) h[i] = 0;
+    uint32_t prefix;
+    int krem;
+    select_pick(p, q, 1, prefix, krem, part, sel);
+    if (blockIdx.x == 0 && tid == 0) {
+        p.sel_prefix[p.nq + q] = prefix;
+        p.sel_krem[p.nq + q] = krem;
+    }
+    for (int blk = blockIdx.x * 4 + (tid >> 6); blk < p.nblk; blk += gridDim.x * 4) {
+        const Remaining r(p, q, blk, p.blk_cnt[((size_t)q * p.nblk + blk) * 2]);
+        for (int i = lane; i < r.n; i += 64) {
+            const uint32_t u = ordered_key(r.val[i]);
+            if ((u >> 10) == prefix) atomicAdd(&h[u & 1023u], 1);
+        }
+    }
+    __syncthreads();
+    int *gh = p.hist + ((size_t)q * 3 + 2) * 2048;
+    for (int i = tid; i < 1024; i += 256)
+        if (h[i]) atomicAdd(&gh[i], h[i]);
+}
+
+// The same grid: per block, how many are above (low 16 bits of blk_cnt[0]) / equal to (blk_cnt[1]) the threshold.
+__global__ __launch_bounds__(256) void select_count_rest(SelParams p)
+{
+    __shared__ int part[4];
+    __shared__ int sel[2];
+    const int q = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+    uint32_t T;
+    int need_eq;
+    select_pick(p, q, 2, T, need_eq, part, sel);
+    if (blockIdx.x == 0 && tid == 0) {
+        p.sel_prefix[2 * p.nq + q] = T;
+        p.sel_krem[2 * p.nq + q] = need_eq;
+    }
+    for (int blk = blockIdx.x * 4 + (tid >> 6); blk < p.nblk; blk += gridDim.x * 4) {
+        int *cnt = p.blk_cnt + ((size_t)q * p.nblk + blk) * 2;
+        const int word = cnt[0];
+        const Remaining r(p, q, blk, word);
+        int gt = 0, eq = 0;
+        for (int i0 = 0; i0 < r.n; i0 += 64) {
+            const bool in = i0 + lane < r.n;
+            const uint32_t u = in ? ordered_key(r.val[i0 + lane]) : 0u;
+            gt += __popcll(__ballot(in && u > T));
+            eq += __popcll(__ballot(in && u == T));
+        }
+        if (lane == 0) {
+            cnt[0] = word | gt;                          // at most 4096
+            cnt[1] = eq;
+        }
+    }
+}
+
+// grid (nblk / 4, nq), a wave per block: ordered emission, as range_emit.
+__global__ __launch_bounds__(256) void select_write_rest(SelParams p)
+{
+    __shared__ int red[2][4];
+    const int q = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t T = p.sel_prefix[2 * p.nq + q];
+    const int need_eq = p.sel_krem[2 * p.nq + q];
+    const int *cnt = p.blk_cnt + (size_t)q * p.nblk * 2;
+    const int blk0 = blockIdx.x * 4, blk = blk0 + wave;
+    int gt = 0, eq = 0;                                  // in the blocks before this workgroup's
+    for (int b = tid; b < blk0; b += 256) { gt += cnt[2 * b] & 0xffff; eq += cnt[2 * b + 1]; }
+    gt = __builtin_amdgcn_readlane(wave_incl_scan(gt), 63);
+    eq = __builtin_amdgcn_readlane(wave_incl_scan(eq), 63);
+    if (lane == 0) { red[0][wave] = gt; red[1][wave] = eq; }
+    __syncthreads();
+    gt = red[0][0] + red[0][1] + red[0][2] + red[0][3];
+    eq = red[1][0] + red[1][1] + red[1][2] + red[1][3];
+    if (blk >= p.nblk) return;
+    for (int b = blk0; b < blk; ++b) { gt += cnt[2 * b] & 0xffff; eq += cnt[2 * b + 1]; }
+    const Remaining r(p, q, blk, cnt[2 * blk]);
+    int dest = gt + min(eq, need_eq);
+    const long t0 = (long)blk * kSelBlock;
+    int32_t *oi = p.out_idx + (size_t)q * p.out_ld;
+    float *os = p.out_val ? p.out_val + (size_t)q * p.out_ld : nullptr;
+    long before = 0;                                     // first place that the winners so far have not marked
+    for (int i0 = 0; i0 < r.n; i0 += 64) {
+        const bool in = i0 + lane < r.n;
+        const float v = in ? r.val[i0 + lane] : 0.f;
+        const int t = (int)t0 + (in ? r.place(i0 + lane) : 0);
+        const uint32_t u = ordered_key(v);
+        const unsigned long long me = __ballot(in && u == T);
+        const bool keep = in && (u > T || (u == T && eq + lanes_below(me) < need_eq));
+        const unsigned long long mk = __ballot(keep);
+        const int to = dest + lanes_below(mk);
+        if (keep && to < p.k) {                          // always, whatever the keys were
+            oi[to] = t;
+            if (os) os[to] = v;
+        }
+        if (p.mark && mk) {                              // each winner marks what the one before it has not
+            const unsigned long long below = mk & ((1ull << lane) - 1ull);
+            const int prev = __shfl(t, below ? 63 - __clzll(below) : lane);
+            const long from = below ? prev + p.mark_radius + 1 : before;
+            if (keep) mark_range(p.mark, max(t - p.mark_radius, from), min(t + p.mark_radius, p.N - 1));
+            before = __builtin_amdgcn_readlane(t, 63 - __clzll(mk)) + p.mark_radius + 1;
+        }
+        dest += __popcll(mk);
+        eq += __popcll(me);
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -842,6 +1052,22 @@ hipError_t select_topk(const SelParams &p, hipStream_t st)
     const dim3 sgrid(p.nblk, p.nq);
     const int hblk = max(1, kHistWorkgroups / p.nq);       // workgroups per row of the histogram passes
     const dim3 hgrid(min(p.nblk, hblk), p.nq);
+    if (p.own_vals && p.k <= p.N / kCompactShare && !p.n_sink && !p.n_recent && !p.out_rank && !p.side_src && !p.union_idx &&
+        (p.ld & 3) == 0 && ((uintptr_t)p.vals & 15) == 0) {
+        hipLaunchKernelGGL(select_hist, hgrid, dim3(256), 0, st, p, 0);
+        RF_CHECK_LAUNCH();
+        hipLaunchKernelGGL(select_compact, hgrid, dim3(256), 0, st, p);
+        RF_CHECK_LAUNCH();
+        const dim3 rgrid((p.nblk + 3) / 4, p.nq);
+        const dim3 fgrid(min((int)rgrid.x, max(1, kRestWorkgroups / p.nq)), p.nq);
+        hipLaunchKernelGGL(select_hist_rest, fgrid, dim3(256), 0, st, p);
+        RF_CHECK_LAUNCH();
+        hipLaunchKernelGGL(select_count_rest, fgrid, dim3(256), 0, st, p);
+        RF_CHECK_LAUNCH();
+        hipLaunchKernelGGL(select_write_rest, rgrid, dim3(256), 0, st, p);
+        RF_CHECK_LAUNCH();
+        return hipSuccess;
+    }
     for (int pass = 0; pass < 3; ++pass) {
         hipLaunchKernelGGL(select_hist, hgrid, dim3(256), 0, st, p, pass);
         RF_CHECK_LAUNCH();
