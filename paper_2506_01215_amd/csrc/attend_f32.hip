@@ -139,7 +139,15 @@ __device__ __forceinline__ f32x4 f32_logits(const float (&a)[D / 4], const float
 // 32 busy compute units is what a block waits for (2048 of the 2900 clocks of a step).
 constexpr int kF32FwdWaves = 8;
 
-template <int D>
+// SPLIT: the fp32 matrix pipe of a compute unit is what a row block waits for, so few row blocks share their key blocks
+// over p.shares workgroups each, whose sums go to the workspace: [share][head, row block, row].  They are merged by the
+// launch that forms the score where there is one (attn_merge_score_f32), else by one of its own.  Attention and score:
+// 128 rows over 384 keys, 4 heads of 64 13.6 -> 11.6 us, 16 over 1040, 8/2 heads 20.6 -> 13.2 us, 40 over 940, 4 heads
+// of 128 31.3 -> 19.1 us.
+constexpr int kF32MaxShares = 4;
+__device__ __forceinline__ size_t f32_slot(const AttnParams &p, int nrb, int h, int i) { return ((size_t)h * nrb + i / 16) * 16 + i % 16; }
+
+template <int D, bool SPLIT>
 __global__ __launch_bounds__(kF32FwdWaves * 64) void attn_fwd_f32_mfma(AttnParams p)
 {
     constexpr int NW = kF32FwdWaves, DB = D / 16, PITCH = D + 4;
@@ -148,7 +156,9 @@ __global__ __launch_bounds__(kF32FwdWaves * 64) void attn_fwd_f32_mfma(AttnParam
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int ln = lane & 15, lg = lane >> 4;
     const int nrb = (p.Ct + 15) / 16;
-    const int h = blockIdx.x % p.Hq, i0 = (nrb - 1 - blockIdx.x / p.Hq) * 16;   // late row blocks first
+    const int share = SPLIT ? blockIdx.x % p.shares : 0, bid = SPLIT ? blockIdx.x / p.shares : blockIdx.x;
+    const int h = bid % p.Hq, i0 = (nrb - 1 - bid / p.Hq) * 16;                 // late row blocks first
+    const int b0 = share * NW + wave, step = SPLIT ? p.shares * NW : NW;        // the wave's key blocks
     const int g = h / p.G;
     const float *K = (const float *)p.k + (size_t)g * p.cap * D;
     const float *V = (const float *)p.v + (size_t)g * p.cap * D;
@@ -170,17 +180,17 @@ __global__ __launch_bounds__(kF32FwdWaves * 64) void attn_fwd_f32_mfma(AttnParam
     };
     auto key_row = [&](int b) { return K + (size_t)min(b * 16 + ln, p.n - 1) * D; };
     f32_load_row<D>(q, (const float *)p.q + (size_t)h * p.q_hs + (size_t)min(i0 + ln, p.Ct - 1) * p.q_rs, lg);
-    f32_load_row<D>(k, key_row(wave), lg);
-    load_v(wave);
+    f32_load_row<D>(k, key_row(b0), lg);
+    load_v(b0);
 
     f32x4 o[DB];
 #pragma unroll
     for (int db = 0; db < DB; ++db) o[db] = (f32x4){0.f, 0.f, 0.f, 0.f};
     float m = -INFINITY, l = 0.f;
-    for (int b = wave; b < nblk; b += NW) {
+    for (int b = b0; b < nblk; b += step) {
         const int j0 = b * 16;
         f32x4 s = f32_logits<D>(k, q);
-        f32_load_row<D>(k, key_row(b + NW), lg);         // past the end: the last key again
+        f32_load_row<D>(k, key_row(b + step), lg);         // past the end: the last key again
         float x[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) x[e] = j0 + 4 * lg + e > lim ? -INFINITY : p.scale * s[e];
@@ -228,7 +238,7 @@ __global__ __launch_bounds__(kF32FwdWaves * 64) void attn_fwd_f32_mfma(AttnParam
                             o[db][c] = fmaf(w, V[(size_t)j * D + DB * (4 * lg + c) + db], o[db][c]);
                 }
         }
-        load_v(b + NW);
+        load_v(b + step);
     }
     l += __shfl_xor(l, 16);
     l += __shfl_xor(l, 32);
@@ -266,6 +276,17 @@ __global__ __launch_bounds__(kF32FwdWaves * 64) void attn_fwd_f32_mfma(AttnParam
         f32x4 x = *(const f32x4 *)&so[0][r][c];
 #pragma unroll
         for (int w = 1; w < NW / 2; ++w) x += *(const f32x4 *)&so[w][r][c];
+        if constexpr (SPLIT) {
+            const size_t at = (size_t)share * p.part_rows + f32_slot(p, nrb, h, i0 + r);
+            *(f32x4 *)(p.part_o + at * D + c) = x;
+            if (c == 0) {
+                float mt = -INFINITY;                        // a share without a visible key: -inf, and sums of 0
+#pragma unroll
+                for (int w = 0; w < NW; ++w) mt = fmaxf(mt, sm[w][r]);
+                p.part_ml[at] = make_float2(mt, lt);
+            }
+            continue;
+        }
         *(f32x4 *)((float *)p.out + (size_t)h * p.o_hs + (size_t)(i0 + r) * p.o_rs + c) = x / lt;
         if (c == 0) {
             float mt = -INFINITY;
@@ -282,32 +303,55 @@ __global__ __launch_bounds__(kF32FwdWaves * 64) void attn_fwd_f32_mfma(AttnParam
 // order (identical keys, identical scores).  4 heads, 128 rows over 384 keys 7.8 -> 4 us.
 constexpr int kF32ScoreWaves = 8;
 
-template <int D>
-__global__ __launch_bounds__(kF32ScoreWaves * 64) void attn_score_f32_mfma(AttnParams p)
+// Largest maximum and the sum relative to it of a row's shares.
+__device__ __forceinline__ float2 f32_total(const float2 (&ml)[kF32MaxShares])
+{
+    float m = -INFINITY, l = 0.f;
+#pragma unroll
+    for (int s = 0; s < kF32MaxShares; ++s) m = fmaxf(m, ml[s].x);
+#pragma unroll
+    for (int s = 0; s < kF32MaxShares; ++s) l += ml[s].x == -INFINITY ? 0.f : ml[s].y * expf(ml[s].x - m);
+    return make_float2(m, l);
+}
+
+template <int D, bool PIECES>
+__device__ __forceinline__ void f32_score_keys(const AttnParams &p, int bid)
 {
     constexpr int NW = kF32ScoreWaves;
     __shared__ float part[NW][16];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int ln = lane & 15, lg = lane >> 4;
-    const int g = blockIdx.x % p.Hkv, j0 = blockIdx.x / p.Hkv * 16;
+    const int g = bid % p.Hkv, j0 = bid / p.Hkv * 16;
     float k[D / 4], q[D / 4];
     f32_load_row<D>(k, (const float *)p.k + ((size_t)g * p.cap + min(j0 + ln, p.n - 1)) * D, lg);
     const int i_first = max(p.Ct - p.W, max(j0 - p.M, 0));     // first row that observes and sees key j0
     const int nb = (p.Ct - i_first + 15) / 16;                 // row blocks per head (>= 1 since j0 < n)
     const int items = p.G * nb;
+    const int nrb = (p.Ct + 15) / 16;
     float lse = 0.f;
+    float2 ml[kF32MaxShares];
     auto load_q = [&](int it) {
         it = min(it, items - 1);
         const int h = g * p.G + it / nb, i = min(i_first + it % nb * 16 + ln, p.Ct - 1);
         f32_load_row<D>(q, (const float *)p.q + (size_t)h * p.q_hs + (size_t)i * p.q_rs, lg);
-        lse = p.lse[(size_t)h * p.Ct + i];
+        if constexpr (PIECES) {
+#pragma unroll
+            for (int s = 0; s < kF32MaxShares; ++s)
+                ml[s] = s < p.shares ? p.part_ml[(size_t)s * p.part_rows + f32_slot(p, nrb, h, i)] : make_float2(-INFINITY, 0.f);
+        } else {
+            lse = p.lse[(size_t)h * p.Ct + i];
+        }
     };
     load_q(wave);
     f32x4 col = {0.f, 0.f, 0.f, 0.f};
     for (int it = wave; it < items; it += NW) {
         const int i = i_first + it % nb * 16 + ln, lim = i < p.Ct ? p.M + i : -1;
         const f32x4 s = f32_logits<D>(k, q);
-        const float ls = lse;
+        float ls = lse;
+        if constexpr (PIECES) {
+            const float2 t = f32_total(ml);
+            ls = t.x + logf(t.y);
+        }
         load_q(it + NW);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -333,10 +377,95 @@ __global__ __launch_bounds__(kF32ScoreWaves * 64) void attn_score_f32_mfma(AttnP
 }
 
 template <int D>
-static hipError_t launch_fwd_f32(const AttnParams &p, hipStream_t st)
+__global__ __launch_bounds__(kF32ScoreWaves * 64) void attn_score_f32_mfma(AttnParams p)
 {
-    const unsigned grid = (unsigned)p.Hq * ((p.Ct + 15) / 16);
-    hipLaunchKernelGGL(attn_fwd_f32_mfma<D>, dim3(grid), dim3(kF32FwdWaves * 64), 0, st, p);
+    f32_score_keys<D, false>(p, blockIdx.x);
+}
+
+// Output and lse of one row block of a head from its shares.
+template <int D>
+__device__ __forceinline__ void f32_merge_rows(const AttnParams &p, int bid)
+{
+    const int nrb = (p.Ct + 15) / 16, h = bid % p.Hq, i0 = bid / p.Hq * 16;
+    for (int t = threadIdx.x; t < 16 * (D / 4); t += kF32ScoreWaves * 64) {
+        const int i = i0 + t / (D / 4), c = t % (D / 4) * 4;
+        if (i >= p.Ct) break;
+        float2 ml[kF32MaxShares];
+        f32x4 o[kF32MaxShares];
+#pragma unroll
+        for (int s = 0; s < kF32MaxShares; ++s) {
+            const size_t at = (size_t)min(s, p.shares - 1) * p.part_rows + f32_slot(p, nrb, h, i);
+            ml[s] = p.part_ml[at];
+            o[s] = *(const f32x4 *)(p.part_o + at * D + c);
+            if (s >= p.shares) ml[s] = make_float2(-INFINITY, 0.f);
+        }
+        const float2 tot = f32_total(ml);
+        f32x4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < kF32MaxShares; ++s)
+            if (ml[s].x != -INFINITY) x += o[s] * expf(ml[s].x - tot.x);
+        *(f32x4 *)((float *)p.out + (size_t)h * p.o_hs + (size_t)i * p.o_rs + c) = x / tot.y;
+        if (c == 0) p.lse[(size_t)h * p.Ct + i] = tot.x + logf(tot.y);
+    }
+}
+
+template <int D>
+__global__ __launch_bounds__(kF32ScoreWaves * 64) void attn_merge_f32(AttnParams p)
+{
+    f32_merge_rows<D>(p, blockIdx.x);
+}
+
+// Both in one launch: the first n_score workgroups form the score, with the normalisers from the shares.
+template <int D>
+__global__ __launch_bounds__(kF32ScoreWaves * 64) void attn_merge_score_f32(AttnParams p, int n_score)
+{
+    if ((int)blockIdx.x < n_score) f32_score_keys<D, true>(p, blockIdx.x);
+    else f32_merge_rows<D>(p, blockIdx.x - n_score);
+}
+
+// Shares of a problem (1: whole) with and without a score behind it.  A wave's step over a key block is 1.2 us;
+// the launch that merges costs 3 us where it is not the score's.
+static int f32_shares(const AttnParams &p, bool score)
+{
+    if (p.D != 32 && p.D != 64 && p.D != 128) return 1;
+    const long groups = (long)p.Hq * ((p.Ct + 15) / 16), cus = device_compute_units() > 0 ? device_compute_units() : 256;
+    const int steps = ((p.n - 1) / 16 + kF32FwdWaves) / kF32FwdWaves;
+    int shares = (int)(cus / groups < kF32MaxShares ? cus / groups : kF32MaxShares);
+    if (shares > steps) shares = steps;
+    if (shares < 2 || (!score && (steps - (steps + shares - 1) / shares) * 1.2 < 3.0)) return 1;
+    return shares;
+}
+
+static size_t f32_rows(const AttnParams &p) { return (size_t)p.Hq * ((p.Ct + 15) / 16) * 16; }
+
+size_t attend_f32_scratch_bytes(const AttnParams &p)
+{
+    const int shares = f32_shares(p, true);                  // with a score at least as many as without
+    return shares > 1 ? (size_t)shares * f32_rows(p) * (p.D * sizeof(float) + sizeof(float2)) : 0;
+}
+
+// Attention, and with `score` the score: in two launches of the same kind each, split or not.
+template <int D>
+static hipError_t launch_f32(AttnParams p, void *part, size_t part_bytes, bool score, hipStream_t st)
+{
+    const unsigned groups = (unsigned)p.Hq * ((p.Ct + 15) / 16), n_score = (unsigned)p.Hkv * ((p.n + 15) / 16);
+    const dim3 fwd(kF32FwdWaves * 64), sc(kF32ScoreWaves * 64);
+    p.shares = f32_shares(p, score);
+    const size_t rows = f32_rows(p);
+    if (p.shares < 2 || !part || part_bytes < p.shares * rows * (D * sizeof(float) + sizeof(float2))) {
+        hipLaunchKernelGGL((attn_fwd_f32_mfma<D, false>), dim3(groups), fwd, 0, st, p);
+        if (score && hipPeekAtLastError() == hipSuccess)
+            hipLaunchKernelGGL(attn_score_f32_mfma<D>, dim3(n_score), sc, 0, st, p);
+        return hipGetLastError();
+    }
+    p.part_rows = (int)rows;
+    p.part_o = (float *)part;
+    p.part_ml = (float2 *)(p.part_o + p.shares * rows * D);
+    hipLaunchKernelGGL((attn_fwd_f32_mfma<D, true>), dim3(groups * p.shares), fwd, 0, st, p);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (score) hipLaunchKernelGGL(attn_merge_score_f32<D>, dim3(n_score + groups), sc, 0, st, p, (int)n_score);
+    else hipLaunchKernelGGL(attn_merge_f32<D>, dim3(groups), sc, 0, st, p);
     return hipGetLastError();
 }
 
@@ -348,13 +477,17 @@ static hipError_t launch_score_f32(const AttnParams &p, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t attend_f32_forward(const AttnParams &p, hipStream_t st)
+hipError_t attend_f32_score(const AttnParams &p, hipStream_t st);
+
+// Attention and, with `score`, the score of one call.  part: scratch for the shares' sums.
+hipError_t attend_f32_forward(const AttnParams &p, void *part, size_t part_bytes, bool score, hipStream_t st)
 {
-    if (p.D == 32) return launch_fwd_f32<32>(p, st);
-    if (p.D == 64) return launch_fwd_f32<64>(p, st);
-    if (p.D == 128) return launch_fwd_f32<128>(p, st);
+    if (p.D == 32) return launch_f32<32>(p, part, part_bytes, score, st);
+    if (p.D == 64) return launch_f32<64>(p, part, part_bytes, score, st);
+    if (p.D == 128) return launch_f32<128>(p, part, part_bytes, score, st);
     hipLaunchKernelGGL(attn_fwd_f32, dim3((unsigned)p.Hq * p.Ct), dim3(64), 0, st, p);
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess && score ? attend_f32_score(p, st) : e;
 }
 
 hipError_t attend_f32_score(const AttnParams &p, hipStream_t st)

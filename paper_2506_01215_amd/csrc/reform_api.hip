@@ -12,7 +12,8 @@ hipError_t attend_bf16_forward(const AttnParams &p, void *part, size_t part_byte
 size_t attend_bf16_scratch_bytes(const AttnParams &sizes);
 hipError_t attend_bf16_both(const AttnParams &p, void *part, size_t part_bytes, hipStream_t st);
 hipError_t attend_bf16_score(const AttnParams &p, void *part, size_t part_bytes, hipStream_t st);
-hipError_t attend_f32_forward(const AttnParams &p, hipStream_t st);
+hipError_t attend_f32_forward(const AttnParams &p, void *part, size_t part_bytes, bool score, hipStream_t st);
+size_t attend_f32_scratch_bytes(const AttnParams &sizes);
 hipError_t attend_f32_score(const AttnParams &p, hipStream_t st);
 
 hipError_t evict_run(EvictParams p, hipStream_t st);
@@ -238,7 +239,8 @@ size_t reform_chunk_attend_score_workspace(const reform_attn_desc *d)
 {
     if (check_attn(d) != REFORM_OK) return 0;
     size_t bytes = attn_lse_bytes(d);
-    if (d->dtype == REFORM_BF16) bytes += align_up(attend_bf16_scratch_bytes(attn_sizes(d)));
+    const AttnParams p = attn_sizes(d);
+    bytes += align_up(d->dtype == REFORM_BF16 ? attend_bf16_scratch_bytes(p) : attend_f32_scratch_bytes(p));
     return bytes;
 }
 
@@ -266,8 +268,8 @@ reform_status reform_chunk_attend_score(const reform_attn_desc *d, const void *q
         else if (do_attn) e = attend_bf16_forward(p, part, part_bytes, st);
         else if (do_score) e = attend_bf16_score(p, part, part_bytes, st);
     } else {
-        if (do_attn) e = attend_f32_forward(p, st);
-        if (e == hipSuccess && do_score) e = attend_f32_score(p, st);
+        if (do_attn) e = attend_f32_forward(p, part, part_bytes, do_score, st);
+        else if (do_score) e = attend_f32_score(p, st);
     }
     return e == hipSuccess ? REFORM_OK : REFORM_ERR_RUNTIME;
 }
