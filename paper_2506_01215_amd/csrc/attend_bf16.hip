@@ -1273,9 +1273,9 @@ static hipError_t launch_fwd_pieces(const AttnParams &p, hipStream_t st)
 }
 
 template <int D>
-static hipError_t launch_fwd(AttnParams p, void *part, size_t part_bytes, hipStream_t st)
+static hipError_t launch_fwd(const AttnParams &p, bool split, hipStream_t st)
 {
-    if (!fwd_place<D>(p, part, part_bytes)) return launch_fwd_form<D, false>(p, p.Hkv * p.n_row_blocks, st);
+    if (!split) return launch_fwd_form<D, false>(p, p.Hkv * p.n_row_blocks, st);
     const hipError_t e = launch_fwd_pieces<D>(p, st);
     if (e != hipSuccess) return e;
     // pieces of the longest row block: two or three where row blocks are many, a head's shares for a token
@@ -1380,22 +1380,6 @@ static hipError_t launch_score_tiled(const AttnParams &p, hipStream_t st)
     return hipGetLastError();
 }
 
-// Both passes where the first is split and the second takes few rows.  Merging is then a workgroup per row, so
-// there must not be many (a window of a longer chunk).
-template <int D>
-static bool launch_both(AttnParams p, void *part, size_t part_bytes, hipStream_t st, hipError_t &e)
-{
-    if (score_few(p) != 1 || !fwd_place<D>(p, part, part_bytes) || (long)p.Hkv * p.n_row_blocks * p.part_rows > 2048)
-        return false;
-    e = launch_fwd_pieces<D>(p, st);
-    if (e != hipSuccess) return true;
-    const int n_score = p.Hkv * ((p.n + 64 * kFewKB - 1) / (64 * kFewKB));
-    const int n_merge = p.part_rows * p.n_row_blocks * p.Hkv;
-    hipLaunchKernelGGL((attn_merge_score<D, kFewKB>), dim3(n_score + n_merge), dim3(256), 0, st, p, n_score);
-    e = hipGetLastError();
-    return true;
-}
-
 template <int D>
 static hipError_t launch_score(AttnParams p, void *part, size_t part_bytes, hipStream_t st)
 {
@@ -1417,6 +1401,25 @@ static hipError_t launch_score(AttnParams p, void *part, size_t part_bytes, hipS
     return waves == 8 ? launch_score_tiled<D, 8>(p, st) : launch_score_tiled<D, 4>(p, st);
 }
 
+// Both passes.  Where the first is split and the second takes few rows, merging and the score are one launch;
+// merging is then a workgroup per row, so there must not be many (a window of a longer chunk).
+template <int D>
+static hipError_t launch_both(const AttnParams &p, void *part, size_t part_bytes, hipStream_t st)
+{
+    AttnParams f = p;
+    const bool split = fwd_place<D>(f, part, part_bytes);
+    if (!split || score_few(p) != 1 || (long)f.Hkv * f.n_row_blocks * f.part_rows > 2048) {
+        const hipError_t e = launch_fwd<D>(f, split, st);
+        return e == hipSuccess ? launch_score<D>(p, part, part_bytes, st) : e;
+    }
+    const hipError_t e = launch_fwd_pieces<D>(f, st);
+    if (e != hipSuccess) return e;
+    const int n_score = f.Hkv * ((f.n + 64 * kFewKB - 1) / (64 * kFewKB));
+    const int n_merge = f.part_rows * f.n_row_blocks * f.Hkv;
+    hipLaunchKernelGGL((attn_merge_score<D, kFewKB>), dim3(n_score + n_merge), dim3(256), 0, st, f, n_score);
+    return hipGetLastError();
+}
+
 // Scratch of either pass (they run one after the other and share it).
 size_t attend_bf16_scratch_bytes(const AttnParams &sizes)
 {
@@ -1431,27 +1434,30 @@ size_t attend_bf16_scratch_bytes(const AttnParams &sizes)
     return fwd > score ? fwd : score;
 }
 
-hipError_t attend_bf16_forward(const AttnParams &p, void *part, size_t part_bytes, hipStream_t st)
+template <int D>
+static hipError_t launch_attention(AttnParams p, void *part, size_t part_bytes, hipStream_t st)
 {
-    if (p.D == 128) return launch_fwd<128>(p, part, part_bytes, st);
-    return launch_fwd<64>(p, part, part_bytes, st);
+    const bool split = fwd_place<D>(p, part, part_bytes);
+    return launch_fwd<D>(p, split, st);
 }
 
-hipError_t attend_bf16_score(const AttnParams &p, void *part, size_t part_bytes, hipStream_t st);
-
-// Attention and score of one call.
-hipError_t attend_bf16_both(const AttnParams &p, void *part, size_t part_bytes, hipStream_t st)
+hipError_t attend_bf16_forward(const AttnParams &p, void *part, size_t part_bytes, hipStream_t st)
 {
-    hipError_t e = hipSuccess;
-    if (p.D == 128 ? launch_both<128>(p, part, part_bytes, st, e) : launch_both<64>(p, part, part_bytes, st, e)) return e;
-    e = attend_bf16_forward(p, part, part_bytes, st);
-    return e == hipSuccess ? attend_bf16_score(p, part, part_bytes, st) : e;
+    if (p.D == 128) return launch_attention<128>(p, part, part_bytes, st);
+    return launch_attention<64>(p, part, part_bytes, st);
 }
 
 hipError_t attend_bf16_score(const AttnParams &p, void *part, size_t part_bytes, hipStream_t st)
 {
     if (p.D == 128) return launch_score<128>(p, part, part_bytes, st);
     return launch_score<64>(p, part, part_bytes, st);
+}
+
+// Attention and score of one call.
+hipError_t attend_bf16_both(const AttnParams &p, void *part, size_t part_bytes, hipStream_t st)
+{
+    if (p.D == 128) return launch_both<128>(p, part, part_bytes, st);
+    return launch_both<64>(p, part, part_bytes, st);
 }
 
 }  // namespace reform
