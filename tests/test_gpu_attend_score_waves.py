@@ -44,3 +44,17 @@ def test_score_matches_oracle(Hq, Hkv, d, M, Ct, W, accumulate):
     assert (score[:, n:] == (0.25 if accumulate else 7.0)).all()
     if M > 40:
         assert (score[:, M - 1] == score[:, 2]).all()
+
+
+@pytest.mark.parametrize("W", [63, 64, 65, 129, 193])
+def test_tiles_begin_with_the_window(W):
+    """Too many keys for the form above: query tiles of 64, counted from the first observing row."""
+    Hq, Hkv, d, M, Ct = 8, 2, 64, 16500, 200
+    g = torch.Generator().manual_seed(W)
+    q = torch.randn((Hq, Ct, d), generator=g).to(torch.bfloat16)
+    k = (1.5 * torch.randn((Hkv, M + Ct, d), generator=g)).to(torch.bfloat16)
+    v = torch.randn((Hkv, M + Ct, d), generator=g).to(torch.bfloat16)
+    _, _, s_ref = oracle.attend_score(to_np(q), to_np(k), to_np(v), M, 0.125, W)
+    _, _, score = binding.reform_chunk_attend_score(q.to(DEV), k.to(DEV), v.to(DEV), M, 0.125, obs_window=W)
+    torch.cuda.synchronize()
+    assert_scores_close(to_np(score), s_ref, 1e-5, "score")
