@@ -103,7 +103,7 @@ __global__ __launch_bounds__(kSimThreads) void sim_bf16_mfma(GatherParams p)
     // Past the wave's last group the cursor stays on one line of the store, so that the unconditional loads
     // there cost no traffic.
     const u16 *const idle = E + 8 * lg;
-    const u16 *l_base = grp < ngroups ? row_ptr(grp) : idle;
+    const u16 *l_base = row_ptr(grp);
     auto load_next = [&](v4u (&dst)[kChunk]) {
         if (FULL) {
 #pragma unroll
@@ -172,9 +172,13 @@ __global__ __launch_bounds__(kSimThreads) void sim_bf16_mfma(GatherParams p)
             keep(c0);
         }
         fetch(c0);
-        load_next(cur);
-        load_next(nx1);
-        keep(c0);
+        if (grp < ngroups) {
+            load_next(cur);
+            load_next(nx1);
+            keep(c0);
+        } else {                           // a wave without a group (short stores): no loads in the others' way
+            keep(c0);
+        }
 #pragma unroll
         for (int i = 0; i < NQ; ++i) {
             const float t = wave_sum(ss[i]);
@@ -533,10 +537,10 @@ static hipError_t similarity_passes(GatherParams p, bool bf16, hipStream_t st)
     const int cus = device_compute_units() > 0 ? device_compute_units() : 256;
     const size_t lds = 160 * 1024, block = (size_t)16 * (p.D + ((32 - 2 * p.D) & 255) / 2) * sizeof(u16);
     const bool mfma = bf16 && p.D % 32 == 0 && (size_t)16 * (p.D + 128) * 2 <= 150 * 1024;
-    // one / a few queries over a short store: a wave per row is as fast (2048 x 256, one query 12.4 and 12.6 us) or faster
-    // (700 x 64, one query 15.2 and 16.4 us)
+    // little work: a wave per row is as fast (2048 x 256, one query 12.4 and 12.6 us) or faster (700 x 64, one query 15.2
+    // and 16.4 us, 4126 x 64, one 20.0 and 20.3 us); 4100 x 128, one query 15.1 and 14.7 us, 1100 x 512, four 19.8 and 17.9 us
     const bool f32_mfma = !bf16 && p.D % 16 == 0 && (size_t)16 * sim_f32_pitch(p.D) * sizeof(float) <= 140 * 1024 &&
-                          p.N * p.nq >= 4096;
+                          (double)p.N * p.nq * p.D > 524288.0;
     // blocks of 16 queries: as few passes over the store as the LDS allows, evenly filled
     const int blocks = (p.nq + 15) / 16;
     const int fit = mfma ? (int)min((size_t)4, (lds - 1024) / block) : 1;

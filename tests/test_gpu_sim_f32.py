@@ -14,7 +14,7 @@ DEV = "cuda:0"
 
 
 @pytest.mark.parametrize("N,D,nq", [
-    (4096, 16, 1), (4095, 16, 1), (273, 32, 15), (1025, 48, 4), (300, 80, 17), (511, 256, 16), (4113, 272, 1),
+    (2048, 256, 1), (2049, 256, 1), (33000, 16, 1), (273, 32, 15), (1025, 48, 4), (300, 80, 17), (511, 256, 16), (4113, 272, 1),
     (257, 512, 33), (130, 1040, 40), (400, 2000, 16), (300, 2208, 14), (300, 2400, 14),
 ])
 def test_similarities_and_their_maximum(N, D, nq):
