@@ -756,7 +756,7 @@ __global__ __launch_bounds__(256) void attn_fwd_merge(AttnParams p)
 //
 // Per logit the VALU does one v_fma (scale and -lse folded), one v_exp and one v_add; the mask is
 // applied only on the tiles that straddle the causal diagonal (separate, rarely taken path), and
-// rows outside the observation window or past the chunk end are switched off through lse = +inf.
+// rows past the chunk end are switched off through lse = +inf.
 template <int D, int NT>
 struct QStage {
     static constexpr int QT = 64;
@@ -780,10 +780,8 @@ struct QStage {
         lpre = 0.f;
         lvalid = false;
     }
-    // Qt: first row of the tile (uniform); lse_t: lse of that row; rows_left = Ct - i0 (>= 1);
-    // first_obs = first observing row relative to the tile (<= 0 when the whole tile observes)
-    __device__ __forceinline__ void load(const u16 *Qt, const float *lse_t, int rows_left, int first_obs,
-                                         long q_rs, int tid)
+    // Qt: first row of the tile (uniform); lse_t: lse of that row; rows_left = Ct - i0 (>= 1)
+    __device__ __forceinline__ void load(const u16 *Qt, const float *lse_t, int rows_left, long q_rs, int tid)
     {
         const char *qb = (const char *)Qt;
         if (rows_left >= QT) {
@@ -799,7 +797,7 @@ struct QStage {
         }
         // raw value only: multiplying here would wait for the load right after issuing it
         if (tid < QT) {
-            lvalid = tid >= first_obs && tid < rows_left;
+            lvalid = tid < rows_left;
             lpre = lvalid ? lse_t[tid] : 0.f;
         }
     }
@@ -819,7 +817,8 @@ struct QStage {
 // alternates between two registers costs 4 % less than a new A operand on every MFMA.  The
 // 32x32x16 form of this kernel (32 keys x 32 rows per MFMA, new key fragment every MFMA) was
 // 1.2 % slower.
-template <int D, int KB, int NW>
+// WINDOW: not every row observes.  Without it the first observing row is 0 at compile time.
+template <int D, int KB, int NW, bool WINDOW>
 __global__ __launch_bounds__(NW * 64, 2) void attn_score_bf16(AttnParams p)
 {
     constexpr int NT = NW * 64;
@@ -848,15 +847,16 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_score_bf16(AttnParams p)
     const int j_wg = kt * (NW * WKEYS);
     const int jw = j_wg + wave * WKEYS;
 
-    const int i_lo = p.Ct - p.W;                         // first observing row
+    const int i_lo = WINDOW ? p.Ct - p.W : 0;            // first observing row
     const int i_first = max(i_lo, max(j_wg - p.M, 0));   // first row that both observes and sees j_wg
     // query tiles of this slice, counted from the first observing row for every key block: a window of 128 rows
     // is two tiles wherever it begins, not three (whole calls: 128 of 3001 rows over 11193 keys, 24/8 heads of 64 235.4
     // -> 229.2 us, 128 of 400 over 30400, 14/2 heads of 64 94.7 -> 85.3 us)
     const int s_lo = tile_slice * p.slice_tiles;
     const int qt0 = max((i_first - i_lo) / QT, s_lo);
-    const int ntq = min((p.W + QT - 1) / QT, s_lo + p.slice_tiles) - qt0;    // per head
+    const int ntq = min(((WINDOW ? p.W : p.Ct) + QT - 1) / QT, s_lo + p.slice_tiles) - qt0;    // per head
     if (ntq <= 0) return;                                // the whole slice lies before the diagonal
+    const int i_base = i_lo + qt0 * QT;
 
     const u16 *Kg = (const u16 *)p.k + (size_t)kvh * p.cap * D;
     v4u kreg[KB][KS];
@@ -881,9 +881,9 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_score_bf16(AttnParams p)
     st.init(tid, p.q_rs);
     auto load_q = [&](int it) {
         const int head = kvh * p.G + g0 + it / ntq;
-        const int i0 = i_lo + (qt0 + it % ntq) * QT;
+        const int i0 = i_base + it % ntq * QT;
         st.load((const u16 *)p.q + (size_t)head * p.q_hs + (size_t)i0 * p.q_rs,
-                p.lse + (size_t)head * p.Ct + i0, p.Ct - i0, i_lo - i0, p.q_rs, tid);
+                p.lse + (size_t)head * p.Ct + i0, p.Ct - i0, p.q_rs, tid);
     };
     load_q(0);
     st.store(ldsQ[0], ldsL[0], tid);
@@ -952,7 +952,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_score_bf16(AttnParams p)
     };
     for (int it = 0; it < iters; ++it) {
         const int buf = it & 1;
-        const int i0 = i_lo + (qt0 + it % ntq) * QT;
+        const int i0 = i_base + it % ntq * QT;
         if (jw < p.n) {
             const u16 *sq = ldsQ[buf] + q_frag0;
             if (jw + WKEYS - 1 <= p.M + i0) {
@@ -1375,7 +1375,8 @@ static hipError_t launch_score_tiled(const AttnParams &p, hipStream_t st)
 {
     constexpr int KB = 4, keys_wg = NW * 16 * KB;
     const int grid = p.Hkv * ((p.n + keys_wg - 1) / keys_wg) * p.slices;
-    hipLaunchKernelGGL((attn_score_bf16<D, KB, NW>), dim3(grid), dim3(NW * 64), 0, st, p);
+    if (p.W == p.Ct) hipLaunchKernelGGL((attn_score_bf16<D, KB, NW, false>), dim3(grid), dim3(NW * 64), 0, st, p);
+    else hipLaunchKernelGGL((attn_score_bf16<D, KB, NW, true>), dim3(grid), dim3(NW * 64), 0, st, p);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.slices == 1) return e;
     hipLaunchKernelGGL(attn_score_sum, dim3((p.n + 255) / 256, p.Hkv), dim3(256), 0, st, p, keys_wg);
