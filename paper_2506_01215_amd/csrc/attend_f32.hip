@@ -280,7 +280,7 @@ __global__ __launch_bounds__(kF32FwdWaves * 64) void attn_fwd_f32_mfma(AttnParam
             const size_t at = (size_t)share * p.part_rows + f32_slot(p, nrb, h, i0 + r);
             *(f32x4 *)(p.part_o + at * D + c) = x;
             if (c == 0) {
-                float mt = -INFINITY;                        // a share without a visible key: -inf, and sums of 0
+                float mt = -INFINITY;                        // stays where the row has no finite logit in this share
 #pragma unroll
                 for (int w = 0; w < NW; ++w) mt = fmaxf(mt, sm[w][r]);
                 p.part_ml[at] = make_float2(mt, lt);
@@ -303,14 +303,19 @@ __global__ __launch_bounds__(kF32FwdWaves * 64) void attn_fwd_f32_mfma(AttnParam
 // order (identical keys, identical scores).  4 heads, 128 rows over 384 keys 7.8 -> 4 us.
 constexpr int kF32ScoreWaves = 8;
 
-// Largest maximum and the sum relative to it of a row's shares.
+// Weight of a share whose maximum is m_share.  A share without a visible key counts 0 times its sums of 0; one
+// whose visible keys all have NaN logits has that maximum too (fmaxf passes over NaN), and 0 times its NaN sums
+// is NaN, as without shares.  So sums are always multiplied, never left out.
+__device__ __forceinline__ float f32_weight(float m_share, float m) { return m_share == -INFINITY ? 0.f : expf(m_share - m); }
+
+// Largest maximum and the sum relative to it of a row's shares; places behind the last share hold (-inf, 0).
 __device__ __forceinline__ float2 f32_total(const float2 (&ml)[kF32MaxShares])
 {
     float m = -INFINITY, l = 0.f;
 #pragma unroll
     for (int s = 0; s < kF32MaxShares; ++s) m = fmaxf(m, ml[s].x);
 #pragma unroll
-    for (int s = 0; s < kF32MaxShares; ++s) l += ml[s].x == -INFINITY ? 0.f : ml[s].y * expf(ml[s].x - m);
+    for (int s = 0; s < kF32MaxShares; ++s) l += ml[s].y * f32_weight(ml[s].x, m);
     return make_float2(m, l);
 }
 
@@ -397,13 +402,15 @@ __device__ __forceinline__ void f32_merge_rows(const AttnParams &p, int bid)
             const size_t at = (size_t)min(s, p.shares - 1) * p.part_rows + f32_slot(p, nrb, h, i);
             ml[s] = p.part_ml[at];
             o[s] = *(const f32x4 *)(p.part_o + at * D + c);
-            if (s >= p.shares) ml[s] = make_float2(-INFINITY, 0.f);
+            if (s >= p.shares) {
+                ml[s] = make_float2(-INFINITY, 0.f);
+                o[s] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            }
         }
         const float2 tot = f32_total(ml);
         f32x4 x = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int s = 0; s < kF32MaxShares; ++s)
-            if (ml[s].x != -INFINITY) x += o[s] * expf(ml[s].x - tot.x);
+        for (int s = 0; s < kF32MaxShares; ++s) x += o[s] * f32_weight(ml[s].x, tot.x);
         *(f32x4 *)((float *)p.out + (size_t)h * p.o_hs + (size_t)i * p.o_rs + c) = x / tot.y;
         if (c == 0) p.lse[(size_t)h * p.Ct + i] = tot.x + logf(tot.y);
     }

@@ -1,6 +1,6 @@
 """fp32 attention whose key blocks are shared by several workgroups: shares without a visible key, rows that end
 inside a block, windows, accumulated scores, with the score (merged by its launch) and without, and with a
-workspace that has no room for the shares' sums; against the fp64 oracle."""
+workspace that has no room for the shares' sums; against the fp64 oracle.  And shares all of whose logits are NaN."""
 import math
 
 import pytest
@@ -50,3 +50,31 @@ def test_matches_oracle(Hq, Hkv, d, M, Ct, W):
             if want_score:
                 assert_scores_close(to_np(score)[:, :n], s_ref[:, :n] + 0.25, 1e-5, "score")
                 assert (score[:, n:] == 0.25).all()
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("M,Ct,lo,hi", [
+    (0, 129, 128, 129),               # the last row alone sees the second share's only key
+    (600, 1, 384, 512),               # the fourth share's keys; split without the score too
+])
+def test_nan_logits_of_a_whole_share_reach_the_row(M, Ct, lo, hi, d):
+    """A row that sees a NaN key is NaN in out and lse, and so is the score of every key it sees, however the keys are
+    shared; the rows before it are the rows of the same call without the NaN."""
+    g = torch.Generator().manual_seed(d + M)
+    n = M + Ct
+    q, k, v = (torch.randn((1, r, d), generator=g).to(DEV) for r in (Ct, n, n))
+    bad = k.clone()
+    bad[:, lo:hi] = float("nan")
+    need = binding.attend_workspace_bytes(binding.attn_desc(q, k, q, M, 0.1))
+    whole = (Ct * 4 + 255) // 256 * 256
+    assert need > whole
+    for nbytes in (need, whole):
+        for want_score in (True, False):
+            ws = torch.full((nbytes + 256,), 0xff, dtype=torch.uint8, device=DEV)
+            ref = binding.reform_chunk_attend_score(q, k, v, M, 0.1, want_score=want_score, workspace=ws)
+            out, lse, score = binding.reform_chunk_attend_score(q, bad, v, M, 0.1, want_score=want_score, workspace=ws)
+            torch.cuda.synchronize()
+            assert out[:, -1].isnan().all() and lse[:, -1].isnan().all()
+            assert torch.equal(out[:, :-1], ref[0][:, :-1]) and torch.equal(lse[:, :-1], ref[1][:, :-1])
+            if want_score:
+                assert score.isnan().all()
