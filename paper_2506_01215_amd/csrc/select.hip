@@ -23,6 +23,9 @@ namespace reform {
 
 constexpr int kSelBlock = 4096;      // candidates per selection workgroup (256 threads x 16)
 constexpr int kRestWorkgroups = 1024; // the passes over what remains of compacted rows
+// Up to so many blocks in all these take one at a time with all waves, beyond four.  One / four, us: 80 queries, 33000 x
+// 128 77 / 93, 40 queries, 90000 x 128 73 / 82 (920 blocks); 16 queries, 600000 x 512 193 / 187 (2352), 2^20 x 512 296 / 287.
+constexpr int kRestFewBlocks = 2048;
 constexpr int kHistWorkgroups = 2048; // the histogram passes use about this many workgroups at most
 
 __device__ __forceinline__ uint32_t sel_key(const SelParams &p, const float *row, long t)
@@ -403,16 +406,26 @@ __global__ __launch_bounds__(256) void select_write(SelParams p)
 // Rows that are the call's own scratch and of which at most 1/16 is selected: the second pass leaves of each block
 // of 4096 candidates only those with at least the first pass's digit (2 to 4 % where 1/64 is selected),
 // ascending, at the block's own place: their values and behind them their places in the block (16 bits
-// each).  A block of which more than two thirds remain stays as it is.  blk_cnt[0] of a block holds 1 + the number that
+// each).  A block of which more than a quarter remains stays as it is.  blk_cnt[0] of a block holds 1 + the number that
 // remain, shifted by 16, or 0 there.  The passes that follow read a few percent of the row.  16 rows of
-// 2^20 of which 1/64 is selected: passes of 18 + 20 + 17 + 15 + 28 us -> 18 + 21 + 5 + 5 + 9 us, the whole gather
-// 860 -> 817 us; 600000 x 512, 16 queries, 1/64 225 -> 190 us, five queries, 1/33 170 -> 162 us; 150000 x 256, 23
-// queries, 1/37 73.5 -> 67.0 us; but where 1/8 is selected 200000 x 512, 16 queries 115 -> 122 us.
+// 2^20 of which 1/64 is selected: passes of 18 + 20 + 17 + 15 + 28 us -> 18 + 21 + 5 + 5 + 10 us.
+//
+// How much remains depends on the values: where most similarities share the first digit (cosines around 0.56) no block
+// is compacted, and the passes read whole blocks as fast as the plain ones do.  Whole gathers, us, plain passes /
+// these, spread similarities and such ones:
+//     16 queries, 600000 x 512, 1/64    229 / 187    274 / 260        23 queries, 150000 x 256, 1/37    69 / 58    78 / 73
+//     16 queries, 2^20 x 512, 1/64      331 / 287    373 / 365        80 queries, 33000 x 128, 1/20     86 / 77    92 / 87
+//     5 queries, 600000 x 512, 1/33     180 / 167    187 / 176        40 queries, 90000 x 128, 1/16     86 / 73    95 / 86
+// (with one wave to a whole block and 4-byte loads the last column was 320, 413, 253, 137, 194, 179).  The worst form seen
+// is similar rows in runs of 3000 of 2^20, whose marks queue on few words: 632 / 651 us, within what two
+// runs of one side differ.  At 1/16 itself: 200000 x 512, 16 queries 93.9 / 80.4 us, 90000 x 512, 23 82.3 / 66.3,
+// 40000 x 256, 64 84.1 / 71.6.  At 1/8 spread similarities still gain (103.4 / 90.6, 93.5 / 81.5, 116.7 / 105.9 us), those
+// that share a digit were not measured there.
 constexpr int kCompactShare = 16;
 
 struct Remaining {
     const float *val;
-    const u16 *at;           // null: nothing was left out
+    const u16 *at;           // null: the block is as it was
     int n;
     __device__ __forceinline__ Remaining(const SelParams &p, int q, int blk, int word)
     {
@@ -420,9 +433,7 @@ struct Remaining {
         val = p.vals + (size_t)q * p.ld + t0;
         n = (word >> 16) - 1;
         at = n < 0 ? nullptr : (const u16 *)(val + n);
-        if (n < 0) n = (int)min((long)kSelBlock, p.N - t0);
     }
-    __device__ __forceinline__ int place(int i) const { return at ? at[i] : i; }
 };
 
 // grid (<= nblk, nq): histogram of the second digit, as select_hist, and the compaction.
@@ -469,7 +480,7 @@ __global__ __launch_bounds__(256) void select_compact(SelParams p)
             base += w < wave ? wtot[w] : 0;
             c += wtot[w];
         }
-        const bool fits = 3 * c <= 2 * have;             // values and places within the block's own bytes
+        const bool fits = 4 * c <= have;                 // values and places then fill 3/8 of the block
         if (fits) {
             u16 *at = (u16 *)(row + t0 + c);
 #pragma unroll
@@ -497,13 +508,49 @@ __global__ __launch_bounds__(256) void select_compact(SelParams p)
         if (h[i]) atomicAdd(&gh[i], h[i]);
 }
 
-// grid (workgroups, nq), a wave per block of candidates: histogram of the last digit of what remains.
+// The passes over what remains.  A workgroup takes PER blocks of candidates at a time, a grid apart (winners that lie
+// together fill neighbouring blocks, which then go to different workgroups), 4 / PER waves to a block that was
+// compacted, and with all its waves every block that was not.
+constexpr int kRestBatch = 4;                            // loads of a lane in flight
+
+// Values of block blk that was not compacted, four consecutive ones per step and lane; at or beyond `have`: not the row's.
+__device__ __forceinline__ int whole_block(const SelParams &p, int q, int blk, f32x4 (&v)[4])
+{
+    const long t0 = (long)blk * kSelBlock;
+    const float *row = p.vals + (size_t)q * p.ld + t0;
+    const int have = (int)min((long)kSelBlock, p.N - t0);
+#pragma unroll
+    for (int it = 0; it < 4; ++it) v[it] = *(const f32x4 *)(row + min(it * 1024 + 4 * (int)threadIdx.x, (have - 1) & ~3));
+    return have;
+}
+
+// The words of a workgroup's blocks blk0 + i * gridDim.x, asked for together: this wave's (0 behind the last block), and
+// which of the blocks were not compacted.
+template <int PER>
+__device__ __forceinline__ int rest_words(const SelParams &p, const int *cnt, int blk0, int i_mine, unsigned &whole)
+{
+    int mine = 0;
+    whole = 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int blk = blk0 + i * gridDim.x;
+        const int word = blk < p.nblk ? cnt[2 * blk] : 0;
+        if (i == i_mine) mine = word;
+        whole |= blk < p.nblk && !(word >> 16) ? 1u << i : 0u;
+    }
+    whole = __builtin_amdgcn_readfirstlane(whole);
+    return mine;
+}
+
+// grid (workgroups, nq): histogram of the last digit of what remains.
+template <int PER>
 __global__ __launch_bounds__(256) void select_hist_rest(SelParams p)
 {
     __shared__ int h[1024];
     __shared__ int part[4];
     __shared__ int sel[2];
-    const int q = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+    const int q = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int sharing = 4 / PER;
     for (int i = tid; i < 1024; i += 256) h[i] = 0;
     uint32_t prefix;
     int krem;
@@ -512,11 +559,31 @@ __global__ __launch_bounds__(256) void select_hist_rest(SelParams p)
         p.sel_prefix[p.nq + q] = prefix;
         p.sel_krem[p.nq + q] = krem;
     }
-    for (int blk = blockIdx.x * 4 + (tid >> 6); blk < p.nblk; blk += gridDim.x * 4) {
-        const Remaining r(p, q, blk, p.blk_cnt[((size_t)q * p.nblk + blk) * 2]);
-        for (int i = lane; i < r.n; i += 64) {
-            const uint32_t u = ordered_key(r.val[i]);
-            if ((u >> 10) == prefix) atomicAdd(&h[u & 1023u], 1);
+    auto add = [&](float v, bool in) {
+        const uint32_t u = ordered_key(v);
+        if (in && (u >> 10) == prefix) atomicAdd(&h[u & 1023u], 1);
+    };
+    const int *cnt = p.blk_cnt + (size_t)q * p.nblk * 2;
+    for (int blk0 = blockIdx.x; blk0 < p.nblk; blk0 += gridDim.x * PER) {
+        unsigned whole;
+        const int word = rest_words<PER>(p, cnt, blk0, wave / sharing, whole);
+        const Remaining r(p, q, blk0 + wave / sharing * gridDim.x, word);
+        if (r.at)
+            for (int i0 = wave % sharing * 64 + lane; i0 < r.n; i0 += 64 * sharing * kRestBatch) {
+                float v[kRestBatch];
+#pragma unroll
+                for (int b = 0; b < kRestBatch; ++b) v[b] = r.val[min(i0 + 64 * sharing * b, r.n - 1)];
+#pragma unroll
+                for (int b = 0; b < kRestBatch; ++b) add(v[b], i0 + 64 * sharing * b < r.n);
+            }
+        for (; whole; whole &= whole - 1) {
+            const int i = __builtin_ctz(whole);
+            f32x4 v[4];
+            const int have = whole_block(p, q, blk0 + i * gridDim.x, v);
+#pragma unroll
+            for (int it = 0; it < 4; ++it)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) add(v[it][j], it * 1024 + 4 * tid + j < have);
         }
     }
     __syncthreads();
@@ -526,11 +593,14 @@ __global__ __launch_bounds__(256) void select_hist_rest(SelParams p)
 }
 
 // The same grid: per block, how many are above (low 16 bits of blk_cnt[0]) / equal to (blk_cnt[1]) the threshold.
+template <int PER>
 __global__ __launch_bounds__(256) void select_count_rest(SelParams p)
 {
     __shared__ int part[4];
     __shared__ int sel[2];
-    const int q = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+    __shared__ int sum[PER][2];
+    const int q = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int sharing = 4 / PER;
     uint32_t T;
     int need_eq;
     select_pick(p, q, 2, T, need_eq, part, sel);
@@ -538,71 +608,157 @@ __global__ __launch_bounds__(256) void select_count_rest(SelParams p)
         p.sel_prefix[2 * p.nq + q] = T;
         p.sel_krem[2 * p.nq + q] = need_eq;
     }
-    for (int blk = blockIdx.x * 4 + (tid >> 6); blk < p.nblk; blk += gridDim.x * 4) {
-        int *cnt = p.blk_cnt + ((size_t)q * p.nblk + blk) * 2;
-        const int word = cnt[0];
-        const Remaining r(p, q, blk, word);
+    int *cnt = p.blk_cnt + (size_t)q * p.nblk * 2;
+    for (int blk0 = blockIdx.x; blk0 < p.nblk; blk0 += gridDim.x * PER) {
+        if (tid < PER * 2) sum[tid >> 1][tid & 1] = 0;
+        __syncthreads();
         int gt = 0, eq = 0;
-        for (int i0 = 0; i0 < r.n; i0 += 64) {
-            const bool in = i0 + lane < r.n;
-            const uint32_t u = in ? ordered_key(r.val[i0 + lane]) : 0u;
+        auto add = [&](float v, bool in) {
+            const uint32_t u = ordered_key(v);
             gt += __popcll(__ballot(in && u > T));
             eq += __popcll(__ballot(in && u == T));
+        };
+        auto total = [&](int i) {
+            if (lane == 0) { atomicAdd(&sum[i][0], gt); atomicAdd(&sum[i][1], eq); }
+            gt = eq = 0;
+        };
+        unsigned whole;
+        const int word = rest_words<PER>(p, cnt, blk0, wave / sharing, whole);
+        const Remaining r(p, q, blk0 + wave / sharing * gridDim.x, word);
+        if (r.at) {
+            for (int i0 = wave % sharing * 64; i0 < r.n; i0 += 64 * sharing * kRestBatch) {
+                float v[kRestBatch];
+#pragma unroll
+                for (int b = 0; b < kRestBatch; ++b) v[b] = r.val[min(i0 + 64 * sharing * b + lane, r.n - 1)];
+#pragma unroll
+                for (int b = 0; b < kRestBatch; ++b) add(v[b], i0 + 64 * sharing * b + lane < r.n);
+            }
+            total(wave / sharing);
         }
-        if (lane == 0) {
-            cnt[0] = word | gt;                          // at most 4096
-            cnt[1] = eq;
+        for (; whole; whole &= whole - 1) {
+            const int i = __builtin_ctz(whole);
+            f32x4 v[4];
+            const int have = whole_block(p, q, blk0 + i * gridDim.x, v);
+#pragma unroll
+            for (int it = 0; it < 4; ++it)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) add(v[it][j], it * 1024 + 4 * tid + j < have);
+            total(i);
         }
+        __syncthreads();
+        const int blk = blk0 + tid * gridDim.x;
+        if (tid < PER && blk < p.nblk) {
+            cnt[2 * blk] |= sum[tid][0];                 // at most 4096
+            cnt[2 * blk + 1] = sum[tid][1];
+        }
+        __syncthreads();                                 // sum is cleared for the next blocks
     }
 }
 
-// grid (nblk / 4, nq), a wave per block: ordered emission, as range_emit.
+// grid (nblk / PER, nq): ordered emission, as range_emit.
+template <int PER>
 __global__ __launch_bounds__(256) void select_write_rest(SelParams p)
 {
-    __shared__ int red[2][4];
+    __shared__ v4u keys[kSelBlock / 4];
+    __shared__ int red[2][4], wtot[2][4];
     const int q = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t T = p.sel_prefix[2 * p.nq + q];
     const int need_eq = p.sel_krem[2 * p.nq + q];
     const int *cnt = p.blk_cnt + (size_t)q * p.nblk * 2;
-    const int blk0 = blockIdx.x * 4, blk = blk0 + wave;
-    int gt = 0, eq = 0;                                  // in the blocks before this workgroup's
-    for (int b = tid; b < blk0; b += 256) { gt += cnt[2 * b] & 0xffff; eq += cnt[2 * b + 1]; }
+    const int step = gridDim.x, first = blockIdx.x;      // blocks first + i * step
+    constexpr int sharing = 4 / PER;
+    const int blk = first + wave / sharing * step;
+    unsigned whole;
+    const int word = rest_words<PER>(p, cnt, first, wave / sharing, whole);
+    const Remaining r(p, q, blk, word);                  // at most 1024: a quarter of them is one batch
+    const int share = ((r.n + sharing - 1) / sharing + 63) & ~63;
+    const int i_lo = wave % sharing * share, i_hi = min(i_lo + share, r.n);
+    float vals[kRestBatch];
+    int places[kRestBatch];
+    auto fetch = [&](int i0) {
+#pragma unroll
+        for (int b = 0; b < kRestBatch; ++b) {
+            const int i = max(min(i0 + 64 * b + lane, r.n - 1), 0);
+            vals[b] = r.val[i];
+            places[b] = r.at[i];
+        }
+    };
+    if (r.at) fetch(i_lo);                               // on their way during the sums
+    // candidates above / equal to T in the blocks before, a wave for those between two blocks of this workgroup
+    // (PER = 1: for a quarter of those before it)
+    const int lo = PER == 1 ? first * wave / 4 : wave ? first + (wave - 1) * step : 0;
+    const int hi = PER == 1 ? first * (wave + 1) / 4 : min(first + wave * step, p.nblk);
+    int gt = 0, eq = 0;
+    for (int b = lo + lane; b < hi; b += 64) { gt += cnt[2 * b] & 0xffff; eq += cnt[2 * b + 1]; }
     gt = __builtin_amdgcn_readlane(wave_incl_scan(gt), 63);
     eq = __builtin_amdgcn_readlane(wave_incl_scan(eq), 63);
     if (lane == 0) { red[0][wave] = gt; red[1][wave] = eq; }
     __syncthreads();
-    gt = red[0][0] + red[0][1] + red[0][2] + red[0][3];
-    eq = red[1][0] + red[1][1] + red[1][2] + red[1][3];
-    if (blk >= p.nblk) return;
-    for (int b = blk0; b < blk; ++b) { gt += cnt[2 * b] & 0xffff; eq += cnt[2 * b + 1]; }
-    const Remaining r(p, q, blk, cnt[2 * blk]);
-    int dest = gt + min(eq, need_eq);
-    const long t0 = (long)blk * kSelBlock;
-    int32_t *oi = p.out_idx + (size_t)q * p.out_ld;
-    float *os = p.out_val ? p.out_val + (size_t)q * p.out_ld : nullptr;
-    long before = 0;                                     // first place that the winners so far have not marked
-    for (int i0 = 0; i0 < r.n; i0 += 64) {
-        const bool in = i0 + lane < r.n;
-        const float v = in ? r.val[i0 + lane] : 0.f;
-        const int t = (int)t0 + (in ? r.place(i0 + lane) : 0);
-        const uint32_t u = ordered_key(v);
-        const unsigned long long me = __ballot(in && u == T);
-        const bool keep = in && (u > T || (u == T && eq + lanes_below(me) < need_eq));
-        const unsigned long long mk = __ballot(keep);
-        const int to = dest + lanes_below(mk);
-        if (keep && to < p.k) {                          // always, whatever the keys were
-            oi[to] = t;
-            if (os) os[to] = v;
+    auto before_block = [&](int i) {                     // the i-th of this workgroup
+        gt = eq = 0;
+        for (int w = 0; w <= (PER == 1 ? 3 : i); ++w) { gt += red[0][w]; eq += red[1][w]; }
+    };
+    if (r.at) {
+        before_block(wave / sharing);
+        if (PER == 1) {                                  // and in the waves before: all four are here
+            int gt_w = 0, eq_w = 0;
+#pragma unroll
+            for (int b = 0; b < kRestBatch; ++b) {
+                const bool in = i_lo + 64 * b + lane < i_hi;
+                const uint32_t u = ordered_key(vals[b]);
+                gt_w += __popcll(__ballot(in && u > T));
+                eq_w += __popcll(__ballot(in && u == T));
+            }
+            if (lane == 0) { wtot[0][wave] = gt_w; wtot[1][wave] = eq_w; }
+            __syncthreads();
+            for (int w = 0; w < wave; ++w) { gt += wtot[0][w]; eq += wtot[1][w]; }
         }
-        if (p.mark && mk) {                              // each winner marks what the one before it has not
-            const unsigned long long below = mk & ((1ull << lane) - 1ull);
-            const int prev = __shfl(t, below ? 63 - __clzll(below) : lane);
-            const long from = below ? prev + p.mark_radius + 1 : before;
-            if (keep) mark_range(p.mark, max(t - p.mark_radius, from), min(t + p.mark_radius, p.N - 1));
-            before = __builtin_amdgcn_readlane(t, 63 - __clzll(mk)) + p.mark_radius + 1;
+        int dest = gt + min(eq, need_eq);
+        const long t0 = (long)blk * kSelBlock;
+        int32_t *oi = p.out_idx + (size_t)q * p.out_ld;
+        float *os = p.out_val ? p.out_val + (size_t)q * p.out_ld : nullptr;
+        long before = 0;                                 // first place that the wave's winners so far have not marked
+        for (int i0 = i_lo; i0 < i_hi; i0 += 64 * kRestBatch) {
+            if (i0 > i_lo) fetch(i0);
+#pragma unroll
+            for (int b = 0; b < kRestBatch; ++b) {
+                const bool in = i0 + 64 * b + lane < i_hi;
+                const float v = vals[b];
+                const int t = (int)t0 + places[b];
+                const uint32_t u = ordered_key(v);
+                const unsigned long long me = __ballot(in && u == T);
+                const bool keep = in && (u > T || (u == T && eq + lanes_below(me) < need_eq));
+                const unsigned long long mk = __ballot(keep);
+                const int to = dest + lanes_below(mk);
+                if (keep && to < p.k) {                  // always, whatever the keys were
+                    oi[to] = t;
+                    if (os) os[to] = v;
+                }
+                if (p.mark && mk) {                      // each winner marks what the one before it has not
+                    const unsigned long long below = mk & ((1ull << lane) - 1ull);
+                    const int prev = __shfl(t, below ? 63 - __clzll(below) : lane);
+                    const long from = below ? prev + p.mark_radius + 1 : before;
+                    if (keep) mark_range(p.mark, max(t - p.mark_radius, from), min(t + p.mark_radius, p.N - 1));
+                    before = __builtin_amdgcn_readlane(t, 63 - __clzll(mk)) + p.mark_radius + 1;
+                }
+                dest += __popcll(mk);
+                eq += __popcll(me);
+            }
         }
-        dest += __popcll(mk);
-        eq += __popcll(me);
+    }
+    for (; whole; whole &= whole - 1) {
+        const int i = __builtin_ctz(whole), N = (int)p.N;
+        const int w_lo = (first + i * step) * kSelBlock + wave * 1024;
+        v4u *mine = keys + wave * 256;
+        load_keys(p, p.vals + (size_t)q * p.ld, N, w_lo, 4, mine);
+        int gt_w, eq_w;
+        range_count(mine, N, w_lo, 4, T, gt_w, eq_w);
+        __syncthreads();                                 // wtot may still be read for the block before
+        if (lane == 0) { wtot[0][wave] = gt_w; wtot[1][wave] = eq_w; }
+        __syncthreads();
+        before_block(i);
+        for (int w = 0; w < wave; ++w) { gt += wtot[0][w]; eq += wtot[1][w]; }
+        range_emit(p, q, mine, N, w_lo, 4, T, need_eq, gt + min(eq, need_eq), eq);
     }
 }
 
@@ -1021,6 +1177,19 @@ constexpr int kFusedMaxN = 8192;
 // of 16384 938 / 909 us.
 constexpr int kRowMaxN = 8 * 4096;
 
+template <int PER>
+static hipError_t select_rest(const SelParams &p, hipStream_t st)
+{
+    const dim3 grid((p.nblk + PER - 1) / PER, p.nq), few(min((int)grid.x, max(1, kRestWorkgroups / p.nq)), p.nq);
+    hipLaunchKernelGGL(select_hist_rest<PER>, few, dim3(256), 0, st, p);
+    RF_CHECK_LAUNCH();
+    hipLaunchKernelGGL(select_count_rest<PER>, few, dim3(256), 0, st, p);
+    RF_CHECK_LAUNCH();
+    hipLaunchKernelGGL(select_write_rest<PER>, grid, dim3(256), 0, st, p);
+    RF_CHECK_LAUNCH();
+    return hipSuccess;
+}
+
 hipError_t select_topk(const SelParams &p, hipStream_t st)
 {
     int nit = 0, parts = 1;
@@ -1058,15 +1227,7 @@ hipError_t select_topk(const SelParams &p, hipStream_t st)
         RF_CHECK_LAUNCH();
         hipLaunchKernelGGL(select_compact, hgrid, dim3(256), 0, st, p);
         RF_CHECK_LAUNCH();
-        const dim3 rgrid((p.nblk + 3) / 4, p.nq);
-        const dim3 fgrid(min((int)rgrid.x, max(1, kRestWorkgroups / p.nq)), p.nq);
-        hipLaunchKernelGGL(select_hist_rest, fgrid, dim3(256), 0, st, p);
-        RF_CHECK_LAUNCH();
-        hipLaunchKernelGGL(select_count_rest, fgrid, dim3(256), 0, st, p);
-        RF_CHECK_LAUNCH();
-        hipLaunchKernelGGL(select_write_rest, rgrid, dim3(256), 0, st, p);
-        RF_CHECK_LAUNCH();
-        return hipSuccess;
+        return (long)p.nblk * p.nq <= kRestFewBlocks ? select_rest<1>(p, st) : select_rest<4>(p, st);
     }
     for (int pass = 0; pass < 3; ++pass) {
         hipLaunchKernelGGL(select_hist, hgrid, dim3(256), 0, st, p, pass);
