@@ -1048,8 +1048,6 @@ __global__ __launch_bounds__(256) void attn_score_sum(AttnParams p, int keys)
 //
 // PIECES: the attention of the same call left pieces that are not merged yet; the workgroup forms the rows'
 // normalisers from the pieces' maxima and sums itself, in LDS (see attn_merge_score).
-constexpr int kFewBlocks = 8;                            // row blocks over all heads of a group, at most (RW = 1)
-
 template <int D, int KB, int RW, bool PIECES>
 __device__ __forceinline__ void score_few_keys(const AttnParams &p, int bid)
 {
@@ -1295,81 +1293,6 @@ static hipError_t launch_fwd(const AttnParams &p, bool split, hipStream_t st)
     return hipGetLastError();
 }
 
-// How the score pass of a problem is cut into workgroups: waves per workgroup (returned), slices,
-// slice_tiles, head_slices and slice_heads.  Time is estimated in query tiles that a compute unit takes against 512 keys (2.1 us
-// at head_dim 128); at most two workgroups of four waves or one of eight are resident on it.
-//   - Eight waves, uncut: the fewest Q bytes per key, the best form where its workgroups fill the chip
-//     evenly.  Keys of the cache (and of the chunk before the window) cost the same each; those of
-//     the window itself are triangular and fill up what the others leave.
-//   - Four waves, cut: half the keys and 1/slices of the rows per workgroup, at the price of a start-up
-//     of about 1.5 tiles each and of a launch that adds the slices up (2 tiles).
-// Measured with 32/8 heads, head_dim 128: 8192 rows over 8192 keys 974 -> 828 us with 8 slices (256
-// uncut workgroups, half of them triangular); 512 rows over 8192 keys 77 -> 63 us with 4; 32768
-// over 32768 12.1 ms uncut, 12.3 ms in 4 or 8 slices; 700 over 30000 207 us uncut, 223 us in 4;
-// 128 rows over 8192 keys 23 us uncut, 28 us with four waves.
-static int score_plan(AttnParams &p)
-{
-    const int cus = compute_units();
-    const int tiles = (p.W + 63) / 64;
-    const double iters = (double)p.G * tiles;
-    const long full = (long)p.Hkv * ((p.n - p.W + 511) / 512), all = (long)p.Hkv * ((p.n + 511) / 512);
-    const double total = (full + 0.5 * (double)(all - full)) * iters / cus;       // per compute unit
-    // Uncut workgroups in the order they are dispatched: `whole` rounds of full ones, then on the units that a last,
-    // partly filled round leaves (`room`) the triangular ones, the longest of which is a full one as well, and
-    // with more than there is room for the longest left over behind the shortest.
-    const long whole = full / cus, room = cus - full % cus, tri = all - full;
-    double best = (double)(whole + (room < cus || tri > 0)) * iters;
-    if (tri > room) {
-        const double pair = (2.0 - 2.0 * (double)room / (double)tri) * iters;
-        if (best < (double)whole * iters + pair) best = (double)whole * iters + pair;
-    }
-    if (best < total) best = total;
-    int waves = 8;
-    p.slices = p.head_slices = 1;
-    p.slice_tiles = tiles;
-    p.slice_heads = p.G;
-    auto consider = [&](int per, int heads) {            // slices of `per` tiles of `heads` heads
-        const int hs = (p.G + heads - 1) / heads, slices = (tiles + per - 1) / per * hs;
-        const double item = (double)heads * per, items = 2.0 * total * cus / item;
-        double t = total + 0.5 * item;
-        if (t < item) t = item;
-        t += 1.5 * items / (2.0 * cus) + (slices > 1 ? 2.0 : 0.0);
-        if (t >= best) return;
-        best = t;
-        waves = 4;
-        p.slices = slices;
-        p.slice_tiles = per;
-        p.head_slices = hs;
-        p.slice_heads = heads;
-    };
-    for (int want = 1; want <= 16; want *= 2) consider((tiles + want - 1) / want, p.G);
-    // Where that leaves compute units without a workgroup the heads are cut as well: 60 rows over 8000 keys
-    // with 14/2 heads of 64 (32 workgroups of 7 tiles) 38 -> 31 us for the call, 30 over 1000 with 14/2 of
-    // 128 38 -> 28 us.  (On a chip that is busy it gives nothing: 2000 rows over 1000 keys, 32/8 heads, 18.9
-    // -> 19.8 us.)
-    if ((waves == 8 ? all : (long)p.Hkv * ((p.n + 255) / 256) * p.slices) < cus)
-        for (int heads = (p.G + 1) / 2; heads >= 1; heads = heads > 1 ? (heads + 1) / 2 : 0) consider(1, heads);
-    return waves;
-}
-
-constexpr int kFewKB = 2;                               // 16-key blocks of a wave of the register-only form
-
-// Few observing rows over not too many keys: the register-only form.  Its waves (one per 32 keys of a KV
-// head) fetch every query row themselves, so it loses its lead as rows or waves grow: 17 rows over 4113 keys of 8 heads
-// 10 -> 6 us, 4 x 32 rows over 4128 keys 16.5 -> 12.3 us, 64 rows over 16064 keys 12 -> 18 us.
-// Returns how many waves share their keys (RW above), 0 where this is not the form to take.  Four of them: also for
-// more row blocks, as long as the keys are not so many that each workgroup's walk over all rows tells.  Whole
-// calls, tiled / four waves: 88 rows over 1234 keys, 16/4 heads 32.1 -> 27.4 us, 201 over 1407 36.8 -> 32.5 us, 128
-// of 3039 over 4057, 14/2 heads 91.1 -> 85.9 us, 47 over 14688, 14/2 heads of 64 31.9 -> 30.4 us (19 thousand workgroups
-// times blocks), 327 over 327, 32/8 heads 31.2 -> 29.9 us (84 blocks); but 447 over 447, 16/4 heads (112 blocks) 32.6 ->
-// 35.9 us, and with few blocks over many keys 12 rows over 18878, 32/8 heads 54.7 -> 69.9 us.
-static int score_few(const AttnParams &p)
-{
-    const long blocks = (long)p.G * ((p.W + 15) / 16);
-    if (blocks <= 2 || (blocks <= kFewBlocks && (long)p.Hkv * p.n <= 65536)) return 1;
-    return blocks > kFewBlocks && blocks <= 96 && p.Hkv * ((p.n + 16l * kFewKB - 1) / (16 * kFewKB)) * blocks <= 20000 ? 4 : 0;
-}
-
 template <int D, int NW>
 static hipError_t launch_score_tiled(const AttnParams &p, hipStream_t st)
 {
@@ -1393,7 +1316,7 @@ static hipError_t launch_score(AttnParams p, void *part, size_t part_bytes, hipS
         else hipLaunchKernelGGL((attn_score_few<D, KB, 4>), dim3(grid), dim3(256), 0, st, p);
         return hipGetLastError();
     }
-    int waves = score_plan(p);
+    int waves = score_plan(p, compute_units());
     if (p.slices > 1 && (!part || part_bytes < (size_t)p.slices * p.Hkv * p.n * sizeof(float))) {
         p.slice_tiles *= p.slices;                       // no room for partial sums: uncut
         p.slice_heads = p.G;
@@ -1429,7 +1352,7 @@ size_t attend_bf16_scratch_bytes(const AttnParams &sizes)
     AttnParams p = sizes;
     size_t score = 0;
     if (!score_few(p)) {
-        score_plan(p);
+        score_plan(p, compute_units());
         if (p.slices > 1) score = (size_t)p.slices * p.Hkv * p.n * sizeof(float);
     }
     fwd_plan(p, compute_units());

@@ -1,7 +1,7 @@
 // Replays the walk of every workgroup of the split forward pass and the piece ranges of the merge, as host
 // code over the same header.  Returns 0 if every key tile of every row block is covered exactly once and the
 // merge reads exactly the slots that were written for it, 1 if the problem is not split, else a number
-// that tells what failed.
+// that tells what failed.  score_form: the form of the score pass.
 #include "attend_plan.h"
 
 #include <algorithm>
@@ -10,6 +10,7 @@
 using namespace reform;
 
 struct Plan { int Hkv, G, D, M, Ct, n_row_blocks, by_head, shares, start, tiles, part_rows; };
+struct ScorePlan { int Hkv, G, n, W, slices, slice_tiles, head_slices, slice_heads; };
 struct Piece { long t0, t1, slot; };
 
 extern "C" int replay(int Hkv, int G, int D, int M, int Ct, int cus)
@@ -58,4 +59,14 @@ extern "C" int replay(int Hkv, int G, int D, int M, int Ct, int cus)
         pos += nt;
     }
     return pos == p.tiles ? 0 : 12;
+}
+
+// Waves that share their keys in the register-only form (1 or 4); 0: the tiled form, uncut; 16 * slices: cut.
+extern "C" int score_form(int Hkv, int G, int M, int Ct, int W, int cus)
+{
+    ScorePlan p = {};
+    p.Hkv = Hkv; p.G = G; p.n = M + Ct; p.W = W ? W : Ct;
+    if (const int waves = score_few(p)) return waves;
+    score_plan(p, cus);
+    return p.slices > 1 ? 16 * p.slices : 0;
 }

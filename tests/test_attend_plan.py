@@ -1,6 +1,7 @@
 """The cut of the split forward pass, replayed on the CPU: every key tile of every row block of a problem
-belongs to exactly one workgroup, and the merge reads the slots that were written.  The header that the
-kernels use is compiled as host code (attend_plan_replay.cpp)."""
+belongs to exactly one workgroup, and the merge reads the slots that were written; and the form of the score pass
+that the GPU tests' shapes take.  The header that the kernels use is compiled as host code
+(attend_plan_replay.cpp)."""
 import ctypes
 import os
 import random
@@ -8,17 +9,25 @@ import subprocess
 
 import pytest
 
+import test_gpu_attend_score_waves
+import test_gpu_attend_split
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "..", "paper_2506_01215_amd", "csrc")
 
 
 @pytest.fixture(scope="module")
-def replay(tmp_path_factory):
+def plan(tmp_path_factory):
     lib = str(tmp_path_factory.mktemp("plan") / "replay.so")
     subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-fsanitize=undefined",
                     "-fno-sanitize-recover=undefined", "-static-libubsan", "-shared", "-fPIC", "-I", CSRC,
                     os.path.join(HERE, "attend_plan_replay.cpp"), "-o", lib], check=True)
-    return ctypes.CDLL(lib).replay
+    return ctypes.CDLL(lib)
+
+
+@pytest.fixture(scope="module")
+def replay(plan):
+    return plan.replay
 
 
 @pytest.mark.parametrize("G", range(1, 33))
@@ -44,3 +53,17 @@ def test_caches_whose_keys_times_heads_pass_32_bits(replay, Hkv, G):
             continue
         for Ct in (1, 256 // G + 1, 16, 33, 700):
             assert replay(Hkv, G, 64, M + rng.randint(0, 63), Ct, 256) in (0, 1), (Hkv, G, M, Ct)
+
+
+def test_the_score_shapes_of_the_gpu_tests_take_the_form_they_are_for(plan):
+    def form(Hq, Hkv, d, M, Ct, W):
+        return plan.score_form(Hkv, Hq // Hkv, M, Ct, W, 256)
+
+    for shape in test_gpu_attend_split.SLICED:
+        assert form(*shape) > 16, shape
+    for shape in test_gpu_attend_split.FEW_ROWS:
+        assert form(*shape) == 1, shape
+    for shape in test_gpu_attend_score_waves.FOUR_WAVES:
+        assert form(*shape) == 4, shape
+    for shape in test_gpu_attend_score_waves.TILED:
+        assert form(*shape) % 16 == 0, shape

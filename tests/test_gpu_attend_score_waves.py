@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-@pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W", [
+# Which form a shape takes is checked on the CPU (test_attend_plan.py).
+FOUR_WAVES = [
     (9, 1, 128, 15, 16, 16),          # nine blocks, 31 keys
     (4, 1, 64, 0, 33, 33),            # twelve, 33 keys, diagonal
     (2, 2, 128, 1000, 150, 150),      # ten, from one head each
@@ -22,7 +23,11 @@ DEV = "cuda:0"
     (8, 1, 128, 64, 192, 192),        # 96, the most
     (3, 1, 64, 2047, 65, 65),
     (11, 1, 128, 96, 1, 1),           # one row, a block per head
-])
+]
+TILED = [(8, 2, 64, 21000, 200, W) for W in (63, 64, 65, 129, 193)]
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W", FOUR_WAVES)
 @pytest.mark.parametrize("accumulate", [False, True])
 def test_score_matches_oracle(Hq, Hkv, d, M, Ct, W, accumulate):
     g = torch.Generator().manual_seed(Hq + M + Ct + W)
@@ -46,10 +51,9 @@ def test_score_matches_oracle(Hq, Hkv, d, M, Ct, W, accumulate):
         assert (score[:, M - 1] == score[:, 2]).all()
 
 
-@pytest.mark.parametrize("W", [63, 64, 65, 129, 193])
-def test_tiles_begin_with_the_window(W):
+@pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W", TILED)
+def test_tiles_begin_with_the_window(Hq, Hkv, d, M, Ct, W):
     """Too many keys for the form above: query tiles of 64, counted from the first observing row."""
-    Hq, Hkv, d, M, Ct = 8, 2, 64, 16500, 200
     g = torch.Generator().manual_seed(W)
     q = torch.randn((Hq, Ct, d), generator=g).to(torch.bfloat16)
     k = (1.5 * torch.randn((Hkv, M + Ct, d), generator=g)).to(torch.bfloat16)

@@ -63,14 +63,23 @@ def test_split_forward_matches_oracle(shape):
     assert torch.equal(results[0][0], results[1][0]) and torch.equal(results[0][1], results[1][1])
 
 
-@pytest.mark.parametrize("shape", [
+# Which form a shape takes is checked on the CPU (test_attend_plan.py).
+SLICED = [
     (16, 4, 128, 100, 700, 0),      # slices of one tile, the last of 60 rows
-    (2, 2, 64, 0, 1500, 0),         # every key block on the diagonal
-    (8, 2, 128, 1000, 600, 301),    # window begins inside a tile
+    (2, 2, 64, 0, 1600, 0),         # every key block on the diagonal
+    (16, 2, 128, 1000, 600, 301),   # window ends inside a tile
     (4, 4, 128, 515, 2048, 2048),
-    (8, 8, 128, 300, 17, 0),        # few rows: two row blocks, the second of one row
-    (3, 1, 64, 5, 20, 9),           # few rows, fewer keys than a workgroup holds
+]
+FEW_ROWS = [
+    (8, 8, 128, 300, 17, 0),        # two row blocks, the second of one row
+    (3, 1, 64, 5, 20, 9),           # fewer keys than a workgroup holds
     (16, 2, 64, 700, 1, 0),         # eight row blocks of one row
+]
+
+
+@pytest.mark.parametrize("shape", SLICED + FEW_ROWS + [
+    (2, 2, 64, 0, 1500, 0),         # four waves share their keys: every one on the diagonal
+    (8, 2, 128, 1000, 600, 301),    # window begins inside a row block
 ], ids=lambda s: "x".join(map(str, s)))
 def test_score_slices_match_oracle(shape):
     Hq, Hkv, d, M, Ct, W = shape
@@ -97,13 +106,9 @@ def test_score_slices_match_oracle(shape):
 
 
 def test_the_shapes_split():
-    """Every shape but the two-tile one asks for more workspace than the lse rows, and so do the
-    score shapes that are cut into slices."""
+    """Every shape but the two-tile one asks for more workspace than the lse rows."""
     for Hq, Hkv, d, M, Ct, W in SHAPES:
         q, k, _ = inputs(Hq, Hkv, d, M, Ct, seed=1)
         need = binding.attend_workspace_bytes(binding.attn_desc(q, k, q, M, 0.1, W))
         whole = (Hq * Ct * 4 + 255) // 256 * 256
         assert (need > whole) == (M + Ct > 128), (Hq, Hkv, d, M, Ct, need, whole)
-    for Hq, Hkv, d, M, Ct, W in [(16, 4, 128, 100, 700, 0), (2, 2, 64, 0, 1500, 0), (8, 2, 128, 1000, 600, 301)]:
-        q, k, _ = inputs(Hq, Hkv, d, M, Ct, seed=1)
-        assert binding.attend_workspace_bytes(binding.attn_desc(q, k, q, M, 0.1, W)) > (Hq * Ct * 4 + 255) // 256 * 256
