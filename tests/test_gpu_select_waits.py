@@ -95,18 +95,19 @@ def top(x, k):
 
 
 @pytest.mark.parametrize("kind", ["spread", "ties"])
-@pytest.mark.parametrize("N,nq,radius", [(8193, 1, 0), (40001, 3, 8), (131000, 2, 1)])
-def test_gather_is_exact_whatever_expires(N, nq, radius, kind):
+@pytest.mark.parametrize("N,nq,radius,tail", [(8193, 1, 0, 9), (40001, 3, 8, 9), (131000, 2, 1, 9),
+                                              (131000, 1, 0, 0)])       # the union written by the selection
+def test_gather_is_exact_whatever_expires(N, nq, radius, tail, kind):
     emb, qry = store(N, nq, kind, N)
     k = N // 20
     sim = binding.reform_gather_similarity(emb, qry).cpu().numpy()
     want = np.stack([top(sim[q], k) for q in range(nq)])
-    union_ref = numpy_union(want, N, radius, 0, 9)
+    union_ref = numpy_union(want, N, radius, 0, tail)
     for limit in LIMITS:
         print(f"[waits] gather {N} {kind} limit {limit}", flush=True)
         binding.debug_set_move_spin_limit(limit)
-        ws = filled(binding.gather_workspace_bytes(binding.gather_desc(emb, qry, k, radius, 0, 9)))
-        idx, val, union, count = binding.reform_gather_topk(emb, qry, k, radius, 0, 9, workspace=ws)
+        ws = filled(binding.gather_workspace_bytes(binding.gather_desc(emb, qry, k, radius, 0, tail)))
+        idx, val, union, count = binding.reform_gather_topk(emb, qry, k, radius, 0, tail, workspace=ws)
         torch.cuda.synchronize()
         np.testing.assert_array_equal(idx.cpu().numpy(), want)
         np.testing.assert_array_equal(val.cpu().numpy(), np.take_along_axis(sim, want, 1))
