@@ -661,8 +661,8 @@ __global__ __launch_bounds__(kFwdWaves * 64) void attn_fwd_few(AttnParams p)
 #pragma unroll
             for (int w = 0; w < NW; ++w) m_row = fmaxf(m_row, sm[w][r]);
 #pragma unroll
-            for (int w = 0; w < NW; ++w)
-                l_row += sm[w][r] == -INFINITY ? 0.f : sl[w][r] * __builtin_amdgcn_exp2f((sm[w][r] - m_row) * c);
+            for (int w = 0; w < NW; ++w)                 // multiplied, not left out: NaN logits alone leave -inf and a NaN sum
+                l_row += sl[w][r] * (sm[w][r] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((sm[w][r] - m_row) * c));
             pml[r] = make_float2(m_row * c, l_row);
         }
     }

@@ -3,7 +3,7 @@
 Forward attention with the key range split over workgroups (few row blocks, or a last round of
 workgroups that would be nearly empty), against the fp64 oracle: ranges cut inside the causal
 diagonal, row blocks shared by many workgroups or by two, heads and chunk ends that leave a
-workgroup partly idle; and the same call with a workspace too small for the partial results.
+workgroup partly idle; keys with NaN logits; and the same call with a workspace too small for the partial results.
 
 The eviction score with the observing rows cut into slices, and its form for few rows: windows that
 begin inside a query tile, key blocks on the diagonal, accumulation, identical keys."""
@@ -112,3 +112,25 @@ def test_the_shapes_split():
         need = binding.attend_workspace_bytes(binding.attn_desc(q, k, q, M, 0.1, W))
         whole = (Hq * Ct * 4 + 255) // 256 * 256
         assert (need > whole) == (M + Ct > 128), (Hq, Hkv, d, M, Ct, need, whole)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Ct", [1, 40])
+@pytest.mark.parametrize("lo,hi", [(64, 96), (0, 128)])
+def test_nan_logits_reach_every_output(d, Ct, lo, hi):
+    """Keys whose logits are NaN, all that one wave or one share of the keys sees: rows are NaN in out and lse and the
+    score of every key is NaN, as with a workspace that has no room to split."""
+    Hq, Hkv, M = 8, 2, 1000
+    q, k, v = inputs(Hq, Hkv, d, M, Ct, seed=d + Ct)
+    k[:, lo:hi] = float("nan")
+    need = binding.attend_workspace_bytes(binding.attn_desc(q, k, q, M, 0.1))
+    whole = (Hq * Ct * 4 + 255) // 256 * 256
+    assert need > whole
+    for nbytes in (need, whole):
+        ws = torch.full((nbytes + 256,), 0xff, dtype=torch.uint8, device=DEV)
+        out, lse, score = binding.reform_chunk_attend_score(q, k, v, M, 0.1, workspace=ws)
+        torch.cuda.synchronize()
+        assert out.isnan().all() and lse.isnan().all() and score[:, :M + Ct].isnan().all()
+        out, lse, _ = binding.reform_chunk_attend_score(q, k, v, M, 0.1, want_score=False, workspace=ws)
+        torch.cuda.synchronize()
+        assert out.isnan().all() and lse.isnan().all()
