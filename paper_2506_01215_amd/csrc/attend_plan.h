@@ -1,7 +1,7 @@
 // How the bf16 forward pass and the score pass of a problem are cut into workgroups.  Plain arithmetic without a
 // device type, shared by the launcher, the kernels and a host program that replays it; P is AttnParams, or
 // has its fields Hkv, G, D, M, Ct, n_row_blocks, by_head, shares, start, tiles and part_rows, and for the
-// score n, W, slices, slice_tiles, head_slices and slice_heads.  Sizes reach 2^30 keys and 2^31 query rows,
+// score D, n, W, slices, slice_tiles, head_slices and slice_heads.  Sizes reach 2^30 keys and 2^31 query rows,
 // so no product of keys and heads may be formed in 32 bits.
 #pragma once
 
@@ -192,18 +192,26 @@ constexpr int kFewKB = 2;                                // 16-key blocks of a w
 // Few observing rows over not too many keys: the register-only form.  Its waves (one per 32 keys of a KV
 // head) fetch every query row themselves, so it loses its lead as rows or waves grow: 17 rows over 4113 keys of 8 heads
 // 10 -> 6 us, 4 x 32 rows over 4128 keys 16.5 -> 12.3 us, 64 rows over 16064 keys 12 -> 18 us.
-// Returns how many waves share their keys (RW in attn_score_few), 0 where this is not the form to take.  Four of them: also for
-// more row blocks, as long as the keys are not so many that each workgroup's walk over all rows tells.  Whole
-// calls, tiled / four waves: 88 rows over 1234 keys, 16/4 heads 32.1 -> 27.4 us, 201 over 1407 36.8 -> 32.5 us, 128
-// of 3039 over 4057, 14/2 heads 91.1 -> 85.9 us, 47 over 14688, 14/2 heads of 64 31.9 -> 30.4 us (19 thousand workgroups
-// times blocks), 327 over 327, 32/8 heads 31.2 -> 29.9 us (84 blocks); but 447 over 447, 16/4 heads (112 blocks) 32.6 ->
-// 35.9 us, and with few blocks over many keys 12 rows over 18878, 32/8 heads 54.7 -> 69.9 us.
+// Returns how many waves share their keys (RW in attn_score_few), 0 where this is not the form to take.
+//
+// Four of them for more row blocks: a workgroup per 32 keys of a KV head, which walks all rows.  At head_dim 128 its time
+// goes by rounds of workgroups over the 256 compute units, each the longer the more blocks there are, about 3.5 + rounds
+// (1.7 + blocks / 10) us, while the tiled form with its slices stays at 12 to 18 us.  Score alone, tiled / four waves, us,
+// with one round: 12 blocks 10.4 / 6.3, 48 11.6 / 9.8, 64 11.7 / 11.4; two: 16 blocks 10.8 / 9.8, 28 13.1 / 13.0,
+// 63 16.5 / 20.0; three: 9 blocks 14.0 / 11.3, 16 17.4 / 13.2, 24 13.8 / 15.1; five: 9 blocks 14.0 / 17.2; nine:
+// 9 blocks 14.9 / 28.5.  More than 64 blocks pay where one round is more than half full (91 blocks, 152 workgroups
+// 16.7 / 15.1; 96 blocks, 176 16.4 / 15.2; but 96 blocks, 60 workgroups 12.3 / 15.0).
+// At 64 a round costs half: 9 blocks, 1104 workgroups 12.0 / 10.3, 1552 11.2 / 13.0; 21 blocks, 946 13.6 / 11.5; 64, 304
+// 14.1 / 11.1; 96, 104 12.7 / 10.0.
 template <class P>
 inline int score_few(const P &p)
 {
     const long blocks = (long)p.G * ((p.W + 15) / 16);
     if (blocks <= 2 || (blocks <= kFewBlocks && (long)p.Hkv * p.n <= 65536)) return 1;
-    return blocks > kFewBlocks && blocks <= 96 && p.Hkv * ((p.n + 16l * kFewKB - 1) / (16 * kFewKB)) * blocks <= 20000 ? 4 : 0;
+    if (blocks <= kFewBlocks || blocks > 96) return 0;
+    const long groups = p.Hkv * ((p.n + 16l * kFewKB - 1) / (16 * kFewKB)), rounds = (groups + 255) / 256;
+    if (p.D == 64) return groups <= 1280 && groups * blocks <= 20000 ? 4 : 0;
+    return (blocks <= 64 && rounds * (blocks + 14) <= 90) || (groups > 150 && groups <= 256) ? 4 : 0;
 }
 
 }  // namespace reform

@@ -10,7 +10,7 @@
 using namespace reform;
 
 struct Plan { int Hkv, G, D, M, Ct, n_row_blocks, by_head, shares, start, tiles, part_rows; };
-struct ScorePlan { int Hkv, G, n, W, slices, slice_tiles, head_slices, slice_heads; };
+struct ScorePlan { int Hkv, G, D, n, W, slices, slice_tiles, head_slices, slice_heads; };
 struct Piece { long t0, t1, slot; };
 
 extern "C" int replay(int Hkv, int G, int D, int M, int Ct, int cus)
@@ -62,10 +62,10 @@ extern "C" int replay(int Hkv, int G, int D, int M, int Ct, int cus)
 }
 
 // Waves that share their keys in the register-only form (1 or 4); 0: the tiled form, uncut; 16 * slices: cut.
-extern "C" int score_form(int Hkv, int G, int M, int Ct, int W, int cus)
+extern "C" int score_form(int Hkv, int G, int D, int M, int Ct, int W, int cus)
 {
     ScorePlan p = {};
-    p.Hkv = Hkv; p.G = G; p.n = M + Ct; p.W = W ? W : Ct;
+    p.Hkv = Hkv; p.G = G; p.D = D; p.n = M + Ct; p.W = W ? W : Ct;
     if (const int waves = score_few(p)) return waves;
     score_plan(p, cus);
     return p.slices > 1 ? 16 * p.slices : 0;

@@ -57,7 +57,7 @@ def test_caches_whose_keys_times_heads_pass_32_bits(replay, Hkv, G):
 
 def test_the_score_shapes_of_the_gpu_tests_take_the_form_they_are_for(plan):
     def form(Hq, Hkv, d, M, Ct, W):
-        return plan.score_form(Hkv, Hq // Hkv, M, Ct, W, 256)
+        return plan.score_form(Hkv, Hq // Hkv, d, M, Ct, W, 256)
 
     for shape in test_gpu_attend_split.SLICED:
         assert form(*shape) > 16, shape
@@ -67,3 +67,26 @@ def test_the_score_shapes_of_the_gpu_tests_take_the_form_they_are_for(plan):
         assert form(*shape) == 4, shape
     for shape in test_gpu_attend_score_waves.TILED:
         assert form(*shape) % 16 == 0, shape
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W", [
+    (8, 8, 128, 8686, 141, 0),        # score alone 14.9 us tiled, 28.5 us with four waves to 32 keys
+    (24, 8, 128, 4366, 45, 0),        # 15.1, 17.1
+    (32, 8, 128, 4096, 40, 0),        # 18.4, 19.2
+    (16, 4, 128, 94, 381, 0),         # 12.3, 15.1
+    (8, 8, 64, 8686, 141, 0),         # 11.8, 16.0
+    (24, 8, 64, 6158, 45, 0),         # 11.2, 13.0
+])
+def test_score_forms_measured_faster_tiled_stay_tiled(plan, Hq, Hkv, d, M, Ct, W):
+    assert plan.score_form(Hkv, Hq // Hkv, d, M, Ct, W, 256) % 16 == 0
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W", [
+    (16, 4, 128, 1614, 45, 0),        # 10.4 us tiled, 6.3 us with four waves
+    (14, 2, 128, 3406, 141, 0),       # 16.2, 11.7
+    (8, 8, 128, 2510, 141, 0),        # 14.7, 11.3
+    (32, 8, 64, 958, 253, 0),         # 14.1, 11.1
+    (14, 2, 64, 14641, 47, 0),
+])
+def test_score_forms_measured_faster_with_four_waves_take_them(plan, Hq, Hkv, d, M, Ct, W):
+    assert plan.score_form(Hkv, Hq // Hkv, d, M, Ct, W, 256) == 4

@@ -20,11 +20,13 @@ FOUR_WAVES = [
     (4, 1, 64, 0, 33, 33),            # twelve, 33 keys, diagonal
     (2, 2, 128, 1000, 150, 150),      # ten, from one head each
     (14, 2, 64, 500, 40, 25),         # the window begins inside a block
-    (8, 1, 128, 64, 192, 192),        # 96, the most
+    (8, 1, 64, 64, 192, 192),         # 96, the most
+    (8, 1, 128, 4900, 192, 192),      # the same at head_dim 128, 160 workgroups
+    (4, 1, 128, 0, 256, 256),         # 64
     (3, 1, 64, 2047, 65, 65),
     (11, 1, 128, 96, 1, 1),           # one row, a block per head
 ]
-TILED = [(8, 2, 64, 21000, 200, W) for W in (63, 64, 65, 129, 193)]
+TILED = [(8, 2, 64, 21000, 200, W) for W in (63, 64, 65, 129, 193)] + [(8, 1, 128, 64, 192, 192)]
 
 
 @pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W", FOUR_WAVES)
@@ -53,7 +55,7 @@ def test_score_matches_oracle(Hq, Hkv, d, M, Ct, W, accumulate):
 
 @pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W", TILED)
 def test_tiles_begin_with_the_window(Hq, Hkv, d, M, Ct, W):
-    """Too many keys for the form above: query tiles of 64, counted from the first observing row."""
+    """Too many keys for the form above, or too few for that many blocks: query tiles of 64, counted from the first observing row."""
     g = torch.Generator().manual_seed(W)
     q = torch.randn((Hq, Ct, d), generator=g).to(torch.bfloat16)
     k = (1.5 * torch.randn((Hkv, M + Ct, d), generator=g)).to(torch.bfloat16)
