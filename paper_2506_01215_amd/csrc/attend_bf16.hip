@@ -1123,19 +1123,17 @@ __device__ __forceinline__ void score_few_keys(const AttnParams &p, int bid)
     load(x, rw);
     load(y, rw + RW);
     if constexpr (PIECES) {                              // while the keys and the first rows are on their way
-        const int rows = p.G * p.Ct, r_first = (p.Ct - p.W) * p.G, rb0 = r_first / kFwdRows;
+        const int rb0 = (p.Ct - p.W) * p.G / kFwdRows;
         const int pos0 = fwd_row_block_pos(p, rb0), nt0 = fwd_row_block_tiles(p, rb0);
         // the rows lie in row block rb0 and at most the next one
         const int rb1 = min(rb0 + 1, p.n_row_blocks - 1);
         const int pos1 = rb1 > rb0 ? pos0 + nt0 + p.start : pos0;
         const FwdPieces<AttnParams> pc0(p, pos0, nt0), pc1(p, pos1, fwd_row_block_tiles(p, rb1));
         // T threads to a row, each over every T-th piece
-        const int entries = p.G * w16;
-        int T = 256;
-        while (T * entries > 256) T >>= 1;
+        const int entries = p.G * p.W, T = merge_score_lanes(entries);
         const int e = threadIdx.x / T, sub = threadIdx.x % T;
         if (e < entries) {                               // the same for all T lanes of a row
-            const int row = min(p.Ct - p.W + e % w16, p.Ct - 1), gi = e / w16, r = min(row * p.G + gi, rows - 1);
+            const int row = p.Ct - p.W + e % p.W, gi = e / p.W, r = row * p.G + gi;
             const bool second = r / kFwdRows > rb0;
             const int j0 = second ? pc1.j0 : pc0.j0, j1 = second ? pc1.j1 : pc0.j1, pr = r % kFwdRows;
             float m = -INFINITY, l = 0.f;
@@ -1156,7 +1154,7 @@ __device__ __forceinline__ void score_few_keys(const AttnParams &p, int bid)
                         l = fmaf(l, a, w * x[u].y);
                     }
                 }
-            for (int o = 1; o < T && o < 64; o <<= 1) {
+            for (int o = 1; o < T; o <<= 1) {
                 const float om = __shfl_xor(m, o), ol = __shfl_xor(l, o);
                 const float m_new = fmaxf(m, om);
                 const float a = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - m_new);
@@ -1165,7 +1163,7 @@ __device__ __forceinline__ void score_few_keys(const AttnParams &p, int bid)
                 l = fmaf(l, a, w * ol);
             }
             if (sub == 0)
-                slse[e] = j0 < j1 ? m + __builtin_amdgcn_logf(l) : p.lse[(size_t)(kvh * p.G + gi) * p.Ct + row] * kLog2e;
+                slse[gi * w16 + e % p.W] = j0 < j1 ? m + __builtin_amdgcn_logf(l) : p.lse[(size_t)(kvh * p.G + gi) * p.Ct + row] * kLog2e;
         }
         __syncthreads();
         if (jw >= p.n) return;
@@ -1212,8 +1210,9 @@ __global__ __launch_bounds__(256) void attn_score_few(AttnParams p)
 // short launches of 3 us and more, and the score only needs the pieces' maxima and sums, a few KB.
 // The first n_score workgroups are the score's, the others merge as attn_fwd_merge<D, true> does, one row
 // each.  Whole calls: 17 rows over 4113 keys of 8 heads 17.7 -> 16.0 us, 25 rows over 5025, 32/8 heads 29.0 -> 25.6
-// us, 200 rows (128 observe) over 6200, 8 heads 37.9 -> 34.0 us, 30 over 30030, 8 heads 51.2 -> 50.8 us; with the
-// normalisers formed before the keys are asked for, 30 over 30030 55.5 us.
+// us, 200 rows (128 observe) over 6200, 8 heads 37.9 -> 34.0 us.  With the normalisers formed before the keys are asked
+// for, 30 over 30030, 8 heads took 55.5 instead of 50.8 us; with those of the rows that fill up a head's block of 16 formed
+// as well, one token over 20000, 14/2 heads of 64 20.5 instead of 13.3 us.  Where it is taken: merge_with_score.
 template <int D, int KB>
 __global__ __launch_bounds__(256) void attn_merge_score(AttnParams p, int n_score)
 {
@@ -1327,14 +1326,13 @@ static hipError_t launch_score(AttnParams p, void *part, size_t part_bytes, hipS
     return waves == 8 ? launch_score_tiled<D, 8>(p, st) : launch_score_tiled<D, 4>(p, st);
 }
 
-// Both passes.  Where the first is split and the second takes few rows, merging and the score are one launch;
-// merging is then a workgroup per row, so there must not be many (a window of a longer chunk).
+// Both passes.  Where the first is split and the second takes few rows, merging and the score are one launch.
 template <int D>
 static hipError_t launch_both(const AttnParams &p, void *part, size_t part_bytes, hipStream_t st)
 {
     AttnParams f = p;
     const bool split = fwd_place<D>(f, part, part_bytes);
-    if (!split || score_few(p) != 1 || (long)f.Hkv * f.n_row_blocks * f.part_rows > 2048) {
+    if (!split || !merge_with_score(f)) {
         const hipError_t e = launch_fwd<D>(f, split, st);
         return e == hipSuccess ? launch_score<D>(p, part, part_bytes, st) : e;
     }

@@ -1,7 +1,7 @@
 // How the bf16 forward pass and the score pass of a problem are cut into workgroups.  Plain arithmetic without a
 // device type, shared by the launcher, the kernels and a host program that replays it; P is AttnParams, or
 // has its fields Hkv, G, D, M, Ct, n_row_blocks, by_head, shares, start, tiles and part_rows, and for the
-// score D, n, W, slices, slice_tiles, head_slices and slice_heads.  Sizes reach 2^30 keys and 2^31 query rows,
+// score also n, W, slices, slice_tiles, head_slices and slice_heads.  Sizes reach 2^30 keys and 2^31 query rows,
 // so no product of keys and heads may be formed in 32 bits.
 #pragma once
 
@@ -212,6 +212,34 @@ inline int score_few(const P &p)
     const long groups = p.Hkv * ((p.n + 16l * kFewKB - 1) / (16 * kFewKB)), rounds = (groups + 255) / 256;
     if (p.D == 64) return groups <= 1280 && groups * blocks <= 20000 ? 4 : 0;
     return (blocks <= 64 && rounds * (blocks + 14) <= 90) || (groups > 150 && groups <= 256) ? 4 : 0;
+}
+
+// Lanes that read the pieces of one observing row in attn_merge_score; entries: G W rows, 128 at most.
+RF_PLAN int merge_score_lanes(int entries)
+{
+    int lanes = 64;
+    while (lanes * entries > 256) lanes >>= 1;
+    return lanes;
+}
+
+// Whether a split forward pass (planned) is merged by the launch that forms its score.  That saves a launch, 2 to 3 us, and
+// costs every workgroup of the score, one per 128 keys of a KV head, the rows' normalisers from all their pieces.
+// Whole calls, two launches / one, us:
+//   - one token over 20000 keys, 14/2 heads of 64 17.0 / 13.3, 8/8 heads of 128 29.0 / 28.6 (1250 workgroups of the score);
+//     16 rows over 14000, 8/8 of 128 28.9 / 27.1 (875), over 20000 34.8 / 35.8 (1250), over 60000 84.7 / 87.2; 16 over
+//     30000, 8/8 of 64 29.4 / 28.0 (1875), one over 60000 41.1 / 42.6 (3750): not beyond four a compute unit, eight at 64.
+//   - with many rows to merge, a workgroup each, fewer: 200 rows over 6000 keys, 8/8 of 64 29.8 / 27.9 (1975 workgroups
+//     in all), 250 (17 observe) over 6000 27.1 / 26.8 (2375), over 10000 28.8 / 29.3 (2625), over 20000 34.5 / 36.5.
+//   - a lane reads its row's pieces four at a time: 5 rows over 20000, 14/2 of 64 20.2 / 20.1 (eight times), 16 over 6000
+//     17.7 / 16.4 (six), over 20000 24.4 / 27.3 (sixteen), of 128 33.5 / 36.6.
+template <class P>
+inline bool merge_with_score(const P &p)
+{
+    const long n_merge = (long)p.Hkv * p.n_row_blocks * p.part_rows;
+    const long n_score = p.Hkv * ((p.n + 64l * kFewKB - 1) / (64 * kFewKB));
+    if (score_few(p) != 1 || n_merge > 2048 || n_merge + n_score > 2400 || n_score > (p.D == 64 ? 2048 : 1024)) return false;
+    const long pieces = ((p.M + p.Ct - 1) / 64 + 1l) * p.shares / p.tiles;     // of the longest row block
+    return pieces <= 8 * 4 * merge_score_lanes(p.G * p.W);
 }
 
 }  // namespace reform

@@ -1,7 +1,8 @@
 // Replays the walk of every workgroup of the split forward pass and the piece ranges of the merge, as host
 // code over the same header.  Returns 0 if every key tile of every row block is covered exactly once and the
 // merge reads exactly the slots that were written for it, 1 if the problem is not split, else a number
-// that tells what failed.  score_form: the form of the score pass.
+// that tells what failed.  score_form: the form of the score pass.  merged: whether its launch merges a split
+// forward pass.
 #include "attend_plan.h"
 
 #include <algorithm>
@@ -9,7 +10,7 @@
 
 using namespace reform;
 
-struct Plan { int Hkv, G, D, M, Ct, n_row_blocks, by_head, shares, start, tiles, part_rows; };
+struct Plan { int Hkv, G, D, M, Ct, n_row_blocks, by_head, shares, start, tiles, part_rows, n, W; };
 struct ScorePlan { int Hkv, G, D, n, W, slices, slice_tiles, head_slices, slice_heads; };
 struct Piece { long t0, t1, slot; };
 
@@ -69,4 +70,13 @@ extern "C" int score_form(int Hkv, int G, int D, int M, int Ct, int W, int cus)
     if (const int waves = score_few(p)) return waves;
     score_plan(p, cus);
     return p.slices > 1 ? 16 * p.slices : 0;
+}
+
+// Whether a call that wants both is split (bit 0), and merged by the launch that forms the score (bit 1).
+extern "C" int merged(int Hkv, int G, int D, int M, int Ct, int W, int cus)
+{
+    Plan p = {};
+    p.Hkv = Hkv; p.G = G; p.D = D; p.M = M; p.Ct = Ct; p.n = M + Ct; p.W = W ? W : Ct;
+    fwd_plan(p, cus);
+    return p.shares ? 1 + 2 * merge_with_score(p) : 0;
 }

@@ -9,6 +9,7 @@ import subprocess
 
 import pytest
 
+import test_gpu_attend_merge_score
 import test_gpu_attend_score_waves
 import test_gpu_attend_split
 
@@ -67,6 +68,8 @@ def test_the_score_shapes_of_the_gpu_tests_take_the_form_they_are_for(plan):
         assert form(*shape) == 4, shape
     for shape in test_gpu_attend_score_waves.TILED:
         assert form(*shape) % 16 == 0, shape
+    for Hq, Hkv, d, M, Ct, W in test_gpu_attend_merge_score.MERGED:
+        assert plan.merged(Hkv, Hq // Hkv, d, M, Ct, W, 256) == 3, (Hq, Hkv, d, M, Ct, W)
 
 
 @pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W", [
@@ -90,3 +93,16 @@ def test_score_forms_measured_faster_tiled_stay_tiled(plan, Hq, Hkv, d, M, Ct, W
 ])
 def test_score_forms_measured_faster_with_four_waves_take_them(plan, Hq, Hkv, d, M, Ct, W):
     assert plan.score_form(Hkv, Hq // Hkv, d, M, Ct, W, 256) == 4
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W,merged", [
+    (8, 8, 128, 59999, 1, 0, False),  # 68.1 us in two launches, 71.2 in one
+    (8, 8, 128, 19970, 30, 0, False), # 35.8, 37.3
+    (8, 8, 64, 19750, 250, 17, False),# 34.5, 36.5
+    (14, 2, 64, 19984, 16, 0, False), # 24.4, 27.3
+    (14, 2, 64, 19999, 1, 0, True),   # 17.0, 13.3
+    (8, 8, 128, 13970, 30, 0, True),  # 29.9, 28.4
+    (8, 8, 128, 4096, 17, 0, True),
+])
+def test_merging_in_the_score_launch_where_it_was_measured_faster(plan, Hq, Hkv, d, M, Ct, W, merged):
+    assert plan.merged(Hkv, Hq // Hkv, d, M, Ct, W, 256) == (3 if merged else 1)

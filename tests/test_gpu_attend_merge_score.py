@@ -1,5 +1,5 @@
 """Split attention whose pieces are merged by the launch that also forms the score of few rows: observing rows
-in one row block and across two, windows that end inside a 16-row block, row blocks with one piece and with many,
+in one row block and across two, windows that end inside a 16-row block, row blocks with few pieces and with many,
 waves behind the last key, accumulated scores, against the fp64 oracle and the two calls by themselves."""
 import math
 
@@ -14,16 +14,23 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-@pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W", [
+# That these take the one launch is checked on the CPU (test_attend_plan.py).
+MERGED = [
     (2, 2, 128, 1000, 300, 100),      # rows 200..299: two row blocks
-    (2, 2, 64, 0, 300, 128),          # no cache: short row blocks, some with one piece
+    (2, 2, 64, 0, 500, 128),          # no cache: row blocks of few pieces
     (4, 1, 128, 3000, 20, 20),        # eight blocks of rows, half of each empty
     (14, 2, 64, 900, 16, 16),
     (8, 1, 128, 700, 1, 1),           # one token
     (1, 1, 128, 5000, 260, 1),        # only the last row observes
     (8, 8, 128, 4096, 17, 17),
-    (3, 1, 64, 130, 31, 5),
-])
+    (3, 1, 64, 200, 31, 5),
+    (14, 2, 128, 9000, 1, 1),         # seven rows of many pieces, 32 lanes each
+    (1, 1, 64, 3000, 40, 3),          # three rows, 64 lanes each
+]
+WHOLE = [(2, 2, 64, 0, 300, 128), (3, 1, 64, 130, 31, 5)]     # chunks that are not split
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W", MERGED + WHOLE)
 @pytest.mark.parametrize("accumulate", [False, True])
 def test_one_call_matches_oracle(Hq, Hkv, d, M, Ct, W, accumulate):
     g = torch.Generator().manual_seed(Hq + M + Ct + W)
