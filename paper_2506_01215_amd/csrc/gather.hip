@@ -537,8 +537,10 @@ static hipError_t similarity_passes(GatherParams p, bool bf16, hipStream_t st)
     const int cus = device_compute_units() > 0 ? device_compute_units() : 256;
     const size_t lds = 160 * 1024, block = (size_t)16 * (p.D + ((32 - 2 * p.D) & 255) / 2) * sizeof(u16);
     const bool mfma = bf16 && p.D % 32 == 0 && (size_t)16 * (p.D + 128) * 2 <= 150 * 1024;
-    // little work: a wave per row is as fast (2048 x 256, one query 12.4 and 12.6 us) or faster (700 x 64, one query 15.2
-    // and 16.4 us, 4126 x 64, one 20.0 and 20.3 us); 4100 x 128, one query 15.1 and 14.7 us, 1100 x 512, four 19.8 and 17.9 us
+    // Little work: a wave per row is as fast or faster, similarity alone, that / matrix form, us.  One query crosses between 260
+    // and 700 thousand products of rows and dims: 1024 x 256 4.4 / 5.1, 2048 x 256 4.9 / 5.2, 2734 x 256 5.3 / 5.2, 2048 x 64
+    // 4.1 / 4.9, 4096 x 128 5.2 / 5.1, but 1367 x 512 5.8 / 6.0; four queries at 150 to 350 thousand: 512 x 64 4.6 / 4.8,
+    // 1562 x 64 5.1 / 4.9, 512 x 256 5.9 / 5.1.
     const bool f32_mfma = !bf16 && p.D % 16 == 0 && (size_t)16 * sim_f32_pitch(p.D) * sizeof(float) <= 140 * 1024 &&
                           (double)p.N * p.nq * p.D > 524288.0;
     // blocks of 16 queries: as few passes over the store as the LDS allows, evenly filled
@@ -567,7 +569,11 @@ static hipError_t similarity_passes(GatherParams p, bool bf16, hipStream_t st)
         } else if (f32_mfma) {
             smem = (size_t)16 * sim_f32_pitch(p.D) * sizeof(float);
             threads = 256;
-            grid = min((p.N + 15) / 16, (long)cus * 8);
+            // Each workgroup stages the queries and starts its stream anew, so two per compute unit, one where the LDS holds
+            // no more.  Similarity alone with one / two / three per unit, us: 110000 x 256, four queries 44.7 / 27.6 /
+            // 35.2; 45000 x 16, one 15.7 / 10.2 / 13.3; 20000 x 2048, one 37.4 / 41.7 / 47.4.  With eight one query over
+            // 30000 x 64 took 15.9 us, a wave per row 12.8, with two 9.6.
+            grid = min((p.N + 15) / 16, (long)cus * (smem <= 70 * 1024 ? 2 : 1));
             kern = sim_f32_mfma<MAX>;
         } else {
             smem = (size_t)p.nq_grp * p.D * sizeof(float);

@@ -16,6 +16,7 @@ DEV = "cuda:0"
 @pytest.mark.parametrize("N,D,nq", [
     (2048, 256, 1), (2049, 256, 1), (33000, 16, 1), (273, 32, 15), (1025, 48, 4), (300, 80, 17), (511, 256, 16), (4113, 272, 1),
     (257, 512, 33), (130, 1040, 40), (400, 2000, 16), (300, 2208, 14), (300, 2400, 14),
+    (8209, 64, 3), (9000, 1200, 2),          # a second and a third round of workgroups
 ])
 def test_similarities_and_their_maximum(N, D, nq):
     g = torch.Generator().manual_seed(N + D + nq)
