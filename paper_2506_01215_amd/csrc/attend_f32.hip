@@ -135,14 +135,14 @@ __device__ __forceinline__ f32x4 f32_logits(const float (&a)[D / 4], const float
 // with a running maximum of its own, and meet in LDS once at the end.  With one wave per row the
 // keys of a row were a chain of dependent steps: 4 heads, 128 rows over 384 keys, head_dim 64
 // 81 -> 11 us, and with the waves' factors formed once per row at the end, not per output element, 10 us.  Batches of
-// two or three blocks that share the maximum and overlap their MFMA chains give nothing: the fp32 matrix pipe of the
-// 32 busy compute units is what a block waits for (2048 of the 2900 clocks of a step).
+// two or three blocks that share the maximum and overlap their MFMA chains give nothing: the fp32 matrix pipe of a
+// compute unit is what a row block waits for (2048 of the 2900 clocks of a step).
 constexpr int kF32FwdWaves = 8;
 
 // SPLIT: the fp32 matrix pipe of a compute unit is what a row block waits for, so few row blocks share their key blocks
 // over p.shares workgroups each, whose sums go to the workspace: [share][head, row block, row].  They are merged by the
 // launch that forms the score where there is one (attn_merge_score_f32), else by one of its own.  Attention and score:
-// 128 rows over 384 keys, 4 heads of 64 13.6 -> 11.6 us, 16 over 1040, 8/2 heads 20.6 -> 13.2 us, 40 over 940, 4 heads
+// 128 rows over 384 keys, 4 heads of 64 13.4 -> 11.2 us, 16 over 1040, 8/2 heads 20.6 -> 13.2 us, 40 over 940, 4 heads
 // of 128 31.3 -> 19.1 us.
 constexpr int kF32MaxShares = 4;
 __device__ __forceinline__ size_t f32_slot(const AttnParams &p, int nrb, int h, int i) { return ((size_t)h * nrb + i / 16) * 16 + i % 16; }
@@ -430,13 +430,21 @@ __global__ __launch_bounds__(kF32ScoreWaves * 64) void attn_merge_score_f32(Attn
     else f32_merge_rows<D>(p, blockIdx.x - n_score);
 }
 
-// Shares of a problem (1: whole) with and without a score behind it.  A wave's step over a key block is 1.2 us;
-// the launch that merges costs 3 us where it is not the score's.
+// Shares of a problem (1: whole) with and without a score behind it.  The four matrix pipes of a compute unit divide a row
+// block's key blocks, so up to twelve of them (192 keys) shares save nothing and cost the score's launch the sums of
+// all shares: whole / two shares, attention and score, us: 4 heads of 128, 16 rows over 140 keys 13.0 / 14.9, over 180
+// 13.8 / 14.8, over 200 15.5 / 14.8; 4 of 64, 60 rows 9.5 / 10.2, 10.0 / 10.3, 10.7 / 10.3; 8/2 of 32, 60 rows 9.0 / 9.6,
+// 9.2 / 9.6, 9.8 / 9.5.  At head_dim 32 with more than 16 row blocks over the heads of a group up to twenty (8/2, 128 rows
+// over 290 keys 11.9 / 12.3, over 330 12.6 / 12.4).
+// A launch of its own for the merge takes 3 us, a step of eight waves over their key blocks 1.2 us at head_dim 64, the measure
+// here, 0.9 at 32 and 2.2 at 128: whole / four shares without the score, 60 rows over 400 keys, 4 heads of 32 6.9 / 6.8, of
+// 64 9.5 / 8.2, of 128 16.1 / 11.7; over 330 keys they stay whole.
 static int f32_shares(const AttnParams &p, bool score)
 {
     if (p.D != 32 && p.D != 64 && p.D != 128) return 1;
     const long groups = (long)p.Hq * ((p.Ct + 15) / 16), cus = device_compute_units() > 0 ? device_compute_units() : 256;
-    const int steps = ((p.n - 1) / 16 + kF32FwdWaves) / kF32FwdWaves;
+    const int blocks = (p.n - 1) / 16 + 1, steps = (blocks - 1) / kF32FwdWaves + 1;
+    if (blocks <= (p.D == 32 && (long)p.G * ((p.W + 15) / 16) > 16 ? 20 : 12)) return 1;
     int shares = (int)(cus / groups < kF32MaxShares ? cus / groups : kF32MaxShares);
     if (shares > steps) shares = steps;
     if (shares < 2 || (!score && (steps - (steps + shares - 1) / shares) * 1.2 < 3.0)) return 1;

@@ -8,10 +8,12 @@ import random
 import subprocess
 
 import pytest
+import torch
 
 import test_gpu_attend_merge_score
 import test_gpu_attend_score_waves
 import test_gpu_attend_split
+from paper_2506_01215_amd import binding
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "..", "paper_2506_01215_amd", "csrc")
@@ -106,3 +108,18 @@ def test_score_forms_measured_faster_with_four_waves_take_them(plan, Hq, Hkv, d,
 ])
 def test_merging_in_the_score_launch_where_it_was_measured_faster(plan, Hq, Hkv, d, M, Ct, W, merged):
     assert plan.merged(Hkv, Hq // Hkv, d, M, Ct, W, 256) == (3 if merged else 1)
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,M,Ct,shared", [
+    (4, 4, 128, 124, 16, False),      # 13.0 us whole, 14.9 us with two shares
+    (4, 4, 64, 120, 60, False),       # 10.0, 10.3
+    (8, 2, 32, 162, 128, False),      # 11.9, 12.3
+    (4, 4, 128, 184, 16, True),       # 15.5, 14.8
+    (4, 4, 32, 140, 60, True),        # 8.3, 8.1
+    (8, 2, 32, 272, 128, True),
+    (4, 4, 64, 256, 128, True),
+])
+def test_fp32_key_blocks_are_shared_where_that_was_measured_faster(Hq, Hkv, d, M, Ct, shared):
+    q, k = torch.empty((Hq, Ct, d)), torch.empty((Hkv, M + Ct, d))
+    need = binding.attend_workspace_bytes(binding.attn_desc(q, k, q, M, 0.1))
+    assert (need > (Hq * Ct * 4 + 255) // 256 * 256) == shared

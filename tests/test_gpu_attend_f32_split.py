@@ -21,7 +21,10 @@ DEV = "cuda:0"
     (4, 4, 32, 0, 300, 0),            # early row blocks leave shares without a key
     (4, 2, 128, 500, 33, 20),
     (2, 1, 128, 1500, 7, 7),
-    (1, 1, 32, 127, 2, 1),            # two steps, two shares
+    (1, 1, 32, 127, 2, 1),            # nine key blocks: whole
+    (1, 1, 32, 191, 2, 1),            # thirteen, two shares
+    (1, 1, 128, 176, 20, 20),
+    (16, 1, 32, 303, 32, 20),         # 32 row blocks: from 21 key blocks on
     (1, 1, 64, 111, 16, 16),          # one step: whole
 ])
 def test_matches_oracle(Hq, Hkv, d, M, Ct, W):
@@ -54,7 +57,7 @@ def test_matches_oracle(Hq, Hkv, d, M, Ct, W):
 
 @pytest.mark.parametrize("d", [32, 64, 128])
 @pytest.mark.parametrize("M,Ct,lo,hi", [
-    (0, 129, 128, 129),               # the last row alone sees the second share's only key
+    (0, 193, 128, 193),               # all that the last rows see of the second share
     (600, 1, 384, 512),               # the fourth share's keys; split without the score too
 ])
 def test_nan_logits_of_a_whole_share_reach_the_row(M, Ct, lo, hi, d):
@@ -67,6 +70,7 @@ def test_nan_logits_of_a_whole_share_reach_the_row(M, Ct, lo, hi, d):
     bad[:, lo:hi] = float("nan")
     need = binding.attend_workspace_bytes(binding.attn_desc(q, k, q, M, 0.1))
     whole = (Ct * 4 + 255) // 256 * 256
+    first = max(lo - M, 0)            # the first row that sees one
     assert need > whole
     for nbytes in (need, whole):
         for want_score in (True, False):
@@ -74,7 +78,7 @@ def test_nan_logits_of_a_whole_share_reach_the_row(M, Ct, lo, hi, d):
             ref = binding.reform_chunk_attend_score(q, k, v, M, 0.1, want_score=want_score, workspace=ws)
             out, lse, score = binding.reform_chunk_attend_score(q, bad, v, M, 0.1, want_score=want_score, workspace=ws)
             torch.cuda.synchronize()
-            assert out[:, -1].isnan().all() and lse[:, -1].isnan().all()
-            assert torch.equal(out[:, :-1], ref[0][:, :-1]) and torch.equal(lse[:, :-1], ref[1][:, :-1])
+            assert out[:, first:].isnan().all() and lse[:, first:].isnan().all()
+            assert torch.equal(out[:, :first], ref[0][:, :first]) and torch.equal(lse[:, :first], ref[1][:, :first])
             if want_score:
                 assert score.isnan().all()
