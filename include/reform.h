@@ -104,7 +104,9 @@ typedef struct {
  * (n_q_heads * chunk_len floats, rounded up to 256 bytes), or with none if lse is given, the call
  * runs such problems in their unshared form, slower (one token over 16640 keys, 32/8 heads: 17 times)
  * and with sums in another order.  A caller that sized its workspace some other way than by this query
- * gets that form without further notice.                                                       */
+ * gets that form without further notice.  Whether the score is asked for in the same call (phases 0 or 3, score not NULL)
+ * or not can change the order of the sums too: out, lse and score then agree to rounding (fp32 sums of the same terms), not
+ * bit for bit.                                                                                  */
 size_t reform_chunk_attend_score_workspace(const reform_attn_desc *desc);
 
 reform_status reform_chunk_attend_score(const reform_attn_desc *desc,

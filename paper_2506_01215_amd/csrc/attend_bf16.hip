@@ -668,12 +668,6 @@ __global__ __launch_bounds__(kFwdWaves * 64) void attn_fwd_few(AttnParams p)
     }
 }
 
-// Merges the pieces of the row blocks that several workgroups share: a group of D/4 lanes adds up
-// pieces of one query row, four output columns per lane.  Each piece is a dependent load and an
-// exponential, so with many pieces per row (MANY: a token's row has as many as its KV head has
-// shares) all groups of a workgroup take one row together, and their sums meet in LDS: 33 pieces
-// of one row 8 us with one group, 3 us with eight.  grid (rows of a row block / rows per
-// workgroup, row block, KV head).
 // List position of row block rb's first tile, by the 64 lanes of a wave.
 __device__ __forceinline__ int fwd_row_block_pos(const AttnParams &p, int rb)
 {
@@ -684,6 +678,12 @@ __device__ __forceinline__ int fwd_row_block_pos(const AttnParams &p, int rb)
     return pos + p.start;
 }
 
+// Merges the pieces of the row blocks that several workgroups share: a group of D/4 lanes adds up
+// pieces of one query row, four output columns per lane.  Each piece is a dependent load and an
+// exponential, so with many pieces per row (MANY: a token's row has as many as its KV head has
+// shares) all groups of a workgroup take one row together, and their sums meet in LDS: 33 pieces
+// of one row 8 us with one group, 3 us with eight.  grid (rows of a row block / rows per
+// workgroup, row block, KV head).
 template <int D, bool MANY>
 __device__ __forceinline__ void fwd_merge(const AttnParams &p, int bx, int rb, int kvh)
 {

@@ -479,7 +479,7 @@ reform_status reform_gather_topk(const reform_gather_desc *d, const void *emb, c
     p.sel.out_idx = topk_idx; p.sel.out_val = topk_score; p.sel.out_ld = d->k;
     if (union_idx && d->n_query == 1 && d->radius == 0 && d->n_head_keep == 0 && d->n_tail_keep == 0) {
         // One query, no neighbours, nothing forced: the union is the selection, which writes it as well instead of
-        // marking a bitmap (2048 rows 17.0 -> 14.3 us, 131072 rows 71.0 -> 65.2 us, 15000 of 20000 rows, whose
+        // marking a bitmap (2048 rows 16.2 -> 13.1 us, 131072 rows 71.0 -> 65.2 us, 15000 of 20000 rows, whose
         // marks queue on few words, 60 -> 22 us).
         p.sel.union_idx = union_idx;
         p.sel.union_count = union_count;

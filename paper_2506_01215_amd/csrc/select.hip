@@ -767,9 +767,8 @@ __global__ __launch_bounds__(256) void select_write_rest(SelParams p)
 // owning nit * 256 candidates, nit <= 8).  The row is read once; its keys stay in LDS through the
 // radix passes (LDS histogram, pick by a workgroup scan) and the ordered emission.  As soon as the
 // digits picked so far are shared by at most kSelList candidates (nearly always after two passes:
-// the rest is ties) these go into a list, and the k-th largest is found by counting for each of them
-// how many are larger.  Results are identical to the multi-launch path; the per-pass selection state
-// is not written back.
+// the rest is ties) these go into a list, whose k-th largest list_pick finds.  Results are identical to
+// the multi-launch path; the per-pass selection state is not written back.
 //
 // One workgroup per row (MULTI = false) serves short rows and many rows: its compute unit does all the
 // work of a row, so a few long ones are faster with more of them.
