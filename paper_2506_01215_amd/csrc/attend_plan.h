@@ -199,8 +199,11 @@ constexpr int kFewKB = 2;                                // 16-key blocks of a w
 // (1.7 + blocks / 10) us, while the tiled form with its slices stays at 12 to 18 us.  Score alone, tiled / four waves, us,
 // with one round: 12 blocks 10.4 / 6.3, 48 11.6 / 9.8, 64 11.7 / 11.4; two: 16 blocks 10.8 / 9.8, 28 13.1 / 13.0,
 // 63 16.5 / 20.0; three: 9 blocks 14.0 / 11.3, 16 17.4 / 13.2, 24 13.8 / 15.1; five: 9 blocks 14.0 / 17.2; nine:
-// 9 blocks 14.9 / 28.5.  More than 64 blocks pay where one round is more than half full (91 blocks, 152 workgroups
-// 16.7 / 15.1; 96 blocks, 176 16.4 / 15.2; but 96 blocks, 60 workgroups 12.3 / 15.0).
+// 9 blocks 14.9 / 28.5.  In a round of few workgroups the tiled form is short as well, so more than 72 blocks need more of
+// them.  Time with four waves over the tiled form's, one round: 68 to 72 blocks 0.85 to 1.01 from 20 workgroups on; 76 to 80
+// blocks 1.04 to 1.10 at 50 to 88 (32 and 64 heads 0.90 to 0.94), 0.80 to 0.94 from 100 on; 84 to 90 blocks 1.11 to 1.15 at
+// 50, 0.83 to 1.06 from 100 on (above 1 with 4 KV heads at 130 to 180 only, 0.5 us); 91 to 96 blocks 0.88 to 1.13 at 100 to
+// 152, 0.90 to 0.96 at 180.
 // At 64 a round costs half: 9 blocks, 1104 workgroups 12.0 / 10.3, 1552 11.2 / 13.0; 21 blocks, 946 13.6 / 11.5; 64, 304
 // 14.1 / 11.1; 96, 104 12.7 / 10.0.
 template <class P>
@@ -211,7 +214,8 @@ inline int score_few(const P &p)
     if (blocks <= kFewBlocks || blocks > 96) return 0;
     const long groups = p.Hkv * ((p.n + 16l * kFewKB - 1) / (16 * kFewKB)), rounds = (groups + 255) / 256;
     if (p.D == 64) return groups <= 1280 && groups * blocks <= 20000 ? 4 : 0;
-    return (blocks <= 64 && rounds * (blocks + 14) <= 90) || (groups > 150 && groups <= 256) ? 4 : 0;
+    if (rounds == 1) return blocks <= (groups < 100 ? 72 : groups <= 170 ? 90 : 96) ? 4 : 0;
+    return rounds * (blocks + 14) <= 90 ? 4 : 0;
 }
 
 // Lanes that read the pieces of one observing row in attn_merge_score; entries: G W rows, 128 at most.

@@ -79,6 +79,8 @@ def test_the_score_shapes_of_the_gpu_tests_take_the_form_they_are_for(plan):
     (24, 8, 128, 4366, 45, 0),        # 15.1, 17.1
     (32, 8, 128, 4096, 40, 0),        # 18.4, 19.2
     (16, 4, 128, 94, 381, 0),         # 12.3, 15.1
+    (16, 4, 128, 812, 381, 0),        # 96 blocks, 152 workgroups: 1.13 times
+    (14, 2, 128, 620, 173, 0),        # 77 blocks, 50 workgroups: 1.05 times
     (8, 8, 64, 8686, 141, 0),         # 11.8, 16.0
     (24, 8, 64, 6158, 45, 0),         # 11.2, 13.0
 ])
@@ -91,6 +93,9 @@ def test_score_forms_measured_faster_tiled_stay_tiled(plan, Hq, Hkv, d, M, Ct, W
     (14, 2, 128, 3406, 141, 0),       # 16.2, 11.7
     (8, 8, 128, 2510, 141, 0),        # 14.7, 11.3
     (32, 8, 64, 958, 253, 0),         # 14.1, 11.1
+    (32, 8, 128, 64, 269, 0),         # 68 blocks, 88 workgroups: 0.87 times
+    (24, 8, 128, 52, 461, 0),         # 87 blocks, 136 workgroups: 0.89 times
+    (64, 8, 128, 524, 189, 0),        # 96 blocks, 184 workgroups: 0.94 times
     (14, 2, 64, 14641, 47, 0),
 ])
 def test_score_forms_measured_faster_with_four_waves_take_them(plan, Hq, Hkv, d, M, Ct, W):

@@ -21,7 +21,7 @@ FOUR_WAVES = [
     (2, 2, 128, 1000, 150, 150),      # ten, from one head each
     (14, 2, 64, 500, 40, 25),         # the window begins inside a block
     (8, 1, 64, 64, 192, 192),         # 96, the most
-    (8, 1, 128, 4900, 192, 192),      # the same at head_dim 128, 160 workgroups
+    (8, 1, 128, 5300, 192, 192),      # the same at head_dim 128, 172 workgroups
     (4, 1, 128, 0, 256, 256),         # 64
     (3, 1, 64, 2047, 65, 65),
     (11, 1, 128, 96, 1, 1),           # one row, a block per head
