@@ -817,9 +817,18 @@ struct QStage {
 // alternates between two registers costs 4 % less than a new A operand on every MFMA.  The
 // 32x32x16 form of this kernel (32 keys x 32 rows per MFMA, new key fragment every MFMA) was
 // 1.2 % slower.
+//
+// At head_dim 64 a logit costs half the MFMAs and the same VALU work, which then is the bound (v_fma, v_exp and v_add 17
+// cycles, its MFMAs 8, most of which do not overlap), so what counts is that some wave always has VALU work to issue: a
+// wave of the four-wave form holds 32 keys there, not 64 (107 registers, four waves per SIMD instead of two; three per
+// SIMD with 64 keys spill and gain half as much, five spill), and six VALU instructions follow an MFMA, not three.
+// Score alone, back to back: 8192 rows over 16384 keys, 16/4 heads 334 -> 289 us; 16384 over 24576, 32/8 heads 1697 -> 1423;
+// 1000 over 4000, 32/8 44.6 -> 36.4; 128 of 3001 rows over 11193, 24/8 19.7 -> 15.0; VALU busy 0.60 -> 0.74 of the cycles.
+// At 128 the same form only lowers the clock (power).
+//
 // WINDOW: not every row observes.  Without it the first observing row is 0 at compile time.
 template <int D, int KB, int NW, bool WINDOW>
-__global__ __launch_bounds__(NW * 64, 2) void attn_score_bf16(AttnParams p)
+__global__ __launch_bounds__(NW * 64, KB == 2 ? 4 : 2) void attn_score_bf16(AttnParams p)
 {
     constexpr int NT = NW * 64;
     constexpr int KS = D / 32;                           // MFMA k-steps
@@ -947,7 +956,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_score_bf16(AttnParams p)
 #pragma unroll
         for (int u = 0; u < 2 * KS * KB; ++u) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);     // one MFMA ...
-            __builtin_amdgcn_sched_group_barrier(0x402, 3, 0);     // ... then three VALU/transcendental ops
+            __builtin_amdgcn_sched_group_barrier(0x402, 384 / D, 0);   // ... then its share of the VALU/transcendental ops
         }
     };
     for (int it = 0; it < iters; ++it) {
@@ -1295,7 +1304,7 @@ static hipError_t launch_fwd(const AttnParams &p, bool split, hipStream_t st)
 template <int D, int NW>
 static hipError_t launch_score_tiled(const AttnParams &p, hipStream_t st)
 {
-    constexpr int KB = 4, keys_wg = NW * 16 * KB;
+    constexpr int KB = D == 64 && NW == 4 ? 2 : 4, keys_wg = NW * 16 * KB;
     const int grid = p.Hkv * ((p.n + keys_wg - 1) / keys_wg) * p.slices;
     if (p.W == p.Ct) hipLaunchKernelGGL((attn_score_bf16<D, KB, NW, false>), dim3(grid), dim3(NW * 64), 0, st, p);
     else hipLaunchKernelGGL((attn_score_bf16<D, KB, NW, true>), dim3(grid), dim3(NW * 64), 0, st, p);
@@ -1320,7 +1329,7 @@ static hipError_t launch_score(AttnParams p, void *part, size_t part_bytes, hipS
         p.slice_tiles *= p.slices;                       // no room for partial sums: uncut
         p.slice_heads = p.G;
         p.slices = p.head_slices = 1;
-        waves = 8;
+        waves = D == 64 ? 4 : 8;
     }
     p.part_score = (float *)part;
     return waves == 8 ? launch_score_tiled<D, 8>(p, st) : launch_score_tiled<D, 4>(p, st);

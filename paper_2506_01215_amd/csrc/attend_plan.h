@@ -141,6 +141,13 @@ inline void fwd_plan(P &p, int cus)
 // uncut workgroups, half of them triangular); 512 rows over 8192 keys 77 -> 63 us with 4; 32768
 // over 32768 12.1 ms uncut, 12.3 ms in 4 or 8 slices; 700 over 30000 207 us uncut, 223 us in 4;
 // 128 rows over 8192 keys 23 us uncut, 28 us with four waves.
+//
+// At head_dim 64 a workgroup of four waves takes 128 keys and four of them are resident, so the unit is their query tile
+// against 512 keys, 1.35 us, of which eight waves take 1.2 and 2.7 us more to begin.  Short items leave less behind at the
+// end.  Score alone, us, eight waves / four uncut / 4 / 8 / 16 / 32 slices: 8192 rows over 16384 keys, 16/4 heads 752 / 500
+// / 340 / 300 / 289 / 301; 16384 over 49152, 8/8 1123 / 893 / 893 / 909 / 944 / 1033; 12000 over 12000, 14/2 1904 / 994 /
+// 362 / 255 / 224 / 205; 1000 over 4000, 32/8 111 / 55 / 36 / 36 / 38 / 38; a window of 128 rows over 11193, 24/8 19.6 /
+// 15.0, over 32000, 16/4 19.8 / 20.8, over 20000, 8/8 19.0 / 10.7.
 template <class P>
 inline int score_plan(P &p, int cus)
 {
@@ -158,16 +165,20 @@ inline int score_plan(P &p, int cus)
         if (best < (double)whole * iters + pair) best = (double)whole * iters + pair;
     }
     if (best < total) best = total;
+    const bool narrow = p.D == 64;
+    if (narrow) best = 1.2 * best + 2.0;
+    const double resident = narrow ? 4.0 : 2.0, tail = narrow ? 0.33 : 0.5, alone = narrow ? 0.5 : 1.0;
+    const double begin = narrow ? 1.6 : 1.5, add_up = narrow ? 3.0 : 2.0;
     int waves = 8;
     p.slices = p.head_slices = 1;
     p.slice_tiles = tiles;
     p.slice_heads = p.G;
     auto consider = [&](int per, int heads) {            // slices of `per` tiles of `heads` heads
         const int hs = (p.G + heads - 1) / heads, slices = (tiles + per - 1) / per * hs;
-        const double item = (double)heads * per, items = 2.0 * total * cus / item;
-        double t = total + 0.5 * item;
-        if (t < item) t = item;
-        t += 1.5 * items / (2.0 * cus) + (slices > 1 ? 2.0 : 0.0);
+        const double item = (double)heads * per, items = resident * total * cus / item;
+        double t = total + tail * item;
+        if (t < alone * item) t = alone * item;
+        t += begin * items / (resident * cus) + (slices > 1 ? add_up : 0.0);
         if (t >= best) return;
         best = t;
         waves = 4;
@@ -176,7 +187,7 @@ inline int score_plan(P &p, int cus)
         p.head_slices = hs;
         p.slice_heads = heads;
     };
-    for (int want = 1; want <= 16; want *= 2) consider((tiles + want - 1) / want, p.G);
+    for (int want = 1; want <= (narrow ? 32 : 16); want *= 2) consider((tiles + want - 1) / want, p.G);
     // Where that leaves compute units without a workgroup the heads are cut as well: 60 rows over 8000 keys
     // with 14/2 heads of 64 (32 workgroups of 7 tiles) 38 -> 31 us for the call, 30 over 1000 with 14/2 of
     // 128 38 -> 28 us.  (On a chip that is busy it gives nothing: 2000 rows over 1000 keys, 32/8 heads, 18.9
@@ -204,8 +215,9 @@ constexpr int kFewKB = 2;                                // 16-key blocks of a w
 // blocks 1.04 to 1.10 at 50 to 88 (32 and 64 heads 0.90 to 0.94), 0.80 to 0.94 from 100 on; 84 to 90 blocks 1.11 to 1.15 at
 // 50, 0.83 to 1.06 from 100 on (above 1 with 4 KV heads at 130 to 180 only, 0.5 us); 91 to 96 blocks 0.88 to 1.13 at 100 to
 // 152, 0.90 to 0.96 at 180.
-// At 64 a round costs half: 9 blocks, 1104 workgroups 12.0 / 10.3, 1552 11.2 / 13.0; 21 blocks, 946 13.6 / 11.5; 64, 304
-// 14.1 / 11.1; 96, 104 12.7 / 10.0.
+// At 64 a round costs half, tiled / four waves: 16 blocks, 210 workgroups 8.9 / 7.6; 20, 788 11.9 / 10.6; 32, 622 12.8 /
+// 10.9; 56, 302 11.1 / 10.9; 40, 616 18.8 / 11.6; 72, 448 14.8 / 12.4; 91, 394 16.2 / 14.8; but 28, 856 10.3 / 11.8; 16, 1444
+// 10.4 / 12.7; 37, 800 12.0 / 12.5; 64, 704 14.9 / 16.5; 80, 568 16.2 / 17.5; 12, 1592 8.2 / 15.3.
 template <class P>
 inline int score_few(const P &p)
 {
@@ -213,7 +225,7 @@ inline int score_few(const P &p)
     if (blocks <= 2 || (blocks <= kFewBlocks && (long)p.Hkv * p.n <= 65536)) return 1;
     if (blocks <= kFewBlocks || blocks > 96) return 0;
     const long groups = p.Hkv * ((p.n + 16l * kFewKB - 1) / (16 * kFewKB)), rounds = (groups + 255) / 256;
-    if (p.D == 64) return groups <= 1280 && groups * blocks <= 20000 ? 4 : 0;
+    if (p.D == 64) return groups * blocks <= (groups <= 640 ? 36000 : groups <= 1280 ? 20000 : 0) ? 4 : 0;
     if (rounds == 1) return blocks <= (groups < 100 ? 72 : groups <= 170 ? 90 : 96) ? 4 : 0;
     return rounds * (blocks + 14) <= 90 ? 4 : 0;
 }

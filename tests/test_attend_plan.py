@@ -11,6 +11,7 @@ import pytest
 import torch
 
 import test_gpu_attend_merge_score
+import test_gpu_attend_score_narrow
 import test_gpu_attend_score_waves
 import test_gpu_attend_split
 from paper_2506_01215_amd import binding
@@ -72,6 +73,11 @@ def test_the_score_shapes_of_the_gpu_tests_take_the_form_they_are_for(plan):
         assert form(*shape) % 16 == 0, shape
     for Hq, Hkv, d, M, Ct, W in test_gpu_attend_merge_score.MERGED:
         assert plan.merged(Hkv, Hq // Hkv, d, M, Ct, W, 256) == 3, (Hq, Hkv, d, M, Ct, W)
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W", test_gpu_attend_score_narrow.NARROW)
+def test_score_shapes_of_the_narrow_form_are_tiled(plan, Hq, Hkv, d, M, Ct, W):
+    assert plan.score_form(Hkv, Hq // Hkv, d, M, Ct, W, 256) % 16 == 0
 
 
 @pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W", [
