@@ -99,8 +99,8 @@ typedef struct {
 
 /* The query returns room for the lse rows (used if the caller passes lse = NULL) and, for problems
  * whose keys or rows are shared out over more workgroups than there are row or key blocks, for
- * their partial results: up to 68 MB for the attention (bf16; fp32 a few MB), and about 64 bytes per key of every
- * KV head for the score, 128 at head_dim 64 (the two share it).  Only the lse rows are needed: with a workspace that holds just these
+ * their partial results: up to 68 MB for the attention (bf16; fp32 a few MB), and about 128 bytes per key of every
+ * KV head for the score (the two share it).  Only the lse rows are needed: with a workspace that holds just these
  * (n_q_heads * chunk_len floats, rounded up to 256 bytes), or with none if lse is given, the call
  * runs such problems in their unshared form, slower (one token over 16640 keys, 32/8 heads: 17 times)
  * and with sums in another order.  A caller that sized its workspace some other way than by this query

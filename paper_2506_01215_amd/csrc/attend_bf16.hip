@@ -818,17 +818,18 @@ struct QStage {
 // 32x32x16 form of this kernel (32 keys x 32 rows per MFMA, new key fragment every MFMA) was
 // 1.2 % slower.
 //
-// At head_dim 64 a logit costs half the MFMAs and the same VALU work, which then is the bound (v_fma, v_exp and v_add 17
-// cycles, its MFMAs 8, most of which do not overlap), so what counts is that some wave always has VALU work to issue: a
-// wave of the four-wave form holds 32 keys there, not 64 (107 registers, four waves per SIMD instead of two; three per
-// SIMD with 64 keys spill and gain half as much, five spill), and six VALU instructions follow an MFMA, not three.
-// Score alone, back to back: 8192 rows over 16384 keys, 16/4 heads 334 -> 289 us; 16384 over 24576, 32/8 heads 1697 -> 1423;
-// 1000 over 4000, 32/8 44.6 -> 36.4; 128 of 3001 rows over 11193, 24/8 19.7 -> 15.0; VALU busy 0.60 -> 0.74 of the cycles.
-// At 128 the same form only lowers the clock (power).
+// KB = 2 (the narrow form): a wave holds 32 keys, in 107 registers at head_dim 64 and 158 at 128, so that four or three
+// waves share a SIMD instead of two.  At 64 a logit costs half the MFMAs and the same VALU work, which then is the bound
+// (v_fma, v_exp and v_add 17 cycles, its MFMAs 8, most of which do not overlap), so what counts is that some wave always has
+// VALU work to issue (three waves per SIMD with 64 keys spill and gain half as much, five with 32 spill); six VALU instructions follow an
+// MFMA there, not three.  At 128 it serves passes of up to some 250 us, whose starts it hides; longer ones are bound by the
+// power budget.  Score alone, back to back: 64 wide, 8192 rows over 16384 keys, 16/4 heads 334 -> 289 us (VALU busy 0.60 ->
+// 0.74 of the cycles); 16384 over 24576, 32/8 1697 -> 1423; 1000 over 4000, 32/8 44.6 -> 36.4; 128 of 3001 rows over 11193,
+// 24/8 19.7 -> 15.0; 128 wide, 1000 over 3000, 32/8 48.7 -> 38.6; 500 over 4596, 8/8 23.3 -> 16.7.  See score_plan.
 //
 // WINDOW: not every row observes.  Without it the first observing row is 0 at compile time.
 template <int D, int KB, int NW, bool WINDOW>
-__global__ __launch_bounds__(NW * 64, KB == 2 ? 4 : 2) void attn_score_bf16(AttnParams p)
+__global__ __launch_bounds__(NW * 64, KB == 2 ? (D == 64 ? 4 : 3) : 2) void attn_score_bf16(AttnParams p)
 {
     constexpr int NT = NW * 64;
     constexpr int KS = D / 32;                           // MFMA k-steps
@@ -1301,10 +1302,10 @@ static hipError_t launch_fwd(const AttnParams &p, bool split, hipStream_t st)
     return hipGetLastError();
 }
 
-template <int D, int NW>
+template <int D, int KB, int NW>
 static hipError_t launch_score_tiled(const AttnParams &p, hipStream_t st)
 {
-    constexpr int KB = D == 64 && NW == 4 ? 2 : 4, keys_wg = NW * 16 * KB;
+    constexpr int keys_wg = NW * 16 * KB;
     const int grid = p.Hkv * ((p.n + keys_wg - 1) / keys_wg) * p.slices;
     if (p.W == p.Ct) hipLaunchKernelGGL((attn_score_bf16<D, KB, NW, false>), dim3(grid), dim3(NW * 64), 0, st, p);
     else hipLaunchKernelGGL((attn_score_bf16<D, KB, NW, true>), dim3(grid), dim3(NW * 64), 0, st, p);
@@ -1324,15 +1325,18 @@ static hipError_t launch_score(AttnParams p, void *part, size_t part_bytes, hipS
         else hipLaunchKernelGGL((attn_score_few<D, KB, 4>), dim3(grid), dim3(256), 0, st, p);
         return hipGetLastError();
     }
-    int waves = score_plan(p, compute_units());
+    int form = score_plan(p, compute_units());
     if (p.slices > 1 && (!part || part_bytes < (size_t)p.slices * p.Hkv * p.n * sizeof(float))) {
         p.slice_tiles *= p.slices;                       // no room for partial sums: uncut
         p.slice_heads = p.G;
         p.slices = p.head_slices = 1;
-        waves = D == 64 ? 4 : 8;
+        form = D == 64 ? kScoreNarrow : kScoreEight;
     }
     p.part_score = (float *)part;
-    return waves == 8 ? launch_score_tiled<D, 8>(p, st) : launch_score_tiled<D, 4>(p, st);
+    if (form == kScoreEight) return launch_score_tiled<D, 4, 8>(p, st);
+    if constexpr (D == 128)
+        if (form == kScoreFour) return launch_score_tiled<D, 4, 4>(p, st);
+    return launch_score_tiled<D, 2, 4>(p, st);
 }
 
 // Both passes.  Where the first is split and the second takes few rows, merging and the score are one launch.

@@ -129,22 +129,31 @@ inline void fwd_plan(P &p, int cus)
 }
 
 // ------------------------------------------------------------------------------------------
-// How the score pass of a problem is cut into workgroups: waves per workgroup (returned), slices,
-// slice_tiles, head_slices and slice_heads.  Time is estimated in query tiles that a compute unit takes against 512 keys (2.1 us
-// at head_dim 128); at most two workgroups of four waves or one of eight are resident on it.
+// Forms of the tiled score pass (see attn_score_bf16): waves of a workgroup and keys of a wave.
+constexpr int kScoreEight = 8;                           // eight waves of 64 keys
+constexpr int kScoreFour = 4;                            // four of 64
+constexpr int kScoreNarrow = 2;                          // four of 32
+
+// How the score pass of a problem is cut into workgroups: form (returned), slices, slice_tiles, head_slices and
+// slice_heads.  Time is estimated in query tiles that a compute unit takes against 512 keys (2.1 us at head_dim 128,
+// 1.35 us at 64); two workgroups of four waves of 64 keys, three of 32 (four at head_dim 64) or one of eight are resident on it.
 //   - Eight waves, uncut: the fewest Q bytes per key, the best form where its workgroups fill the chip
 //     evenly.  Keys of the cache (and of the chunk before the window) cost the same each; those of
-//     the window itself are triangular and fill up what the others leave.
-//   - Four waves, cut: half the keys and 1/slices of the rows per workgroup, at the price of a start-up
-//     of about 1.5 tiles each and of a launch that adds the slices up (2 tiles).
-// Measured with 32/8 heads, head_dim 128: 8192 rows over 8192 keys 974 -> 828 us with 8 slices (256
-// uncut workgroups, half of them triangular); 512 rows over 8192 keys 77 -> 63 us with 4; 32768
-// over 32768 12.1 ms uncut, 12.3 ms in 4 or 8 slices; 700 over 30000 207 us uncut, 223 us in 4;
-// 128 rows over 8192 keys 23 us uncut, 28 us with four waves.
-//
-// At head_dim 64 a workgroup of four waves takes 128 keys and four of them are resident, so the unit is their query tile
-// against 512 keys, 1.35 us, of which eight waves take 1.2 and 2.7 us more to begin.  Short items leave less behind at the
-// end.  Score alone, us, eight waves / four uncut / 4 / 8 / 16 / 32 slices: 8192 rows over 16384 keys, 16/4 heads 752 / 500
+//     the window itself are triangular and fill up what the others leave.  Each round of them begins anew (8 us at 128).
+//   - Four waves, cut: half or a quarter of the keys and 1/slices of the rows per workgroup, at the price of a start-up
+//     of about 1.5 tiles each and of a launch that adds the slices up (2 tiles, 3 of the narrow form's).
+//   - Which four-wave form: a workgroup of the narrow one starts and ends sooner, and with three or four on a compute unit
+//     one's start and loads lie under the others' work; a long pass is bound by the power budget, and there twice the reads
+//     of Q per key cost 5 %.  At 64 a pass is bound by its VALU work and the narrow form is the faster one at every size.
+// Measured at head_dim 128, us, eight waves / four of 64 keys / of 32, each with its best number of slices: 300 rows over
+// 1300 keys, 32/8 heads 46 / 18 / 15.2; 500 over 4596, 8/8 25.5 / 19.9 / 16.1; 4000 over 4000, 16/4 467 / 78 / 62; 1000 over
+// 3000, 32/8 132 / 46 / 37.8; 3000 over 3512, 8/8 94 / 36.6 / 28.7; 150 over 20150, 24/8 49 / 44.9 / 35.7; windows of 128 over
+// 11193, 24/8 22.6 / 23.4 / 18.2, over 20000, 8/8 24.8 / 20.2 / 16.7, over 32000, 16/4 23.5 / 28.8 / 28.8; 4264 over 7945, 16/4
+// 495 / 147 / 127; 5814 over 12828, 16/4 670 / 280 / 266 (114 tiles a compute unit); 2500 over 22500, 14/2 528 / 223 / 220 (92);
+// from 146 on the other way: 6629 over 14487, 16/4 765 / 326 / 334; 6782 over 20108, 16/4 777 / 480 / 493; 1500 over
+// 34268, 32/8 554 / 437 / 453; 8192 over 16384, 32/8 940 / 816 / 860; 16384 over 49152, 8/8 1416 / 1276 / 1373; 32768
+// over 65536, 32/8 12.1 ms uncut, 12.3 ms in 4 or 8 slices.
+// At 64, us, eight waves / narrow uncut / in 4 / 8 / 16 / 32 slices: 8192 rows over 16384 keys, 16/4 heads 752 / 500
 // / 340 / 300 / 289 / 301; 16384 over 49152, 8/8 1123 / 893 / 893 / 909 / 944 / 1033; 12000 over 12000, 14/2 1904 / 994 /
 // 362 / 255 / 224 / 205; 1000 over 4000, 32/8 111 / 55 / 36 / 36 / 38 / 38; a window of 128 rows over 11193, 24/8 19.6 /
 // 15.0, over 32000, 16/4 19.8 / 20.8, over 20000, 8/8 19.0 / 10.7.
@@ -165,36 +174,43 @@ inline int score_plan(P &p, int cus)
         if (best < (double)whole * iters + pair) best = (double)whole * iters + pair;
     }
     if (best < total) best = total;
-    const bool narrow = p.D == 64;
-    if (narrow) best = 1.2 * best + 2.0;
-    const double resident = narrow ? 4.0 : 2.0, tail = narrow ? 0.33 : 0.5, alone = narrow ? 0.5 : 1.0;
-    const double begin = narrow ? 1.6 : 1.5, add_up = narrow ? 3.0 : 2.0;
-    int waves = 8;
+    best = p.D == 64 ? 1.2 * best + 2.0 : best + 4.0 * (double)((all + cus - 1) / cus);   // in the unit above, with the starts
+    int form = kScoreEight;
     p.slices = p.head_slices = 1;
     p.slice_tiles = tiles;
     p.slice_heads = p.G;
-    auto consider = [&](int per, int heads) {            // slices of `per` tiles of `heads` heads
+    // slices of `per` tiles of `heads` heads, by workgroups of `keys` keys, `resident` of them on a compute unit; a full one
+    // takes `rate` a tile, the first tile `begin` more, the last ones leave `tail` of an item idle
+    auto price = [&](int f, int keys, double resident, double rate, double tail, double alone, double begin, double fixed,
+                     int per, int heads) {
         const int hs = (p.G + heads - 1) / heads, slices = (tiles + per - 1) / per * hs;
-        const double item = (double)heads * per, items = resident * total * cus / item;
-        double t = total + tail * item;
+        const double item = (double)heads * per, items = 512.0 / keys * total * cus / item;
+        double t = rate * total + tail * item;
         if (t < alone * item) t = alone * item;
-        t += begin * items / (resident * cus) + (slices > 1 ? add_up : 0.0);
+        t += begin * items / (resident * cus) + fixed + (slices == 1 ? 0.0 : f == kScoreFour ? 2.0 : 3.0);
         if (t >= best) return;
         best = t;
-        waves = 4;
+        form = f;
         p.slices = slices;
         p.slice_tiles = per;
         p.head_slices = hs;
         p.slice_heads = heads;
     };
-    for (int want = 1; want <= (narrow ? 32 : 16); want *= 2) consider((tiles + want - 1) / want, p.G);
+    const bool four = p.D != 64 && total >= 120.0;
+    auto consider = [&](int per, int heads) {
+        if (four) price(kScoreFour, 256, 2.0, 1.0, 0.5, 1.0, 1.5, 3.0, per, heads);
+        else if (p.D == 64) price(kScoreNarrow, 128, 4.0, 1.0, 0.33, 0.5, 1.6, 0.0, per, heads);
+        else price(kScoreNarrow, 128, 3.0, 1.06, 0.35, 0.8, 1.6, 0.0, per, heads);
+    };
+    for (int want = 1; want <= (four ? 16 : 32); want *= 2) consider((tiles + want - 1) / want, p.G);
     // Where that leaves compute units without a workgroup the heads are cut as well: 60 rows over 8000 keys
     // with 14/2 heads of 64 (32 workgroups of 7 tiles) 38 -> 31 us for the call, 30 over 1000 with 14/2 of
     // 128 38 -> 28 us.  (On a chip that is busy it gives nothing: 2000 rows over 1000 keys, 32/8 heads, 18.9
     // -> 19.8 us.)
-    if ((waves == 8 ? all : (long)p.Hkv * ((p.n + 255) / 256) * p.slices) < cus)
+    const int keys = form == kScoreEight ? 512 : form == kScoreFour ? 256 : 128;
+    if ((long)p.Hkv * ((p.n + keys - 1) / keys) * p.slices < cus)
         for (int heads = (p.G + 1) / 2; heads >= 1; heads = heads > 1 ? (heads + 1) / 2 : 0) consider(1, heads);
-    return waves;
+    return form;
 }
 
 constexpr int kFewBlocks = 8;                            // row blocks over all heads of a group, at most (one wave)

@@ -76,7 +76,7 @@ def test_the_score_shapes_of_the_gpu_tests_take_the_form_they_are_for(plan):
 
 
 @pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W", test_gpu_attend_score_narrow.NARROW)
-def test_score_shapes_of_the_narrow_form_are_tiled(plan, Hq, Hkv, d, M, Ct, W):
+def test_score_shapes_of_the_narrow_tests_are_tiled(plan, Hq, Hkv, d, M, Ct, W):
     assert plan.score_form(Hkv, Hq // Hkv, d, M, Ct, W, 256) % 16 == 0
 
 

@@ -1,4 +1,4 @@
-"""Score pass at head_dim 64, tiled: four waves of 32 keys each.  Key counts around a workgroup's 128 and a wave's 32, row
+"""Score pass, tiled, the narrow form: four waves of 32 keys each.  Key counts around a workgroup's 128 and a wave's 32, row
 counts around a query tile's 64, windows, many slices, and the uncut form of a workspace without room for slices; against
 the fp64 oracle, and identical cache keys get identical scores."""
 import math
@@ -23,6 +23,7 @@ NARROW = [
     (8, 1, 64, 1000, 300, 201),       # a window that is no multiple of a tile
     (4, 4, 64, 9000, 2048, 2048),     # full tiles only
 ]
+NARROW += [(Hq, Hkv, 128, M, Ct, W) for Hq, Hkv, _, M, Ct, W in NARROW]
 
 
 @pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W", NARROW)
