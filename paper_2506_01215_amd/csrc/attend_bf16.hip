@@ -19,6 +19,7 @@
 #include "common.h"
 #include "attend_plan.h"
 
+#include <algorithm>
 #include <atomic>
 
 namespace reform {
@@ -141,6 +142,10 @@ __device__ __forceinline__ float softmax_row(const f32x4 (&s)[4], float c, float
 // heads 108 us, now 41; one over 20000 with 14/2 heads of 64 24 us, now 13.6; 300 rows over 1500 keys
 // with 24/8 heads 66 us, now 56 (with the score).
 //
+// NW = 4 (the narrow form; where it is taken and what it gives: fwd_choose): 128 rows by four waves, two V slots and no wave
+// lagging, as the other workgroups of the compute unit (two, at head_dim 64 three: 168 registers there) are out of step by
+// themselves.  At 64 three waves per SIMD take 15 % fewer cycles on a large problem, at a clock that falls by 10 % (power).
+//
 // MFMA shape: v_mfma_f32_16x16x32_bf16 (A[m][k]: lane l holds m = l%16, k = 8*(l/16)..+7; B[k][n]:
 // n = l%16, same k; C[m][n]: n = l%16, m = 4*(l/16) + e).  Measured on gfx950 with random bf16
 // operands the matrix pipe is limited by the power budget, and this shape sustains 2.03 PFLOP/s
@@ -163,20 +168,21 @@ __device__ __forceinline__ float softmax_row(const f32x4 (&s)[4], float c, float
 //   - tile addresses are a uniform base plus per-thread constants computed once.
 constexpr float kBigSum = 65536.0f;
 
-template <int D>
+template <int D, int NW>
 constexpr size_t fwd_lds_bytes()
 {
-    return sizeof(u16) * (size_t)(5 * 64 * (D + 16));      // two K slots, three V slots
+    return sizeof(u16) * (size_t)((NW == kFwdWaves ? 5 : 4) * 64 * (D + 16));      // two K slots, three V slots (two if no wave lags)
 }
 
 // One workgroup's pass of row block rb over the key tiles [t0, t1).  With
 // SPLIT the result is either final (the range covers the whole row block) or goes, unnormalised,
 // to partial slot `slot`; without it the range is the whole row block.
-template <int D, bool SPLIT>
+template <int D, int NW, bool SPLIT>
 __device__ __forceinline__ void fwd_segment(const AttnParams &p, u16 *smem, int kvh, int rb, int t0, int t1, long slot)
 {
-    constexpr int NW = kFwdWaves;
-    constexpr int NT = NW * 64;
+    constexpr int NT = NW * 64, ROWS = NW * 32;
+    constexpr bool LAG = NW == kFwdWaves;                // see below
+    constexpr int VSLOTS = LAG ? 3 : 2;
     constexpr int KS = D / 32;           // MFMA k-steps of Q.K^T
     constexpr int DB = D / 16;           // 16-wide output blocks of P.V
     using Stage = TileStage<D, NT>;
@@ -200,7 +206,7 @@ __device__ __forceinline__ void fwd_segment(const AttnParams &p, u16 *smem, int 
     // + ln).  p.by_head (G divides the waves, so a full row block is kFwdRows / G chunk rows of every head): consecutive
     // chunk rows of one head; otherwise consecutive rows.
     const int slab = p.by_head ? wave / p.G : wave, rstep = p.by_head ? p.G : 1;
-    const int row0 = rb * kFwdRows + slab * 32 * rstep + (p.by_head ? wave % p.G : 0);
+    const int row0 = rb * ROWS + slab * 32 * rstep + (p.by_head ? wave % p.G : 0);
     // Chunk row and head of this lane's row.  Formed where needed, from a G the compiler cannot relate to
     // the other uses: kept, the four values cost registers in the main loop.
     auto locate = [&](int nb, int &chunk_row, size_t &head) {
@@ -230,7 +236,7 @@ __device__ __forceinline__ void fwd_segment(const AttnParams &p, u16 *smem, int 
         }
     }
 
-    const int ntiles = SPLIT ? t1 - t0 : fwd_row_block_tiles(p, rb);
+    const int ntiles = SPLIT ? t1 - t0 : fwd_row_block_tiles<ROWS>(p, rb);
     const int wave_first_row = row0 / p.G;
     const int wave_last_key = (row0 < rows) ? M + min(row0 + 31 * rstep, rows - 1) / p.G : -1;
 
@@ -258,7 +264,7 @@ __device__ __forceinline__ void fwd_segment(const AttnParams &p, u16 *smem, int 
     // O^T += V^T P^T one tile late: iteration t does P.V of tile t-1 first, then Q.K^T and the
     // softmax of tile t, keeping the probabilities in registers across the barrier.  V therefore
     // lives in three LDS slots (tile u in slot u%3), K in two.
-    const bool lag = wave >= NW / 2;
+    const bool lag = LAG && wave >= NW / 2;
     // last tile of the range this wave needs
     const int tl = SPLIT ? (wave_last_key >= 0 ? min(wave_last_key / BN, ntiles - 1) : -1)
                          : (wave_last_key >= 0 ? wave_last_key / BN : -1);
@@ -437,14 +443,14 @@ __device__ __forceinline__ void fwd_segment(const AttnParams &p, u16 *smem, int 
         }
         // stage tile t+1 (already in registers), prefetch tile t+2
         if (t + 1 < ntiles) {
-            const int vnext = vslot == 2 ? 0 : vslot + 1;
+            const int vnext = vslot == VSLOTS - 1 ? 0 : vslot + 1;
             st.store(ldsK + ((t + 1) & 1) * KTILE, ldsV + vnext * VTILE);
             if (t + 2 < ntiles) {
                 const size_t off = (size_t)(j0 + 2 * BN) * D;
                 st.load(Kg + off, Vg + off, n - (j0 + 2 * BN));
             }
         }
-        vslot = vslot == 2 ? 0 : vslot + 1;
+        vslot = vslot == VSLOTS - 1 ? 0 : vslot + 1;
         __syncthreads();
     }
     if (lag && tl == ntiles - 1) {
@@ -471,7 +477,7 @@ __device__ __forceinline__ void fwd_segment(const AttnParams &p, u16 *smem, int 
             float l_tot = l_run[nb] + __shfl_xor(l_run[nb], 16);
             l_tot += __shfl_xor(l_tot, 32);
             if (row >= rows) continue;
-            const int pr = row - rb * kFwdRows;
+            const int pr = row - rb * ROWS;
 #pragma unroll
             for (int db = 0; db < DB; ++db)
                 *(f32x4 *)(po + (size_t)pr * D + db * 16 + 4 * lg) = o[nb][db];
@@ -510,8 +516,8 @@ __device__ __forceinline__ void fwd_segment(const AttnParams &p, u16 *smem, int 
 // blocks these cut through.  A row block that one workgroup covers alone is finished there, the pieces of the
 // others are merged by attn_fwd_merge.  blockIdx % Hkv is the KV head in both forms, so with
 // eight of them an XCD's L2 sees one head's K/V.
-template <int D, bool SPLIT>
-__global__ __launch_bounds__(kFwdWaves * 64, 2) void attn_fwd_bf16(AttnParams p)
+template <int D, int NW, bool SPLIT>
+__global__ __launch_bounds__(NW * 64, NW == kFwdWaves ? 2 : kFwdNarrowResident<D>) void attn_fwd_bf16(AttnParams p)
 {
     extern __shared__ __attribute__((aligned(16))) u16 smem[];
     const int bid = blockIdx.x;
@@ -519,19 +525,19 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2) void attn_fwd_bf16(AttnParams p)
     if constexpr (SPLIT) {
         const int share = bid / p.Hkv;
         const int begin = fwd_share_begin(p, share), end = fwd_share_begin(p, share + 1);
-        FwdWalk<AttnParams> w(p);
+        FwdWalk<AttnParams, NW * 32> w(p);
         while (w.pos + w.nt <= begin) w.next(p);
         bool first = true;
         while (w.pos < end) {
             const int t0 = max(begin - w.pos, 0), t1 = min(end - w.pos, w.nt);      // t0 < nt, t1 > 0
             if (!first) __syncthreads();                 // lagging waves still read the last V tile
             first = false;
-            fwd_segment<D, true>(p, smem, kvh, w.rb, t0, t1, fwd_slot(p, share, kvh, t0, t1, w.nt));
+            fwd_segment<D, NW, true>(p, smem, kvh, w.rb, t0, t1, fwd_slot(p, share, kvh, t0, t1, w.nt));
             w.next(p);
         }
     } else {
         // block -> (kv head, row block); heavy (late) row blocks first
-        fwd_segment<D, false>(p, smem, kvh, p.n_row_blocks - 1 - bid / p.Hkv, 0, 0, -1);
+        fwd_segment<D, NW, false>(p, smem, kvh, p.n_row_blocks - 1 - bid / p.Hkv, 0, 0, -1);
     }
 }
 
@@ -669,10 +675,11 @@ __global__ __launch_bounds__(kFwdWaves * 64) void attn_fwd_few(AttnParams p)
 }
 
 // List position of row block rb's first tile, by the 64 lanes of a wave.
+template <int ROWS>
 __device__ __forceinline__ int fwd_row_block_pos(const AttnParams &p, int rb)
 {
     int pos = 0;
-    for (int b = threadIdx.x & 63; b < rb; b += 64) pos += p.start + fwd_row_block_tiles(p, b);
+    for (int b = threadIdx.x & 63; b < rb; b += 64) pos += p.start + fwd_row_block_tiles<ROWS>(p, b);
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) pos += __shfl_xor(pos, o);
     return pos + p.start;
@@ -684,22 +691,22 @@ __device__ __forceinline__ int fwd_row_block_pos(const AttnParams &p, int rb)
 // shares) all groups of a workgroup take one row together, and their sums meet in LDS: 33 pieces
 // of one row 8 us with one group, 3 us with eight.  grid (rows of a row block / rows per
 // workgroup, row block, KV head).
-template <int D, bool MANY>
+template <int D, int ROWS, bool MANY>
 __device__ __forceinline__ void fwd_merge(const AttnParams &p, int bx, int rb, int kvh)
 {
     constexpr int L = D / 4, GROUPS = 256 / L;
     __shared__ f32x4 so[MANY ? GROUPS : 1][L];
     __shared__ float2 sml[GROUPS];
-    const int pos = fwd_row_block_pos(p, rb);
-    const int nt = fwd_row_block_tiles(p, rb);
+    const int pos = fwd_row_block_pos<ROWS>(p, rb);
+    const int nt = fwd_row_block_tiles<ROWS>(p, rb);
     const FwdPieces<AttnParams> pieces(p, pos, nt);
     const int j0 = pieces.j0, j1 = pieces.j1;
     if (j0 == j1) return;                                // finished by one workgroup
     const int grp = threadIdx.x / L, c4 = (threadIdx.x % L) * 4;
     const int pr = MANY ? bx : bx * GROUPS + grp;
     if (pr >= p.part_rows) return;
-    if (rb * kFwdRows + pr >= p.G * p.Ct) return;
-    const int row = (rb * kFwdRows + pr) / p.G, head = kvh * p.G + (rb * kFwdRows + pr) % p.G;
+    if (rb * ROWS + pr >= p.G * p.Ct) return;
+    const int row = (rb * ROWS + pr) / p.G, head = kvh * p.G + (rb * ROWS + pr) % p.G;
     auto piece = [&](int j) -> size_t { return (size_t)pieces.slot(p, j, kvh) * p.part_rows + pr; };
     const int first = MANY ? j0 + grp : j0, step = MANY ? GROUPS : 1;
     float m = -INFINITY, l = 0.f;
@@ -741,10 +748,10 @@ __device__ __forceinline__ void fwd_merge(const AttnParams &p, int bx, int rb, i
     if (c4 == 0) p.lse[(size_t)head * p.Ct + row] = (m + __builtin_amdgcn_logf(l)) * kLn2;
 }
 
-template <int D, bool MANY>
+template <int D, int ROWS, bool MANY>
 __global__ __launch_bounds__(256) void attn_fwd_merge(AttnParams p)
 {
-    fwd_merge<D, MANY>(p, blockIdx.x, blockIdx.y, blockIdx.z);
+    fwd_merge<D, ROWS, MANY>(p, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1058,9 +1065,10 @@ __global__ __launch_bounds__(256) void attn_score_sum(AttnParams p, int keys)
 //
 // PIECES: the attention of the same call left pieces that are not merged yet; the workgroup forms the rows'
 // normalisers from the pieces' maxima and sums itself, in LDS (see attn_merge_score).
-template <int D, int KB, int RW, bool PIECES>
+template <int D, int KB, int RW, int ROWS>
 __device__ __forceinline__ void score_few_keys(const AttnParams &p, int bid)
 {
+    constexpr bool PIECES = ROWS > 0;
     static_assert(RW == 1 || (RW == 4 && !PIECES), "one wave or all waves of the workgroup to a set of keys");
     __shared__ float slse[PIECES ? kFewBlocks * 16 : 1];
     __shared__ float part[RW > 1 ? 4 : 1][16 * KB];
@@ -1133,19 +1141,19 @@ __device__ __forceinline__ void score_few_keys(const AttnParams &p, int bid)
     load(x, rw);
     load(y, rw + RW);
     if constexpr (PIECES) {                              // while the keys and the first rows are on their way
-        const int rb0 = (p.Ct - p.W) * p.G / kFwdRows;
-        const int pos0 = fwd_row_block_pos(p, rb0), nt0 = fwd_row_block_tiles(p, rb0);
+        const int rb0 = (p.Ct - p.W) * p.G / ROWS;
+        const int pos0 = fwd_row_block_pos<ROWS>(p, rb0), nt0 = fwd_row_block_tiles<ROWS>(p, rb0);
         // the rows lie in row block rb0 and at most the next one
         const int rb1 = min(rb0 + 1, p.n_row_blocks - 1);
         const int pos1 = rb1 > rb0 ? pos0 + nt0 + p.start : pos0;
-        const FwdPieces<AttnParams> pc0(p, pos0, nt0), pc1(p, pos1, fwd_row_block_tiles(p, rb1));
+        const FwdPieces<AttnParams> pc0(p, pos0, nt0), pc1(p, pos1, fwd_row_block_tiles<ROWS>(p, rb1));
         // T threads to a row, each over every T-th piece
         const int entries = p.G * p.W, T = merge_score_lanes(entries);
         const int e = threadIdx.x / T, sub = threadIdx.x % T;
         if (e < entries) {                               // the same for all T lanes of a row
             const int row = p.Ct - p.W + e % p.W, gi = e / p.W, r = row * p.G + gi;
-            const bool second = r / kFwdRows > rb0;
-            const int j0 = second ? pc1.j0 : pc0.j0, j1 = second ? pc1.j1 : pc0.j1, pr = r % kFwdRows;
+            const bool second = r / ROWS > rb0;
+            const int j0 = second ? pc1.j0 : pc0.j0, j1 = second ? pc1.j1 : pc0.j1, pr = r % ROWS;
             float m = -INFINITY, l = 0.f;
             if (j0 < j1)
                 for (int j = j0 + sub; j <= j1; j += 4 * T) {        // four pieces in flight
@@ -1213,7 +1221,7 @@ __device__ __forceinline__ void score_few_keys(const AttnParams &p, int bid)
 template <int D, int KB, int RW>
 __global__ __launch_bounds__(256) void attn_score_few(AttnParams p)
 {
-    score_few_keys<D, KB, RW, false>(p, blockIdx.x);
+    score_few_keys<D, KB, RW, 0>(p, blockIdx.x);
 }
 
 // The merge of a split forward pass and the score of few rows in one launch: a ragged last chunk is a chain of
@@ -1223,12 +1231,12 @@ __global__ __launch_bounds__(256) void attn_score_few(AttnParams p)
 // us, 200 rows (128 observe) over 6200, 8 heads 37.9 -> 34.0 us.  With the normalisers formed before the keys are asked
 // for, 30 over 30030, 8 heads took 55.5 instead of 50.8 us; with those of the rows that fill up a head's block of 16 formed
 // as well, one token over 20000, 14/2 heads of 64 20.5 instead of 13.3 us.  Where it is taken: merge_with_score.
-template <int D, int KB>
+template <int D, int KB, int ROWS>
 __global__ __launch_bounds__(256) void attn_merge_score(AttnParams p, int n_score)
 {
     const int bid = blockIdx.x - n_score;
-    if (bid < 0) score_few_keys<D, KB, 1, true>(p, blockIdx.x);
-    else fwd_merge<D, true>(p, bid % p.part_rows, bid / p.part_rows % p.n_row_blocks, bid / p.part_rows / p.n_row_blocks);
+    if (bid < 0) score_few_keys<D, KB, 1, ROWS>(p, blockIdx.x);
+    else fwd_merge<D, ROWS, true>(p, bid % p.part_rows, bid / p.part_rows % p.n_row_blocks, bid / p.part_rows / p.n_row_blocks);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1241,11 +1249,11 @@ static size_t fwd_split_bytes(const AttnParams &p)
     return (size_t)p.shares * p.Hkv * 2 * p.part_rows * (p.D * sizeof(float) + sizeof(float2));
 }
 
-template <int D, bool SPLIT>
+template <int D, int NW, bool SPLIT>
 static hipError_t launch_fwd_form(const AttnParams &p, int grid, hipStream_t st)
 {
-    const size_t smem = fwd_lds_bytes<D>();
-    auto kern = attn_fwd_bf16<D, SPLIT>;
+    const size_t smem = fwd_lds_bytes<D, NW>();
+    auto kern = attn_fwd_bf16<D, NW, SPLIT>;
     // the kernel needs more than the default 64 KB of LDS: raised once per device, not per launch
     static std::atomic<bool> lds_raised[64];
     int dev = 0;
@@ -1256,15 +1264,15 @@ static hipError_t launch_fwd_form(const AttnParams &p, int grid, hipStream_t st)
         if (e != hipSuccess) return e;
         if (dev >= 0 && dev < 64) lds_raised[dev].store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kFwdWaves * 64), smem, st, p);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(NW * 64), smem, st, p);
     return hipGetLastError();
 }
 
 // `part` (part_bytes): scratch for partial results; the key range is only split if they fit (true).
 template <int D>
-static bool fwd_place(AttnParams &p, void *part, size_t part_bytes)
+static bool fwd_place(AttnParams &p, bool scored, void *part, size_t part_bytes)
 {
-    fwd_plan(p, compute_units());
+    fwd_choose(p, compute_units(), scored);
     if (!p.shares || !part || part_bytes < fwd_split_bytes(p)) return false;
     p.part_o = (float *)part;
     p.part_ml = (float2 *)(p.part_o + (size_t)p.shares * p.Hkv * 2 * p.part_rows * D);
@@ -1276,7 +1284,8 @@ template <int D>
 static hipError_t launch_fwd_pieces(const AttnParams &p, hipStream_t st)
 {
     const int grid = p.shares * p.Hkv;
-    if (p.G * p.Ct > 16) return launch_fwd_form<D, true>(p, grid, st);
+    if (p.narrow) return launch_fwd_form<D, 4, true>(p, grid, st);
+    if (p.G * p.Ct > 16) return launch_fwd_form<D, kFwdWaves, true>(p, grid, st);
     hipLaunchKernelGGL(attn_fwd_few<D>, dim3(grid), dim3(kFwdWaves * 64), 0, st, p);
     return hipGetLastError();
 }
@@ -1284,7 +1293,10 @@ static hipError_t launch_fwd_pieces(const AttnParams &p, hipStream_t st)
 template <int D>
 static hipError_t launch_fwd(const AttnParams &p, bool split, hipStream_t st)
 {
-    if (!split) return launch_fwd_form<D, false>(p, p.Hkv * p.n_row_blocks, st);
+    if (!split) {
+        const int grid = p.Hkv * p.n_row_blocks;
+        return p.narrow ? launch_fwd_form<D, 4, false>(p, grid, st) : launch_fwd_form<D, kFwdWaves, false>(p, grid, st);
+    }
     const hipError_t e = launch_fwd_pieces<D>(p, st);
     if (e != hipSuccess) return e;
     // pieces of the longest row block: two or three where row blocks are many, a head's shares for a token
@@ -1294,10 +1306,12 @@ static hipError_t launch_fwd(const AttnParams &p, bool split, hipStream_t st)
     const long merged_rows = (long)p.Hkv * p.n_row_blocks * p.part_rows;
     if (pieces > 12 || (pieces > 6 && merged_rows <= 2048)) {
         const dim3 mgrid(p.part_rows, p.n_row_blocks, p.Hkv);
-        hipLaunchKernelGGL((attn_fwd_merge<D, true>), mgrid, dim3(256), 0, st, p);
+        if (p.narrow) hipLaunchKernelGGL((attn_fwd_merge<D, kFwdNarrowRows, true>), mgrid, dim3(256), 0, st, p);
+        else hipLaunchKernelGGL((attn_fwd_merge<D, kFwdRows, true>), mgrid, dim3(256), 0, st, p);
     } else {
         const dim3 mgrid((p.part_rows + groups - 1) / groups, p.n_row_blocks, p.Hkv);
-        hipLaunchKernelGGL((attn_fwd_merge<D, false>), mgrid, dim3(256), 0, st, p);
+        if (p.narrow) hipLaunchKernelGGL((attn_fwd_merge<D, kFwdNarrowRows, false>), mgrid, dim3(256), 0, st, p);
+        else hipLaunchKernelGGL((attn_fwd_merge<D, kFwdRows, false>), mgrid, dim3(256), 0, st, p);
     }
     return hipGetLastError();
 }
@@ -1344,7 +1358,7 @@ template <int D>
 static hipError_t launch_both(const AttnParams &p, void *part, size_t part_bytes, hipStream_t st)
 {
     AttnParams f = p;
-    const bool split = fwd_place<D>(f, part, part_bytes);
+    const bool split = fwd_place<D>(f, true, part, part_bytes);
     if (!split || !merge_with_score(f)) {
         const hipError_t e = launch_fwd<D>(f, split, st);
         return e == hipSuccess ? launch_score<D>(p, part, part_bytes, st) : e;
@@ -1353,7 +1367,8 @@ static hipError_t launch_both(const AttnParams &p, void *part, size_t part_bytes
     if (e != hipSuccess) return e;
     const int n_score = f.Hkv * ((f.n + 64 * kFewKB - 1) / (64 * kFewKB));
     const int n_merge = f.part_rows * f.n_row_blocks * f.Hkv;
-    hipLaunchKernelGGL((attn_merge_score<D, kFewKB>), dim3(n_score + n_merge), dim3(256), 0, st, f, n_score);
+    if (f.narrow) hipLaunchKernelGGL((attn_merge_score<D, kFewKB, kFwdNarrowRows>), dim3(n_score + n_merge), dim3(256), 0, st, f, n_score);
+    else hipLaunchKernelGGL((attn_merge_score<D, kFewKB, kFwdRows>), dim3(n_score + n_merge), dim3(256), 0, st, f, n_score);
     return hipGetLastError();
 }
 
@@ -1366,15 +1381,18 @@ size_t attend_bf16_scratch_bytes(const AttnParams &sizes)
         score_plan(p, compute_units());
         if (p.slices > 1) score = (size_t)p.slices * p.Hkv * p.n * sizeof(float);
     }
-    fwd_plan(p, compute_units());
-    const size_t fwd = fwd_split_bytes(p);
-    return fwd > score ? fwd : score;
+    size_t bytes = score;
+    for (const bool scored : {false, true}) {
+        fwd_choose(p, compute_units(), scored);
+        bytes = std::max(bytes, fwd_split_bytes(p));
+    }
+    return bytes;
 }
 
 template <int D>
 static hipError_t launch_attention(AttnParams p, void *part, size_t part_bytes, hipStream_t st)
 {
-    const bool split = fwd_place<D>(p, part, part_bytes);
+    const bool split = fwd_place<D>(p, false, part, part_bytes);
     return launch_fwd<D>(p, split, st);
 }
 

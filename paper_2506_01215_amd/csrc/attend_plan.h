@@ -16,13 +16,15 @@ namespace reform {
 
 constexpr int kFwdWaves = 8;
 constexpr int kFwdRows = kFwdWaves * 32;                       // query rows of a row block
+constexpr int kFwdNarrowRows = 128;                            // those of the narrow form, four waves
+template <int D> constexpr int kFwdNarrowResident = D == 64 ? 3 : 2;   // its workgroups on a compute unit
 
 // Key tiles of row block rb (64-key tiles up to the last key its last row sees): (M + (last row) / G) / 64 + 1.
-template <class P>
+template <int ROWS = kFwdRows, class P>
 RF_PLAN int fwd_row_block_tiles(const P &p, int rb)
 {
     const int rows = p.G * p.Ct;
-    const int last = (rb + 1 < p.n_row_blocks ? (rb + 1) * kFwdRows : rows) - 1;
+    const int last = (rb + 1 < p.n_row_blocks ? (rb + 1) * ROWS : rows) - 1;
     return (p.M + last / p.G) / 64 + 1;
 }
 
@@ -31,10 +33,10 @@ template <class P>
 RF_PLAN int fwd_share_begin(const P &p, int j) { return (int)((unsigned)j * (unsigned)p.tiles / (unsigned)p.shares); }
 
 // Walks a KV head's list row block by row block without dividing: for a full row block the number of tiles is
-// (a + rows / 64 * rb) / G + 1 with a = (M G + rows - 1) / 64, rows = kFwdRows being a multiple of 64; q
+// (a + rows / 64 * rb) / G + 1 with a = (M G + rows - 1) / 64, rows = ROWS being a multiple of 64; q
 // and r are quotient and remainder of a + rows / 64 * rb by G.  M G itself may not fit 32 bits (32 heads
 // over 2^26 keys): with M = 64 m + k, a = m G + (k G + rows - 1) / 64.
-template <class P>
+template <class P, int ROWS = kFwdRows>
 struct FwdWalk {
     int rb, pos, nt;                                     // row block, list position of its first tile, its tiles
     int q, r;
@@ -46,7 +48,7 @@ struct FwdWalk {
     RF_PLAN explicit FwdWalk(const P &p) : rb(0), pos(p.start)
     {
         // 63 G fits: a split problem has at most four row blocks per compute unit, so G < 2^20
-        const int a = (p.M % 64 * p.G + kFwdRows - 1) / 64;
+        const int a = (p.M % 64 * p.G + ROWS - 1) / 64;
         q = p.M / 64 + a / p.G;
         r = a % p.G;
         nt = count(p);
@@ -55,7 +57,7 @@ struct FwdWalk {
     {
         pos += nt + p.start;
         ++rb;
-        for (r += kFwdRows / 64; r >= p.G; r -= p.G) ++q;
+        for (r += ROWS / 64; r >= p.G; r -= p.G) ++q;
         nt = count(p);
     }
 };
@@ -88,44 +90,122 @@ struct FwdPieces {
     }
 };
 
-// How the forward pass of a problem is cut into workgroups: n_row_blocks and, if the key range is to be
-// split, shares, tiles and part_rows.
 template <class P>
-inline void fwd_plan(P &p, int cus)
+inline bool merge_with_score(const P &p, double *gain = nullptr);
+
+// What the parts of a forward pass cost, in us on 256 compute units; fitted to 2900 timings of 143 problems of 8 to 5000
+// rows over up to 37000 keys, with 32/8, 24/8, 16/4, 14/2 and 8/8 heads, each whole and with 7 to 12 numbers of shares: the
+// fits miss by 3 to 6 % in the mean.  A key tile's time depends on how many workgroups share its compute unit.
+struct FwdCost {
+    int resident;                                        // workgroups on a compute unit
+    double whole, whole_begin, whole_tile[3];            // a launch; the start of a row block, in tiles; a tile with 1, 2, 3 on the unit
+    double split, split_begin, split_tile[3], write, part;   // the same where keys are shared out; a MB of partial results; a whole slot of them
+};
+template <int ROWS>
+inline FwdCost fwd_cost(int D)
+{
+    if (ROWS == kFwdRows)
+        return D == 64 ? FwdCost{1, 2.0, 5.2, {1.02, 1.02, 1.02}, 8.6, 3.3, {1.07, 1.07, 1.07}, 0.52, 1.34}
+                       : FwdCost{1, 3.0, 3.4, {1.46, 1.46, 1.46}, 7.5, 3.4, {1.46, 1.46, 1.46}, 0.36, 4.0};
+    return D == 64 ? FwdCost{3, 5.3, 0.0, {0.78, 0.98, 1.47}, 9.6, 2.9, {0.88, 1.20, 1.75}, 0.49, 0.0}
+                   : FwdCost{2, 3.1, 3.2, {1.19, 1.61, 1.66}, 8.8, 1.7, {1.29, 1.77, 1.77}, 0.46, 0.64};
+}
+
+// How the forward pass of a problem is cut into workgroups of ROWS query rows: n_row_blocks and, if the key range is to be
+// split, shares, tiles and part_rows.  Returns the time estimated for it (0: whole row blocks, of which there are enough).
+// scored: the call forms the score as well, so that the launch which merges shares may be the score's.
+template <int ROWS = kFwdRows, class P>
+inline double fwd_plan(P &p, int cus, bool scored = true)
 {
     const int rows = p.G * p.Ct;
-    p.n_row_blocks = (int)(((long)rows + kFwdRows - 1) / kFwdRows);
+    p.n_row_blocks = (int)(((long)rows + ROWS - 1) / ROWS);
     p.shares = 0;
-    p.part_rows = rows < kFwdRows ? rows : kFwdRows;
+    p.part_rows = rows < ROWS ? rows : ROWS;
     // Waves of one head are 0.6 % to 1.3 % faster where they are full (8192 rows over 8192 keys, 32768 over
     // 32768, 32/8 heads); with few chunk rows they would be nearly empty (one token: 20.6 instead of 18.3 us).
-    p.by_head = kFwdWaves % p.G == 0 && p.Ct >= 32;
+    p.by_head = ROWS / 32 % p.G == 0 && p.Ct >= 32;
     const long whole = (long)p.Hkv * p.n_row_blocks;
-    if (whole > 4l * cus || p.Hkv > cus) return;         // at least four well-filled rounds
-    const long longest = (p.M + p.Ct - 1) / 64 + 1;
-    p.start = p.n_row_blocks > 1 ? 4 : 0;
+    const FwdCost cost = fwd_cost<ROWS>(p.D);
+    if (whole > 4l * cus * kFwdRows / ROWS || p.Hkv > cus) return 0.0;   // at least four well-filled rounds
+    p.start = p.n_row_blocks == 1 ? 0 : ROWS == kFwdRows ? 4 : 3;
     long tiles = 0;
-    for (int rb = 0; rb < p.n_row_blocks; ++rb) tiles += p.start + fwd_row_block_tiles(p, rb);
-    // Time of either form, in key tiles of one workgroup (1.45 us at head_dim 128, 1.1 us at 64; one
-    // workgroup is resident per compute unit).  Only ratios decide, and of these only the launches' would differ
-    // (4 tiles are 5.8 us at 128 and 4.4 us at 64), so one set of constants serves both.  Whole row blocks run in rounds.  Equal shares pay the
-    // launch that merges them and the partial results, written and read back, which grow with their
-    // size, with the number of shares, and double where a share can begin and end inside row blocks.
-    // Fitted to (us; whole, then with the number of shares per KV head): 60 rows over 8000 keys, 32/8
-    // heads 183, 38 (8), 29 (16), 26 (32); 300 over 1500, 24/8 heads 48, 45 (8), 37 (13), 43 (32); 2000
-    // over 4000, 8 heads 138, 95 (13), 66 (24), 61 (32); 60 over 8000, 14/2 heads, head_dim 64 136, 28
-    // (16), 18.6 (64), 20.6 (128).  One token over 16640 keys (32/8 heads) 290 -> 18 us.
-    const double rounds = (double)((whole + cus - 1) / cus);
-    double best = whole <= cus ? 4.0 + (double)longest : rounds * (double)tiles * p.Hkv / (double)whole;
-    const double slot = p.part_rows * p.D / (256.0 * 128.0) * (p.n_row_blocks > 1 ? 2.0 : 1.0);
+    for (int rb = 0; rb < p.n_row_blocks; ++rb) tiles += p.start + fwd_row_block_tiles<ROWS>(p, rb);
+    const long pure = tiles - (long)p.start * p.n_row_blocks;
     long shares = 0;
-    for (long s = tiles / 2 < cus / p.Hkv ? tiles / 2 : cus / p.Hkv; s >= 2; s -= (s + 7) / 8) {
-        const double t = (double)tiles / s + 4.0 + slot * (4.5 + 5.5 * (double)s * p.Hkv / cus);
-        if (t < best) { best = t; shares = s; }
+    double best;
+    if (rows <= 16) {
+        // attn_fwd_few, in key tiles: one token over 16640 keys (32/8 heads) 290 us whole, 18 us with 32 shares
+        best = 4.0 + (double)((p.M + p.Ct - 1) / 64 + 1);
+        const double slot = p.part_rows * p.D / (256.0 * 128.0);
+        for (long s = tiles / 2 < cus / p.Hkv ? tiles / 2 : cus / p.Hkv; s >= 2; s -= (s + 7) / 8) {
+            const double t = (double)tiles / s + 4.0 + slot * (4.5 + 5.5 * (double)s * p.Hkv / cus);
+            if (t < best) { best = t; shares = s; }
+        }
+    } else {
+        // Whole row blocks, the longest first.  With one workgroup on a unit every second round pairs its longest with the
+        // shortest of the round before; with several, the units fill up in that order and their tiles slow down.
+        auto length = [&](long i) {
+            return i < whole ? cost.whole_begin + fwd_row_block_tiles<ROWS>(p, p.n_row_blocks - 1 - (int)(i / p.Hkv)) : 0.0;
+        };
+        if (cost.resident == 1) {
+            double t = 0.0;
+            for (long r = 0; r < whole; r += 2l * cus) t += r + cus < whole ? 2.0 * length(r + cus) : length(r);
+            best = cost.whole + cost.whole_tile[0] * (t < length(0) ? length(0) : t);
+        } else {
+            double t = 0.0;
+            for (int r = 0; r < cost.resident; ++r)
+                t += (cost.whole_tile[r] - (r ? cost.whole_tile[r - 1] : 0.0)) * length((long)r * cus);
+            const double all = (pure + cost.whole_begin * p.n_row_blocks) * p.Hkv / cus / cost.resident;
+            const double behind = cost.whole_tile[cost.resident - 1] * (all + 0.5 * length((long)cost.resident * cus));
+            best = cost.whole + (whole > (long)cost.resident * cus && t < behind ? behind : t);
+        }
+        // Equal shares pay the launch that merges them and the partial results, written and read back, which double where
+        // a share begins and ends inside row blocks.  They read K and V each at a place of its own, while whole row blocks
+        // walk the same keys and find them in the L2; with more than one round of these that shows beyond the estimates
+        // (11419 rows, 16/4 heads 514 us whole, 545 with 64 shares).
+        const double whole_time = best;
+        if (whole > cus) best *= 0.94;
+        const long most = (long)cost.resident * cus / p.Hkv;
+        // (pieces of one row block are merged sooner: 132 rows over 5890 keys, 32/8 heads 22.1 us with 32 shares, 22.7 with 28)
+        const double mb = p.part_rows * p.D * (p.n_row_blocks == 1 ? 3e-6 : 4e-6), full = p.part_rows * p.D / (256.0 * 128.0);
+        for (long s = tiles / 2 < most ? tiles / 2 : most; s >= 2; s -= (s + 7) / 8) {
+            const double cut = p.n_row_blocks > s ? 1.0 : (p.n_row_blocks - 1.0) / s;
+            const int on_unit = (int)((s * p.Hkv - 1) / cus);
+            p.shares = (int)s;
+            p.tiles = (int)tiles;
+            double launch = 0.0;
+            if (scored && tiles * (s + 1) < (1l << 31)) merge_with_score(p, &launch);
+            const double t = cost.split - launch + cost.split_tile[on_unit] * (pure + cost.split_begin * p.n_row_blocks) / s +
+                             cost.write * mb * s * p.Hkv * (1.0 + cut) + cost.part * full;
+            if (t < best) { best = t; shares = s; }
+        }
+        if (!shares) best = whole_time;
     }
-    if (!shares || tiles * (shares + 1) >= (1l << 31)) return;
-    p.shares = (int)shares;
+    p.shares = tiles * (shares + 1) < (1l << 31) ? (int)shares : 0;
     p.tiles = (int)tiles;
+    return best;
+}
+
+// Which form the forward pass takes.  Workgroups of four waves and 128 rows start sooner, wait for fewer waves at a barrier,
+// leave less of a row block empty, and two of them (three at head_dim 64) overlap on a compute unit; but alone on it one
+// reaches 0.6 of the rate, and each stages K and V for half the rows, so passes that fill the chip for long
+// stay with eight waves.  us, eight / four, each with its best number of shares: 312 rows over 312 keys, 32/8 heads 16.2 /
+// 12.1; 1998 over 1998 55.8 / 50.5; 1269 over 1808 48.9 / 45.5; 223 over 1518, 14/2 24.4 / 21.3; 78 over 8020, 16/4 27.4 /
+// 23.2; 185 over 2775, 32/8 29.3 / 30.2; 1354 over 2834, 16/4 45.2 / 48.6; 335 over 12938, 32/8 82.9 / 96.6; 64 wide: 907 over
+// 1423, 32/8 30.6 / 24.0; 4907 over 4907 131 / 115; 1767 over 1767, 24/8 34.6 / 29.2; 2592 over 14640, 8/8 96.4 / 98.5.
+template <class P>
+inline void fwd_choose(P &p, int cus, bool scored)
+{
+    const double eight = fwd_plan(p, cus, scored);
+    p.narrow = 0;
+    if (eight == 0.0 || p.G * p.Ct <= 16) return;
+    // Shares have to promise more: estimated 4 % ahead, 326 rows over 23729 keys, 8/8 heads took 80.8 us, not 77.5.  One row
+    // block of many keys is bound by reading them, with half the loads in flight (96 over 30179, 24/8 30 us, with four 36).
+    P q = p;
+    const double four = fwd_plan<kFwdNarrowRows>(q, cus, scored);
+    if (four >= (q.shares ? 0.95 : 0.98) * eight || (q.n_row_blocks == 1 && q.shares)) return;
+    p = q;
+    p.narrow = 1;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -187,6 +267,14 @@ inline int score_plan(P &p, int cus)
         const double item = (double)heads * per, items = 512.0 / keys * total * cus / item;
         double t = rate * total + tail * item;
         if (t < alone * item) t = alone * item;
+        if (f == kScoreNarrow && p.D != 64 && slices == 1) {
+            // a last round that is not full takes more than its part: 25 rows over 15606 keys, 32/8 heads (976 workgroups) 19.6 us, eight
+            // waves 17.2
+            double rounds = p.Hkv * (double)((p.n + keys - 1) / keys) / (resident * cus);
+            if (rounds > 1.0) rounds = 0.5 * (rounds + (double)(long)rounds + 1.0);
+            const double uncut = (rounds < 1.0 ? 1.0 : rounds) * (0.8 * item + begin) + 1.5 - begin * items / (resident * cus);
+            if (t < uncut) t = uncut;
+        }
         t += begin * items / (resident * cus) + fixed + (slices == 1 ? 0.0 : f == kScoreFour ? 2.0 : 3.0);
         if (t >= best) return;
         best = t;
@@ -264,14 +352,17 @@ RF_PLAN int merge_score_lanes(int entries)
 //     in all), 250 (17 observe) over 6000 27.1 / 26.8 (2375), over 10000 28.8 / 29.3 (2625), over 20000 34.5 / 36.5.
 //   - a lane reads its row's pieces four at a time: 5 rows over 20000, 14/2 of 64 20.2 / 20.1 (eight times), 16 over 6000
 //     17.7 / 16.4 (six), over 20000 24.4 / 27.3 (sixteen), of 128 33.5 / 36.6.
+// gain: what it saves, us, if it does.
 template <class P>
-inline bool merge_with_score(const P &p)
+inline bool merge_with_score(const P &p, double *gain)
 {
     const long n_merge = (long)p.Hkv * p.n_row_blocks * p.part_rows;
     const long n_score = p.Hkv * ((p.n + 64l * kFewKB - 1) / (64 * kFewKB));
     if (score_few(p) != 1 || n_merge > 2048 || n_merge + n_score > 2400 || n_score > (p.D == 64 ? 2048 : 1024)) return false;
     const long pieces = ((p.M + p.Ct - 1) / 64 + 1l) * p.shares / p.tiles;     // of the longest row block
-    return pieces <= 8 * 4 * merge_score_lanes(p.G * p.W);
+    const int most = 8 * 4 * merge_score_lanes(p.G * p.W);
+    if (gain && pieces < most) *gain = 3.0 * (1.0 - (double)pieces / most);
+    return pieces <= most;
 }
 
 }  // namespace reform

@@ -1,0 +1,67 @@
+"""The form that the forward pass takes, eight waves or four, replayed on the CPU: every key tile of every row block belongs to
+exactly one workgroup and the merge reads the slots that were written; the GPU tests' shapes take the form they are for;
+and shapes measured in both forms take the faster one."""
+import ctypes
+import os
+import random
+import subprocess
+
+import pytest
+
+import test_gpu_attend_fwd_narrow
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(HERE, "..", "paper_2506_01215_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("plan") / "replay.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-fsanitize=undefined",
+                    "-fno-sanitize-recover=undefined", "-static-libubsan", "-shared", "-fPIC", "-I", CSRC,
+                    os.path.join(HERE, "attend_plan_narrow_replay.cpp"), "-o", lib], check=True)
+    return ctypes.CDLL(lib)
+
+
+@pytest.mark.parametrize("G", list(range(1, 17)) + [32, 71])
+def test_every_tile_has_one_workgroup(plan, G):
+    rng = random.Random(G)
+    narrow = 0
+    for _ in range(300):
+        Hkv, d = rng.choice([1, 2, 4, 8, 32]), rng.choice([64, 128])
+        M = rng.choice([0, rng.randint(0, 300), rng.randint(0, 70000)])
+        Ct = rng.choice([rng.randint(1, 40), rng.randint(1, 400), rng.randint(1, 6000)])
+        scored, cus = rng.randint(0, 1), rng.choice([256, 256, 32, 304])
+        assert plan.replay_chosen(Hkv, G, d, M, Ct, scored, cus) == 0, (Hkv, G, d, M, Ct, scored, cus)
+        narrow += plan.form(Hkv, G, d, M, Ct, 0, scored, cus) & 1
+    assert narrow > 20
+
+
+@pytest.mark.parametrize("Hkv,G", [(1, 16), (2, 16), (1, 71), (8, 4), (1, 128)])
+def test_caches_whose_keys_times_heads_pass_32_bits(plan, Hkv, G):
+    for M in [(1 << 31) // G - 300, (1 << 31) // G + 300, (1 << 32) // G + 77, (1 << 30) - 65]:
+        if Hkv * M > (1 << 30):
+            continue
+        for Ct in (1, 256 // G + 1, 33, 700):
+            for d in (64, 128):
+                assert plan.replay_chosen(Hkv, G, d, M, Ct, 0, 256) == 0, (Hkv, G, d, M, Ct)
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W,form", test_gpu_attend_fwd_narrow.NARROW)
+def test_the_shapes_of_the_gpu_test_take_the_form_they_are_for(plan, Hq, Hkv, d, M, Ct, W, form):
+    assert plan.form(Hkv, Hq // Hkv, d, M, Ct, W, 1, 256) == form
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,M,Ct,form", [
+    (32, 8, 128, 0, 312, 1),          # 16.2 us with eight waves, 12.1 with four
+    (32, 8, 128, 0, 1998, 1),         # 55.8, 50.5
+    (16, 4, 128, 7942, 78, 3),        # 27.4, 23.2
+    (32, 8, 64, 0, 4907, 1),          # 131, 115
+    (32, 8, 128, 12603, 335, 2),      # 82.9, 96.6
+    (8, 8, 128, 1113, 4033, 2),       # 69.3, 77.0
+    (16, 4, 64, 10178, 873, 2),       # 56.8, 61.5
+    (32, 8, 128, 569, 2651, 0),       # 87.5, 98.4
+    (32, 8, 128, 32768, 32768, 0),
+])
+def test_the_faster_form_is_taken(plan, Hq, Hkv, d, M, Ct, form):
+    assert plan.form(Hkv, Hq // Hkv, d, M, Ct, 0, 0, 256) == form
