@@ -29,11 +29,17 @@ __device__ __forceinline__ double rope_quarters(const RopeParams &p, int c)
 // polynomials interpolated at Chebyshev points of x^2 on [0, 1/4] (error 3e-9 and 4e-9), pi/2
 // in two parts.  Over whole turns the error against 64 bits is 1.7e-8 in the root mean square (a
 // fraction of a turn rounded to fp32, times 2 pi, into an exact sine: 6.0e-8), at most 7.4e-8.
+//
+// Rounding to whole quarter turns is an addition of 1.5 * 2^52, which leaves the whole number in the sum's low bits: at most
+// 2^31 positions of at most one radian each (theta > 1) are far below the 2^51 up to which it is exact.
+// (rint and a conversion to 64 bits for the quadrant are a fifth of a pair's instructions: 8 heads x 4096 rows x 128 bf16 6.2 -> 5.6 us, x
+// 32768 rows 25.0 -> 24.0, 8 x 12000 rows of 64 7.6 -> 6.8.)
 __device__ __forceinline__ void sin_cos_quarter(double turns4, float &sn, float &cs)
 {
-    const double whole = rint(turns4);
-    const float x = (float)(turns4 - whole), u = x * x;
-    const int quadrant = (int)(long long)whole;
+    constexpr double kRound = 6755399441055744.0;
+    const double t = turns4 + kRound;
+    const uint32_t quadrant = (uint32_t)__double2loint(t);
+    const float x = (float)(turns4 - (t - kRound)), u = x * x;
     float a = fmaf(0.00015820629902386097f, u, -0.004681266254496438f);
     a = fmaf(a, u, 0.07969258272529528f);
     a = fmaf(a, u, -0.6459640961467789f);
@@ -45,10 +51,8 @@ __device__ __forceinline__ void sin_cos_quarter(double turns4, float &sn, float 
     b = fmaf(b, u, -1.2337005501352676f);
     const float c = fmaf(b, u, 1.0f);
     const bool odd = quadrant & 1;
-    sn = odd ? c : s;
-    cs = odd ? s : c;
-    if (quadrant & 2) sn = -sn;
-    if ((quadrant + 1) & 2) cs = -cs;
+    sn = __uint_as_float(__float_as_uint(odd ? c : s) ^ ((quadrant << 30) & 0x80000000u));
+    cs = __uint_as_float(__float_as_uint(odd ? s : c) ^ (((quadrant + 1) << 30) & 0x80000000u));
 }
 
 template <bool BF16>
