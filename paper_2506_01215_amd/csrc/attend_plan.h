@@ -200,10 +200,16 @@ inline void fwd_choose(P &p, int cus, bool scored)
     p.narrow = 0;
     if (eight == 0.0 || p.G * p.Ct <= 16) return;
     // Shares have to promise more: estimated 4 % ahead, 326 rows over 23729 keys, 8/8 heads took 80.8 us, not 77.5.  One row
-    // block of many keys is bound by reading them, with half the loads in flight (96 over 30179, 24/8 30 us, with four 36).
+    // block of many keys is bound by reading them, with half the loads in flight (96 over 30179, 8/8 29.7 us, with four 36.6).
     P q = p;
     const double four = fwd_plan<kFwdNarrowRows>(q, cus, scored);
     if (four >= (q.shares ? 0.95 : 0.98) * eight || (q.n_row_blocks == 1 && q.shares)) return;
+    // Long shares are bound by what the estimate leaves out: every row block reads its K and V by itself, and there are up to
+    // twice as many.  Problems for which the estimate is for shared-out four waves, time with four over that with eight (mean,
+    // worst) by the tiles of a share, at 128: up to 7 0.88, 1.07 (660 problems); 7 to 9 0.94, 1.08 (121); 9 to 12 0.98, 1.10
+    // (47); 12 to 18 1.07, 1.16 (15); beyond 1.18, 1.28 (26; 379 rows over 52252 keys, 8/8 heads 98.2 us, with four 115.0).  At 64,
+    // with half the bytes, 0.90 with eight KV heads, 0.95 with four, 0.99 with two beyond 9 tiles, at worst 1.07.
+    if (p.D == 128 && q.shares && q.tiles / q.shares >= 9) return;
     p = q;
     p.narrow = 1;
 }

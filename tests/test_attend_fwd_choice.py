@@ -62,6 +62,17 @@ def test_the_shapes_of_the_gpu_test_take_the_form_they_are_for(plan, Hq, Hkv, d,
     (16, 4, 64, 10178, 873, 2),       # 56.8, 61.5
     (32, 8, 128, 569, 2651, 0),       # 87.5, 98.4
     (32, 8, 128, 32768, 32768, 0),
+    # shares of many tiles
+    (8, 8, 128, 51873, 379, 2),       # 98.5, 120.3
+    (8, 8, 128, 53803, 284, 2),       # 94.7, 111.7
+    (12, 4, 128, 94625, 86, 2),       # 84.3, 108.2
+    (24, 8, 128, 46280, 127, 2),      # 90.7, 107.8
+    (4, 4, 128, 18726, 344, 2),       # 32.9, 38.1
+    (14, 2, 128, 31140, 53, 2),       # 31.3, 36.2
+    (16, 4, 64, 76065, 90, 3),        # 54.7, 52.0
+    (14, 2, 128, 6287, 69, 3),        # 25.6, 22.3
+    (8, 8, 64, 31055, 281, 3),        # 48.4, 44.1
+    (12, 4, 64, 14271, 117, 3),       # 26.1, 22.2
 ])
 def test_the_faster_form_is_taken(plan, Hq, Hkv, d, M, Ct, form):
     assert plan.form(Hkv, Hq // Hkv, d, M, Ct, 0, 0, 256) == form
