@@ -281,7 +281,7 @@ inline int score_plan(P &p, int cus)
             const double uncut = (rounds < 1.0 ? 1.0 : rounds) * (0.8 * item + begin) + 1.5 - begin * items / (resident * cus);
             if (t < uncut) t = uncut;
         }
-        t += begin * items / (resident * cus) + fixed + (slices == 1 ? 0.0 : f == kScoreFour ? 2.0 : 3.0);
+        t += begin * items / (resident * cus) + fixed + (slices == 1 ? 0.0 : f == kScoreFour ? 2.0 : 3.0) + (p.D == 64 ? 0.1 * (hs - 1) : 0.0);
         if (t >= best) return;
         best = t;
         form = f;
@@ -293,16 +293,19 @@ inline int score_plan(P &p, int cus)
     const bool four = p.D != 64 && total >= 120.0;
     auto consider = [&](int per, int heads) {
         if (four) price(kScoreFour, 256, 2.0, 1.0, 0.5, 1.0, 1.5, 3.0, per, heads);
-        else if (p.D == 64) price(kScoreNarrow, 128, 4.0, 1.0, 0.33, 0.5, 1.6, 0.0, per, heads);
+        else if (p.D == 64) price(kScoreNarrow, 128, 4.0, 1.0, 0.33, 0.75, 1.6, 0.0, per, heads);
         else price(kScoreNarrow, 128, 3.0, 1.06, 0.35, 0.8, 1.6, 0.0, per, heads);
     };
     for (int want = 1; want <= (four ? 16 : 32); want *= 2) consider((tiles + want - 1) / want, p.G);
     // Where that leaves compute units without a workgroup the heads are cut as well: 60 rows over 8000 keys
     // with 14/2 heads of 64 (32 workgroups of 7 tiles) 38 -> 31 us for the call, 30 over 1000 with 14/2 of
     // 128 38 -> 28 us.  (On a chip that is busy it gives nothing: 2000 rows over 1000 keys, 32/8 heads, 18.9
-    // -> 19.8 us.)
+    // -> 19.8 us.)  At 64 four workgroups share
+    // a unit and one alone reaches a third of its rate, so there with up to two to a unit as well: windows of 128 rows, 64/8
+    // heads over 3211 keys 23.9 us uncut, 17.2 with the heads in two; 14/2 over 15117 20.5 and 15.7; 16/4 over 5292 16.2 and
+    // 13.6.  Each set of heads costs the launch that adds up a little: 540 rows, 14/2 13.1 us in four sets, 14.3 in seven.
     const int keys = form == kScoreEight ? 512 : form == kScoreFour ? 256 : 128;
-    if ((long)p.Hkv * ((p.n + keys - 1) / keys) * p.slices < cus)
+    if ((long)p.Hkv * ((p.n + keys - 1) / keys) * p.slices < (p.D == 64 ? 2l : 1l) * cus)
         for (int heads = (p.G + 1) / 2; heads >= 1; heads = heads > 1 ? (heads + 1) / 2 : 0) consider(1, heads);
     return form;
 }

@@ -108,6 +108,17 @@ def test_score_forms_measured_faster_with_four_waves_take_them(plan, Hq, Hkv, d,
     assert plan.score_form(Hkv, Hq // Hkv, d, M, Ct, W, 256) == 4
 
 
+@pytest.mark.parametrize("Hq,Hkv,M,Ct,W", [
+    (64, 8, 0, 3211, 128),            # score alone 23.9 us uncut, 17.2 us with the heads in two
+    (64, 8, 2985, 487, 128),          # 23.1, 16.4
+    (16, 2, 12949, 278, 117),         # 22.8, 16.3
+    (14, 2, 14253, 864, 128),         # 20.5, 15.7
+    (16, 4, 5121, 158, 158),          # 16.8, 13.9
+])
+def test_heads_are_cut_where_that_was_measured_faster(plan, Hq, Hkv, M, Ct, W):
+    assert plan.score_form(Hkv, Hq // Hkv, 64, M, Ct, W, 256) >= 32
+
+
 @pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W,merged", [
     (8, 8, 128, 59999, 1, 0, False),  # 68.1 us in two launches, 71.2 in one
     (8, 8, 128, 19970, 30, 0, False), # 35.8, 37.3
