@@ -293,7 +293,7 @@ inline int score_plan(P &p, int cus)
     const bool four = p.D != 64 && total >= 120.0;
     auto consider = [&](int per, int heads) {
         if (four) price(kScoreFour, 256, 2.0, 1.0, 0.5, 1.0, 1.5, 3.0, per, heads);
-        else if (p.D == 64) price(kScoreNarrow, 128, 4.0, 1.0, 0.33, 0.75, 1.6, 0.0, per, heads);
+        else if (p.D == 64) price(kScoreNarrow, 128, 4.0, 1.0, 0.33, p.G == 1 ? 0.5 : 0.75, 1.6, 0.0, per, heads);
         else price(kScoreNarrow, 128, 3.0, 1.06, 0.35, 0.8, 1.6, 0.0, per, heads);
     };
     for (int want = 1; want <= (four ? 16 : 32); want *= 2) consider((tiles + want - 1) / want, p.G);
@@ -301,7 +301,8 @@ inline int score_plan(P &p, int cus)
     // with 14/2 heads of 64 (32 workgroups of 7 tiles) 38 -> 31 us for the call, 30 over 1000 with 14/2 of
     // 128 38 -> 28 us.  (On a chip that is busy it gives nothing: 2000 rows over 1000 keys, 32/8 heads, 18.9
     // -> 19.8 us.)  At 64 four workgroups share
-    // a unit and one alone reaches a third of its rate, so there with up to two to a unit as well: windows of 128 rows, 64/8
+    // a unit and one alone reaches a third of its rate (half with one head to a group: 520 rows over 2928 keys, 8/8 heads 11.8 us
+    // uncut, 13.3 in three slices), so there with up to two to a unit as well: windows of 128 rows, 64/8
     // heads over 3211 keys 23.9 us uncut, 17.2 with the heads in two; 14/2 over 15117 20.5 and 15.7; 16/4 over 5292 16.2 and
     // 13.6.  Each set of heads costs the launch that adds up a little: 540 rows, 14/2 13.1 us in four sets, 14.3 in seven.
     const int keys = form == kScoreEight ? 512 : form == kScoreFour ? 256 : 128;

@@ -119,6 +119,15 @@ def test_heads_are_cut_where_that_was_measured_faster(plan, Hq, Hkv, M, Ct, W):
     assert plan.score_form(Hkv, Hq // Hkv, 64, M, Ct, W, 256) >= 32
 
 
+@pytest.mark.parametrize("Hq,Hkv,M,Ct,W", [
+    (8, 8, 2408, 520, 0),             # 11.8 us uncut, 13.3 us in three slices
+    (8, 8, 3606, 1084, 0),            # 17.6, 19.0
+    (4, 4, 2195, 4124, 594),          # 12.3, 13.5
+])
+def test_one_head_to_a_group_stays_uncut_where_that_was_measured_faster(plan, Hq, Hkv, M, Ct, W):
+    assert plan.score_form(Hkv, Hq // Hkv, 64, M, Ct, W, 256) == 0
+
+
 @pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W,merged", [
     (8, 8, 128, 59999, 1, 0, False),  # 68.1 us in two launches, 71.2 in one
     (8, 8, 128, 19970, 30, 0, False), # 35.8, 37.3
