@@ -1339,13 +1339,7 @@ static hipError_t launch_score(AttnParams p, void *part, size_t part_bytes, hipS
         else hipLaunchKernelGGL((attn_score_few<D, KB, 4>), dim3(grid), dim3(256), 0, st, p);
         return hipGetLastError();
     }
-    int form = score_plan(p, compute_units());
-    if (p.slices > 1 && (!part || part_bytes < (size_t)p.slices * p.Hkv * p.n * sizeof(float))) {
-        p.slice_tiles *= p.slices;                       // no room for partial sums: uncut
-        p.slice_heads = p.G;
-        p.slices = p.head_slices = 1;
-        form = D == 64 ? kScoreNarrow : kScoreEight;
-    }
+    const int form = score_plan(p, compute_units(), part ? part_bytes : 0);
     p.part_score = (float *)part;
     if (form == kScoreEight) return launch_score_tiled<D, 4, 8>(p, st);
     if constexpr (D == 128)
@@ -1379,7 +1373,7 @@ size_t attend_bf16_scratch_bytes(const AttnParams &sizes)
     size_t score = 0;
     if (!score_few(p)) {
         score_plan(p, compute_units());
-        if (p.slices > 1) score = (size_t)p.slices * p.Hkv * p.n * sizeof(float);
+        score = score_slice_bytes(p);
     }
     size_t bytes = score;
     for (const bool scored : {false, true}) {

@@ -5,6 +5,8 @@
 // so no product of keys and heads may be formed in 32 bits.
 #pragma once
 
+#include <stddef.h>
+
 #ifdef __HIPCC__
 #include <hip/hip_runtime.h>
 #define RF_PLAN __host__ __device__ __forceinline__
@@ -220,6 +222,10 @@ constexpr int kScoreEight = 8;                           // eight waves of 64 ke
 constexpr int kScoreFour = 4;                            // four of 64
 constexpr int kScoreNarrow = 2;                          // four of 32
 
+// Bytes of the slices' sums of a planned score pass.
+template <class P>
+inline size_t score_slice_bytes(const P &p) { return p.slices > 1 ? (size_t)p.slices * p.Hkv * p.n * sizeof(float) : 0; }
+
 // How the score pass of a problem is cut into workgroups: form (returned), slices, slice_tiles, head_slices and
 // slice_heads.  Time is estimated in query tiles that a compute unit takes against 512 keys (2.1 us at head_dim 128,
 // 1.35 us at 64); two workgroups of four waves of 64 keys, three of 32 (four at head_dim 64) or one of eight are resident on it.
@@ -243,8 +249,10 @@ constexpr int kScoreNarrow = 2;                          // four of 32
 // / 340 / 300 / 289 / 301; 16384 over 49152, 8/8 1123 / 893 / 893 / 909 / 944 / 1033; 12000 over 12000, 14/2 1904 / 994 /
 // 362 / 255 / 224 / 205; 1000 over 4000, 32/8 111 / 55 / 36 / 36 / 38 / 38; a window of 128 rows over 11193, 24/8 19.6 /
 // 15.0, over 32000, 16/4 19.8 / 20.8, over 20000, 8/8 19.0 / 10.7.
+// scratch: bytes there are for the slices' sums; the cuts that fit are considered, so that a workspace kept from a smaller cut
+// still serves for one like it.
 template <class P>
-inline int score_plan(P &p, int cus)
+inline int score_plan(P &p, int cus, size_t scratch = (size_t)-1)
 {
     const int tiles = (p.W + 63) / 64;
     const double iters = (double)p.G * tiles;
@@ -270,6 +278,7 @@ inline int score_plan(P &p, int cus)
     auto price = [&](int f, int keys, double resident, double rate, double tail, double alone, double begin, double fixed,
                      int per, int heads) {
         const int hs = (p.G + heads - 1) / heads, slices = (tiles + per - 1) / per * hs;
+        if (slices > 1 && (size_t)slices * p.Hkv * p.n * sizeof(float) > scratch) return;
         const double item = (double)heads * per, items = 512.0 / keys * total * cus / item;
         double t = rate * total + tail * item;
         if (t < alone * item) t = alone * item;

@@ -72,6 +72,17 @@ extern "C" int score_form(int Hkv, int G, int D, int M, int Ct, int W, int cus)
     return p.slices > 1 ? 16 * p.slices : 0;
 }
 
+// Slices of the tiled score pass with that many bytes for their sums (negative: as many as it wants); -1 where they need more.
+extern "C" int score_slices(int Hkv, int G, int D, int M, int Ct, int W, int cus, long scratch)
+{
+    ScorePlan p = {};
+    p.Hkv = Hkv; p.G = G; p.D = D; p.n = M + Ct; p.W = W ? W : Ct;
+    score_plan(p, cus, scratch < 0 ? (size_t)-1 : (size_t)scratch);
+    const int tiles = (p.W + 63) / 64, sets = (tiles + p.slice_tiles - 1) / p.slice_tiles;
+    if (p.slices != sets * p.head_slices || p.head_slices != (G + p.slice_heads - 1) / p.slice_heads) return -2;
+    return scratch >= 0 && score_slice_bytes(p) > (size_t)scratch ? -1 : p.slices;
+}
+
 // Whether a call that wants both is split (bit 0), and merged by the launch that forms the score (bit 1).
 extern "C" int merged(int Hkv, int G, int D, int M, int Ct, int W, int cus)
 {

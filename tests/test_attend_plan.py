@@ -108,6 +108,43 @@ def test_score_forms_measured_faster_with_four_waves_take_them(plan, Hq, Hkv, d,
     assert plan.score_form(Hkv, Hq // Hkv, d, M, Ct, W, 256) == 4
 
 
+def slices_in(plan, shape, scratch):
+    Hq, Hkv, d, M, Ct, W = shape
+    return plan.score_slices(Hkv, Hq // Hkv, d, M, Ct, W, 256, ctypes.c_long(scratch))
+
+
+@pytest.mark.parametrize("shape", [
+    (14, 2, 64, 0, 12000, 0),         # uncut 994 us, in 4 slices 362, in 32 205
+    (16, 4, 64, 8192, 8192, 0),       # 500, 340, in 16 289
+    (16, 4, 128, 0, 4000, 0),
+    (32, 8, 128, 8192, 8192, 0),
+])
+def test_score_takes_the_slices_that_its_scratch_holds(plan, shape):
+    slice_bytes = shape[1] * (shape[3] + shape[4]) * 4
+    most = slices_in(plan, shape, -1)
+    assert most >= 8
+    assert slices_in(plan, shape, most * slice_bytes) == most
+    fewer = slices_in(plan, shape, most * slice_bytes - 1)
+    assert most / 3 < fewer < most
+    assert slices_in(plan, shape, 5 * slice_bytes - 1) in (3, 4)
+    assert slices_in(plan, shape, 2 * slice_bytes - 1) == 1
+    assert slices_in(plan, shape, 0) == 1
+
+
+def test_score_plans_fit_their_scratch(plan):
+    rng = random.Random(2)
+    cut = 0
+    for _ in range(4000):
+        Hkv, G = rng.choice([1, 2, 4, 8]), rng.choice([1, 2, 3, 4, 7, 8])
+        shape = (Hkv * G, Hkv, rng.choice([64, 128]), rng.choice([0, rng.randint(0, 40000)]), rng.randint(1, 9000), 0)
+        most = slices_in(plan, shape, -1)
+        scratch = rng.randint(0, most * Hkv * (shape[3] + shape[4]) * 4)
+        got = slices_in(plan, shape, scratch)
+        assert got >= 1, (shape, scratch)
+        cut += 1 < got != most
+    assert cut > 500
+
+
 @pytest.mark.parametrize("Hq,Hkv,M,Ct,W", [
     (64, 8, 0, 3211, 128),            # score alone 23.9 us uncut, 17.2 us with the heads in two
     (64, 8, 2985, 487, 128),          # 23.1, 16.4
