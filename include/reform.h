@@ -99,14 +99,16 @@ typedef struct {
 
 /* The query returns room for the lse rows (used if the caller passes lse = NULL) and, for problems
  * whose keys or rows are shared out over more workgroups than there are row or key blocks, for
- * their partial results: up to 68 MB for the attention (bf16; fp32 a few MB), and about 128 bytes per key of every
- * KV head for the score (the two share it).  Only the lse rows are needed: with a workspace that holds just these
- * (n_q_heads * chunk_len floats, rounded up to 256 bytes), or with none if lse is given, the call
- * runs such problems in their unshared form, slower (one token over 16640 keys, 32/8 heads: 17 times)
- * and with sums in another order.  A caller that sized its workspace some other way than by this query
- * gets that form without further notice.  Whether the score is asked for in the same call (phases 0 or 3, score not NULL)
- * or not can change the order of the sums too: out, lse and score then agree to rounding (fp32 sums of the same terms), not
- * bit for bit.                                                                                  */
+ * their partial results: up to 68 MB for the attention (bf16; fp32 a few MB), and for the score four
+ * bytes per key of every KV head and slice, of which there are up to 32, more where a short pass is
+ * cut into single heads as well (the two share it).  Only the lse rows are needed: with a workspace
+ * that holds just these (n_q_heads * chunk_len floats, rounded up to 256 bytes), or with none if lse
+ * is given, the call runs such problems in their unshared form, slower (one token over 16640 keys,
+ * 32/8 heads: 17 times) and with sums in another order; with room for some of the partial results
+ * (bf16) it makes as many parts as fit.  A caller that sized its workspace some other way than by
+ * this query gets that without further notice.  Whether the score is asked for in the same call
+ * (phases 0 or 3, score not NULL) or not can change the order of the sums too: out, lse and score
+ * then agree to rounding (fp32 sums of the same terms), not bit for bit.                         */
 size_t reform_chunk_attend_score_workspace(const reform_attn_desc *desc);
 
 reform_status reform_chunk_attend_score(const reform_attn_desc *desc,

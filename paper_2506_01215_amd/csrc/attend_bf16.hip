@@ -1243,12 +1243,6 @@ __global__ __launch_bounds__(256) void attn_merge_score(AttnParams p, int n_scor
 // Host-side launchers (called from the C-ABI file).
 static int compute_units() { return device_compute_units() > 0 ? device_compute_units() : 256; }
 
-// Bytes of the partial results of a planned problem.
-static size_t fwd_split_bytes(const AttnParams &p)
-{
-    return (size_t)p.shares * p.Hkv * 2 * p.part_rows * (p.D * sizeof(float) + sizeof(float2));
-}
-
 template <int D, int NW, bool SPLIT>
 static hipError_t launch_fwd_form(const AttnParams &p, int grid, hipStream_t st)
 {
@@ -1268,12 +1262,12 @@ static hipError_t launch_fwd_form(const AttnParams &p, int grid, hipStream_t st)
     return hipGetLastError();
 }
 
-// `part` (part_bytes): scratch for partial results; the key range is only split if they fit (true).
+// `part` (part_bytes): scratch for partial results; true if the key range is split.
 template <int D>
 static bool fwd_place(AttnParams &p, bool scored, void *part, size_t part_bytes)
 {
-    fwd_choose(p, compute_units(), scored);
-    if (!p.shares || !part || part_bytes < fwd_split_bytes(p)) return false;
+    fwd_choose(p, compute_units(), scored, part ? part_bytes : 0);
+    if (!p.shares) return false;
     p.part_o = (float *)part;
     p.part_ml = (float2 *)(p.part_o + (size_t)p.shares * p.Hkv * 2 * p.part_rows * D);
     return true;

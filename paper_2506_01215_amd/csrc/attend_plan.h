@@ -5,7 +5,10 @@
 // so no product of keys and heads may be formed in 32 bits.
 #pragma once
 
+#include <limits.h>
 #include <stddef.h>
+
+#include <algorithm>
 
 #ifdef __HIPCC__
 #include <hip/hip_runtime.h>
@@ -113,11 +116,19 @@ inline FwdCost fwd_cost(int D)
                    : FwdCost{2, 3.1, 3.2, {1.19, 1.61, 1.66}, 8.8, 1.7, {1.29, 1.77, 1.77}, 0.46, 0.64};
 }
 
+// Bytes of the partial results of a planned forward pass: two slots to every share, fp32 sums, maximum and sum of each row.
+template <class P>
+inline size_t fwd_split_bytes(const P &p)
+{
+    return (size_t)p.shares * p.Hkv * 2 * p.part_rows * (p.D + 2) * sizeof(float);
+}
+
 // How the forward pass of a problem is cut into workgroups of ROWS query rows: n_row_blocks and, if the key range is to be
 // split, shares, tiles and part_rows.  Returns the time estimated for it (0: whole row blocks, of which there are enough).
 // scored: the call forms the score as well, so that the launch which merges shares may be the score's.
+// scratch: bytes there are for partial results; the numbers of shares that fit are considered.
 template <int ROWS = kFwdRows, class P>
-inline double fwd_plan(P &p, int cus, bool scored = true)
+inline double fwd_plan(P &p, int cus, bool scored = true, size_t scratch = (size_t)-1)
 {
     const int rows = p.G * p.Ct;
     p.n_row_blocks = (int)(((long)rows + ROWS - 1) / ROWS);
@@ -133,13 +144,16 @@ inline double fwd_plan(P &p, int cus, bool scored = true)
     long tiles = 0;
     for (int rb = 0; rb < p.n_row_blocks; ++rb) tiles += p.start + fwd_row_block_tiles<ROWS>(p, rb);
     const long pure = tiles - (long)p.start * p.n_row_blocks;
+    p.shares = 1;
+    const size_t room = scratch / fwd_split_bytes(p);
+    const long most = std::min({tiles / 2, (long)cost.resident * cus / p.Hkv, (long)std::min(room, (size_t)INT_MAX)});
     long shares = 0;
     double best;
     if (rows <= 16) {
         // attn_fwd_few, in key tiles: one token over 16640 keys (32/8 heads) 290 us whole, 18 us with 32 shares
         best = 4.0 + (double)((p.M + p.Ct - 1) / 64 + 1);
         const double slot = p.part_rows * p.D / (256.0 * 128.0);
-        for (long s = tiles / 2 < cus / p.Hkv ? tiles / 2 : cus / p.Hkv; s >= 2; s -= (s + 7) / 8) {
+        for (long s = most; s >= 2; s -= (s + 7) / 8) {
             const double t = (double)tiles / s + 4.0 + slot * (4.5 + 5.5 * (double)s * p.Hkv / cus);
             if (t < best) { best = t; shares = s; }
         }
@@ -167,13 +181,12 @@ inline double fwd_plan(P &p, int cus, bool scored = true)
         // (11419 rows, 16/4 heads 514 us whole, 545 with 64 shares).
         const double whole_time = best;
         if (whole > cus) best *= 0.94;
-        const long most = (long)cost.resident * cus / p.Hkv;
         // (pieces of one row block are merged sooner: 132 rows over 5890 keys, 32/8 heads 22.1 us with 32 shares, 22.7 with 28)
         const double mb = p.part_rows * p.D * (p.n_row_blocks == 1 ? 3e-6 : 4e-6), full = p.part_rows * p.D / (256.0 * 128.0);
-        for (long s = tiles / 2 < most ? tiles / 2 : most; s >= 2; s -= (s + 7) / 8) {
+        for (long s = most; s >= 2; s -= (s + 7) / 8) {
+            p.shares = (int)s;
             const double cut = p.n_row_blocks > s ? 1.0 : (p.n_row_blocks - 1.0) / s;
             const int on_unit = (int)((s * p.Hkv - 1) / cus);
-            p.shares = (int)s;
             p.tiles = (int)tiles;
             double launch = 0.0;
             if (scored && tiles * (s + 1) < (1l << 31)) merge_with_score(p, &launch);
@@ -196,15 +209,15 @@ inline double fwd_plan(P &p, int cus, bool scored = true)
 // 23.2; 185 over 2775, 32/8 29.3 / 30.2; 1354 over 2834, 16/4 45.2 / 48.6; 335 over 12938, 32/8 82.9 / 96.6; 64 wide: 907 over
 // 1423, 32/8 30.6 / 24.0; 4907 over 4907 131 / 115; 1767 over 1767, 24/8 34.6 / 29.2; 2592 over 14640, 8/8 96.4 / 98.5.
 template <class P>
-inline void fwd_choose(P &p, int cus, bool scored)
+inline void fwd_choose(P &p, int cus, bool scored, size_t scratch = (size_t)-1)
 {
-    const double eight = fwd_plan(p, cus, scored);
+    const double eight = fwd_plan(p, cus, scored, scratch);
     p.narrow = 0;
     if (eight == 0.0 || p.G * p.Ct <= 16) return;
     // Shares have to promise more: estimated 4 % ahead, 326 rows over 23729 keys, 8/8 heads took 80.8 us, not 77.5.  One row
     // block of many keys is bound by reading them, with half the loads in flight (96 over 30179, 8/8 29.7 us, with four 36.6).
     P q = p;
-    const double four = fwd_plan<kFwdNarrowRows>(q, cus, scored);
+    const double four = fwd_plan<kFwdNarrowRows>(q, cus, scored, scratch);
     if (four >= (q.shares ? 0.95 : 0.98) * eight || (q.n_row_blocks == 1 && q.shares)) return;
     // Long shares are bound by what the estimate leaves out: every row block reads its K and V by itself, and there are up to
     // twice as many.  Problems for which the estimate is for shared-out four waves, time with four over that with eight (mean,

@@ -10,7 +10,7 @@
 
 using namespace reform;
 
-struct Plan { int Hkv, G, D, M, Ct, n_row_blocks, by_head, shares, start, tiles, part_rows, n, W; };
+struct Plan { int Hkv, G, D, M, Ct, n_row_blocks, by_head, narrow, shares, start, tiles, part_rows, n, W; };
 struct ScorePlan { int Hkv, G, D, n, W, slices, slice_tiles, head_slices, slice_heads; };
 struct Piece { long t0, t1, slot; };
 
@@ -70,6 +70,16 @@ extern "C" int score_form(int Hkv, int G, int D, int M, int Ct, int W, int cus)
     if (const int waves = score_few(p)) return waves;
     score_plan(p, cus);
     return p.slices > 1 ? 16 * p.slices : 0;
+}
+
+// Shares of the forward pass with that many bytes for partial results (negative: as many as it wants), bytes: what they take.
+extern "C" int fwd_shares(int Hkv, int G, int D, int M, int Ct, int scored, int cus, long scratch, long *bytes)
+{
+    Plan p = {};
+    p.Hkv = Hkv; p.G = G; p.D = D; p.M = M; p.Ct = Ct; p.n = M + Ct; p.W = Ct;
+    fwd_choose(p, cus, scored, scratch < 0 ? (size_t)-1 : (size_t)scratch);
+    *bytes = (long)fwd_split_bytes(p);
+    return p.shares;
 }
 
 // Slices of the tiled score pass with that many bytes for their sums (negative: as many as it wants); -1 where they need more.

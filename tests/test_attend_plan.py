@@ -108,6 +108,46 @@ def test_score_forms_measured_faster_with_four_waves_take_them(plan, Hq, Hkv, d,
     assert plan.score_form(Hkv, Hq // Hkv, d, M, Ct, W, 256) == 4
 
 
+def shares_in(plan, shape, scratch, scored=0):
+    Hq, Hkv, d, M, Ct = shape
+    need = ctypes.c_long()
+    shares = plan.fwd_shares(Hkv, Hq // Hkv, d, M, Ct, scored, 256, ctypes.c_long(scratch), ctypes.byref(need))
+    return shares, need.value
+
+
+@pytest.mark.parametrize("shape", [
+    (32, 8, 128, 16640, 1),           # one token: 290 us whole, 18 us with 32 shares
+    (8, 8, 128, 4096, 17),
+    (16, 4, 64, 30000, 40),
+    (8, 8, 128, 51873, 379),
+    (32, 8, 128, 2000, 100),
+])
+def test_the_forward_pass_takes_the_shares_that_its_scratch_holds(plan, shape):
+    most, need = shares_in(plan, shape, -1)
+    assert most >= 8
+    assert shares_in(plan, shape, need) == (most, need)
+    fewer, less = shares_in(plan, shape, need - 1)
+    assert fewer >= 2 and 0.7 * need < less < need
+    some, used = shares_in(plan, shape, need // 3)
+    assert some >= 2 and 0.5 * (need // 3) < used <= need // 3
+    assert shares_in(plan, shape, 0) == (0, 0)
+
+
+def test_forward_plans_fit_their_scratch(plan):
+    rng = random.Random(3)
+    cut = 0
+    for _ in range(4000):
+        Hkv, G = rng.choice([1, 2, 4, 8]), rng.choice([1, 2, 3, 4, 7, 8])
+        shape = (Hkv * G, Hkv, rng.choice([64, 128]), rng.choice([0, rng.randint(0, 40000)]), int(2 ** rng.uniform(0, 13)))
+        scored = rng.randint(0, 1)
+        most, need = shares_in(plan, shape, -1, scored)
+        scratch = rng.randint(0, need)
+        got, used = shares_in(plan, shape, scratch, scored)
+        assert used <= scratch and (used > 0) == (got > 0) and got != 1, (shape, scratch)
+        cut += 0 < got != most
+    assert cut > 500
+
+
 def slices_in(plan, shape, scratch):
     Hq, Hkv, d, M, Ct, W = shape
     return plan.score_slices(Hkv, Hq // Hkv, d, M, Ct, W, 256, ctypes.c_long(scratch))

@@ -63,6 +63,34 @@ def test_split_forward_matches_oracle(shape):
     assert torch.equal(results[0][0], results[1][0]) and torch.equal(results[0][1], results[1][1])
 
 
+@pytest.mark.parametrize("shape", [
+    (8, 2, 128, 1000, 1, 0),
+    (14, 2, 64, 2000, 300, 128),
+    (6, 3, 128, 2003, 513, 77),
+    (2, 1, 128, 6001, 40, 40),
+    (16, 2, 128, 1000, 600, 301),
+    (2, 2, 64, 0, 1600, 0),
+], ids=lambda s: "x".join(map(str, s)))
+def test_a_workspace_between_none_and_all(shape):
+    """Room for some of the shares and slices: a cut that fits, and nothing behind its end is touched."""
+    Hq, Hkv, d, M, Ct, W = shape
+    q, k, v = inputs(Hq, Hkv, d, M, Ct, seed=5 + M + Ct)
+    scale = 1.0 / math.sqrt(d)
+    o_ref, l_ref, s_ref = oracle.attend_score(to_np(q), to_np(k), to_np(v), M, scale, W=W)
+    lse_bytes = (Hq * Ct * 4 + 255) // 256 * 256
+    need = binding.attend_workspace_bytes(binding.attn_desc(q, k, q, M, scale, W)) - lse_bytes
+    for part in (0.9, 0.5, 0.2, 0.05):
+        nbytes = lse_bytes + int(part * need)
+        ws = torch.full((nbytes + 4096,), 0xa5, dtype=torch.uint8, device=DEV)
+        out, lse, score = binding.reform_chunk_attend_score(q, k, v, M, scale, obs_window=W, workspace=ws[:nbytes])
+        torch.cuda.synchronize()
+        # the bounds of the other attention tests
+        assert_close(to_np(out), o_ref, 2e-2, "out", row_floor=True)
+        assert_close(to_np(lse), l_ref, 1e-5, "lse")
+        assert_scores_close(to_np(score)[:, :M + Ct], s_ref[:, :M + Ct], 1e-5, "score")
+        assert (ws[nbytes:] == 0xa5).all()
+
+
 # Which form a shape takes is checked on the CPU (test_attend_plan.py).
 SLICED = [
     (16, 4, 128, 100, 700, 0),      # slices of one tile, the last of 60 rows
