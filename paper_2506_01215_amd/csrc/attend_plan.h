@@ -146,7 +146,9 @@ inline double fwd_plan(P &p, int cus, bool scored = true, size_t scratch = (size
     const long pure = tiles - (long)p.start * p.n_row_blocks;
     p.shares = 1;
     const size_t room = scratch / fwd_split_bytes(p);
-    const long most = std::min({tiles / 2, (long)cost.resident * cus / p.Hkv, (long)std::min(room, (size_t)INT_MAX)});
+    // a place in the list times the shares is formed in 32 bits
+    const long most = std::min({tiles / 2, (long)cost.resident * cus / p.Hkv, INT_MAX / tiles - 1,
+                                (long)std::min(room, (size_t)INT_MAX)});
     long shares = 0;
     double best;
     if (rows <= 16) {
@@ -189,14 +191,14 @@ inline double fwd_plan(P &p, int cus, bool scored = true, size_t scratch = (size
             const int on_unit = (int)((s * p.Hkv - 1) / cus);
             p.tiles = (int)tiles;
             double launch = 0.0;
-            if (scored && tiles * (s + 1) < (1l << 31)) merge_with_score(p, &launch);
+            if (scored) merge_with_score(p, &launch);
             const double t = cost.split - launch + cost.split_tile[on_unit] * (pure + cost.split_begin * p.n_row_blocks) / s +
                              cost.write * mb * s * p.Hkv * (1.0 + cut) + cost.part * full;
             if (t < best) { best = t; shares = s; }
         }
         if (!shares) best = whole_time;
     }
-    p.shares = tiles * (shares + 1) < (1l << 31) ? (int)shares : 0;
+    p.shares = (int)shares;
     p.tiles = (int)tiles;
     return best;
 }

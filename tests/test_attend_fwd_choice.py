@@ -47,6 +47,18 @@ def test_caches_whose_keys_times_heads_pass_32_bits(plan, Hkv, G):
                 assert plan.replay_chosen(Hkv, G, d, M, Ct, 0, 256) == 0, (Hkv, G, d, M, Ct)
 
 
+@pytest.mark.parametrize("Hkv,G,d,M,Ct", [
+    (1, 8, 64, 4194304, 4096),        # 43.7 ms shared out, 69.7 whole: 128 row blocks on 256 compute units
+    (1, 8, 128, 4194304, 4096),
+    (1, 1, 64, 8388608, 16384),
+    (2, 4, 64, 1 << 25, 1024),
+])
+def test_lists_too_long_for_every_share_are_shared_by_fewer(plan, Hkv, G, d, M, Ct):
+    """A place in the list times the number of shares has to stay in 32 bits; the form is chosen by what is then run."""
+    assert plan.form(Hkv, G, d, M, Ct, 0, 0, 256) & 2
+    assert plan.replay_chosen(Hkv, G, d, M, Ct, 0, 256) == 0
+
+
 @pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W,form", test_gpu_attend_fwd_narrow.NARROW)
 def test_the_shapes_of_the_gpu_test_take_the_form_they_are_for(plan, Hq, Hkv, d, M, Ct, W, form):
     assert plan.form(Hkv, Hq // Hkv, d, M, Ct, W, 1, 256) == form
