@@ -226,3 +226,17 @@ def stores_for(cfg, emb, qry):
         return (build_store_gpu(emb.to(dev)), build_store_gpu(qry.to(dev)),
                 build_store_oracle(emb), build_store_oracle(qry))
     return emb.to(dev), qry.to(dev), emb.cpu(), qry.cpu()
+
+
+def load_attend_plan(tmp_path_factory):
+    """tests/attend_plan_replay.cpp over the kernels' own plan header, compiled for the host."""
+    import ctypes
+    import os
+    import subprocess
+    here = os.path.dirname(os.path.abspath(__file__))
+    lib = str(tmp_path_factory.mktemp("plan") / "replay.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-fsanitize=undefined",
+                    "-fno-sanitize-recover=undefined", "-static-libubsan", "-shared", "-fPIC",
+                    "-I", os.path.join(here, "..", "paper_2506_01215_amd", "csrc"),
+                    os.path.join(here, "attend_plan_replay.cpp"), "-o", lib], check=True)
+    return ctypes.CDLL(lib)

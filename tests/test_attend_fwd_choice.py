@@ -1,26 +1,20 @@
 """The form that the forward pass takes, eight waves or four, replayed on the CPU: every key tile of every row block belongs to
 exactly one workgroup and the merge reads the slots that were written; the GPU tests' shapes take the form they are for;
 and shapes measured in both forms take the faster one."""
-import ctypes
-import os
 import random
-import subprocess
 
 import pytest
 
+import helpers
 import test_gpu_attend_fwd_narrow
+import test_gpu_attend_merge_score
+import test_gpu_attend_split
 
-HERE = os.path.dirname(os.path.abspath(__file__))
-CSRC = os.path.join(HERE, "..", "paper_2506_01215_amd", "csrc")
 
 
 @pytest.fixture(scope="module")
 def plan(tmp_path_factory):
-    lib = str(tmp_path_factory.mktemp("plan") / "replay.so")
-    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-fsanitize=undefined",
-                    "-fno-sanitize-recover=undefined", "-static-libubsan", "-shared", "-fPIC", "-I", CSRC,
-                    os.path.join(HERE, "attend_plan_narrow_replay.cpp"), "-o", lib], check=True)
-    return ctypes.CDLL(lib)
+    return helpers.load_attend_plan(tmp_path_factory)
 
 
 @pytest.mark.parametrize("G", list(range(1, 17)) + [32, 71])
@@ -62,6 +56,22 @@ def test_lists_too_long_for_every_share_are_shared_by_fewer(plan, Hkv, G, d, M, 
 @pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W,form", test_gpu_attend_fwd_narrow.NARROW)
 def test_the_shapes_of_the_gpu_test_take_the_form_they_are_for(plan, Hq, Hkv, d, M, Ct, W, form):
     assert plan.form(Hkv, Hq // Hkv, d, M, Ct, W, 1, 256) == form
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W,form", test_gpu_attend_split.SHAPES + test_gpu_attend_merge_score.MERGED +
+                         test_gpu_attend_merge_score.WHOLE)
+def test_the_shapes_of_the_tests_of_shares_and_merging_take_the_form_they_are_for(plan, Hq, Hkv, d, M, Ct, W, form):
+    assert plan.form(Hkv, Hq // Hkv, d, M, Ct, W, 1, 256) == form
+
+
+def test_shared_out_row_blocks_of_eight_waves_have_their_shapes():
+    """Several row blocks, at either width, with one head to a wave's rows, with a wave to each head and neither."""
+    def kind(shape):
+        Hq, Hkv, d, M, Ct = shape[:5]
+        G = Hq // Hkv
+        return d, "one head" if G == 1 else "a wave to a head" if 8 % G == 0 and Ct >= 32 else "rows"
+    kinds = {kind(s) for s in test_gpu_attend_split.SHAPES if s[6] == 2 and s[0] // s[1] * s[4] > 256}
+    assert kinds == {(d, k) for d in (64, 128) for k in ("one head", "a wave to a head", "rows")}
 
 
 @pytest.mark.parametrize("Hq,Hkv,d,M,Ct,form", [

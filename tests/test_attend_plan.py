@@ -1,37 +1,31 @@
-"""The cut of the split forward pass, replayed on the CPU: every key tile of every row block of a problem
-belongs to exactly one workgroup, and the merge reads the slots that were written; and the form of the score pass
-that the GPU tests' shapes take.  The header that the kernels use is compiled as host code
-(attend_plan_replay.cpp)."""
+"""The plans of the attention, replayed on the CPU: every key tile of every row block of a forward pass split in the form
+of eight waves belongs to exactly one workgroup, and the merge reads the slots that were written; the form that the GPU tests'
+shapes take; and what is planned for a workspace without room for all of it.  The header that the kernels use is
+compiled as host code (attend_plan_replay.cpp)."""
 import ctypes
-import os
 import random
-import subprocess
 
 import pytest
 import torch
 
-import test_gpu_attend_merge_score
+import helpers
 import test_gpu_attend_score_narrow
 import test_gpu_attend_score_waves
+import test_gpu_attend_score_wide
 import test_gpu_attend_split
 from paper_2506_01215_amd import binding
 
-HERE = os.path.dirname(os.path.abspath(__file__))
-CSRC = os.path.join(HERE, "..", "paper_2506_01215_amd", "csrc")
+EIGHT, FOUR, NARROW = 8, 4, 2      # kScoreEight, kScoreFour, kScoreNarrow
 
 
 @pytest.fixture(scope="module")
 def plan(tmp_path_factory):
-    lib = str(tmp_path_factory.mktemp("plan") / "replay.so")
-    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-fsanitize=undefined",
-                    "-fno-sanitize-recover=undefined", "-static-libubsan", "-shared", "-fPIC", "-I", CSRC,
-                    os.path.join(HERE, "attend_plan_replay.cpp"), "-o", lib], check=True)
-    return ctypes.CDLL(lib)
+    return helpers.load_attend_plan(tmp_path_factory)
 
 
 @pytest.fixture(scope="module")
 def replay(plan):
-    return plan.replay
+    return plan.replay_eight
 
 
 @pytest.mark.parametrize("G", range(1, 33))
@@ -59,25 +53,41 @@ def test_caches_whose_keys_times_heads_pass_32_bits(replay, Hkv, G):
             assert replay(Hkv, G, 64, M + rng.randint(0, 63), Ct, 256) in (0, 1), (Hkv, G, M, Ct)
 
 
+def score_form(plan, shape):
+    Hq, Hkv, d, M, Ct, W = shape
+    return plan.score_form(Hkv, Hq // Hkv, d, M, Ct, W, 256)
+
+
+def form_and_slices(plan, shape):
+    return divmod(score_form(plan, shape), 1000)
+
+
 def test_the_score_shapes_of_the_gpu_tests_take_the_form_they_are_for(plan):
-    def form(Hq, Hkv, d, M, Ct, W):
-        return plan.score_form(Hkv, Hq // Hkv, d, M, Ct, W, 256)
-
     for shape in test_gpu_attend_split.SLICED:
-        assert form(*shape) > 16, shape
+        assert form_and_slices(plan, shape)[0] and form_and_slices(plan, shape)[1] > 1, shape
     for shape in test_gpu_attend_split.FEW_ROWS:
-        assert form(*shape) == 1, shape
+        assert score_form(plan, shape) == 1, shape
     for shape in test_gpu_attend_score_waves.FOUR_WAVES:
-        assert form(*shape) == 4, shape
+        assert score_form(plan, shape) == 4, shape
     for shape in test_gpu_attend_score_waves.TILED:
-        assert form(*shape) % 16 == 0, shape
-    for Hq, Hkv, d, M, Ct, W in test_gpu_attend_merge_score.MERGED:
-        assert plan.merged(Hkv, Hq // Hkv, d, M, Ct, W, 256) == 3, (Hq, Hkv, d, M, Ct, W)
+        assert form_and_slices(plan, shape)[0], shape
 
 
-@pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W", test_gpu_attend_score_narrow.NARROW)
-def test_score_shapes_of_the_narrow_tests_are_tiled(plan, Hq, Hkv, d, M, Ct, W):
-    assert plan.score_form(Hkv, Hq // Hkv, d, M, Ct, W, 256) % 16 == 0
+@pytest.mark.parametrize("shape", test_gpu_attend_score_narrow.NARROW)
+def test_score_shapes_of_the_narrow_tests_take_the_narrow_form_in_slices(plan, shape):
+    form, slices = form_and_slices(plan, shape)
+    assert form == NARROW and slices > 1
+
+
+@pytest.mark.parametrize("shape", test_gpu_attend_score_wide.EIGHT)
+def test_score_shapes_of_the_tests_of_eight_waves_take_them(plan, shape):
+    assert form_and_slices(plan, shape) == (EIGHT, 1)
+
+
+@pytest.mark.parametrize("shape", test_gpu_attend_score_wide.FOUR)
+def test_score_shapes_of_the_tests_of_four_waves_take_them_in_slices(plan, shape):
+    form, slices = form_and_slices(plan, shape)
+    assert form == FOUR and slices > 1
 
 
 @pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W", [
@@ -91,7 +101,7 @@ def test_score_shapes_of_the_narrow_tests_are_tiled(plan, Hq, Hkv, d, M, Ct, W):
     (24, 8, 64, 6158, 45, 0),         # 11.2, 13.0
 ])
 def test_score_forms_measured_faster_tiled_stay_tiled(plan, Hq, Hkv, d, M, Ct, W):
-    assert plan.score_form(Hkv, Hq // Hkv, d, M, Ct, W, 256) % 16 == 0
+    assert score_form(plan, (Hq, Hkv, d, M, Ct, W)) >= 1000
 
 
 @pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W", [
@@ -105,7 +115,7 @@ def test_score_forms_measured_faster_tiled_stay_tiled(plan, Hq, Hkv, d, M, Ct, W
     (14, 2, 64, 14641, 47, 0),
 ])
 def test_score_forms_measured_faster_with_four_waves_take_them(plan, Hq, Hkv, d, M, Ct, W):
-    assert plan.score_form(Hkv, Hq // Hkv, d, M, Ct, W, 256) == 4
+    assert score_form(plan, (Hq, Hkv, d, M, Ct, W)) == 4
 
 
 def shares_in(plan, shape, scratch, scored=0):
@@ -193,7 +203,7 @@ def test_score_plans_fit_their_scratch(plan):
     (16, 4, 5121, 158, 158),          # 16.8, 13.9
 ])
 def test_heads_are_cut_where_that_was_measured_faster(plan, Hq, Hkv, M, Ct, W):
-    assert plan.score_form(Hkv, Hq // Hkv, 64, M, Ct, W, 256) >= 32
+    assert form_and_slices(plan, (Hq, Hkv, 64, M, Ct, W))[1] > 1
 
 
 @pytest.mark.parametrize("Hq,Hkv,M,Ct,W", [
@@ -202,7 +212,7 @@ def test_heads_are_cut_where_that_was_measured_faster(plan, Hq, Hkv, M, Ct, W):
     (4, 4, 2195, 4124, 594),          # 12.3, 13.5
 ])
 def test_one_head_to_a_group_stays_uncut_where_that_was_measured_faster(plan, Hq, Hkv, M, Ct, W):
-    assert plan.score_form(Hkv, Hq // Hkv, 64, M, Ct, W, 256) == 0
+    assert form_and_slices(plan, (Hq, Hkv, 64, M, Ct, W)) == (NARROW, 1)
 
 
 @pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W,merged", [
@@ -215,7 +225,7 @@ def test_one_head_to_a_group_stays_uncut_where_that_was_measured_faster(plan, Hq
     (8, 8, 128, 4096, 17, 0, True),
 ])
 def test_merging_in_the_score_launch_where_it_was_measured_faster(plan, Hq, Hkv, d, M, Ct, W, merged):
-    assert plan.merged(Hkv, Hq // Hkv, d, M, Ct, W, 256) == (3 if merged else 1)
+    assert plan.form(Hkv, Hq // Hkv, d, M, Ct, W, 1, 256) == (6 if merged else 2)
 
 
 @pytest.mark.parametrize("Hq,Hkv,d,M,Ct,shared", [

@@ -14,25 +14,29 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-# That these take the one launch is checked on the CPU (test_attend_plan.py).
+# The last entry of a shape is the form of the forward pass, which is checked on the CPU (test_attend_fwd_choice.py): 6 shared
+# out and merged by the score's launch, 7 the same with row blocks of 128; 1 whole row blocks of 128.
 MERGED = [
-    (2, 2, 128, 1000, 300, 100),      # rows 200..299: two row blocks
-    (2, 2, 64, 0, 500, 128),          # no cache: row blocks of few pieces
-    (4, 1, 128, 3000, 20, 20),        # eight blocks of rows, half of each empty
-    (14, 2, 64, 900, 16, 16),
-    (8, 1, 128, 700, 1, 1),           # one token
-    (1, 1, 128, 5000, 260, 1),        # only the last row observes
-    (8, 8, 128, 4096, 17, 17),
-    (3, 1, 64, 200, 31, 5),
-    (14, 2, 128, 9000, 1, 1),         # seven rows of many pieces, 32 lanes each
-    (1, 1, 64, 3000, 40, 3),          # three rows, 64 lanes each
+    (2, 2, 128, 1000, 300, 100, 7),   # rows 200..299: two row blocks
+    (2, 2, 64, 0, 500, 128, 6),       # no cache: row blocks of few pieces
+    (4, 1, 128, 3000, 20, 20, 6),     # eight blocks of rows, half of each empty
+    (14, 2, 64, 900, 16, 16, 6),
+    (8, 1, 128, 700, 1, 1, 6),        # one token
+    (1, 1, 128, 5000, 260, 1, 7),     # only the last row observes
+    (8, 8, 128, 4096, 17, 17, 6),
+    (3, 1, 64, 400, 31, 5, 6),
+    (14, 2, 128, 9000, 1, 1, 6),      # seven rows of many pieces, 32 lanes each
+    (1, 1, 64, 3000, 40, 3, 6),       # three rows, 64 lanes each
+    (2, 2, 64, 0, 300, 128, 6),       # the observing rows end the first row block and are the second
+    (4, 4, 128, 8351, 397, 128, 6),
+    (8, 2, 128, 300, 40, 16, 7),
 ]
-WHOLE = [(2, 2, 64, 0, 300, 128), (3, 1, 64, 130, 31, 5)]     # chunks that are not split
+WHOLE = [(2, 2, 64, 0, 200, 128, 1), (3, 1, 64, 130, 31, 5, 1), (3, 1, 64, 200, 31, 5, 1)]     # chunks that are not split
 
 
-@pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W", MERGED + WHOLE)
+@pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W,form", MERGED + WHOLE)
 @pytest.mark.parametrize("accumulate", [False, True])
-def test_one_call_matches_oracle(Hq, Hkv, d, M, Ct, W, accumulate):
+def test_one_call_matches_oracle(Hq, Hkv, d, M, Ct, W, form, accumulate):
     g = torch.Generator().manual_seed(Hq + M + Ct + W)
     n = M + Ct
     q = torch.randn((Hq, Ct, d), generator=g).to(torch.bfloat16)

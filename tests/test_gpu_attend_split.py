@@ -19,16 +19,23 @@ from paper_2506_01215_amd import binding
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
-SHAPES = [  # Hq, Hkv, d, cache, chunk, window
-    (8, 2, 128, 1000, 1, 0),        # one token: every workgroup holds a few tiles of one row block
-    (8, 2, 64, 127, 1, 0),          # two tiles a head: one workgroup, nothing to merge
-    (8, 8, 128, 4096, 17, 0),
-    (14, 2, 64, 2000, 300, 128),    # seven query heads per KV head
-    (1, 1, 128, 0, 1500, 0),        # no cache: ranges begin on tiles that rows do not see
-    (1, 1, 64, 900, 257, 0),        # last row block of one row
-    (4, 1, 128, 900, 65, 0),
-    (6, 3, 128, 2003, 513, 77),       # two heads of a group in one workgroup
-    (2, 1, 128, 6001, 40, 40),
+# Hq, Hkv, d, cache, chunk, window and the form of the forward pass, which is checked on the CPU (test_attend_fwd_choice.py):
+# 1 four waves (else eight), 2 shared out, 4 merged by the score's launch.
+SHAPES = [
+    (8, 2, 128, 1000, 1, 0, 6),       # one token: every workgroup holds a few tiles of one row block
+    (8, 2, 64, 127, 1, 0, 0),         # two tiles a head: one workgroup, nothing to merge
+    (8, 8, 128, 4096, 17, 0, 6),
+    (14, 2, 64, 2000, 300, 128, 3),   # seven query heads per KV head
+    (1, 1, 128, 0, 1500, 0, 3),       # no cache: ranges begin on tiles that rows do not see
+    (1, 1, 64, 900, 257, 0, 2),       # last row block of one row
+    (4, 1, 128, 900, 65, 0, 3),
+    (6, 3, 128, 2003, 513, 77, 3),    # two heads of a group in one workgroup
+    (2, 1, 128, 6001, 40, 40, 6),
+    (2, 2, 128, 12747, 386, 0, 2),    # eight waves, two row blocks and more
+    (32, 8, 128, 3199, 99, 99, 2),
+    (6, 2, 128, 12738, 131, 128, 2),
+    (3, 1, 64, 366, 90, 0, 2),
+    (2, 1, 64, 351, 132, 128, 2),
 ]
 
 
@@ -43,7 +50,7 @@ def inputs(Hq, Hkv, d, M, Ct, seed):
 
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
 def test_split_forward_matches_oracle(shape):
-    Hq, Hkv, d, M, Ct, W = shape
+    Hq, Hkv, d, M, Ct, W, _ = shape
     q, k, v = inputs(Hq, Hkv, d, M, Ct, seed=M + Ct)
     scale = 1.0 / math.sqrt(d)
     desc = binding.attn_desc(q, k, q, M, scale, W)
@@ -135,7 +142,7 @@ def test_score_slices_match_oracle(shape):
 
 def test_the_shapes_split():
     """Every shape but the two-tile one asks for more workspace than the lse rows."""
-    for Hq, Hkv, d, M, Ct, W in SHAPES:
+    for Hq, Hkv, d, M, Ct, W, _ in SHAPES:
         q, k, _ = inputs(Hq, Hkv, d, M, Ct, seed=1)
         need = binding.attend_workspace_bytes(binding.attn_desc(q, k, q, M, 0.1, W))
         whole = (Hq * Ct * 4 + 255) // 256 * 256
