@@ -64,6 +64,11 @@ def test_the_shapes_of_the_tests_of_shares_and_merging_take_the_form_they_are_fo
     assert plan.form(Hkv, Hq // Hkv, d, M, Ct, W, 1, 256) == form
 
 
+@pytest.mark.parametrize("Hq,Hkv,d,M,Ct", test_gpu_attend_split.MANY)
+def test_many_row_blocks_are_taken_whole_by_eight_waves(plan, Hq, Hkv, d, M, Ct):
+    assert plan.form(Hkv, Hq // Hkv, d, M, Ct, 0, 0, 256) == 0
+
+
 def test_shared_out_row_blocks_of_eight_waves_have_their_shapes():
     """Several row blocks, at either width, with one head to a wave's rows, with a wave to each head and neither."""
     def kind(shape):

@@ -13,7 +13,7 @@ import pytest
 import torch
 
 import oracle
-from helpers import assert_close, assert_scores_close, to_np
+from helpers import assert_close, assert_scores_close, oracle_kv_heads_dense, to_np
 from paper_2506_01215_amd import binding
 
 pytestmark = pytest.mark.gpu
@@ -68,6 +68,29 @@ def test_split_forward_matches_oracle(shape):
         assert_scores_close(to_np(score)[:, :M + Ct], s_ref[:, :M + Ct], 2e-2, "score")
         results.append((out, lse))
     assert torch.equal(results[0][0], results[1][0]) and torch.equal(results[0][1], results[1][1])
+
+
+# More than four rounds of row blocks: eight waves, whole.
+MANY = [
+    (136, 136, 64, 100, 2001),      # 1088 row blocks, a wave to a head, the last block of 209 rows
+    (132, 44, 64, 0, 2001),         # 1056, three heads
+    (132, 44, 128, 100, 2001),
+]
+
+
+@pytest.mark.parametrize("shape", MANY, ids=lambda s: "x".join(map(str, s)))
+def test_many_row_blocks_match_oracle(shape):
+    Hq, Hkv, d, M, Ct = shape
+    G = Hq // Hkv
+    q, k, v = inputs(Hq, Hkv, d, M, Ct, seed=7 + M + Ct)
+    scale = 1.0 / math.sqrt(d)
+    out, lse, _ = binding.reform_chunk_attend_score(q, k, v, M, scale, want_score=False)
+    torch.cuda.synchronize()
+    for g in (0, Hkv - 1):
+        o_ref, l_ref, _ = oracle_kv_heads_dense(to_np(q), to_np(k), to_np(v), M, scale, [g])
+        # the bounds of the other attention tests
+        assert_close(to_np(out)[g * G:(g + 1) * G], o_ref, 2e-2, "out", row_floor=True)
+        assert_close(to_np(lse)[g * G:(g + 1) * G], l_ref, 1e-5, "lse")
 
 
 @pytest.mark.parametrize("shape", [
