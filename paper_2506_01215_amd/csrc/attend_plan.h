@@ -211,7 +211,7 @@ inline double fwd_plan(P &p, int cus, bool scored = true, size_t scratch = (size
 // 23.2; 185 over 2775, 32/8 29.3 / 30.2; 1354 over 2834, 16/4 45.2 / 48.6; 335 over 12938, 32/8 82.9 / 96.6; 64 wide: 907 over
 // 1423, 32/8 30.6 / 24.0; 4907 over 4907 131 / 115; 1767 over 1767, 24/8 34.6 / 29.2; 2592 over 14640, 8/8 96.4 / 98.5.
 template <class P>
-inline void fwd_choose(P &p, int cus, bool scored, size_t scratch = (size_t)-1)
+inline void fwd_choose_within(P &p, int cus, bool scored, size_t scratch)
 {
     const double eight = fwd_plan(p, cus, scored, scratch);
     p.narrow = 0;
@@ -229,6 +229,14 @@ inline void fwd_choose(P &p, int cus, bool scored, size_t scratch = (size_t)-1)
     if (p.D == 128 && q.shares && q.tiles / q.shares >= 9) return;
     p = q;
     p.narrow = 1;
+}
+
+// scratch: bytes there are for partial results.  What the plan wants of them does not depend on how much more there is.
+template <class P>
+inline void fwd_choose(P &p, int cus, bool scored, size_t scratch = (size_t)-1)
+{
+    fwd_choose_within(p, cus, scored, (size_t)-1);
+    if (fwd_split_bytes(p) > scratch) fwd_choose_within(p, cus, scored, scratch);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -264,10 +272,9 @@ inline size_t score_slice_bytes(const P &p) { return p.slices > 1 ? (size_t)p.sl
 // / 340 / 300 / 289 / 301; 16384 over 49152, 8/8 1123 / 893 / 893 / 909 / 944 / 1033; 12000 over 12000, 14/2 1904 / 994 /
 // 362 / 255 / 224 / 205; 1000 over 4000, 32/8 111 / 55 / 36 / 36 / 38 / 38; a window of 128 rows over 11193, 24/8 19.6 /
 // 15.0, over 32000, 16/4 19.8 / 20.8, over 20000, 8/8 19.0 / 10.7.
-// scratch: bytes there are for the slices' sums; the cuts that fit are considered, so that a workspace kept from a smaller cut
-// still serves for one like it.
+// scratch: bytes there are for the slices' sums; the cuts that fit are considered.
 template <class P>
-inline int score_plan(P &p, int cus, size_t scratch = (size_t)-1)
+inline int score_plan_within(P &p, int cus, size_t scratch)
 {
     const int tiles = (p.W + 63) / 64;
     const double iters = (double)p.G * tiles;
@@ -333,6 +340,15 @@ inline int score_plan(P &p, int cus, size_t scratch = (size_t)-1)
     if ((long)p.Hkv * ((p.n + keys - 1) / keys) * p.slices < (p.D == 64 ? 2l : 1l) * cus)
         for (int heads = (p.G + 1) / 2; heads >= 1; heads = heads > 1 ? (heads + 1) / 2 : 0) consider(1, heads);
     return form;
+}
+
+// The same, as cut as it is with room for all slices where those fit: a workspace kept from a smaller cut still serves
+// for one like it.
+template <class P>
+inline int score_plan(P &p, int cus, size_t scratch = (size_t)-1)
+{
+    const int form = score_plan_within(p, cus, (size_t)-1);
+    return score_slice_bytes(p) > scratch ? score_plan_within(p, cus, scratch) : form;
 }
 
 constexpr int kFewBlocks = 8;                            // row blocks over all heads of a group, at most (one wave)

@@ -151,6 +151,8 @@ def test_forward_plans_fit_their_scratch(plan):
         shape = (Hkv * G, Hkv, rng.choice([64, 128]), rng.choice([0, rng.randint(0, 40000)]), int(2 ** rng.uniform(0, 13)))
         scored = rng.randint(0, 1)
         most, need = shares_in(plan, shape, -1, scored)
+        for more in (0, 4096, need // 9):
+            assert shares_in(plan, shape, need + more, scored) == (most, need), (shape, more)
         scratch = rng.randint(0, need)
         got, used = shares_in(plan, shape, scratch, scored)
         assert used <= scratch and (used > 0) == (got > 0) and got != 1, (shape, scratch)
@@ -188,6 +190,8 @@ def test_score_plans_fit_their_scratch(plan):
         Hkv, G = rng.choice([1, 2, 4, 8]), rng.choice([1, 2, 3, 4, 7, 8])
         shape = (Hkv * G, Hkv, rng.choice([64, 128]), rng.choice([0, rng.randint(0, 40000)]), rng.randint(1, 9000), 0)
         most = slices_in(plan, shape, -1)
+        for more in (0, 4096, most * Hkv):
+            assert slices_in(plan, shape, most * Hkv * (shape[3] + shape[4]) * 4 + more) == most, (shape, more)
         scratch = rng.randint(0, most * Hkv * (shape[3] + shape[4]) * 4)
         got = slices_in(plan, shape, scratch)
         assert got >= 1, (shape, scratch)
