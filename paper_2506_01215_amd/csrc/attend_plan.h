@@ -100,7 +100,9 @@ inline bool merge_with_score(const P &p, double *gain = nullptr);
 
 // What the parts of a forward pass cost, in us on 256 compute units; fitted to 2900 timings of 143 problems of 8 to 5000
 // rows over up to 37000 keys, with 32/8, 24/8, 16/4, 14/2 and 8/8 heads, each whole and with 7 to 12 numbers of shares: the
-// fits miss by 3 to 6 % in the mean.  A key tile's time depends on how many workgroups share its compute unit.
+// fits miss by 3 to 6 % in the mean there.  Of 97 larger problems at 128, more than one round of row blocks, they fall short by
+// 9 % whole and 12 % in shares, of 123 at 64 by 4 % and 2 %.  A key tile's time depends on how many workgroups share its compute
+// unit.  (Three at 64: 1.47 in that fit, in which few problems have as many; 8 % too much for the 123.)
 struct FwdCost {
     int resident;                                        // workgroups on a compute unit
     double whole, whole_begin, whole_tile[3];            // a launch; the start of a row block, in tiles; a tile with 1, 2, 3 on the unit
@@ -112,7 +114,7 @@ inline FwdCost fwd_cost(int D)
     if (ROWS == kFwdRows)
         return D == 64 ? FwdCost{1, 2.0, 5.2, {1.02, 1.02, 1.02}, 8.6, 3.3, {1.07, 1.07, 1.07}, 0.52, 1.34}
                        : FwdCost{1, 3.0, 3.4, {1.46, 1.46, 1.46}, 7.5, 3.4, {1.46, 1.46, 1.46}, 0.36, 4.0};
-    return D == 64 ? FwdCost{3, 5.3, 0.0, {0.78, 0.98, 1.47}, 9.6, 2.9, {0.88, 1.20, 1.75}, 0.49, 0.0}
+    return D == 64 ? FwdCost{3, 5.3, 0.0, {0.78, 0.98, 1.35}, 9.6, 2.9, {0.88, 1.20, 1.75}, 0.49, 0.0}
                    : FwdCost{2, 3.1, 3.2, {1.19, 1.61, 1.66}, 8.8, 1.7, {1.29, 1.77, 1.77}, 0.46, 0.64};
 }
 
@@ -179,11 +181,13 @@ inline double fwd_plan(P &p, int cus, bool scored = true, size_t scratch = (size
         }
         // Equal shares pay the launch that merges them and the partial results, written and read back, which double where
         // a share begins and ends inside row blocks.  They read K and V each at a place of its own, while whole row blocks
-        // walk the same keys and find them in the L2; with more than one round of these that shows beyond the estimates
-        // (11419 rows, 16/4 heads 514 us whole, 545 with 64 shares).
+        // walk the same keys and find them in the L2; with more than one round of these that shows beyond the estimates at 128
+        // (11419 rows, 16/4 heads 464 us whole, 485 with 64 shares).  Of 97 problems of eight waves at 128 and 123 at 64, timed in
+        // both ways, a choice by the estimates takes 0.5 % and 0.2 % more than the faster way, at worst 7 % and 4 %; with the
+        // whole blocks' times 0.94 0.05 % and 0.9 %, at worst 3 % and 13 % (12040 rows, 8/8 heads of 64 188 us in shares, 205 whole).
         const double whole_time = best;
-        if (whole > cus) best *= 0.94;
-        // (pieces of one row block are merged sooner: 132 rows over 5890 keys, 32/8 heads 22.1 us with 32 shares, 22.7 with 28)
+        if (whole > cus && (p.D == 128 || ROWS != kFwdRows)) best *= 0.94;
+        // (pieces of one row block are merged sooner: 132 rows over 5890 keys, 8/8 heads 20.8 us with 32 shares, 21.6 with 28)
         const double mb = p.part_rows * p.D * (p.n_row_blocks == 1 ? 3e-6 : 4e-6), full = p.part_rows * p.D / (256.0 * 128.0);
         for (long s = most; s >= 2; s -= (s + 7) / 8) {
             p.shares = (int)s;
@@ -216,7 +220,7 @@ inline void fwd_choose_within(P &p, int cus, bool scored, size_t scratch)
     const double eight = fwd_plan(p, cus, scored, scratch);
     p.narrow = 0;
     if (eight == 0.0 || p.G * p.Ct <= 16) return;
-    // Shares have to promise more: estimated 4 % ahead, 326 rows over 23729 keys, 8/8 heads took 80.8 us, not 77.5.  One row
+    // Shares have to promise more: estimated 4 % ahead, 326 rows over 23729 keys, 8/8 heads take 62.7 us, not 53.2.  One row
     // block of many keys is bound by reading them, with half the loads in flight (96 over 30179, 8/8 29.7 us, with four 36.6).
     P q = p;
     const double four = fwd_plan<kFwdNarrowRows>(q, cus, scored, scratch);

@@ -89,6 +89,11 @@ def test_shared_out_row_blocks_of_eight_waves_have_their_shapes():
     (16, 4, 64, 10178, 873, 2),       # 56.8, 61.5
     (32, 8, 128, 569, 2651, 0),       # 87.5, 98.4
     (32, 8, 128, 32768, 32768, 0),
+    # more than one round of row blocks at 64
+    (8, 8, 64, 0, 12040, 2),          # 187.8, whole 204.7
+    (14, 2, 64, 4010, 5232, 2),       # 160.1, whole 173.0
+    (16, 4, 64, 0, 5379, 1),          # 95.6 whole, 91.9 in shares, 82.0
+    (16, 4, 64, 0, 4763, 1),          # 77.6 in shares, 71.8
     # shares of many tiles
     (8, 8, 128, 51873, 379, 2),       # 98.5, 120.3
     (8, 8, 128, 53803, 284, 2),       # 94.7, 111.7
