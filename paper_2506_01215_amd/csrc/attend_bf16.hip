@@ -145,6 +145,8 @@ __device__ __forceinline__ float softmax_row(const f32x4 (&s)[4], float c, float
 // NW = 4 (the narrow form; where it is taken and what it gives: fwd_choose): 128 rows by four waves, two V slots and no wave
 // lagging, as the other workgroups of the compute unit (two, at head_dim 64 three: 168 registers there) are out of step by
 // themselves.  At 64 three waves per SIMD take 15 % fewer cycles on a large problem, at a clock that falls by 10 % (power).
+// Shared out it spills in the set-up and the end of a segment, outside the loop over key tiles: 22 registers at 64 (5 where row
+// blocks are whole), 11 at 128 (none); the forms of eight waves spill none.
 //
 // MFMA shape: v_mfma_f32_16x16x32_bf16 (A[m][k]: lane l holds m = l%16, k = 8*(l/16)..+7; B[k][n]:
 // n = l%16, same k; C[m][n]: n = l%16, m = 4*(l/16) + e).  Measured on gfx950 with random bf16
@@ -193,7 +195,7 @@ __device__ __forceinline__ void fwd_segment(const AttnParams &p, u16 *smem, int 
     constexpr int NV = 2 * DB;           // V^T fragments per tile (key pair, d block)
 
     u16 *ldsK = smem;                          // [2][KTILE]
-    u16 *ldsV = smem + 2 * KTILE;              // [3][VTILE]
+    u16 *ldsV = smem + 2 * KTILE;              // [VSLOTS][VTILE]
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -203,7 +205,7 @@ __device__ __forceinline__ void fwd_segment(const AttnParams &p, u16 *smem, int 
 
     const int rows = p.G * p.Ct;
     // Which 32 of the row block's rows the wave has: lane's row in 16-row block nb is row0 + rstep * (16 nb
-    // + ln).  p.by_head (G divides the waves, so a full row block is kFwdRows / G chunk rows of every head): consecutive
+    // + ln).  p.by_head (G divides the waves, so a full row block is ROWS / G chunk rows of every head): consecutive
     // chunk rows of one head; otherwise consecutive rows.
     const int slab = p.by_head ? wave / p.G : wave, rstep = p.by_head ? p.G : 1;
     const int row0 = rb * ROWS + slab * 32 * rstep + (p.by_head ? wave % p.G : 0);
@@ -263,13 +265,14 @@ __device__ __forceinline__ void fwd_segment(const AttnParams &p, u16 *smem, int 
     // To make one wave's MFMAs meet the other's softmax, the waves of the upper half run their
     // O^T += V^T P^T one tile late: iteration t does P.V of tile t-1 first, then Q.K^T and the
     // softmax of tile t, keeping the probabilities in registers across the barrier.  V therefore
-    // lives in three LDS slots (tile u in slot u%3), K in two.
+    // lives in three LDS slots (tile u in slot u%3), K in two.  (Without lagging waves V has two: every wave
+    // reads tile t between the barriers around it.)
     const bool lag = LAG && wave >= NW / 2;
     // last tile of the range this wave needs
     const int tl = SPLIT ? (wave_last_key >= 0 ? min(wave_last_key / BN, ntiles - 1) : -1)
                          : (wave_last_key >= 0 ? wave_last_key / BN : -1);
     v4u pb[2][2];
-    int vslot = 0;                                                    // t mod 3
+    int vslot = 0;                                                    // t mod VSLOTS
 
     auto mask_tile = [&](f32x4 (&s)[2][4], int j0) {
         if (j0 + BN - 1 > M + wave_first_row) {
@@ -454,7 +457,7 @@ __device__ __forceinline__ void fwd_segment(const AttnParams &p, u16 *smem, int 
         __syncthreads();
     }
     if (lag && tl == ntiles - 1) {
-        // the lagging waves still owe the P.V of their last tile (slot (ntiles-1) % 3)
+        // the lagging waves (three V slots) still owe the P.V of their last tile (slot (ntiles-1) % 3)
         const u16 *sv = ldsV + (vslot == 0 ? 2 : vslot - 1) * VTILE + v_frag0;
 #pragma unroll
         for (int f = 0; f < NV; ++f) {

@@ -1,7 +1,7 @@
 // How the bf16 forward pass and the score pass of a problem are cut into workgroups.  Plain arithmetic without a
 // device type, shared by the launcher, the kernels and a host program that replays it; P is AttnParams, or
-// has its fields Hkv, G, D, M, Ct, n_row_blocks, by_head, shares, start, tiles and part_rows, and for the
-// score also n, W, slices, slice_tiles, head_slices and slice_heads.  Sizes reach 2^30 keys and 2^31 query rows,
+// has its fields Hkv, G, D, M, Ct, n, W, n_row_blocks, by_head, narrow, shares, start, tiles and part_rows, and for
+// the score slices, slice_tiles, head_slices and slice_heads.  Sizes reach 2^30 keys and 2^31 query rows,
 // so no product of keys and heads may be formed in 32 bits.
 #pragma once
 
@@ -52,7 +52,7 @@ struct FwdWalk {
     }
     RF_PLAN explicit FwdWalk(const P &p) : rb(0), pos(p.start)
     {
-        // 63 G fits: a split problem has at most four row blocks per compute unit, so G < 2^20
+        // 63 G fits: a split problem has at most eight row blocks of 128 per compute unit, so G < 2^20
         const int a = (p.M % 64 * p.G + ROWS - 1) / 64;
         q = p.M / 64 + a / p.G;
         r = a % p.G;
@@ -263,7 +263,9 @@ inline size_t score_slice_bytes(const P &p) { return p.slices > 1 ? (size_t)p.sl
 //     of about 1.5 tiles each and of a launch that adds the slices up (2 tiles, 3 of the narrow form's).
 //   - Which four-wave form: a workgroup of the narrow one starts and ends sooner, and with three or four on a compute unit
 //     one's start and loads lie under the others' work; a long pass is bound by the power budget, and there twice the reads
-//     of Q per key cost 5 %.  At 64 a pass is bound by its VALU work and the narrow form is the faster one at every size.
+//     of Q per key cost 5 %.  At 64 a pass is bound by its VALU work, and of the four-wave forms the
+//     narrow one is the faster at every size; eight waves stay where one round of them fills the chip (they are up to 8 % faster
+//     there than estimated: a window of 128 rows over 14086 keys, 24/8 heads 16.5, narrow 17.8).
 // Measured at head_dim 128, us, eight waves / four of 64 keys / of 32, each with its best number of slices: 300 rows over
 // 1300 keys, 32/8 heads 46 / 18 / 15.2; 500 over 4596, 8/8 25.5 / 19.9 / 16.1; 4000 over 4000, 16/4 467 / 78 / 62; 1000 over
 // 3000, 32/8 132 / 46 / 37.8; 3000 over 3512, 8/8 94 / 36.6 / 28.7; 150 over 20150, 24/8 49 / 44.9 / 35.7; windows of 128 over
@@ -299,8 +301,8 @@ inline int score_plan_within(P &p, int cus, size_t scratch)
     p.slices = p.head_slices = 1;
     p.slice_tiles = tiles;
     p.slice_heads = p.G;
-    // slices of `per` tiles of `heads` heads, by workgroups of `keys` keys, `resident` of them on a compute unit; a full one
-    // takes `rate` a tile, the first tile `begin` more, the last ones leave `tail` of an item idle
+    // slices of `per` tiles of `heads` heads, by workgroups of `keys` keys, `resident` of them on a compute unit; a full unit
+    // takes `rate` a tile, a workgroup alone on one `alone`, the first tile `begin` more, the last ones leave `tail` of an item idle
     auto price = [&](int f, int keys, double resident, double rate, double tail, double alone, double begin, double fixed,
                      int per, int heads) {
         const int hs = (p.G + heads - 1) / heads, slices = (tiles + per - 1) / per * hs;
