@@ -767,9 +767,8 @@ __global__ __launch_bounds__(256) void attn_fwd_merge(AttnParams p)
 // Per logit the VALU does one v_fma (scale and -lse folded), one v_exp and one v_add; the mask is
 // applied only on the tiles that straddle the causal diagonal (separate, rarely taken path), and
 // rows past the chunk end are switched off through lse = +inf.
-template <int D, int NT>
+template <int D, int NT, int QT>
 struct QStage {
-    static constexpr int QT = 64;
     static constexpr int QROW = D + 16;
     static constexpr int C8 = D / 8;
     static constexpr int PIECES = QT * C8 / NT;
@@ -838,14 +837,26 @@ struct QStage {
 // 24/8 19.7 -> 15.0; 128 wide, 1000 over 3000, 32/8 48.7 -> 38.6; 500 over 4596, 8/8 23.3 -> 16.7.  See score_plan.
 //
 // WINDOW: not every row observes.  Without it the first observing row is 0 at compile time.
-template <int D, int KB, int NW, bool WINDOW>
+//
+// QT: rows of a query tile, between two barriers.  A wave that waits at one leaves its SIMD to a single wave, which hides
+// neither its exponentials nor its MFMAs, so long passes of eight waves take tiles of 192 rows (64, 128, 192: 12.13, 11.89, 11.76
+// ms for 32768 rows over 65536 keys, 32/8 heads; 256 spill).  With two or more workgroups on a unit one computes while the other
+// waits, and 128 rows give nothing (8192 over 16384 809, 822 us).
+//
+// SPREAD: the exponentials of both units of a loop trip lie between MFMAs.  Left alone the compiler finds the same flush of the
+// pending unit on both sides of the diagonal branch and moves it in front, so that every other unit's VALU work runs by itself.
+// us, moved / spread: 8192 rows over 16384, 32/8 heads 827 / 818, 16/4 of 64 298 / 295, 32768 over 65536, 32/8 of 64 8530 /
+// 8430; but eight waves with tiles of 64 rows 12.01 / 12.13 ms, 25 over 15606 15.86 / 16.03, and windows at 64, of a few trips,
+// 14.9 / 15.1: those keep the former.
+template <int D, int KB, int NW, bool WINDOW, int QT>
 __global__ __launch_bounds__(NW * 64, KB == 2 ? (D == 64 ? 4 : 3) : 2) void attn_score_bf16(AttnParams p)
 {
     constexpr int NT = NW * 64;
     constexpr int KS = D / 32;                           // MFMA k-steps
-    using Stage = QStage<D, NT>;
-    constexpr int QT = Stage::QT, QROW = Stage::QROW;
+    using Stage = QStage<D, NT, QT>;
+    constexpr int QROW = Stage::QROW;
     constexpr int WKEYS = 16 * KB;
+    constexpr bool SPREAD = D == 128 ? NW == 4 || QT > 64 : !WINDOW;
     constexpr int NQB = QT / 16;                         // 16-row query blocks per tile
     static_assert(NQB % 4 == 0, "the rotation below alternates two units of two query blocks");
 
@@ -967,7 +978,12 @@ __global__ __launch_bounds__(NW * 64, KB == 2 ? (D == 64 ? 4 : 3) : 2) void attn
 #pragma unroll
         for (int u = 0; u < 2 * KS * KB; ++u) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);     // one MFMA ...
-            __builtin_amdgcn_sched_group_barrier(0x402, 384 / D, 0);   // ... then its share of the VALU/transcendental ops
+            if constexpr (SPREAD) {
+                __builtin_amdgcn_sched_group_barrier(0x400, 128 / D, 0);   // ... then its share of the exponentials
+                __builtin_amdgcn_sched_group_barrier(0x002, 256 / D, 0);   // and of the other VALU work
+            } else {
+                __builtin_amdgcn_sched_group_barrier(0x402, 384 / D, 0);
+            }
         }
     };
     for (int it = 0; it < iters; ++it) {
@@ -979,8 +995,10 @@ __global__ __launch_bounds__(NW * 64, KB == 2 ? (D == 64 ? 4 : 3) : 2) void attn
                 // ---- every row of the tile sees every key of this wave
 #pragma unroll
                 for (int qb = 0; qb < NQB; qb += 4) {
+                    if (qb > 0 && 16 * qb >= p.Ct - i0) break;   // groups of 64 rows past the chunk's end
                     const float l0 = ldsL[buf][16 * qb + ln], l1 = ldsL[buf][16 * qb + 16 + ln];
                     const float l2 = ldsL[buf][16 * qb + 32 + ln], l3 = ldsL[buf][16 * qb + 48 + ln];
+                    if constexpr (SPREAD) __builtin_amdgcn_sched_barrier(0);
                     issue_mfma2(sA, sq + 16 * qb * QROW);
                     accumulate2(sB, lsB0, lsB1);
                     interleave_pattern();
@@ -993,7 +1011,8 @@ __global__ __launch_bounds__(NW * 64, KB == 2 ? (D == 64 ? 4 : 3) : 2) void attn
                     lsB1 = l3;
                 }
             } else {
-                asm volatile("; diagonal path" ::: "memory");
+                if constexpr (SPREAD) asm volatile("; diagonal path" : "+v"(lsB0), "+v"(lsB1) :: "memory");
+                else asm volatile("; diagonal path" ::: "memory");
                 accumulate2(sB, lsB0, lsB1);          // flush the pending unit first
                 lsB0 = INFINITY;
                 lsB1 = INFINITY;
@@ -1318,8 +1337,12 @@ static hipError_t launch_score_tiled(const AttnParams &p, hipStream_t st)
 {
     constexpr int keys_wg = NW * 16 * KB;
     const int grid = p.Hkv * ((p.n + keys_wg - 1) / keys_wg) * p.slices;
-    if (p.W == p.Ct) hipLaunchKernelGGL((attn_score_bf16<D, KB, NW, false>), dim3(grid), dim3(NW * 64), 0, st, p);
-    else hipLaunchKernelGGL((attn_score_bf16<D, KB, NW, true>), dim3(grid), dim3(NW * 64), 0, st, p);
+    // Long tiles from 512 rows on: eight waves, 512 rows over 60512 keys, 32/8 heads 275 -> 272 us, 2100 over 64100 1028 -> 998,
+    // but 25 over 15606 15.9 -> 25.8.  (Passes of eight waves are uncut, so slices do not meet tiles of another size.)
+    constexpr int LONG = NW == 8 && D == 128 ? 192 : 64;
+    if (p.W == p.Ct && p.Ct >= 512) hipLaunchKernelGGL((attn_score_bf16<D, KB, NW, false, LONG>), dim3(grid), dim3(NW * 64), 0, st, p);
+    else if (p.W == p.Ct) hipLaunchKernelGGL((attn_score_bf16<D, KB, NW, false, 64>), dim3(grid), dim3(NW * 64), 0, st, p);
+    else hipLaunchKernelGGL((attn_score_bf16<D, KB, NW, true, 64>), dim3(grid), dim3(NW * 64), 0, st, p);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.slices == 1) return e;
     hipLaunchKernelGGL(attn_score_sum, dim3((p.n + 255) / 256, p.Hkv), dim3(256), 0, st, p, keys_wg);
