@@ -692,9 +692,15 @@ __device__ __forceinline__ int fwd_row_block_pos(const AttnParams &p, int rb)
 // pieces of one query row, four output columns per lane.  Each piece is a dependent load and an
 // exponential, so with many pieces per row (MANY: a token's row has as many as its KV head has
 // shares) all groups of a workgroup take one row together, and their sums meet in LDS: 33 pieces
-// of one row 8 us with one group, 3 us with eight.  grid (rows of a row block / rows per
-// workgroup, row block, KV head).
-template <int D, int ROWS, bool MANY>
+// of one row 8 us with one group, 3 us with eight.  grid (KV head, rows of a row block / rows per workgroup, row block):
+// the KV head is the fastest index, as in the pass that leaves the pieces, so with eight heads a head's pieces are in
+// the L2 of the XCD that reads them (whole calls, us, KV head slowest / fastest, one state over and over: 300 rows over 1300
+// keys, 32/8 heads 47.4 / 41.2; 40 over 2040 28.4 / 24.9; 130 over 1130, 8/8 22.7 / 21.3; 17 over 4113, 8/8 15.3 / 14.7; three
+// states with a workspace each in turn: 43.3 / 42.4, 25.4 / 25.2, 22.7 / 21.3, 15.68 / 15.64).
+// RPT: rows of a thread, whose pieces are asked for together; two where there are several workgroups to a unit all the same
+// (attention alone, us, one / two / four rows: 3001 over 11193, 32/8 415 / 409 / 409, 1500 over 5500 120.8 / 119.2 /
+// 119.3, 24/8 of 64 208.6 / 207.0 / 207.5, 2500 over 5500, 16/4 of 64 67.0 / 66.1 / 66.8; 1000 over 5000, 8/8 60.4 / - / 61.9).
+template <int D, int ROWS, bool MANY, int RPT = 1>
 __device__ __forceinline__ void fwd_merge(const AttnParams &p, int bx, int rb, int kvh)
 {
     constexpr int L = D / 4, GROUPS = 256 / L;
@@ -706,55 +712,73 @@ __device__ __forceinline__ void fwd_merge(const AttnParams &p, int bx, int rb, i
     const int j0 = pieces.j0, j1 = pieces.j1;
     if (j0 == j1) return;                                // finished by one workgroup
     const int grp = threadIdx.x / L, c4 = (threadIdx.x % L) * 4;
-    const int pr = MANY ? bx : bx * GROUPS + grp;
-    if (pr >= p.part_rows) return;
-    if (rb * ROWS + pr >= p.G * p.Ct) return;
-    const int row = (rb * ROWS + pr) / p.G, head = kvh * p.G + (rb * ROWS + pr) % p.G;
-    auto piece = [&](int j) -> size_t { return (size_t)pieces.slot(p, j, kvh) * p.part_rows + pr; };
+    // rows of this thread: pr0, pr0 + GROUPS, ...
+    const int pr0 = MANY ? bx : bx * RPT * GROUPS + grp;
+    const int rows_here = min(p.part_rows, p.G * p.Ct - rb * ROWS);
+    if (pr0 >= rows_here) return;
     const int first = MANY ? j0 + grp : j0, step = MANY ? GROUPS : 1;
-    float m = -INFINITY, l = 0.f;
-    f32x4 o = {0.f, 0.f, 0.f, 0.f};
-    auto add = [&](float pm, float pl, f32x4 x) {        // pm = -inf: a piece without a visible key
-        const float m_new = fmaxf(m, pm);
-        const float a = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - m_new);
+    float m[RPT], l[RPT];
+    f32x4 o[RPT];
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+        m[i] = -INFINITY;
+        l[i] = 0.f;
+        o[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
+    auto add = [&](int i, float pm, float pl, f32x4 x) { // pm = -inf: a piece without a visible key
+        const float m_new = fmaxf(m[i], pm);
+        const float a = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m[i] - m_new);
         const float w = m_new == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(pm - m_new);
-        m = m_new;
-        l = fmaf(l, a, w * pl);
+        m[i] = m_new;
+        l[i] = fmaf(l[i], a, w * pl);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = fmaf(o[e], a, w * x[e]);
+        for (int e = 0; e < 4; ++e) o[i][e] = fmaf(o[i][e], a, w * x[e]);
     };
-    for (int j = first; j <= j1; j += 4 * step) {        // four pieces in flight
-        float2 ml[4];
-        f32x4 x[4];
+    constexpr int FLY = RPT == 1 ? 4 : 2;                // pieces in flight of each row
+    for (int j = first; j <= j1; j += FLY * step) {
+        float2 ml[FLY][RPT];
+        f32x4 x[FLY][RPT];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const size_t at = piece(min(j + u * step, j1));
-            ml[u] = p.part_ml[at];
-            x[u] = *(const f32x4 *)(p.part_o + at * D + c4);
+        for (int u = 0; u < FLY; ++u) {
+            const size_t at = (size_t)pieces.slot(p, min(j + u * step, j1), kvh) * p.part_rows;
+#pragma unroll
+            for (int i = 0; i < RPT; ++i) {
+                const size_t r = at + min(pr0 + i * GROUPS, rows_here - 1);
+                ml[u][i] = p.part_ml[r];
+                x[u][i] = *(const f32x4 *)(p.part_o + r * D + c4);
+            }
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (j + u * step <= j1) add(ml[u].x, ml[u].y, x[u]);
+        for (int u = 0; u < FLY; ++u)
+            if (j + u * step <= j1) {
+#pragma unroll
+                for (int i = 0; i < RPT; ++i) add(i, ml[u][i].x, ml[u][i].y, x[u][i]);
+            }
     }
     if constexpr (MANY) {
-        so[grp][c4 / 4] = o;
-        if (c4 == 0) sml[grp] = make_float2(m, l);
+        so[grp][c4 / 4] = o[0];
+        if (c4 == 0) sml[grp] = make_float2(m[0], l[0]);
         __syncthreads();
         if (grp) return;
-        for (int g = 1; g < GROUPS; ++g) add(sml[g].x, sml[g].y, so[g][c4 / 4]);
+        for (int g = 1; g < GROUPS; ++g) add(0, sml[g].x, sml[g].y, so[g][c4 / 4]);
     }
-    const float inv = 1.0f / l;
-    v2u w;
-    w.x = pack_bf16x2(o[0] * inv, o[1] * inv);
-    w.y = pack_bf16x2(o[2] * inv, o[3] * inv);
-    *(v2u *)((u16 *)p.out + (size_t)head * p.o_hs + (size_t)row * p.o_rs + c4) = w;
-    if (c4 == 0) p.lse[(size_t)head * p.Ct + row] = (m + __builtin_amdgcn_logf(l)) * kLn2;
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+        if (pr0 + i * GROUPS >= rows_here) break;
+        const int r = rb * ROWS + pr0 + i * GROUPS, row = r / p.G, head = kvh * p.G + r % p.G;
+        const float inv = 1.0f / l[i];
+        v2u w;
+        w.x = pack_bf16x2(o[i][0] * inv, o[i][1] * inv);
+        w.y = pack_bf16x2(o[i][2] * inv, o[i][3] * inv);
+        *(v2u *)((u16 *)p.out + (size_t)head * p.o_hs + (size_t)row * p.o_rs + c4) = w;
+        if (c4 == 0) p.lse[(size_t)head * p.Ct + row] = (m[i] + __builtin_amdgcn_logf(l[i])) * kLn2;
+    }
 }
 
-template <int D, int ROWS, bool MANY>
+template <int D, int ROWS, bool MANY, int RPT>
 __global__ __launch_bounds__(256) void attn_fwd_merge(AttnParams p)
 {
-    fwd_merge<D, ROWS, MANY>(p, blockIdx.x, blockIdx.y, blockIdx.z);
+    fwd_merge<D, ROWS, MANY, RPT>(p, blockIdx.y, blockIdx.z, blockIdx.x);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1059,10 +1083,10 @@ __global__ __launch_bounds__(NW * 64, KB == 2 ? (D == 64 ? 4 : 3) : 2) void attn
 }
 
 // Adds up the slices of every key, in order; slices that lie before a key block's diagonal were
-// not written.  keys: keys of one workgroup of the score pass.
+// not written.  keys: keys of one workgroup of the score pass.  As in that pass the KV head is blockIdx % Hkv (see fwd_merge).
 __global__ __launch_bounds__(256) void attn_score_sum(AttnParams p, int keys)
 {
-    const int j = blockIdx.x * 256 + threadIdx.x, kvh = blockIdx.y;
+    const int j = blockIdx.x / p.Hkv * 256 + threadIdx.x, kvh = blockIdx.x % p.Hkv;
     if (j >= p.n) return;
     const int i_lo = p.Ct - p.W, i_first = max(i_lo, max(j / keys * keys - p.M, 0));
     float x = 0.f;
@@ -1258,7 +1282,7 @@ __global__ __launch_bounds__(256) void attn_merge_score(AttnParams p, int n_scor
 {
     const int bid = blockIdx.x - n_score;
     if (bid < 0) score_few_keys<D, KB, 1, ROWS>(p, blockIdx.x);
-    else fwd_merge<D, ROWS, true>(p, bid % p.part_rows, bid / p.part_rows % p.n_row_blocks, bid / p.part_rows / p.n_row_blocks);
+    else fwd_merge<D, ROWS, true>(p, bid / p.Hkv % p.part_rows, bid / p.Hkv / p.part_rows, bid % p.Hkv);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1321,14 +1345,19 @@ static hipError_t launch_fwd(const AttnParams &p, bool split, hipStream_t st)
     // (11200 rows of up to 8 pieces at head_dim 64: 19 us with a workgroup per row, 6 us without)
     const long merged_rows = (long)p.Hkv * p.n_row_blocks * p.part_rows;
     if (pieces > 12 || (pieces > 6 && merged_rows <= 2048)) {
-        const dim3 mgrid(p.part_rows, p.n_row_blocks, p.Hkv);
-        if (p.narrow) hipLaunchKernelGGL((attn_fwd_merge<D, kFwdNarrowRows, true>), mgrid, dim3(256), 0, st, p);
-        else hipLaunchKernelGGL((attn_fwd_merge<D, kFwdRows, true>), mgrid, dim3(256), 0, st, p);
-    } else {
-        const dim3 mgrid((p.part_rows + groups - 1) / groups, p.n_row_blocks, p.Hkv);
-        if (p.narrow) hipLaunchKernelGGL((attn_fwd_merge<D, kFwdNarrowRows, false>), mgrid, dim3(256), 0, st, p);
-        else hipLaunchKernelGGL((attn_fwd_merge<D, kFwdRows, false>), mgrid, dim3(256), 0, st, p);
+        const dim3 mgrid(p.Hkv, p.part_rows, p.n_row_blocks);
+        if (p.narrow) hipLaunchKernelGGL((attn_fwd_merge<D, kFwdNarrowRows, true, 1>), mgrid, dim3(256), 0, st, p);
+        else hipLaunchKernelGGL((attn_fwd_merge<D, kFwdRows, true, 1>), mgrid, dim3(256), 0, st, p);
+        return hipGetLastError();
     }
+    auto launch = [&](auto rpt) {
+        constexpr int RPT = decltype(rpt)::value;
+        const dim3 mgrid(p.Hkv, (p.part_rows + RPT * groups - 1) / (RPT * groups), p.n_row_blocks);
+        if (p.narrow) hipLaunchKernelGGL((attn_fwd_merge<D, kFwdNarrowRows, false, RPT>), mgrid, dim3(256), 0, st, p);
+        else hipLaunchKernelGGL((attn_fwd_merge<D, kFwdRows, false, RPT>), mgrid, dim3(256), 0, st, p);
+    };
+    if (merged_rows > 16384) launch(std::integral_constant<int, 2>{});
+    else launch(std::integral_constant<int, 1>{});
     return hipGetLastError();
 }
 
@@ -1345,7 +1374,7 @@ static hipError_t launch_score_tiled(const AttnParams &p, hipStream_t st)
     else hipLaunchKernelGGL((attn_score_bf16<D, KB, NW, true, 64>), dim3(grid), dim3(NW * 64), 0, st, p);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.slices == 1) return e;
-    hipLaunchKernelGGL(attn_score_sum, dim3((p.n + 255) / 256, p.Hkv), dim3(256), 0, st, p, keys_wg);
+    hipLaunchKernelGGL(attn_score_sum, dim3((p.n + 255) / 256 * p.Hkv), dim3(256), 0, st, p, keys_wg);
     return hipGetLastError();
 }
 
