@@ -677,6 +677,202 @@ __global__ __launch_bounds__(kFwdWaves * 64) void attn_fwd_few(AttnParams p)
     }
 }
 
+// The whole pass of 32 query rows by one workgroup, for problems of few rows and not too many keys: each wave takes every NW-th
+// 32-key tile, as in attn_fwd_few, and their sums meet in LDS, so there are eight times as many workgroups as row
+// blocks of attn_fwd_bf16, no barrier before the end, no pieces and no launch that merges them.  Bound: K and V, which every
+// workgroup reads by itself, at what a compute unit gets from the L2 (32 keys of 256 bytes 0.2 us).  So both are read as
+// whole rows and pass through LDS of the wave's own: with K as A operands straight from memory, 64 bytes of a row at a time, 739
+// rows over 1691 keys, 8/8 heads 20.5 us, so 18.4.  Eight waves where every workgroup has a compute unit, else four (102 rows
+// over 3078, 32/8 heads of 64 14.6, four 18.1; 302 over 346, 32/32 13.1, four 10.1).  Attention alone, attn_fwd_bf16's plan /
+// this, us: 64 wide, 60 rows over 1060 keys, 32/8 heads 15.4 / 9.2; 767 over 841, 4/4 14.5 / 7.6; 600 over 600, 32/8 12.4 / 8.6;
+// 128 wide, 130 over 1130, 32/8 19.9 / 13.6; 300 over 300, 32/8 12.2 / 9.9; 300 over 1300, 8/8 16.9 / 14.5, 14/2 19.1 / 14.9.
+// Where it is taken: fwd_short.
+template <int D, int NW>
+__global__ __launch_bounds__(NW * 64, 2) void attn_fwd_short(AttnParams p)
+{
+    constexpr int NB = 2, KS = D / 32, DB = D / 16, C8 = D / 8, VP = D / 16;
+    constexpr int VROW = D + 16, OROW = D + 4, R = kFwdShortRows, TILE = 32 * VROW;
+    static_assert(R == 16 * NB, "two query blocks to a wave");
+    __shared__ __attribute__((aligned(16))) union { u16 kv[NW][2 * TILE]; float o[NW / 2][R][OROW]; } sh;
+    __shared__ float sm[NW][R], sl[NW][R];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int ln = lane & 15, lg = lane >> 4;
+    const int kvh = blockIdx.x % p.Hkv, rows = p.G * p.Ct;
+    const int row0 = (p.n_row_blocks - 1 - (int)blockIdx.x / p.Hkv) * R, rows_here = min(R, rows - row0);   // late (long) ones first
+    const int tiles = (p.M + (row0 + rows_here - 1) / p.G) / 32 + 1;
+    const u16 *Kg = (const u16 *)p.k + (size_t)kvh * p.cap * D;
+    const u16 *Vg = (const u16 *)p.v + (size_t)kvh * p.cap * D;
+
+    // 16-byte pieces of a tile: piece i of a lane lies in row lane / C8 + i * (64 / C8)
+    v4u kreg[VP], vreg[VP];
+    const uint32_t off0 = (uint32_t)(lane / C8 * D + lane % C8 * 8) * 2u;
+    auto load = [&](int s) {
+        const char *kt = (const char *)(Kg + (size_t)s * 32 * D), *vt = (const char *)(Vg + (size_t)s * 32 * D);
+        const int last = p.n - 1 - s * 32;
+        if (last >= 31) {
+#pragma unroll
+            for (int i = 0; i < VP; ++i) {
+                kreg[i] = *(const v4u *)(kt + (off0 + (uint32_t)(i * 128 / C8 * D)));
+                vreg[i] = *(const v4u *)(vt + (off0 + (uint32_t)(i * 128 / C8 * D)));
+            }
+        } else {                                         // rows past the end repeat the last one
+#pragma unroll
+            for (int i = 0; i < VP; ++i) {
+                const uint32_t off = (uint32_t)(min(lane / C8 + i * (64 / C8), last) * D + lane % C8 * 8) * 2u;
+                kreg[i] = *(const v4u *)(kt + off);
+                vreg[i] = *(const v4u *)(vt + off);
+            }
+        }
+    };
+    int s = wave;
+    if (s < tiles) load(s);
+    v4u qreg[NB][KS];
+    int lim[NB];                                         // last key the row sees
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        const int row = min(row0 + nb * 16 + ln, rows - 1), chunk_row = row / p.G;
+        lim[nb] = p.M + chunk_row;
+        const u16 *src = (const u16 *)p.q + (size_t)(kvh * p.G + row % p.G) * p.q_hs + (size_t)chunk_row * p.q_rs + 8 * lg;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) qreg[nb][ks] = *(const v4u *)(src + ks * 32);
+    }
+    f32x4 o[NB][DB];
+    float m[NB], l[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        m[nb] = -INFINITY;
+        l[nb] = 0.f;
+#pragma unroll
+        for (int db = 0; db < DB; ++db) o[nb][db] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
+    const float c = p.scale * kLog2e;
+    u16 *sk = sh.kv[wave], *sv = sk + TILE;
+    for (; s < tiles; s += NW) {
+        const int j0 = s * 32;
+#pragma unroll
+        for (int i = 0; i < VP; ++i) {
+            const int at = (lane / C8 + i * (64 / C8)) * VROW + lane % C8 * 8;
+            *(v4u *)(sk + at) = kreg[i];
+            *(v4u *)(sv + at) = vreg[i];
+        }
+        if (s + NW < tiles) load(s + NW);
+        f32x4 x[NB][2];
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) x[nb][0] = x[nb][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) {
+                const v4u a = *(const v4u *)(sk + (kb * 16 + ln) * VROW + 8 * lg + ks * 32);
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) x[nb][kb] = mfma16(a, qreg[nb][ks], x[nb][kb]);
+            }
+        if (j0 + 31 > p.M + row0 / p.G) {
+            asm volatile("; mask path" ::: "memory");
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (j0 + (e >> 2) * 16 + 4 * lg + (e & 3) > lim[nb]) x[nb][e >> 2][e & 3] = -INFINITY;
+        }
+        // as in attn_fwd_bf16: against the reference so far, and anew with the true maximum where a row outgrew it
+        v4u pb[NB];
+        float rs[NB];
+        bool big = false;
+        auto probabilities = [&](int nb, float ref) {
+            float pv[8];
+            rs[nb] = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                pv[e] = __builtin_amdgcn_exp2f(fmaf(x[nb][e >> 2][e & 3], c, -ref));
+                rs[nb] += pv[e];
+            }
+            pb[nb] = (v4u){pack_bf16x2(pv[0], pv[1]), pack_bf16x2(pv[2], pv[3]), pack_bf16x2(pv[4], pv[5]),
+                           pack_bf16x2(pv[6], pv[7])};
+        };
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            probabilities(nb, m[nb] * c);
+            big = big || !(rs[nb] < kBigSum);
+        }
+        if (__builtin_amdgcn_ballot_w64(big) != 0ull) {
+            asm volatile("; rescale path" ::: "memory");
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                float mx = -INFINITY;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) mx = fmaxf(mx, x[nb][e >> 2][e & 3]);
+                mx = fmaxf(mx, __shfl_xor(mx, 16));
+                mx = fmaxf(mx, __shfl_xor(mx, 32));
+                const float m_new = fmaxf(m[nb], mx);
+                const float ref = m_new == -INFINITY ? 0.f : m_new * c;     // -inf: the row sees no key yet
+                const float alpha = __builtin_amdgcn_exp2f(fmaf(m[nb], c, -ref));
+                m[nb] = m_new;
+                l[nb] *= alpha;
+#pragma unroll
+                for (int db = 0; db < DB; ++db) o[nb][db] *= alpha;
+                probabilities(nb, ref);
+            }
+        }
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) l[nb] += rs[nb];
+        const u16 *vf = sv + (4 * lg + (ln >> 2)) * VROW + 4 * (ln & 3);      // see lds_read_tr16
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+            const v2u lo = lds_read_tr16(vf + 16 * db), hi = lds_read_tr16(vf + 16 * VROW + 16 * db);
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) o[nb][db] = mfma16((v4u){lo.x, lo.y, hi.x, hi.y}, pb[nb], o[nb][db]);
+        }
+    }
+    // the waves' sums, as in attn_fwd_few
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        l[nb] += __shfl_xor(l[nb], 16);
+        l[nb] += __shfl_xor(l[nb], 32);
+        if (lg == 0) { sm[wave][nb * 16 + ln] = m[nb]; sl[wave][nb * 16 + ln] = l[nb]; }
+    }
+    __syncthreads();                                     // also: the last V tiles have been read
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        float m_all = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) m_all = fmaxf(m_all, sm[w][nb * 16 + ln]);
+        const float f = m[nb] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m[nb] - m_all) * c);
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+            o[nb][db] *= f;
+            if (wave >= NW / 2) *(f32x4 *)&sh.o[wave - NW / 2][nb * 16 + ln][db * 16 + 4 * lg] = o[nb][db];
+        }
+    }
+    __syncthreads();
+    if (wave < NW / 2) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int db = 0; db < DB; ++db) *(f32x4 *)&sh.o[wave][nb * 16 + ln][db * 16 + 4 * lg] += o[nb][db];
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < rows_here * (D / 4); t += NW * 64) {
+        const int r = t / (D / 4), c4 = t % (D / 4) * 4;
+        f32x4 y = *(const f32x4 *)&sh.o[0][r][c4];
+#pragma unroll
+        for (int w = 1; w < NW / 2; ++w) y += *(const f32x4 *)&sh.o[w][r][c4];
+        float m_row = -INFINITY, l_row = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) m_row = fmaxf(m_row, sm[w][r]);
+#pragma unroll
+        for (int w = 0; w < NW; ++w)                     // multiplied, not left out: NaN logits alone leave -inf and a NaN sum
+            l_row += sl[w][r] * (sm[w][r] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((sm[w][r] - m_row) * c));
+        const int chunk_row = (row0 + r) / p.G, head = kvh * p.G + (row0 + r) % p.G;
+        const float inv = 1.0f / l_row;
+        v2u w;
+        w.x = pack_bf16x2(y[0] * inv, y[1] * inv);
+        w.y = pack_bf16x2(y[2] * inv, y[3] * inv);
+        *(v2u *)((u16 *)p.out + (size_t)head * p.o_hs + (size_t)chunk_row * p.o_rs + c4) = w;
+        if (c4 == 0) p.lse[(size_t)head * p.Ct + chunk_row] = (m_row * c + __builtin_amdgcn_logf(l_row)) * kLn2;
+    }
+}
+
 // List position of row block rb's first tile, by the 64 lanes of a wave.
 template <int ROWS>
 __device__ __forceinline__ int fwd_row_block_pos(const AttnParams &p, int rb)
@@ -1312,7 +1508,12 @@ static hipError_t launch_fwd_form(const AttnParams &p, int grid, hipStream_t st)
 template <int D>
 static bool fwd_place(AttnParams &p, bool scored, void *part, size_t part_bytes)
 {
-    fwd_choose(p, compute_units(), scored, part ? part_bytes : 0);
+    const double est = fwd_choose(p, compute_units(), scored, part ? part_bytes : 0);
+    p.in_short = fwd_short(p, compute_units(), est);
+    if (p.in_short) {
+        p.shares = 0;
+        p.n_row_blocks = (p.G * p.Ct + kFwdShortRows - 1) / kFwdShortRows;
+    }
     if (!p.shares) return false;
     p.part_o = (float *)part;
     p.part_ml = (float2 *)(p.part_o + (size_t)p.shares * p.Hkv * 2 * p.part_rows * D);
@@ -1335,6 +1536,11 @@ static hipError_t launch_fwd(const AttnParams &p, bool split, hipStream_t st)
 {
     if (!split) {
         const int grid = p.Hkv * p.n_row_blocks;
+        if (p.in_short) {
+            if (p.in_short == 8) hipLaunchKernelGGL((attn_fwd_short<D, 8>), dim3(grid), dim3(512), 0, st, p);
+            else hipLaunchKernelGGL((attn_fwd_short<D, 4>), dim3(grid), dim3(256), 0, st, p);
+            return hipGetLastError();
+        }
         return p.narrow ? launch_fwd_form<D, 4, false>(p, grid, st) : launch_fwd_form<D, kFwdWaves, false>(p, grid, st);
     }
     const hipError_t e = launch_fwd_pieces<D>(p, st);

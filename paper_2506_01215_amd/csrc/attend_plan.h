@@ -215,32 +215,52 @@ inline double fwd_plan(P &p, int cus, bool scored = true, size_t scratch = (size
 // 23.2; 185 over 2775, 32/8 29.3 / 30.2; 1354 over 2834, 16/4 45.2 / 48.6; 335 over 12938, 32/8 82.9 / 96.6; 64 wide: 907 over
 // 1423, 32/8 30.6 / 24.0; 4907 over 4907 131 / 115; 1767 over 1767, 24/8 34.6 / 29.2; 2592 over 14640, 8/8 96.4 / 98.5.
 template <class P>
-inline void fwd_choose_within(P &p, int cus, bool scored, size_t scratch)
+inline double fwd_choose_within(P &p, int cus, bool scored, size_t scratch)
 {
     const double eight = fwd_plan(p, cus, scored, scratch);
     p.narrow = 0;
-    if (eight == 0.0 || p.G * p.Ct <= 16) return;
+    if (eight == 0.0 || p.G * p.Ct <= 16) return eight;
     // Shares have to promise more: estimated 4 % ahead, 326 rows over 23729 keys, 8/8 heads take 62.7 us, not 53.2.  One row
     // block of many keys is bound by reading them, with half the loads in flight (96 over 30179, 8/8 29.7 us, with four 36.6).
     P q = p;
     const double four = fwd_plan<kFwdNarrowRows>(q, cus, scored, scratch);
-    if (four >= (q.shares ? 0.95 : 0.98) * eight || (q.n_row_blocks == 1 && q.shares)) return;
+    if (four >= (q.shares ? 0.95 : 0.98) * eight || (q.n_row_blocks == 1 && q.shares)) return eight;
     // Long shares are bound by what the estimate leaves out: every row block reads its K and V by itself, and there are up to
     // twice as many.  Problems for which the estimate is for shared-out four waves, time with four over that with eight (mean,
     // worst) by the tiles of a share, at 128: up to 7 0.88, 1.07 (660 problems); 7 to 9 0.94, 1.08 (121); 9 to 12 0.98, 1.10
     // (47); 12 to 18 1.07, 1.16 (15); beyond 1.18, 1.28 (26; 379 rows over 52252 keys, 8/8 heads 98.2 us, with four 115.0).  At 64,
     // with half the bytes, 0.90 with eight KV heads, 0.95 with four, 0.99 with two beyond 9 tiles, at worst 1.07.
-    if (p.D == 128 && q.shares && q.tiles / q.shares >= 9) return;
+    if (p.D == 128 && q.shares && q.tiles / q.shares >= 9) return eight;
     p = q;
     p.narrow = 1;
+    return four;
 }
 
 // scratch: bytes there are for partial results.  What the plan wants of them does not depend on how much more there is.
+// Returns the estimate of the plan that is made.
 template <class P>
-inline void fwd_choose(P &p, int cus, bool scored, size_t scratch = (size_t)-1)
+inline double fwd_choose(P &p, int cus, bool scored, size_t scratch = (size_t)-1)
 {
-    fwd_choose_within(p, cus, scored, (size_t)-1);
-    if (fwd_split_bytes(p) > scratch) fwd_choose_within(p, cus, scored, scratch);
+    const double est = fwd_choose_within(p, cus, scored, (size_t)-1);
+    return fwd_split_bytes(p) > scratch ? fwd_choose_within(p, cus, scored, scratch) : est;
+}
+
+constexpr int kFwdShortRows = 32;                        // query rows of a workgroup of attn_fwd_short
+
+// Whether a forward pass is formed by attn_fwd_short instead of its plan, which is estimated at est us: the waves of a
+// workgroup of that form (0: not), eight where every workgroup has a compute unit, else four, two workgroups to a unit.  Its
+// time goes by the 32-key tiles of the longest workgroup or of a unit, fitted to 220 timings of 110 problems of 17 to 1300 rows
+// over up to 5000 keys, mean error 3 to 4 %.
+template <class P>
+inline int fwd_short(const P &p, int cus, double est)
+{
+    const long rows = (long)p.G * p.Ct, groups = (rows + kFwdShortRows - 1) / kFwdShortRows * p.Hkv;
+    if (rows <= 16 || est == 0.0 || groups > 4l * cus) return 0;
+    const double longest = (p.M + p.Ct - 1) / 32 + 1, first = p.M / 32 + 1;
+    const double unit = std::max(longest, 0.5 * (first + longest) * groups / cus);
+    const double t = groups <= cus ? (p.D == 64 ? 5.25 + 0.095 * unit : 6.5 + 0.195 * unit)
+                                   : (p.D == 64 ? 5.75 + 0.095 * unit + 0.04 * longest : 6.75 + 0.18 * unit + 0.12 * longest);
+    return t >= 0.88 * est ? 0 : groups <= cus ? 8 : 4;
 }
 
 // ------------------------------------------------------------------------------------------

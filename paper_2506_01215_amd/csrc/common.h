@@ -41,6 +41,7 @@ struct AttnParams {
     int slices;                // number of slices (1: uncut), = slices of the tiles x head_slices
     int slice_tiles, head_slices, slice_heads;   // query tiles of 64 rows and heads of the group in each
     float *part_score;         // [slice][KV head][n] column sums of one slice, when there are several
+    int in_short;              // host only: waves of attn_fwd_short where that forms the forward pass (see fwd_short)
     int narrow;                // host only: row blocks of 128 rows and workgroups of four waves, not 256 and eight (see fwd_choose)
 };
 

@@ -121,3 +121,11 @@ extern "C" int score_slices(int Hkv, int G, int D, int M, int Ct, int W, int cus
     if (p.slices != sets * p.head_slices || p.head_slices != (G + p.slice_heads - 1) / p.slice_heads) return -2;
     return score_slice_bytes(p) > room(scratch) ? -1 : p.slices;
 }
+
+// Waves of attn_fwd_short where that forms the forward pass instead of the plan above, else 0.
+extern "C" int short_waves(int Hkv, int G, int D, int M, int Ct, int W, int scored, int cus)
+{
+    Plan p = problem(Hkv, G, D, M, Ct, W);
+    const double est = fwd_choose(p, cus, scored != 0);
+    return fwd_short(p, cus, est);
+}
