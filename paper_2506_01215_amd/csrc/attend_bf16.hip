@@ -686,8 +686,10 @@ __global__ __launch_bounds__(kFwdWaves * 64) void attn_fwd_few(AttnParams p)
 // over 3078, 32/8 heads of 64 14.6, four 18.1; 302 over 346, 32/32 13.1, four 10.1).  Attention alone, attn_fwd_bf16's plan /
 // this, us: 64 wide, 60 rows over 1060 keys, 32/8 heads 15.4 / 9.2; 767 over 841, 4/4 14.5 / 7.6; 600 over 600, 32/8 12.4 / 8.6;
 // 128 wide, 130 over 1130, 32/8 19.9 / 13.6; 300 over 300, 32/8 12.2 / 9.9; 300 over 1300, 8/8 16.9 / 14.5, 14/2 19.1 / 14.9.
-// Where it is taken: fwd_short.
-template <int D, int NW>
+// SPLIT: each row block's key tiles in equal parts to p.shares workgroups, which leave pieces; with longer caches a block of 256
+// rows shared out leaves eight times the bytes (attention alone: 137 rows over 2287, 14/2 heads of 128 19.2 -> 14.7 us, 90 over
+// 9054, 16/4 of 64 19.7 -> 15.0, 150 over 4008, 24/8 of 128 26.7 -> 22.9).  Where it is taken: fwd_short.
+template <int D, int NW, bool SPLIT>
 __global__ __launch_bounds__(NW * 64, 2) void attn_fwd_short(AttnParams p)
 {
     constexpr int NB = 2, KS = D / 32, DB = D / 16, C8 = D / 8, VP = D / 16;
@@ -698,8 +700,11 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_fwd_short(AttnParams p)
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ln = lane & 15, lg = lane >> 4;
     const int kvh = blockIdx.x % p.Hkv, rows = p.G * p.Ct;
-    const int row0 = (p.n_row_blocks - 1 - (int)blockIdx.x / p.Hkv) * R, rows_here = min(R, rows - row0);   // late (long) ones first
-    const int tiles = (p.M + (row0 + rows_here - 1) / p.G) / 32 + 1;
+    const int group = blockIdx.x / p.Hkv, share = SPLIT ? group % p.shares : 0;
+    const int rb = p.n_row_blocks - 1 - (SPLIT ? group / p.shares : group);        // late (long) ones first
+    const int row0 = rb * R, rows_here = min(R, rows - row0);
+    const int all = (p.M + (row0 + rows_here - 1) / p.G) / 32 + 1;
+    const int begin = SPLIT ? (int)((long)all * share / p.shares) : 0, tiles = SPLIT ? (int)((long)all * (share + 1) / p.shares) : all;
     const u16 *Kg = (const u16 *)p.k + (size_t)kvh * p.cap * D;
     const u16 *Vg = (const u16 *)p.v + (size_t)kvh * p.cap * D;
 
@@ -724,7 +729,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_fwd_short(AttnParams p)
             }
         }
     };
-    int s = wave;
+    int s = begin + wave;
     if (s < tiles) load(s);
     v4u qreg[NB][KS];
     int lim[NB];                                         // last key the row sees
@@ -863,6 +868,12 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_fwd_short(AttnParams p)
 #pragma unroll
         for (int w = 0; w < NW; ++w)                     // multiplied, not left out: NaN logits alone leave -inf and a NaN sum
             l_row += sl[w][r] * (sm[w][r] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((sm[w][r] - m_row) * c));
+        if constexpr (SPLIT) {
+            const size_t at = (size_t)ShortPieces<AttnParams>(p, rb).slot(p, share, kvh) * R + r;
+            *(f32x4 *)(p.part_o + at * D + c4) = y;
+            if (c4 == 0) p.part_ml[at] = make_float2(m_row * c, l_row);
+            continue;
+        }
         const int chunk_row = (row0 + r) / p.G, head = kvh * p.G + (row0 + r) % p.G;
         const float inv = 1.0f / l_row;
         v2u w;
@@ -884,6 +895,13 @@ __device__ __forceinline__ int fwd_row_block_pos(const AttnParams &p, int rb)
     return pos + p.start;
 }
 
+template <int ROWS>
+__device__ __forceinline__ auto row_block_pieces(const AttnParams &p, int rb)
+{
+    if constexpr (ROWS == kFwdShortRows) return ShortPieces<AttnParams>(p, rb);
+    else return FwdPieces<AttnParams>(p, fwd_row_block_pos<ROWS>(p, rb), fwd_row_block_tiles<ROWS>(p, rb));
+}
+
 // Merges the pieces of the row blocks that several workgroups share: a group of D/4 lanes adds up
 // pieces of one query row, four output columns per lane.  Each piece is a dependent load and an
 // exponential, so with many pieces per row (MANY: a token's row has as many as its KV head has
@@ -902,9 +920,7 @@ __device__ __forceinline__ void fwd_merge(const AttnParams &p, int bx, int rb, i
     constexpr int L = D / 4, GROUPS = 256 / L;
     __shared__ f32x4 so[MANY ? GROUPS : 1][L];
     __shared__ float2 sml[GROUPS];
-    const int pos = fwd_row_block_pos<ROWS>(p, rb);
-    const int nt = fwd_row_block_tiles<ROWS>(p, rb);
-    const FwdPieces<AttnParams> pieces(p, pos, nt);
+    const auto pieces = row_block_pieces<ROWS>(p, rb);
     const int j0 = pieces.j0, j1 = pieces.j1;
     if (j0 == j1) return;                                // finished by one workgroup
     const int grp = threadIdx.x / L, c4 = (threadIdx.x % L) * 4;
@@ -1383,26 +1399,30 @@ __device__ __forceinline__ void score_few_keys(const AttnParams &p, int bid)
     load(x, rw);
     load(y, rw + RW);
     if constexpr (PIECES) {                              // while the keys and the first rows are on their way
-        const int rb0 = (p.Ct - p.W) * p.G / ROWS;
-        const int pos0 = fwd_row_block_pos<ROWS>(p, rb0), nt0 = fwd_row_block_tiles<ROWS>(p, rb0);
-        // the rows lie in row block rb0 and at most the next one
-        const int rb1 = min(rb0 + 1, p.n_row_blocks - 1);
+        // the rows lie in row block rb0 and at most the next one (with blocks of 32 rows in up to five)
+        constexpr bool SHORT = ROWS == kFwdShortRows;
+        const int rb0 = (p.Ct - p.W) * p.G / ROWS, rb1 = min(rb0 + 1, p.n_row_blocks - 1);
+        const int pos0 = SHORT ? 0 : fwd_row_block_pos<ROWS>(p, rb0), nt0 = SHORT ? 0 : fwd_row_block_tiles<ROWS>(p, rb0);
         const int pos1 = rb1 > rb0 ? pos0 + nt0 + p.start : pos0;
-        const FwdPieces<AttnParams> pc0(p, pos0, nt0), pc1(p, pos1, fwd_row_block_tiles<ROWS>(p, rb1));
+        const FwdPieces<AttnParams> pc0(p, pos0, nt0), pc1(p, pos1, SHORT ? 0 : fwd_row_block_tiles<ROWS>(p, rb1));
         // T threads to a row, each over every T-th piece
         const int entries = p.G * p.W, T = merge_score_lanes(entries);
         const int e = threadIdx.x / T, sub = threadIdx.x % T;
         if (e < entries) {                               // the same for all T lanes of a row
             const int row = p.Ct - p.W + e % p.W, gi = e / p.W, r = row * p.G + gi;
             const bool second = r / ROWS > rb0;
-            const int j0 = second ? pc1.j0 : pc0.j0, j1 = second ? pc1.j1 : pc0.j1, pr = r % ROWS;
+            const int j0 = SHORT ? 0 : second ? pc1.j0 : pc0.j0, j1 = SHORT ? p.shares - 1 : second ? pc1.j1 : pc0.j1, pr = r % ROWS;
+            auto slot = [&](int j) -> size_t {
+                if constexpr (SHORT) return ShortPieces<AttnParams>(p, r / ROWS).slot(p, j, kvh);
+                else return (second ? pc1 : pc0).slot(p, j, kvh);
+            };
             float m = -INFINITY, l = 0.f;
             if (j0 < j1)
                 for (int j = j0 + sub; j <= j1; j += 4 * T) {        // four pieces in flight
                     float2 x[4];
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
-                        x[u] = p.part_ml[(size_t)(second ? pc1 : pc0).slot(p, min(j + u * T, j1), kvh) * p.part_rows + pr];
+                        x[u] = p.part_ml[slot(min(j + u * T, j1)) * p.part_rows + pr];
                         if (j + u * T > j1) x[u] = make_float2(-INFINITY, 0.f);
                     }
 #pragma unroll
@@ -1508,16 +1528,31 @@ static hipError_t launch_fwd_form(const AttnParams &p, int grid, hipStream_t st)
 template <int D>
 static bool fwd_place(AttnParams &p, bool scored, void *part, size_t part_bytes)
 {
-    const double est = fwd_choose(p, compute_units(), scored, part ? part_bytes : 0);
-    p.in_short = fwd_short(p, compute_units(), est);
-    if (p.in_short) {
-        p.shares = 0;
-        p.n_row_blocks = (p.G * p.Ct + kFwdShortRows - 1) / kFwdShortRows;
-    }
+    const size_t room = part ? part_bytes : 0;
+    const double est = fwd_choose(p, compute_units(), scored, room);
+    p.in_short = fwd_short(p, compute_units(), est, scored, room);
     if (!p.shares) return false;
+    const long slots = (long)p.shares * p.Hkv * (p.in_short ? p.n_row_blocks : 2);
     p.part_o = (float *)part;
-    p.part_ml = (float2 *)(p.part_o + (size_t)p.shares * p.Hkv * 2 * p.part_rows * D);
+    p.part_ml = (float2 *)(p.part_o + (size_t)slots * p.part_rows * D);
     return true;
+}
+
+template <int D, bool SPLIT>
+static hipError_t launch_fwd_short(const AttnParams &p, int grid, hipStream_t st)
+{
+    if (SPLIT || p.in_short == 8) hipLaunchKernelGGL((attn_fwd_short<D, 8, SPLIT>), dim3(grid), dim3(512), 0, st, p);
+    else hipLaunchKernelGGL((attn_fwd_short<D, 4, false>), dim3(grid), dim3(256), 0, st, p);
+    return hipGetLastError();
+}
+
+// f with the rows of a row block as a constant.
+template <class F>
+static void with_block_rows(const AttnParams &p, F f)
+{
+    if (p.in_short) f(std::integral_constant<int, kFwdShortRows>{});
+    else if (p.narrow) f(std::integral_constant<int, kFwdNarrowRows>{});
+    else f(std::integral_constant<int, kFwdRows>{});
 }
 
 // The split pass itself.
@@ -1525,6 +1560,7 @@ template <int D>
 static hipError_t launch_fwd_pieces(const AttnParams &p, hipStream_t st)
 {
     const int grid = p.shares * p.Hkv;
+    if (p.in_short) return launch_fwd_short<D, true>(p, grid * p.n_row_blocks, st);
     if (p.narrow) return launch_fwd_form<D, 4, true>(p, grid, st);
     if (p.G * p.Ct > 16) return launch_fwd_form<D, kFwdWaves, true>(p, grid, st);
     hipLaunchKernelGGL(attn_fwd_few<D>, dim3(grid), dim3(kFwdWaves * 64), 0, st, p);
@@ -1536,11 +1572,7 @@ static hipError_t launch_fwd(const AttnParams &p, bool split, hipStream_t st)
 {
     if (!split) {
         const int grid = p.Hkv * p.n_row_blocks;
-        if (p.in_short) {
-            if (p.in_short == 8) hipLaunchKernelGGL((attn_fwd_short<D, 8>), dim3(grid), dim3(512), 0, st, p);
-            else hipLaunchKernelGGL((attn_fwd_short<D, 4>), dim3(grid), dim3(256), 0, st, p);
-            return hipGetLastError();
-        }
+        if (p.in_short) return launch_fwd_short<D, false>(p, grid, st);
         return p.narrow ? launch_fwd_form<D, 4, false>(p, grid, st) : launch_fwd_form<D, kFwdWaves, false>(p, grid, st);
     }
     const hipError_t e = launch_fwd_pieces<D>(p, st);
@@ -1552,15 +1584,17 @@ static hipError_t launch_fwd(const AttnParams &p, bool split, hipStream_t st)
     const long merged_rows = (long)p.Hkv * p.n_row_blocks * p.part_rows;
     if (pieces > 12 || (pieces > 6 && merged_rows <= 2048)) {
         const dim3 mgrid(p.Hkv, p.part_rows, p.n_row_blocks);
-        if (p.narrow) hipLaunchKernelGGL((attn_fwd_merge<D, kFwdNarrowRows, true, 1>), mgrid, dim3(256), 0, st, p);
-        else hipLaunchKernelGGL((attn_fwd_merge<D, kFwdRows, true, 1>), mgrid, dim3(256), 0, st, p);
+        with_block_rows(p, [&](auto rows) {
+            hipLaunchKernelGGL((attn_fwd_merge<D, decltype(rows)::value, true, 1>), mgrid, dim3(256), 0, st, p);
+        });
         return hipGetLastError();
     }
     auto launch = [&](auto rpt) {
         constexpr int RPT = decltype(rpt)::value;
         const dim3 mgrid(p.Hkv, (p.part_rows + RPT * groups - 1) / (RPT * groups), p.n_row_blocks);
-        if (p.narrow) hipLaunchKernelGGL((attn_fwd_merge<D, kFwdNarrowRows, false, RPT>), mgrid, dim3(256), 0, st, p);
-        else hipLaunchKernelGGL((attn_fwd_merge<D, kFwdRows, false, RPT>), mgrid, dim3(256), 0, st, p);
+        with_block_rows(p, [&](auto rows) {
+            hipLaunchKernelGGL((attn_fwd_merge<D, decltype(rows)::value, false, RPT>), mgrid, dim3(256), 0, st, p);
+        });
     };
     if (merged_rows > 16384) launch(std::integral_constant<int, 2>{});
     else launch(std::integral_constant<int, 1>{});
@@ -1616,8 +1650,9 @@ static hipError_t launch_both(const AttnParams &p, void *part, size_t part_bytes
     if (e != hipSuccess) return e;
     const int n_score = f.Hkv * ((f.n + 64 * kFewKB - 1) / (64 * kFewKB));
     const int n_merge = f.part_rows * f.n_row_blocks * f.Hkv;
-    if (f.narrow) hipLaunchKernelGGL((attn_merge_score<D, kFewKB, kFwdNarrowRows>), dim3(n_score + n_merge), dim3(256), 0, st, f, n_score);
-    else hipLaunchKernelGGL((attn_merge_score<D, kFewKB, kFwdRows>), dim3(n_score + n_merge), dim3(256), 0, st, f, n_score);
+    with_block_rows(f, [&](auto rows) {
+        hipLaunchKernelGGL((attn_merge_score<D, kFewKB, decltype(rows)::value>), dim3(n_score + n_merge), dim3(256), 0, st, f, n_score);
+    });
     return hipGetLastError();
 }
 
@@ -1632,8 +1667,9 @@ size_t attend_bf16_scratch_bytes(const AttnParams &sizes)
     }
     size_t bytes = score;
     for (const bool scored : {false, true}) {
-        fwd_choose(p, compute_units(), scored);
+        const double est = fwd_choose(p, compute_units(), scored);
         bytes = std::max(bytes, fwd_split_bytes(p));
+        if (fwd_short(p, compute_units(), est, scored)) bytes = std::max(bytes, fwd_short_bytes(p));
     }
     return bytes;
 }

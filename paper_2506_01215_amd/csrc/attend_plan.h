@@ -247,20 +247,63 @@ inline double fwd_choose(P &p, int cus, bool scored, size_t scratch = (size_t)-1
 
 constexpr int kFwdShortRows = 32;                        // query rows of a workgroup of attn_fwd_short
 
-// Whether a forward pass is formed by attn_fwd_short instead of its plan, which is estimated at est us: the waves of a
-// workgroup of that form (0: not), eight where every workgroup has a compute unit, else four, two workgroups to a unit.  Its
-// time goes by the 32-key tiles of the longest workgroup or of a unit, fitted to 220 timings of 110 problems of 17 to 1300 rows
-// over up to 5000 keys, mean error 3 to 4 %.
+// The pieces of row block rb where attn_fwd_short's key tiles are shared out: each block's own, in equal parts.
 template <class P>
-inline int fwd_short(const P &p, int cus, double est)
+struct ShortPieces {
+    int j0, j1, rb;
+
+    RF_PLAN ShortPieces(const P &p, int block) : j0(0), j1(p.shares - 1), rb(block) {}
+    RF_PLAN long slot(const P &p, int j, int kvh) const { return ((long)rb * p.shares + j) * p.Hkv + kvh; }
+};
+
+// Bytes of the pieces of attn_fwd_short where its key tiles are shared out.
+template <class P>
+inline size_t fwd_short_bytes(const P &p)
 {
-    const long rows = (long)p.G * p.Ct, groups = (rows + kFwdShortRows - 1) / kFwdShortRows * p.Hkv;
+    return p.shares ? (size_t)p.n_row_blocks * p.shares * p.Hkv * kFwdShortRows * (p.D + 2) * sizeof(float) : 0;
+}
+
+// Whether a forward pass is formed by attn_fwd_short instead of its plan, which is estimated at est us: the waves of a
+// workgroup of that form (0: not; the plan stays), with n_row_blocks and, where every row block's key tiles are shared out
+// over several workgroups, shares, part_rows and tiles.  Eight waves where every workgroup has a compute unit, else four, two
+// workgroups to a unit.  Time goes by the 32-key tiles of the longest workgroup or of a unit; fitted to 220 timings of
+// 110 problems of 17 to 1300 rows over up to 5000 keys, mean error 3 to 4 %.  Estimates of less than 0.88 of the plan's
+// are taken: of these problems and 60 of 9 to 300 rows over 600 to 30000 keys, 17 % and 12 % less in the mean than by the plans
+// alone, none more than 2 % slower; with 1.0 the mean is the same and 13 rows over 1885 keys, 32/8 heads of 64 take 13.5 us, not 12.2.
+//   - Shares pay their merge, 3 us (less with the score's launch, see merge_with_score), and need a tile for every wave.
+//   - K and V have to come from memory once at least, and longer ones than an XCD's L2 holds come oftener: 23 rows over 26798
+//     keys, 24/8 heads of 128 30.1 us by the plan, 35.3 so.  There row blocks that walk the same keys also have to meet on an
+//     XCD, so the number of shares is a multiple of what brings the next block back to it.
+// scratch: bytes there are for pieces.
+template <class P>
+inline int fwd_short(P &p, int cus, double est, bool scored, size_t scratch = (size_t)-1)
+{
+    const long rows = (long)p.G * p.Ct, blocks = (rows + kFwdShortRows - 1) / kFwdShortRows, groups = blocks * p.Hkv;
     if (rows <= 16 || est == 0.0 || groups > 4l * cus) return 0;
     const double longest = (p.M + p.Ct - 1) / 32 + 1, first = p.M / 32 + 1;
     const double unit = std::max(longest, 0.5 * (first + longest) * groups / cus);
-    const double t = groups <= cus ? (p.D == 64 ? 5.25 + 0.095 * unit : 6.5 + 0.195 * unit)
-                                   : (p.D == 64 ? 5.75 + 0.095 * unit + 0.04 * longest : 6.75 + 0.18 * unit + 0.12 * longest);
-    return t >= 0.88 * est ? 0 : groups <= cus ? 8 : 4;
+    double best = groups <= cus ? (p.D == 64 ? 5.25 + 0.095 * unit : 6.5 + 0.195 * unit)
+                                : (p.D == 64 ? 5.75 + 0.095 * unit + 0.04 * longest : 6.75 + 0.18 * unit + 0.12 * longest);
+    P q = p;
+    q.n_row_blocks = (int)blocks;
+    q.part_rows = kFwdShortRows;
+    q.tiles = (p.M + p.Ct - 1) / 64 + 1;                 // of the longest row block, in the unit of the plans
+    long shares = 0, step = 1;
+    if (blocks > 1 && p.n * 4.0 * p.D > 3e6) while (step * p.Hkv % 8) step *= 2;
+    const double stream = 7.0 + 1.3 * 4.0 * p.Hkv * (double)p.n * p.D / 4.5e6;
+    for (long s = 2; s * groups <= cus && 8 * s <= (long)first; ++s) {
+        if (s > step && s % step) continue;
+        q.shares = (int)s;
+        if (fwd_short_bytes(q) > scratch) break;
+        double launch = 0.0;
+        if (scored) merge_with_score(q, &launch);
+        const double t = std::max(p.D == 64 ? 5.25 + 0.095 * longest / s : 6.5 + 0.195 * longest / s, stream) + 3.0 + 0.05 * s - launch;
+        if (t < best) { best = t; shares = s; }
+    }
+    if (best >= 0.88 * est) return 0;
+    q.shares = (int)shares;
+    p = q;
+    return groups <= cus ? 8 : 4;
 }
 
 // ------------------------------------------------------------------------------------------

@@ -122,10 +122,21 @@ extern "C" int score_slices(int Hkv, int G, int D, int M, int Ct, int W, int cus
     return score_slice_bytes(p) > room(scratch) ? -1 : p.slices;
 }
 
-// Waves of attn_fwd_short where that forms the forward pass instead of the plan above, else 0.
-extern "C" int short_waves(int Hkv, int G, int D, int M, int Ct, int W, int scored, int cus)
+// attn_fwd_short where that forms the forward pass instead of the plan above: its waves + 100 times the workgroups to a row
+// block's keys, 10000 more where the score's launch merges them; else 0.
+extern "C" int short_form(int Hkv, int G, int D, int M, int Ct, int W, int scored, int cus)
 {
     Plan p = problem(Hkv, G, D, M, Ct, W);
     const double est = fwd_choose(p, cus, scored != 0);
-    return fwd_short(p, cus, est);
+    const int waves = fwd_short(p, cus, est, scored != 0);
+    if (!waves) return 0;
+    return waves + 100 * std::max(p.shares, 1) + (p.shares && scored && merge_with_score(p) ? 10000 : 0);
+}
+
+// Bytes of its pieces with that much room for them (negative: as much as it wants).
+extern "C" long short_bytes(int Hkv, int G, int D, int M, int Ct, int scored, int cus, long scratch)
+{
+    Plan p = problem(Hkv, G, D, M, Ct, 0);
+    const double est = fwd_choose(p, cus, scored != 0, room(scratch));
+    return fwd_short(p, cus, est, scored != 0, room(scratch)) ? (long)fwd_short_bytes(p) : 0;
 }

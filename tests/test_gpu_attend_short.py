@@ -1,15 +1,15 @@
 """Forward pass of few rows by workgroups of 32, whose waves divide the keys (attn_fwd_short): last row blocks of one row and of
 all, tiles that end with the keys and do not, rows that see none of a wave's keys, odd numbers of heads to a group, four and eight
-waves; against the fp64 oracle.  And shapes beyond it for the forms that small problems used to take."""
+waves; keys shared out over several workgroups, merged by a launch of its own and by the score's; against the fp64 oracle.  And
+shapes beyond it for the forms that small problems used to take."""
+import ctypes
 import math
+import random
 
 import pytest
 import torch
 
 import helpers
-import oracle
-import test_gpu_attend_fwd_narrow
-import test_gpu_attend_merge_score
 import test_gpu_attend_split
 from helpers import assert_close, assert_scores_close, oracle_kv_heads_dense, to_np
 from paper_2506_01215_amd import binding
@@ -20,27 +20,50 @@ SHORT = [
     (8, 8, 128, 0, 33, 8),            # no cache: keys of the last tile that the first rows do not see
     (10, 2, 64, 31, 40, 8),           # 200 rows, 71 keys
     (14, 2, 128, 95, 45, 8),          # the first row block's keys end with a tile
-    (3, 1, 64, 640, 700, 8),          # 2100 rows, the last block of 20, tiles that some of a block's rows do not see
+    (3, 1, 64, 340, 700, 8),          # 2100 rows, the last block of 20, tiles that some of a block's rows do not see
     (4, 2, 128, 1, 95, 8),            # 96 keys: whole tiles
     (17, 1, 64, 500, 33, 8),          # 561 rows: a block of 17
     (32, 1, 128, 0, 64, 8),           # a block is one chunk row of every head
-    (1, 1, 64, 900, 257, 8),          # a last block of one row
+    (1, 1, 64, 400, 257, 8),          # a last block of one row
     (32, 8, 64, 0, 601, 4),
     (32, 8, 128, 63, 257, 4),
     (32, 32, 128, 44, 301, 4),        # one head to a group: blocks of 32 chunk rows, the last of 13
 ]
+# ... and, with their windows, 100 times the workgroups to a row block's keys, 10000 more where the score's launch merges them
+SHARED = [
+    (1, 1, 64, 1533, 185, 0, 308),    # a last block of 25 rows
+    (8, 1, 64, 1647, 20, 0, 308),
+    (3, 3, 128, 834, 129, 0, 308),    # a last block of one row, three KV heads
+    (3, 1, 128, 771, 40, 0, 308),
+    (1, 1, 64, 3365, 212, 0, 608),    # so many pieces that a workgroup merges one row
+    (7, 1, 64, 3441, 31, 17, 608),
+    (7, 1, 128, 1561, 18, 18, 608),
+    (1, 1, 64, 607, 37, 17, 10208),
+    (3, 1, 64, 610, 15, 1, 10208),
+    (1, 1, 128, 485, 120, 120, 10208),   # observing rows in four row blocks
+    (4, 1, 128, 485, 10, 10, 10208),
+]
 LONGER = [
-    (14, 2, 64, 3600, 201, 128, 3),
-    (1, 1, 64, 1720, 268, 0, 2),
-    (3, 1, 64, 1918, 86, 0, 2),
-    (2, 1, 64, 1857, 129, 128, 2),
-    (24, 8, 64, 0, 1366, 0, 1),
-    (32, 8, 128, 0, 1025, 0, 1),
-    (1, 1, 128, 508, 135, 0, 3),
-    (4, 1, 64, 3703, 66, 0, 3),
-    (2, 2, 64, 875, 131, 128, 6),
-    (14, 2, 64, 927, 16, 16, 6),
-    (3, 1, 64, 848, 31, 5, 6),
+    (1, 1, 64, 0, 33, 33, 1),
+    (32, 32, 128, 0, 1030, 0, 1),
+    (256, 32, 128, 0, 33, 0, 1),
+    (12, 2, 128, 2508, 375, 0, 2),    # eight waves, several row blocks, by rows, with a wave to a head, and of one head
+    (12, 3, 128, 2674, 372, 0, 2),
+    (4, 4, 128, 2135, 1215, 0, 2),
+    (3, 1, 64, 3720, 1445, 0, 2),
+    (2, 1, 64, 3014, 2157, 0, 2),
+    (2, 2, 64, 3108, 2231, 0, 2),
+    (5, 1, 64, 1661, 18, 0, 2),       # and one
+    (5, 1, 128, 939, 24, 17, 2),
+    (1, 1, 64, 0, 2913, 0, 3),
+    (5, 1, 64, 29936, 109, 0, 3),
+    (1, 1, 128, 487, 157, 0, 3),
+    (8, 1, 128, 623, 28, 0, 3),
+    (1, 1, 64, 1399, 17, 5, 6),
+    (8, 1, 128, 334, 5, 0, 6),
+    (1, 1, 64, 0, 1549, 5, 7),
+    (1, 1, 128, 0, 131, 1, 7),
+    (2, 1, 128, 39, 66, 5, 7),
 ]
 
 
@@ -51,13 +74,33 @@ def plan(tmp_path_factory):
 
 @pytest.mark.parametrize("Hq,Hkv,d,M,Ct,waves", SHORT)
 def test_the_short_shapes_take_the_form(plan, Hq, Hkv, d, M, Ct, waves):
-    assert plan.short_waves(Hkv, Hq // Hkv, d, M, Ct, 0, 1, 256) == waves
+    assert plan.short_form(Hkv, Hq // Hkv, d, M, Ct, 0, 1, 256) == 100 + waves
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W,form", SHARED)
+def test_the_shared_shapes_take_the_form(plan, Hq, Hkv, d, M, Ct, W, form):
+    assert plan.short_form(Hkv, Hq // Hkv, d, M, Ct, W, 1, 256) == form
 
 
 @pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W,form", LONGER)
 def test_the_longer_shapes_take_the_other_forms(plan, Hq, Hkv, d, M, Ct, W, form):
-    assert plan.short_waves(Hkv, Hq // Hkv, d, M, Ct, W, 1, 256) == 0
+    assert plan.short_form(Hkv, Hq // Hkv, d, M, Ct, W, 1, 256) == 0
     assert plan.form(Hkv, Hq // Hkv, d, M, Ct, W, 1, 256) == form
+
+
+def test_pieces_fit_the_room_there_is(plan):
+    rng = random.Random(3)
+    plan.short_bytes.restype = ctypes.c_long
+    less = 0
+    for _ in range(3000):
+        Hkv, G, d = rng.choice([1, 2, 4, 8]), rng.choice([1, 2, 4, 7]), rng.choice([64, 128])
+        M, Ct, scored = rng.randint(500, 20000), rng.randint(9, 200), rng.randint(0, 1)
+        want = plan.short_bytes(Hkv, G, d, M, Ct, scored, 256, ctypes.c_long(-1))
+        room = rng.randint(0, max(1, 2 * want))
+        got = plan.short_bytes(Hkv, G, d, M, Ct, scored, 256, ctypes.c_long(room))
+        assert got <= room and (want > room or got == want), (Hkv, G, d, M, Ct, scored, want, room, got)
+        less += 0 < got < want
+    assert less > 50
 
 
 @pytest.mark.parametrize("Hq,Hkv,d,M,Ct,taken", [
@@ -68,16 +111,20 @@ def test_the_longer_shapes_take_the_other_forms(plan, Hq, Hkv, d, M, Ct, W, form
     (32, 8, 64, 2976, 102, True),     # 17.9, 14.6
     (32, 32, 128, 44, 302, True),     # 12.5, 10.1
     (8, 8, 128, 952, 739, True),      # 21.8, 18.4
-    (8, 8, 128, 3000, 100, False),    # 16.3, 33
-    (8, 8, 64, 3592, 109, False),     # 12.5, 17.5
     (32, 8, 128, 3063, 958, False),   # 69, 110
-    (24, 8, 128, 2182, 85, False),    # 21.5, 22
-    (16, 4, 128, 3720, 67, False),    # 18.6, 30
+    # keys shared out
+    (14, 2, 128, 2150, 137, True),    # 19.2, 14.7
+    (16, 4, 64, 8964, 90, True),      # 19.7, 15.0
+    (8, 8, 64, 6187, 161, True),      # 16.6, 13.2
+    (24, 8, 128, 3858, 150, True),    # 26.7, 22.9
+    (24, 8, 128, 26775, 23, False),   # 30.1, 35.3
+    (32, 8, 128, 18728, 10, False),   # 20.9, 21.8
+    (4, 4, 64, 10640, 35, False),     # 11.5, 12.2
     (8, 8, 128, 4096, 17, False),
     (32, 8, 128, 16640, 1, False),    # a token
 ])
 def test_the_faster_form_is_taken(plan, Hq, Hkv, d, M, Ct, taken):
-    assert (plan.short_waves(Hkv, Hq // Hkv, d, M, Ct, 0, 0, 256) != 0) == taken
+    assert (plan.short_form(Hkv, Hq // Hkv, d, M, Ct, 0, 0, 256) != 0) == taken
 
 
 @pytest.mark.gpu
@@ -128,6 +175,7 @@ def test_strides_and_logits_that_are_nan():
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("shape", LONGER, ids=lambda s: "x".join(map(str, s)))
-def test_the_other_forms_match_oracle(shape):
+@pytest.mark.parametrize("shape", SHARED + LONGER, ids=lambda s: "x".join(map(str, s)))
+def test_shares_and_the_other_forms_match_oracle(shape):
+    """Twice with room for all pieces, once without."""
     test_gpu_attend_split.test_split_forward_matches_oracle(shape)
