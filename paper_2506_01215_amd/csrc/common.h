@@ -130,6 +130,8 @@ struct EmbedParams {
     float eps;
 };
 
+constexpr int kPoolMaxWindow = 1025;        // odd; halo of 512 on each side
+
 struct PoolParams {
     const float *best;   // [N] largest similarity over the query tokens
     float *pooled;       // [N]

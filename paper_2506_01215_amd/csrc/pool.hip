@@ -6,7 +6,8 @@
 //
 //   (gather.hip)       the similarity pass stores the maximum over the query tokens, one value per
 //                      context token
-//   pool_window        a tile plus its halo in LDS, then a sliding maximum by doubling (after step j
+//   (select.hip)       rows that a selection in one launch takes by up to 8192 tokens a workgroup are pooled there
+//   pool_window        longer ones: a tile plus its halo in LDS, then a sliding maximum by doubling (after step j
 //                      every LDS slot holds the maximum of 2^j consecutive scores; a window of W is
 //                      the maximum of two such spans of the largest power of two <= W), O(log W)
 //                      LDS passes instead of W reads per token.
@@ -17,11 +18,11 @@
 namespace reform {
 
 hipError_t select_topk(const SelParams &p, hipStream_t st);
+bool select_pooled(const PoolParams &p, hipStream_t st, hipError_t &e);
 
 // Context tokens per workgroup.  The pass is a short chain of LDS sweeps, so it is bound by latency:
 // 262144 tokens in 128 tiles of 2048 11 us, in 512 tiles of 512 5 us.
 constexpr int kPoolTile = 512;
-constexpr int kPoolMaxWindow = 1025;     // odd; halo of 512 on each side
 constexpr int kPoolSpan = kPoolTile + kPoolMaxWindow - 1;
 
 __global__ __launch_bounds__(256) void pool_window(PoolParams p)
@@ -54,9 +55,11 @@ __global__ __launch_bounds__(256) void pool_window(PoolParams p)
 
 hipError_t gather_pool_select(const PoolParams &p, hipStream_t st)
 {
+    hipError_t e;
+    if (select_pooled(p, st, e)) return e;
     const unsigned grid = (unsigned)((p.N + kPoolTile - 1) / kPoolTile);
     hipLaunchKernelGGL(pool_window, dim3(grid), dim3(256), 0, st, p);
-    hipError_t e = hipGetLastError();
+    e = hipGetLastError();
     if (e != hipSuccess) return e;
     return select_topk(p.sel, st);
 }

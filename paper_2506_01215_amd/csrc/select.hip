@@ -964,6 +964,156 @@ __device__ __forceinline__ T multi_wait_word(const SelParams &p, const T *word, 
     }
 }
 
+// Largest window in whole quads on one side, and one more for what it begins or ends in.
+constexpr int kPoolHaloQuads = (kPoolMaxWindow - 1) / 8 + 1;
+
+// What a selection that pools its row reads and, beside the selection, writes.
+struct PoolSrc {
+    const float *best;
+    float *pooled;
+    int window;
+};
+
+// LDS of the pooling of nit * 4096 tokens: their quads with the halo, and the quads' maxima twice.
+__host__ __device__ constexpr size_t pool_lds_bytes(int nit) { return (size_t)(nit * 1024 + 2 * kPoolHaloQuads) * (16 + 2 * 4); }
+
+// All 1024 threads: keys of the max-pooled tokens [lo, lo + nit * 4096), nit <= 2, quad by quad, from the similarities, and the
+// pooled values in registers.  With h = 4 a + b tokens to each side (a > 0) the window of a token in quad t is the quads
+// between t - a and t + a, whose maxima come from spans of a power of two (each the larger of two half as long), and up to two
+// quads at either end in part.  Bound: the launch and its barriers, so it saves a launch (pool_window, tiles of 512 tokens that
+// double over single ones) for four or five barriers.  Calls with their gather of rows, us: 30000 x 512, 5 queries
+// 31.9 -> 29.7; 100000 x 1024, 16 74.9 -> 72.2; 8000 x 1024, 8 25.8 -> 24.9; 262144 x 1024, 37 156.1 -> 153.0 (154.1 with the
+// pooled values stored at once, not behind the first histogram).
+__device__ __forceinline__ void load_pooled(const PoolSrc &pool, const SelParams &p, int N, int lo, int nit, v4u *keys, f32x4 *quads,
+                                            f32x4 (&pooled)[2])
+{
+    const int tid = threadIdx.x;
+    const int h = (pool.window - 1) >> 1, a = h >> 2, b = h & 3, halo = a + 1;
+    const int total = nit * 1024 + 2 * halo;             // quad i holds the tokens lo + 4 (i - halo) ..
+    float *m = (float *)(quads + nit * 1024 + 2 * kPoolHaloQuads), *m2 = m + nit * 1024 + 2 * kPoolHaloQuads;
+    __syncthreads();                                     // the last users of this LDS are through
+    for (int i = tid; i < total; i += 1024) {
+        const int t = lo + 4 * (i - halo);
+        f32x4 x = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};          // outside the context: takes no part
+        if (t >= 0 && t + 4 <= N) {
+            x = *(const f32x4 *)(pool.best + t);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (t + j >= 0 && t + j < N) x[j] = pool.best[t + j];
+        }
+        quads[i] = x;
+        m[i] = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
+    }
+    __syncthreads();
+    int len = 1;
+    for (; 2 * len <= 2 * a - 1; len *= 2) {             // m[i]: largest of the quads i .. i + len - 1
+        for (int i = tid; i < total; i += 1024) m2[i] = i + len < total ? fmaxf(m[i], m[i + len]) : m[i];
+        __syncthreads();
+        float *other = m;
+        m = m2;
+        m2 = other;
+    }
+    const int tail = N - p.n_recent;
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+        if (n >= nit) break;
+        const int q = tid + n * 1024, i = q + halo, t = lo + 4 * q;
+        f32x4 &y = pooled[n];
+        if (a == 0) {
+            const float *x = (const float *)(quads + i);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                y[j] = x[j];
+                for (int d = 1; d <= h; ++d) y[j] = fmaxf(y[j], fmaxf(x[j - d], x[j + d]));
+            }
+        } else {
+            const float core = fmaxf(m[i - a + 1], m[i + a - len]);
+            const f32x4 l0 = quads[i - a - 1], l1 = quads[i - a], r0 = quads[i + a], r1 = quads[i + a + 1];
+            // from the end: largest of the last 1 .. 7 tokens of l0 l1; from the start: of the first ones of r0 r1
+            float left[8], right[8];
+            left[0] = right[0] = core;
+#pragma unroll
+            for (int j = 1; j < 8; ++j) {
+                left[j] = fmaxf(left[j - 1], j <= 4 ? l1[4 - j] : l0[8 - j]);
+                right[j] = fmaxf(right[j - 1], j <= 4 ? r0[j - 1] : r1[j - 5]);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {                // 4 - j + b tokens of l0 l1, j + b + 1 of r0 r1
+                float x = 0.f;
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (b == c) x = fmaxf(left[4 - j + c], right[j + c + 1]);
+                y[j] = x;
+            }
+        }
+        v4u u;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            u[j] = t + j >= N ? 0u : t + j < p.n_sink || t + j >= tail ? 0xffffffffu : ordered_key(y[j]);
+        keys[q] = u;
+    }
+    __syncthreads();
+}
+
+// The pooled values of load_pooled, out.
+__device__ __forceinline__ void store_pooled(const PoolSrc &pool, int N, int lo, int nit, const f32x4 (&pooled)[2])
+{
+    const bool aligned = ((uintptr_t)pool.pooled & 15) == 0;
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+        const int t = lo + 4 * (int)(threadIdx.x + n * 1024);
+        if (n >= nit) break;
+        if (aligned && t + 4 <= N) {
+            *(f32x4 *)(pool.pooled + t) = pooled[n];
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (t + j < N) pool.pooled[t + j] = pooled[n][j];
+        }
+    }
+}
+
+// select_alone for a row that is pooled on the way: by the workgroup's own number of tokens at a time, its own last.
+__device__ __forceinline__ void select_alone_pooled(const PoolSrc &pool, const SelParams &p, int N, int lo, int nit, v4u *keys,
+                                                    f32x4 *quads, int *h, int *wtot, int *sel, int *before, uint32_t &T, int &need_eq)
+{
+    const int tid = threadIdx.x, wave = tid >> 6, step = nit * 4096;
+    const v4u *mine = keys + wave * (nit * 64);
+    f32x4 unused[2];
+    uint32_t prefix = 0u;
+    int krem = p.k, in_bin;
+#pragma unroll 1
+    for (int pass = 0; pass < 3; ++pass) {
+        const int bits = pass == 2 ? 10 : 11, shift = pass == 0 ? 21 : pass == 1 ? 10 : 0;
+        __syncthreads();
+        h[tid] = 0;
+        h[tid + 1024] = 0;
+#pragma unroll 1
+        for (int at = 0; at < N; at += step) {
+            load_pooled(pool, p, N, at, nit, keys, quads, unused);
+            radix_hist(mine, N, at + wave * (nit * 256), nit, shift, bits, prefix, h);
+        }
+        __syncthreads();
+        bin_pick(bits, prefix, krem, in_bin, h, wtot, sel);
+    }
+    T = prefix;
+    need_eq = krem;
+    if (tid < 2) before[tid] = 0;
+#pragma unroll 1
+    for (int at = 0; at <= lo; at += step) {             // up to its own, whose keys stay
+        load_pooled(pool, p, N, at, nit, keys, quads, unused);
+        if (at == lo) break;
+        int gt, eq;
+        range_count(mine, N, at + wave * (nit * 256), nit, T, gt, eq);
+        if ((tid & 63) == 0) {
+            atomicAdd(&before[0], gt);
+            atomicAdd(&before[1], eq);
+        }
+    }
+    __syncthreads();
+}
+
 // All 1024 threads, without the other workgroups: the threshold key of row s, how many candidates equal
 // to it are selected, and how many above / equal to it lie before index `lo`.
 __device__ __forceinline__ void select_alone(const SelParams &p, const float *s, int N, int lo, int *h, int *wtot,
@@ -1003,10 +1153,12 @@ __device__ __forceinline__ void select_alone(const SelParams &p, const float *s,
     __syncthreads();
 }
 
-template <bool MULTI>
-__global__ __launch_bounds__(1024) void select_row(SelParams p, int parts, int nit)
+// POOL: the row is max-pooled on the way in.
+template <bool MULTI, bool POOL>
+__global__ __launch_bounds__(1024) void select_row(SelParams p, int parts, int nit, PoolSrc pool)
 {
-    extern __shared__ v4u keys[];                                 // [nit * 1024]
+    extern __shared__ v4u keys[];                                 // [nit * 1024], with POOL its LDS behind them
+    f32x4 *quads = (f32x4 *)(keys + nit * 1024);
     __shared__ int h[2048];
     __shared__ v4u list[kSelList / 4];
     __shared__ int wtot[2][16];
@@ -1024,7 +1176,9 @@ __global__ __launch_bounds__(1024) void select_row(SelParams p, int parts, int n
     if (tid == 3) stop = 0;
     if (tid < kSelList / 4) list[tid] = (v4u){0u, 0u, 0u, 0u};
     __syncthreads();
-    load_keys(p, p.vals + (size_t)q * p.ld, N, w_lo, nit, mine);
+    f32x4 pooled[2];
+    if constexpr (POOL) load_pooled(pool, p, N, wg_lo, nit, keys, quads, pooled);
+    else load_keys(p, p.vals + (size_t)q * p.ld, N, w_lo, nit, mine);
     if (!MULTI && !p.pre_zeroed)
         for (long i = (long)q * 1024 + tid; i < p.zero_extra_n; i += (long)gridDim.x * 1024) p.zero_extra[i] = 0;
 
@@ -1046,10 +1200,12 @@ __global__ __launch_bounds__(1024) void select_row(SelParams p, int parts, int n
             int *gh = p.hist + ((size_t)q * 3 + pass) * 2048;
             for (int i = tid; i < 2048; i += 1024)
                 if (h[i]) atomicAdd(&gh[i], h[i]);
+            if (POOL && pass == 0) store_pooled(pool, N, wg_lo, nit, pooled);   // while the others' counts are on their way
             __syncthreads();
             alone = !multi_wait_hist(p, gh, 1 << bits, in_bin, h, wtot[0], &stop);
             if (alone) break;
         }
+        if (POOL && !MULTI && pass == 0) store_pooled(pool, N, wg_lo, nit, pooled);
         bin_pick(bits, prefix, krem, in_bin, h, wtot[0], sel);
         if (in_bin <= kSelList) break;
     }
@@ -1127,7 +1283,8 @@ __global__ __launch_bounds__(1024) void select_row(SelParams p, int parts, int n
         }
     }
     if (MULTI && alone) {
-        select_alone(p, p.vals + (size_t)q * p.ld, N, wg_lo, h, wtot[0], sel, before, T, need_eq);
+        if constexpr (POOL) select_alone_pooled(pool, p, N, wg_lo, nit, keys, quads, h, wtot[0], sel, before, T, need_eq);
+        else select_alone(p, p.vals + (size_t)q * p.ld, N, wg_lo, h, wtot[0], sel, before, T, need_eq);
         range_count(mine, N, w_lo, nit, T, gt_w, eq_w);
         if (lane == 0) { wtot[0][wave] = gt_w; wtot[1][wave] = eq_w; }
         __syncthreads();
@@ -1146,11 +1303,13 @@ __global__ __launch_bounds__(1024) void select_row(SelParams p, int parts, int n
         if (e_ != hipSuccess) return e_;      \
     } while (0)
 
-template <bool MULTI>
-static hipError_t launch_select_row(const SelParams &p, long parts, int nit, hipStream_t st)
+template <bool MULTI, bool POOL = false>
+static hipError_t launch_select_row(const SelParams &p, long parts, int nit, hipStream_t st, const PoolSrc &pool = {})
 {
-    auto kern = select_row<MULTI>;
-    // the keys of nit = 8 need more than the default 64 KB of LDS: raised once per device, not per launch
+    auto kern = select_row<MULTI, POOL>;
+    const size_t lds = (size_t)nit * 4096 * 4 + (POOL ? pool_lds_bytes(nit) : 0);
+    // the keys of nit = 8, and those of 2 with their pooling, need more than the default 64 KB of LDS: raised once per device, not
+    // per launch
     static std::atomic<bool> lds_raised[64];
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -1160,7 +1319,7 @@ static hipError_t launch_select_row(const SelParams &p, long parts, int nit, hip
         if (e != hipSuccess) return e;
         if (dev >= 0 && dev < 64) lds_raised[dev].store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL(kern, dim3((unsigned)(p.nq * parts)), dim3(1024), (size_t)nit * 4096 * 4, st, p, (int)parts, nit);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(p.nq * parts)), dim3(1024), lds, st, p, (int)parts, nit, pool);
     return hipGetLastError();
 }
 
@@ -1189,22 +1348,37 @@ static hipError_t select_rest(const SelParams &p, hipStream_t st)
     return hipSuccess;
 }
 
+// Several workgroups per row when they can all be resident together: at most half of the
+// compute units (a partitioned device has fewer than 256).  False: not for these rows.
+static bool select_shared(const SelParams &p, int &nit, int &parts)
+{
+    if (p.N <= kFusedMaxN || !p.multi_groups || !p.gave_up) return false;
+    const long max_groups = min((long)p.multi_groups, (long)device_compute_units() / 2);
+    for (nit = 1; nit <= 8; nit *= 2) {
+        const long w = (p.N + (long)nit * 4096 - 1) / ((long)nit * 4096);
+        parts = (int)w;
+        if ((long)p.nq * w <= max_groups) return true;
+    }
+    return false;
+}
+
+// Pools and selects in one launch where a workgroup of it takes at most 8192 tokens; true if it does.  More of them would be
+// pooled one batch after the other, while pool_window has a workgroup for every 512.
+bool select_pooled(const PoolParams &p, hipStream_t st, hipError_t &e)
+{
+    int nit = 1, parts = 1;
+    const bool multi = select_shared(p.sel, nit, parts);
+    if (!multi) nit = p.N <= 4096 ? 1 : 2;
+    if (!p.sel.pre_zeroed || nit > 2 || (long)parts * nit * 4096 < p.N) return false;
+    const PoolSrc pool = {p.best, p.pooled, p.window};
+    e = multi ? launch_select_row<true, true>(p.sel, parts, nit, st, pool) : launch_select_row<false, true>(p.sel, 1, nit, st, pool);
+    return true;
+}
+
 hipError_t select_topk(const SelParams &p, hipStream_t st)
 {
     int nit = 0, parts = 1;
-    if (p.N > kFusedMaxN && p.multi_groups && p.gave_up) {
-        // several workgroups per row when they can all be resident together: at most half of the
-        // compute units (a partitioned device has fewer than 256)
-        const long max_groups = min((long)p.multi_groups, (long)device_compute_units() / 2);
-        for (int n = 1; n <= 8 && !nit; n *= 2) {
-            const long w = (p.N + (long)n * 4096 - 1) / ((long)n * 4096);
-            if ((long)p.nq * w <= max_groups) {
-                nit = n;
-                parts = (int)w;
-            }
-        }
-    }
-    const bool multi = nit > 0;
+    const bool multi = select_shared(p, nit, parts);
     if (!multi && p.N <= kRowMaxN) {
         // this launch would clear the bitmap of a call that has not, while its other workgroups mark in it
         if (p.mark && !p.pre_zeroed) return hipErrorInvalidValue;
