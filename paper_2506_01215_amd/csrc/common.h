@@ -56,6 +56,7 @@ struct SelParams {
     long ld, N;
     int nq, k;
     int n_sink, n_recent;    // first / last slots that are always selected (count inside k)
+    int bin_top;             // sign and exponent bits of the largest values as ordered keys, 0: not known (see kBins)
     int *hist;               // [nq][3][2048]
     uint32_t *sel_prefix;    // [3][nq]  selection state after each radix pass
     int *sel_krem;           // [3][nq]
@@ -129,6 +130,8 @@ struct EmbedParams {
     int pieces, group;   // 16-byte pieces per head vector; lanes per row (power of two >= pieces, <= 64)
     float eps;
 };
+
+constexpr int kCosineTop = 0x17f;           // SelParams::bin_top of values from 1 up to 2
 
 constexpr int kPoolMaxWindow = 1025;        // odd; halo of 512 on each side
 

@@ -471,6 +471,7 @@ reform_status reform_gather_topk(const reform_gather_desc *d, const void *emb, c
     p.sel.vals = p.sim; p.sel.ld = p.sim_ld; p.sel.N = d->n_ctx;
     p.sel.nq = d->n_query; p.sel.k = d->k;
     p.sel.n_sink = 0; p.sel.n_recent = 0;
+    p.sel.bin_top = kCosineTop;
     p.sel.hist = (int *)(ws + L.hist);
     p.sel.sel_prefix = (uint32_t *)(ws + L.prefix);
     p.sel.sel_krem = (int *)(ws + L.krem);
@@ -528,6 +529,7 @@ reform_status reform_gather_pooled(const reform_pooled_desc *d, const void *emb,
     p.sel.vals = p.pooled; p.sel.ld = d->n_ctx; p.sel.N = d->n_ctx;
     p.sel.nq = 1; p.sel.k = d->budget;
     p.sel.n_sink = d->n_head_keep; p.sel.n_recent = d->n_tail_keep;
+    p.sel.bin_top = kCosineTop;
     p.sel.hist = (int *)(ws + L.hist);
     p.sel.sel_prefix = (uint32_t *)(ws + L.prefix);
     p.sel.sel_krem = (int *)(ws + L.krem);

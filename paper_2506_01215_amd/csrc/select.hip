@@ -766,7 +766,7 @@ __global__ __launch_bounds__(256) void select_write_rest(SelParams p)
 // The whole selection of a row in ONE launch, by `parts` workgroups of 1024 threads (16 waves, each
 // owning nit * 256 candidates, nit <= 8).  The row is read once; its keys stay in LDS through the
 // radix passes (LDS histogram, pick by a workgroup scan) and the ordered emission.  As soon as the
-// digits picked so far are shared by at most kSelList candidates (nearly always after two passes:
+// bins or digits picked so far are shared by at most kSelList candidates (nearly always after one or two passes:
 // the rest is ties) these go into a list, whose k-th largest list_pick finds.  Results are identical to
 // the multi-launch path; the per-pass selection state is not written back.
 //
@@ -795,7 +795,54 @@ __global__ __launch_bounds__(256) void select_write_rest(SelParams p)
 // as the launch before left it, so it selects from the whole row by itself (select_alone) and then
 // emits its own part like the others.  The outcome is the same, only late.  It also sets *gave_up, on which
 // the other waits of the call end as well: what they wait for will not come.
-constexpr int kSelList = 256;
+template <bool BINS> constexpr int kSelList = BINS ? 508 : 256;
+// Entries of a list shared between workgroups that take their places one by one.  Atomics on one word queue, so of more each
+// workgroup takes its places together, a round trip behind its own barrier (190 of 131072 similarities 63.7 -> 62.0 us for the call; but
+// 20 of 15000 scores 50.2 -> 51.3).
+constexpr int kSelDirect = 64;
+
+// Where the size of the largest values is known (cosines), a pass of bins of 1/64 of an octave over the sixteen octaves up to
+// `top` (sign and exponent of an ordered key) comes first; what lies below and above falls into the first and the last bin.
+// Digits of a key's first eleven bits are a quarter of an octave, and a threshold's holds several percent of the row, so they need a
+// second pass and, between workgroups, a second exchange of 3 us; one of these holds some hundreds of 10^5.  A
+// threshold in the first or last bin (not positive, or sixteen octaves below) sends the row through the plain digits.  Whole
+// calls, us: gather of 131072 x 1024 63.3 -> 62.0, of 20000 x 1024, 16 queries 34.8 -> 32.6, of 6000 x 256 14.3 -> 12.9; pooled and
+// rows, 30000 x 512 30.2 -> 28.5.  Scores, whose size a sample of the row has to tell, gained nothing (8 heads, 32768
+// of 65536 113.5 -> 114.3, 12000 of 15000 50.5 -> 49.8, 4096 of 4113 30.7 -> 31.4).
+constexpr int kBinShift = 17, kBins = 1024;
+
+__device__ __forceinline__ int bin_base(uint32_t top) { return (int)(top << 6 | 63u) - (kBins - 1); }
+
+__device__ __forceinline__ int bin_of(uint32_t u, int base) { return min(max((int)(u >> kBinShift) - base, 0), kBins - 1); }
+
+// Histogram of the bins over the wave's keys.
+__device__ __forceinline__ void bin_hist(const v4u *keys, int N, int w_lo, int nit, int base, int *h)
+{
+    const int lane = threadIdx.x & 63;
+    int low = 0;                                              // what falls into the first bin is counted without its atomics
+#pragma unroll 1
+    for (int it = 0; it < nit; ++it) {
+        const v4u u = keys[it * 64 + lane];
+        const int t = w_lo + it * 256 + 4 * lane;
+        int d[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            d[j] = t + j < N ? bin_of(u[j], base) : -1;
+            low += __popcll(__ballot(d[j] == 0));
+        }
+        if (d[0] > 0 && d[0] == d[1] && d[0] == d[2] && d[0] == d[3]) {
+            const int first = __builtin_amdgcn_readfirstlane(d[0]);
+            const unsigned long long like = __ballot(d[0] == first);
+            if (d[0] != first) atomicAdd(&h[d[0]], 4);        // a plateau: pooled scores mostly are
+            else if (lane == __builtin_ctzll(like)) atomicAdd(&h[first], 4 * __popcll(like));
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (d[j] > 0) atomicAdd(&h[d[j]], 1);
+        }
+    }
+    if (lane == 0 && low) atomicAdd(&h[0], low);
+}
 
 // Histogram of the digit at `shift` over the wave's keys whose higher bits equal the prefix.
 __device__ __forceinline__ void radix_hist(const v4u *keys, int N, int w_lo, int nit, int shift, int bits,
@@ -867,12 +914,13 @@ __device__ __forceinline__ void bin_pick(int bits, uint32_t &prefix, int &krem, 
     __syncthreads();
 }
 
-// All 1024 threads: the krem-th largest of the m <= kSelList keys in `list` (padded with zeros), which agree from bit
+// All 1024 threads: the krem-th largest of the m <= kSelList<BINS> keys in `list` (padded with zeros), which agree from bit
 // `shift` up.  A short list: four threads per key count how many are larger, 0.5 us at 20 keys and 2.3 us at 256.  A
 // longer one: the first wave holds it all and settles a bit at a time by counting, 0.8 us for 10 bits and
 // 1.3 us for 21 whatever the length.
 constexpr int kCountedList = 96;
 
+template <bool BINS>
 __device__ __forceinline__ void list_pick(const v4u *list, int m, int krem, int shift, uint32_t &T, int &need_eq, int *sel)
 {
     if (m <= kCountedList) {
@@ -891,18 +939,27 @@ __device__ __forceinline__ void list_pick(const v4u *list, int m, int krem, int 
         eq += __builtin_amdgcn_update_dpp(0, eq, 0x4e, 0xf, 0xf, false);
         if (at < m && gt < krem && krem <= gt + eq) { sel[0] = (int)mine; sel[1] = krem - gt; }   // equal keys write the same
     } else if (threadIdx.x < 64) {
-        const v4u x = list[threadIdx.x];
+        constexpr int X = BINS ? 8 : 4;
+        uint32_t x[X];
+#pragma unroll
+        for (int j = 0; j < X; j += 4) {
+            const int i = threadIdx.x + 16 * j;
+            const v4u u = i < kSelList<BINS> / 4 ? list[i] : (v4u){0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int c = 0; c < 4; ++c) x[j + c] = u[c];
+        }
         uint32_t t = __builtin_amdgcn_readfirstlane(x[0]) >> shift << shift;  // the shared bits
         for (int b = shift - 1; b >= 0; --b) {
             const uint32_t up = t | 1u << b;
             int ge = 0;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) ge += __popcll(__ballot(x[j] >= up));
+            for (int j = 0; j < X; ++j)
+                if (j < 4 || m > 256) ge += __popcll(__ballot(x[j] >= up));
             if (ge >= krem) t = up;
         }
         int gt = 0;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) gt += __popcll(__ballot(x[j] > t));
+        for (int j = 0; j < X; ++j) gt += __popcll(__ballot(x[j] > t));
         if (threadIdx.x == 0) { sel[0] = (int)t; sel[1] = krem - gt; }
     }
     __syncthreads();
@@ -1153,14 +1210,16 @@ __device__ __forceinline__ void select_alone(const SelParams &p, const float *s,
     __syncthreads();
 }
 
-// POOL: the row is max-pooled on the way in.
-template <bool MULTI, bool POOL>
+// BINS: a pass of bins before the digits (see kBins).  POOL: the row is max-pooled on the way in.  These launches are so short that
+// code counts which is fetched and skipped: with the bins in every form 12000 of 15000 scores 50.4 -> 51.3 us.
+template <bool MULTI, bool BINS, bool POOL>
 __global__ __launch_bounds__(1024) void select_row(SelParams p, int parts, int nit, PoolSrc pool)
 {
     extern __shared__ v4u keys[];                                 // [nit * 1024], with POOL its LDS behind them
     f32x4 *quads = (f32x4 *)(keys + nit * 1024);
-    __shared__ int h[2048];
-    __shared__ v4u list[kSelList / 4];
+    __shared__ __attribute__((aligned(16))) int h[2048];
+    constexpr int LIST = kSelList<BINS>;
+    __shared__ v4u list[LIST / 4];
     __shared__ int wtot[2][16];
     __shared__ int sel[3], before[2], list_n, stop;
     const int q = blockIdx.x / parts, part = blockIdx.x % parts;
@@ -1174,7 +1233,7 @@ __global__ __launch_bounds__(1024) void select_row(SelParams p, int parts, int n
     if (tid < 2) before[tid] = 0;
     if (tid == 2) list_n = 0;
     if (tid == 3) stop = 0;
-    if (tid < kSelList / 4) list[tid] = (v4u){0u, 0u, 0u, 0u};
+    if (tid < LIST / 4) list[tid] = (v4u){0u, 0u, 0u, 0u};
     __syncthreads();
     f32x4 pooled[2];
     if constexpr (POOL) load_pooled(pool, p, N, wg_lo, nit, keys, quads, pooled);
@@ -1183,31 +1242,53 @@ __global__ __launch_bounds__(1024) void select_row(SelParams p, int parts, int n
         for (long i = (long)q * 1024 + tid; i < p.zero_extra_n; i += (long)gridDim.x * 1024) p.zero_extra[i] = 0;
 
     uint32_t prefix = 0u;
-    int krem = p.k, in_bin = N, shift = 21;
+    int krem = p.k, in_bin = N, shift = kBinShift;
     bool alone = false;                                           // MULTI: this workgroup waits no more
+    // Bins, then 11 and 6 bits; or, without bins or behind them, 11, 11 and 10.  Cleared words of the row (MULTI): 2048 for each of
+    // three passes; the bins and the last digits behind them share the first.
+    int *rh = p.hist + (size_t)q * 3 * 2048;
+    // The workgroups' histograms together, in place of this one's.
+    auto exchange = [&](int *gh, int digits, bool first) {
+        __syncthreads();
+        if constexpr (MULTI) {
+            for (int i = tid; i < digits; i += 1024)
+                if (h[i]) atomicAdd(&gh[i], h[i]);
+            if (POOL && first) store_pooled(pool, N, wg_lo, nit, pooled);   // while the others' counts are on their way
+            __syncthreads();
+            alone = !multi_wait_hist(p, gh, digits, in_bin, h, wtot[0], &stop);
+        } else if (POOL && first) {
+            store_pooled(pool, N, wg_lo, nit, pooled);
+        }
+    };
+    bool binned = false;                                          // bins have settled the threshold's first bits
+    if constexpr (BINS) {
+        const int base = bin_base((uint32_t)p.bin_top);
+        bin_hist(mine, N, w_lo, nit, base, h);
+        exchange(rh, kBins, true);
+        if (!alone) {
+            uint32_t bin = 0u;
+            int rest = krem, inside = N;
+            bin_pick(10, bin, rest, inside, h, wtot[0], sel);
+            if (bin > 0u && bin < (uint32_t)kBins - 1u) {
+                binned = true;
+                prefix = (uint32_t)base + bin;
+                krem = rest;
+                in_bin = inside;
+            }
+        }
+    }
 #pragma unroll 1
-    for (int pass = 0; pass < 3; ++pass) {
-        const int bits = pass == 2 ? 10 : 11;
-        shift = pass == 0 ? 21 : pass == 1 ? 10 : 0;
-        if (pass) {
+    for (int pass = 1; !alone && shift > 0 && (in_bin > LIST || (pass == 1 && !binned)); ++pass) {
+        const int bits = binned ? (pass == 1 ? 11 : 6) : pass == 3 ? 10 : 11;
+        shift = binned ? (pass == 1 ? 6 : 0) : pass == 1 ? 21 : pass == 2 ? 10 : 0;
+        if (BINS || pass > 1) {
             h[tid] = 0;
             h[tid + 1024] = 0;
             __syncthreads();
         }
         radix_hist(mine, N, w_lo, nit, shift, bits, prefix, h);
-        __syncthreads();
-        if constexpr (MULTI) {
-            int *gh = p.hist + ((size_t)q * 3 + pass) * 2048;
-            for (int i = tid; i < 2048; i += 1024)
-                if (h[i]) atomicAdd(&gh[i], h[i]);
-            if (POOL && pass == 0) store_pooled(pool, N, wg_lo, nit, pooled);   // while the others' counts are on their way
-            __syncthreads();
-            alone = !multi_wait_hist(p, gh, 1 << bits, in_bin, h, wtot[0], &stop);
-            if (alone) break;
-        }
-        if (POOL && !MULTI && pass == 0) store_pooled(pool, N, wg_lo, nit, pooled);
-        bin_pick(bits, prefix, krem, in_bin, h, wtot[0], sel);
-        if (in_bin <= kSelList) break;
+        exchange(!BINS ? rh + (pass - 1) * 2048 : pass == 3 ? rh + 1024 : rh + pass * 2048, 1 << bits, POOL && !BINS && pass == 1);
+        if (!alone) bin_pick(bits, prefix, krem, in_bin, h, wtot[0], sel);
     }
     // here prefix holds the threshold's bits from `shift` up, shared by in_bin candidates
     uint32_t T = prefix;
@@ -1215,8 +1296,10 @@ __global__ __launch_bounds__(1024) void select_row(SelParams p, int parts, int n
     const bool listed = shift > 0 && !alone;
     int *c = p.blk_cnt + (size_t)q * parts * 2;                   // MULTI: cleared words, 0 = not published yet
     if (listed) {
-        unsigned long long *glist = (unsigned long long *)(p.hist + ((size_t)q * 3 + 2) * 2048);
-        int *gcount = p.hist + ((size_t)q * 3 + 2) * 2048 + 2047; // the third pass's histogram is still clear
+        int *spare = !BINS || binned ? rh + 2 * 2048 : rh + 1024; // the last pass's histogram is still clear
+        unsigned long long *glist = (unsigned long long *)spare;  // up to kSelList, and their number behind them
+        int *gcount = spare + 1023;
+        unsigned long long *own = (unsigned long long *)h;        // of many entries this workgroup's, see kSelDirect
         int gt = 0;
 #pragma unroll 1
         for (int it = 0; it < nit; ++it) {
@@ -1226,13 +1309,15 @@ __global__ __launch_bounds__(1024) void select_row(SelParams p, int parts, int n
             for (int j = 0; j < 4; ++j) {
                 if (MULTI) gt += __popcll(__ballot(t + j < N && u[j] >> shift > prefix));
                 if (t + j < N && u[j] >> shift == prefix) {
-                    const unsigned at = MULTI ? atomicAdd(gcount, 1) : atomicAdd(&list_n, 1);
-                    if (at >= kSelList) continue;
-                    if (MULTI)
-                        __hip_atomic_store(&glist[at], (unsigned long long)u[j] << 32 | (unsigned)(t + j + 1),
-                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    else
+                    const unsigned at = MULTI && (!BINS || in_bin <= kSelDirect) ? atomicAdd(gcount, 1) : atomicAdd(&list_n, 1);
+                    if (at >= LIST) continue;
+                    if (!MULTI) {
                         ((uint32_t *)list)[at] = u[j];
+                        continue;
+                    }
+                    const unsigned long long e = (unsigned long long)u[j] << 32 | (unsigned)(t + j + 1);
+                    if (!BINS || in_bin <= kSelDirect) __hip_atomic_store(&glist[at], e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    else own[at] = e;
                 }
             }
         }
@@ -1246,7 +1331,11 @@ __global__ __launch_bounds__(1024) void select_row(SelParams p, int parts, int n
 #pragma unroll
                 for (int w = 0; w < 16; ++w) tot += wtot[0][w];
                 __hip_atomic_store(&c[2 * part], tot + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (BINS && list_n) sel[2] = atomicAdd(gcount, list_n);
             }
+            if (BINS && in_bin > kSelDirect) __syncthreads();
+            if (BINS && tid < list_n && sel[2] + tid < LIST)              // always, whatever the keys were
+                __hip_atomic_store(&glist[sel[2] + tid], own[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (tid < in_bin) {
                 const unsigned long long e = multi_wait_word(p, &glist[tid], &stop);
                 key = (uint32_t)(e >> 32);
@@ -1258,7 +1347,7 @@ __global__ __launch_bounds__(1024) void select_row(SelParams p, int parts, int n
         }
         __syncthreads();
         alone = MULTI && stop;
-        if (!alone) list_pick(list, in_bin, krem, shift, T, need_eq, sel);
+        if (!alone) list_pick<BINS>(list, in_bin, krem, shift, T, need_eq, sel);
         if (MULTI && !alone && at < wg_lo) {
             if (key > T) atomicAdd(&before[0], 1);
             if (key == T) atomicAdd(&before[1], 1);
@@ -1303,10 +1392,10 @@ __global__ __launch_bounds__(1024) void select_row(SelParams p, int parts, int n
         if (e_ != hipSuccess) return e_;      \
     } while (0)
 
-template <bool MULTI, bool POOL = false>
+template <bool MULTI, bool BINS, bool POOL = false>
 static hipError_t launch_select_row(const SelParams &p, long parts, int nit, hipStream_t st, const PoolSrc &pool = {})
 {
-    auto kern = select_row<MULTI, POOL>;
+    auto kern = select_row<MULTI, BINS, POOL>;
     const size_t lds = (size_t)nit * 4096 * 4 + (POOL ? pool_lds_bytes(nit) : 0);
     // the keys of nit = 8, and those of 2 with their pooling, need more than the default 64 KB of LDS: raised once per device, not
     // per launch
@@ -1371,7 +1460,7 @@ bool select_pooled(const PoolParams &p, hipStream_t st, hipError_t &e)
     if (!multi) nit = p.N <= 4096 ? 1 : 2;
     if (!p.sel.pre_zeroed || nit > 2 || (long)parts * nit * 4096 < p.N) return false;
     const PoolSrc pool = {p.best, p.pooled, p.window};
-    e = multi ? launch_select_row<true, true>(p.sel, parts, nit, st, pool) : launch_select_row<false, true>(p.sel, 1, nit, st, pool);
+    e = multi ? launch_select_row<true, true, true>(p.sel, parts, nit, st, pool) : launch_select_row<false, true, true>(p.sel, 1, nit, st, pool);
     return true;
 }
 
@@ -1383,14 +1472,14 @@ hipError_t select_topk(const SelParams &p, hipStream_t st)
         // this launch would clear the bitmap of a call that has not, while its other workgroups mark in it
         if (p.mark && !p.pre_zeroed) return hipErrorInvalidValue;
         for (nit = 1; nit * 4096 < p.N;) nit *= 2;
-        return launch_select_row<false>(p, 1, nit, st);
+        return p.bin_top ? launch_select_row<false, true>(p, 1, nit, st) : launch_select_row<false, false>(p, 1, nit, st);
     }
     if (!p.pre_zeroed) {
         const long nz = max((long)p.nq * 3 * 2048, (long)p.zero_extra_n);
         hipLaunchKernelGGL(sel_zero, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, st, p);
         RF_CHECK_LAUNCH();
     }
-    if (multi) return launch_select_row<true>(p, parts, nit, st);
+    if (multi) return p.bin_top ? launch_select_row<true, true>(p, parts, nit, st) : launch_select_row<true, false>(p, parts, nit, st);
     const dim3 sgrid(p.nblk, p.nq);
     const int hblk = max(1, kHistWorkgroups / p.nq);       // workgroups per row of the histogram passes
     const dim3 hgrid(min(p.nblk, hblk), p.nq);
