@@ -8,6 +8,9 @@
 //                    needs the final normaliser of every row, so QK^T is formed a second time; the
 //                    probabilities are never stored.
 //
+// Problems that do not fill the chip have forms of their own (attn_fwd_few, attn_fwd_short, attn_score_few), and parts of
+// shared-out ones meet in attn_fwd_merge, attn_merge_score and attn_score_sum; attend_plan.h says which when.
+//
 // Both kernels compute the TRANSPOSED logit tile  S^T = K Q^T: a lane then owns one query column
 // and a few key rows, so the softmax row statistics are per-lane scalars (exchanged across the
 // lane groups once), and the probabilities are already laid out as the B operand of

@@ -13,7 +13,8 @@
 //   select_compact, select_*_rest
 //                 the second pass and those behind it for rows that may be compacted in place
 //   select_row    all of the above in one launch, keys held in LDS: one workgroup per row, or several that
-//                 wait for each other where every workgroup of the launch fits on the chip at once
+//                 wait for each other where every workgroup of the launch fits on the chip at once.  Cosines go by
+//                 a pass of finer bins first, and a pooled gather's row is max-pooled while it is read
 // Candidates in the first n_sink or last n_recent slots get the maximal key (always selected).
 #include "common.h"
 
@@ -885,7 +886,8 @@ __device__ __forceinline__ int waves_total(const int *wtot, int &before)
     return __builtin_amdgcn_readlane(incl, 15);
 }
 
-// Where the time of a selection goes (time stamps, 131072 similarities in 32 workgroups, 15.4 us before, 13.8 now):
+// Where the time of a selection by digits goes (time stamps, 131072 similarities in 32 workgroups, 13.8 us; similarities have since
+// gone by bins, see kBins, which leaves out the second histogram and its exchange):
 // load 1.5, histogram 0.6, exchange 2.8, pick 0.5 (0.85 with shuffles in place of data-parallel primitives), second
 // histogram 0.5 and exchange 2.5, pick 0.5, list 1.4, its pick 0.9, count 0.6, emission 1.6.  Whole calls: 37
 // queries pooled over 262144 x 1024 162.4 -> 155.7 us (its plateaus queued on few histogram words), 2048
