@@ -273,7 +273,7 @@ inline size_t fwd_short_bytes(const P &p)
 //   - Shares pay their merge, 3 us (less with the score's launch, see merge_with_score), and need a tile for every wave.
 //   - K and V have to come from memory once at least, and longer ones than an XCD's L2 holds come oftener: 23 rows over 26798
 //     keys, 24/8 heads of 128 30.1 us by the plan, 35.3 so.  There row blocks that walk the same keys also have to meet on an
-//     XCD, so the number of shares is a multiple of what brings the next block back to it.
+//     XCD, so shares beyond what brings the next block back to it come in multiples of that.
 // scratch: bytes there are for pieces.
 template <class P>
 inline int fwd_short(P &p, int cus, double est, bool scored, size_t scratch = (size_t)-1)
