@@ -274,12 +274,18 @@ inline size_t fwd_short_bytes(const P &p)
 //   - K and V have to come from memory once at least, and longer ones than an XCD's L2 holds come oftener: 23 rows over 26798
 //     keys, 24/8 heads of 128 30.1 us by the plan, 35.3 so.  There row blocks that walk the same keys also have to meet on an
 //     XCD, so shares beyond what brings the next block back to it come in multiples of that.
+//   - With a key tile or two of the plans and rows for one to three waves the estimates say too little for this form, whose waves
+//     but one are idle and meet all the same.  Forward pass traced, us, plan / this: 8 rows over 8 keys, 32/8 heads of 128 5.6 / 6.6,
+//     14/2 5.4 / 6.1, of 64 4.4 / 4.6; 20 over 20, 24/8 of 128 6.0 / 6.6, 14/2 (140 rows to a head) 7.0 / 6.6; 8 over 98, 32/8 of 128
+//     6.5 / 7.0, 14/2 6.5 / 6.3; at 64 60 rows to a head over 20 5.1 / 5.0, 80 5.3 / 5.1.
 // scratch: bytes there are for pieces.
 template <class P>
 inline int fwd_short(P &p, int cus, double est, bool scored, size_t scratch = (size_t)-1)
 {
     const long rows = (long)p.G * p.Ct, blocks = (rows + kFwdShortRows - 1) / kFwdShortRows, groups = blocks * p.Hkv;
     if (rows <= 16 || est == 0.0 || groups > 4l * cus) return 0;
+    if (p.n <= 64 && rows <= (p.D == 64 ? 64 : 96)) return 0;
+    if (p.n <= 128 && rows <= 32 && p.D == 128) return 0;
     const double longest = (p.M + p.Ct - 1) / 32 + 1, first = p.M / 32 + 1;
     const double unit = std::max(longest, 0.5 * (first + longest) * groups / cus);
     double best = groups <= cus ? (p.D == 64 ? 5.25 + 0.095 * unit : 6.5 + 0.195 * unit)

@@ -17,7 +17,7 @@ from paper_2506_01215_amd import binding
 DEV = "cuda:0"
 # Hq, Hkv, d, cache, chunk and the waves of a workgroup, checked on the CPU below
 SHORT = [
-    (8, 8, 128, 0, 33, 8),            # no cache: keys of the last tile that the first rows do not see
+    (8, 8, 128, 0, 97, 8),            # no cache: keys of the last tile that the first rows do not see
     (10, 2, 64, 31, 40, 8),           # 200 rows, 71 keys
     (14, 2, 128, 95, 45, 8),          # the first row block's keys end with a tile
     (3, 1, 64, 340, 700, 8),          # 2100 rows, the last block of 20, tiles that some of a block's rows do not see
@@ -112,6 +112,15 @@ def test_pieces_fit_the_room_there_is(plan):
     (32, 32, 128, 44, 302, True),     # 12.5, 10.1
     (8, 8, 128, 952, 739, True),      # 21.8, 18.4
     (32, 8, 128, 3063, 958, False),   # 69, 110
+    # a key tile or two of the plans and few rows
+    (32, 8, 128, 0, 8, False),        # 5.6, 6.6
+    (24, 8, 128, 0, 20, False),       # 6.0, 6.6
+    (32, 8, 128, 90, 8, False),       # 6.5, 7.0
+    (32, 8, 64, 40, 8, False),        # 4.9, 4.9
+    (14, 2, 64, 0, 8, False),         # 4.4, 4.6
+    (14, 2, 128, 0, 20, True),        # 7.0, 6.6
+    (14, 2, 128, 90, 8, True),        # 6.5, 6.3
+    (32, 8, 64, 90, 8, True),         # 5.6, 5.2
     # keys shared out
     (14, 2, 128, 2150, 137, True),    # 19.2, 14.7
     (16, 4, 64, 8964, 90, True),      # 19.7, 15.0
