@@ -1031,8 +1031,11 @@ struct QStage {
     // Qt: first row of the tile (uniform); lse_t: lse of that row; rows_left = Ct - i0 (>= 1)
     __device__ __forceinline__ void load(const u16 *Qt, const float *lse_t, int rows_left, long q_rs, int tid)
     {
+        // rows this far apart at most lie within 32 bits of the tile's first; a branch per tile, which is the same for all
+        // waves and costs no registers, while 64-bit offsets would cost two to a piece
+        constexpr long kFar = (0xffffffffl - 2 * D) / (2 * (QT - 1));
         const char *qb = (const char *)Qt;
-        if (rows_left >= QT) {
+        if (rows_left >= QT && q_rs <= kFar) {
 #pragma unroll
             for (int i = 0; i < PIECES; ++i) qpre[i] = *(const v4u *)(qb + (goff + gstep * (uint32_t)i));
         } else {
