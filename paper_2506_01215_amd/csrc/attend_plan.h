@@ -266,10 +266,16 @@ inline size_t fwd_short_bytes(const P &p)
 // Whether a forward pass is formed by attn_fwd_short instead of its plan, which is estimated at est us: the waves of a
 // workgroup of that form (0: not; the plan stays), with n_row_blocks and, where every row block's key tiles are shared out
 // over several workgroups, shares, part_rows and tiles.  Eight waves where every workgroup has a compute unit, else four, two
-// workgroups to a unit.  Time goes by the 32-key tiles of the longest workgroup or of a unit; fitted to 220 timings of
-// 110 problems of 17 to 1300 rows over up to 5000 keys, mean error 3 to 4 %.  Estimates of less than 0.88 of the plan's
-// are taken: of these problems and 60 of 9 to 300 rows over 600 to 30000 keys, 17 % and 12 % less in the mean than by the plans
-// alone, none more than 2 % slower; with 1.0 the mean is the same and 13 rows over 1885 keys, 32/8 heads of 64 take 13.5 us, not 12.2.
+// workgroups to a unit (three at 64).  Time goes by 32-key tiles:
+//   - With a unit to every workgroup by those of the longest.  Fitted to 220 timings of 110 problems of 17 to 1300 rows over up
+//     to 5000 keys, mean error 3 to 4 %.  Of 1300 others of 5 to 1500 rows over up to 30000 keys, the shares below among
+//     them, 820 have estimates of less than 0.88 of the plan's and take 0.76 of its time in the mean, 6 more than 2 % longer than it, at worst 9 %.
+//   - Beyond by the longest workgroup of each round of one to a unit, since just above one (two, three) to a unit some hold one
+//     more than the mean: 206 rows over 5715 keys, 40/8 heads of 64 (1.03 to a unit) 29.1 us by the plan, 38.5 so; 418 over 1901,
+//     40/8 of 128 (2.06) 34.2, 39.7.  The third round begins behind one of the first two.  Fitted to 1580 timings of 17 to 6700
+//     rows over up to 23000 keys, standard error 4 to 5 %.  Of 1507 others of 116 to 25000 rows over up to 29000 keys, a choice
+//     by estimates of less than 0.9 of the plan's takes 0.877 of the plans' time in the mean (the faster way of each 0.874), 28 more than
+//     2 % longer, 11 more than 5 %, at worst 13 % (1471 over 2145, 16/16 of 128 37.9, 42.8); by a unit's mean load 0.883, 104, 68, 32 %.
 //   - Shares pay their merge, 3 us (less with the score's launch, see merge_with_score), and need a tile for every wave.
 //   - K and V have to come from memory once at least, and longer ones than an XCD's L2 holds come oftener: 23 rows over 26798
 //     keys, 24/8 heads of 128 30.1 us by the plan, 35.3 so.  There row blocks that walk the same keys also have to meet on an
@@ -287,9 +293,18 @@ inline int fwd_short(P &p, int cus, double est, bool scored, size_t scratch = (s
     if (p.n <= 64 && rows <= (p.D == 64 ? 64 : 96)) return 0;
     if (p.n <= 128 && rows <= 32 && p.D == 128) return 0;
     const double longest = (p.M + p.Ct - 1) / 32 + 1, first = p.M / 32 + 1;
-    const double unit = std::max(longest, 0.5 * (first + longest) * groups / cus);
-    double best = groups <= cus ? (p.D == 64 ? 5.25 + 0.095 * unit : 6.5 + 0.195 * unit)
-                                : (p.D == 64 ? 5.75 + 0.095 * unit + 0.04 * longest : 6.75 + 0.18 * unit + 0.12 * longest);
+    double best = p.D == 64 ? 5.25 + 0.095 * longest : 6.5 + 0.195 * longest;
+    if (groups > cus) {
+        auto length = [&](long i) {                      // key tiles of the i-th workgroup
+            const long end = std::min((blocks - i / p.Hkv) * kFwdShortRows, rows);
+            return i < groups ? (double)((p.M + (end - 1) / p.G) / 32 + 1) : 0.0;
+        };
+        const double l1 = length(cus), l2 = length(2l * cus), l3 = length(3l * cus);
+        best = p.D == 64 ? 4.6 + 0.15 * longest + 0.045 * l1 : 7.25 + 0.21 * longest + 0.13 * l1;
+        if (l2 > 0.0)
+            best = p.D == 64 ? std::max(best + 0.8, 6.8 + 0.165 * l1 + 0.1 * l2 + 0.15 * l3)
+                             : std::max(best + 0.1, 12.65 + 0.3 * l1 + 0.285 * l2 + 0.11 * l3);
+    }
     P q = p;
     q.n_row_blocks = (int)blocks;
     q.part_rows = kFwdShortRows;
@@ -306,7 +321,7 @@ inline int fwd_short(P &p, int cus, double est, bool scored, size_t scratch = (s
         const double t = std::max(p.D == 64 ? 5.25 + 0.095 * longest / s : 6.5 + 0.195 * longest / s, stream) + 3.0 + 0.05 * s - launch;
         if (t < best) { best = t; shares = s; }
     }
-    if (best >= 0.88 * est) return 0;
+    if (best >= (groups > cus ? 0.9 : 0.88) * est) return 0;
     q.shares = (int)shares;
     p = q;
     return groups <= cus ? 8 : 4;

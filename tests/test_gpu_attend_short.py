@@ -112,6 +112,20 @@ def test_pieces_fit_the_room_there_is(plan):
     (32, 32, 128, 44, 302, True),     # 12.5, 10.1
     (8, 8, 128, 952, 739, True),      # 21.8, 18.4
     (32, 8, 128, 3063, 958, False),   # 69, 110
+    # a little more than one, two or three workgroups to a compute unit
+    (40, 8, 64, 5509, 206, False),    # 29.1, 38.5
+    (6, 3, 64, 3451, 1569, False),    # 28.1, 34.4
+    (71, 1, 128, 143, 350, False),    # 17.0, 21.1
+    (16, 16, 64, 5973, 556, False),   # 34.8, 43.0
+    (4, 4, 64, 2464, 2669, False),    # 29.3, 34.6
+    (40, 8, 128, 1483, 418, False),   # 34.2, 39.7
+    (64, 8, 128, 0, 293, False),      # 12.4, 14.7
+    (24, 8, 128, 1408, 685, False),   # 33.7, 40.2
+    (8, 1, 64, 0, 1134, True),        # 19.9, 10.2
+    (10, 2, 64, 0, 1721, True),       # 24.8, 14.5
+    (32, 8, 64, 551, 281, True),      # 15.2, 9.7
+    (16, 4, 128, 0, 601, True),       # 17.7, 11.9
+    (14, 2, 128, 67, 1144, True),     # 30.0, 18.7
     # a key tile or two of the plans and few rows
     (32, 8, 128, 0, 8, False),        # 5.6, 6.6
     (24, 8, 128, 0, 20, False),       # 6.0, 6.6
