@@ -267,19 +267,23 @@ inline size_t fwd_short_bytes(const P &p)
 // workgroup of that form (0: not; the plan stays), with n_row_blocks and, where every row block's key tiles are shared out
 // over several workgroups, shares, part_rows and tiles.  Eight waves where every workgroup has a compute unit, else four, two
 // workgroups to a unit (three at 64).  Time goes by 32-key tiles:
-//   - With a unit to every workgroup by those of the longest.  Fitted to 220 timings of 110 problems of 17 to 1300 rows over up
-//     to 5000 keys, mean error 3 to 4 %.  Of 1300 others of 5 to 1500 rows over up to 30000 keys, the shares below among
-//     them, 820 have estimates of less than 0.88 of the plan's and take 0.76 of its time in the mean, 6 more than 2 % longer than it, at worst 9 %.
+//   - With a unit to every workgroup by those of the longest, and 0.1 us a MB of K and V beyond 20, which the L2s of few row blocks
+//     do not hold (76 rows over 7673 keys, 40/40 heads of 64 26.2 us by the plan, 35.2 so).  Fitted to 220 timings of 110
+//     problems, mean error 3 to 4 %, and taken at less than 0.88 of the plan's estimate, or 0.84 where the score's launch merges the
+//     plan's pieces at 128, since the form saves less there (20 rows over 2539 keys, 20/5 heads, 20 observing, whole calls 18.2, 19.1).  Of
+//     4800 problems of 5 to 1500 rows over up to 30000 keys that the fit has not seen, with and without score, 3090 take this
+//     form or the shares below, 0.81 of the plan's time in the mean, 20 more than 2 % longer, 2 more than 5 %, at worst 6 %.
 //   - Beyond by the longest workgroup of each round of one to a unit, since just above one (two, three) to a unit some hold one
 //     more than the mean: 206 rows over 5715 keys, 40/8 heads of 64 (1.03 to a unit) 29.1 us by the plan, 38.5 so; 418 over 1901,
-//     40/8 of 128 (2.06) 34.2, 39.7.  The third round begins behind one of the first two.  Fitted to 1580 timings of 17 to 6700
+//     40/8 of 128 (2.06) 34.2, 39.7.  The third round begins behind one of the first two.  Fitted to 1500 timings of 17 to 6700
 //     rows over up to 23000 keys, standard error 4 to 5 %.  Of 1507 others of 116 to 25000 rows over up to 29000 keys, a choice
 //     by estimates of less than 0.9 of the plan's takes 0.877 of the plans' time in the mean (the faster way of each 0.874), 28 more than
 //     2 % longer, 11 more than 5 %, at worst 13 % (1471 over 2145, 16/16 of 128 37.9, 42.8); by a unit's mean load 0.883, 104, 68, 32 %.
 //   - Shares pay their merge, 3 us (less with the score's launch, see merge_with_score), and need a tile for every wave.
 //   - K and V have to come from memory once at least, and longer ones than an XCD's L2 holds come oftener: 23 rows over 26798
 //     keys, 24/8 heads of 128 30.1 us by the plan, 35.3 so.  There row blocks that walk the same keys also have to meet on an
-//     XCD, so shares beyond what brings the next block back to it come in multiples of that.
+//     XCD, so shares come in multiples of what brings the next block back to it, or up to 4.5 MB of K and V a head less than one (109
+//     rows over 24245 keys, 9/3 heads of 128 34.6 us by the plan, 53.0 with seven shares; 384 over 5971, 6/3, 3.1 MB 41.6, 38.9 with three).
 //   - With a key tile or two of the plans and rows for one to three waves the estimates say too little for this form, whose waves
 //     but one are idle and meet all the same.  Forward pass traced, us, plan / this: 8 rows over 8 keys, 32/8 heads of 128 5.6 / 6.6,
 //     14/2 5.4 / 6.1, of 64 4.4 / 4.6; 20 over 20, 24/8 of 128 6.0 / 6.6, 14/2 (140 rows to a head) 7.0 / 6.6; 8 over 98, 32/8 of 128
@@ -293,7 +297,8 @@ inline int fwd_short(P &p, int cus, double est, bool scored, size_t scratch = (s
     if (p.n <= 64 && rows <= (p.D == 64 ? 64 : 96)) return 0;
     if (p.n <= 128 && rows <= 32 && p.D == 128) return 0;
     const double longest = (p.M + p.Ct - 1) / 32 + 1, first = p.M / 32 + 1;
-    double best = p.D == 64 ? 5.25 + 0.095 * longest : 6.5 + 0.195 * longest;
+    const double mb = 4e-6 * p.Hkv * (double)p.n * p.D;
+    double best = (p.D == 64 ? 5.25 + 0.095 * longest : 6.5 + 0.195 * longest) + std::max(0.0, 0.1 * (mb - 20.0));
     if (groups > cus) {
         auto length = [&](long i) {                      // key tiles of the i-th workgroup
             const long end = std::min((blocks - i / p.Hkv) * kFwdShortRows, rows);
@@ -311,9 +316,9 @@ inline int fwd_short(P &p, int cus, double est, bool scored, size_t scratch = (s
     q.tiles = (p.M + p.Ct - 1) / 64 + 1;                 // of the longest row block, in the unit of the plans
     long shares = 0, step = 1;
     if (blocks > 1 && p.n * 4.0 * p.D > 3e6) while (step * p.Hkv % 8) step *= 2;
-    const double stream = 7.0 + 1.3 * 4.0 * p.Hkv * (double)p.n * p.D / 4.5e6;
+    const double stream = 7.0 + 0.29 * mb;
     for (long s = 2; s * groups <= cus && 8 * s <= (long)first; ++s) {
-        if (s > step && s % step) continue;
+        if (s % step && (s > step || p.n * 4.0 * p.D > 4.5e6)) continue;
         q.shares = (int)s;
         if (fwd_short_bytes(q) > scratch) break;
         double launch = 0.0;
@@ -321,7 +326,8 @@ inline int fwd_short(P &p, int cus, double est, bool scored, size_t scratch = (s
         const double t = std::max(p.D == 64 ? 5.25 + 0.095 * longest / s : 6.5 + 0.195 * longest / s, stream) + 3.0 + 0.05 * s - launch;
         if (t < best) { best = t; shares = s; }
     }
-    if (best >= (groups > cus ? 0.9 : 0.88) * est) return 0;
+    const bool merged = p.D == 128 && scored && p.shares && merge_with_score(p);
+    if (best >= (groups > cus ? 0.9 : merged ? 0.84 : 0.88) * est) return 0;
     q.shares = (int)shares;
     p = q;
     return groups <= cus ? 8 : 4;

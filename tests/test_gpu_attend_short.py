@@ -41,7 +41,7 @@ SHARED = [
     (1, 1, 64, 607, 37, 17, 10208),
     (3, 1, 64, 610, 15, 1, 10208),
     (1, 1, 128, 485, 120, 120, 10208),   # observing rows in four row blocks
-    (4, 1, 128, 485, 10, 10, 10208),
+    (4, 1, 128, 505, 15, 10, 10208),
 ]
 LONGER = [
     (1, 1, 64, 0, 33, 33, 1),
@@ -126,6 +126,16 @@ def test_pieces_fit_the_room_there_is(plan):
     (32, 8, 64, 551, 281, True),      # 15.2, 9.7
     (16, 4, 128, 0, 601, True),       # 17.7, 11.9
     (14, 2, 128, 67, 1144, True),     # 30.0, 18.7
+    # more K and V than the L2s hold, for few row blocks
+    (40, 40, 64, 7597, 76, False),    # 26.2, 35.2
+    (40, 40, 64, 11681, 148, False),  # 45.3, 56.1
+    (32, 32, 64, 3482, 77, False),    # 16.1, 17.3
+    (32, 32, 64, 3182, 167, True),    # 21.1, 16.9
+    (40, 40, 128, 1273, 157, True),   # 22.0, 17.5
+    # heads that do not divide by the XCDs, each longer than an L2 holds
+    (9, 3, 128, 24136, 109, False),   # 34.6, 53.0 with seven shares
+    (10, 5, 128, 11981, 130, False),
+    (6, 3, 128, 29745, 152, True),    # 38.4, 37.5 with eight
     # a key tile or two of the plans and few rows
     (32, 8, 128, 0, 8, False),        # 5.6, 6.6
     (24, 8, 128, 0, 20, False),       # 6.0, 6.6
@@ -148,6 +158,20 @@ def test_pieces_fit_the_room_there_is(plan):
 ])
 def test_the_faster_form_is_taken(plan, Hq, Hkv, d, M, Ct, taken):
     assert (plan.short_form(Hkv, Hq // Hkv, d, M, Ct, 0, 0, 256) != 0) == taken
+
+
+@pytest.mark.parametrize("Hq,Hkv,M,Ct,W,taken", [
+    # whole calls at head_dim 128 whose score's launch merges the plan's pieces, us, plan / short
+    (20, 5, 2519, 20, 20, False),     # 18.2, 19.1
+    (64, 8, 585, 8, 4, False),        # 14.8, 15.6
+    (20, 5, 1380, 21, 3, False),      # 15.4, 16.1
+    (16, 4, 317, 10, 10, False),      # 13.2, 14.0
+    (32, 8, 2175, 43, 6, True),       # 21.7, 17.2
+    (4, 4, 7859, 224, 4, True),       # 26.9, 21.8
+    (12, 4, 66, 66, 27, True),        # 16.7, 13.6
+])
+def test_the_faster_form_of_a_call_with_few_observing_rows_is_taken(plan, Hq, Hkv, M, Ct, W, taken):
+    assert (plan.short_form(Hkv, Hq // Hkv, 128, M, Ct, W, 1, 256) != 0) == taken
 
 
 @pytest.mark.gpu
