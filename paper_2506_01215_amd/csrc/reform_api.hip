@@ -471,7 +471,10 @@ reform_status reform_gather_topk(const reform_gather_desc *d, const void *emb, c
     p.sel.vals = p.sim; p.sel.ld = p.sim_ld; p.sel.N = d->n_ctx;
     p.sel.nq = d->n_query; p.sel.k = d->k;
     p.sel.n_sink = 0; p.sel.n_recent = 0;
-    p.sel.bin_top = kCosineTop;
+    // Of more than half of the rows the smallest taken is hardly ever a positive cosine, which the bins would tell apart: they
+    // come to nothing then, and the digits follow (9335 of 12868 rows 24.0 -> 28.7 us for the call, 76938 of 113561 29.4 ->
+    // 33.0; at up to half 0.93 to 1.01 of the time by digits).  A pooled value is the largest of a window and no such case.
+    p.sel.bin_top = 2ll * d->k <= d->n_ctx ? kCosineTop : 0;
     p.sel.hist = (int *)(ws + L.hist);
     p.sel.sel_prefix = (uint32_t *)(ws + L.prefix);
     p.sel.sel_krem = (int *)(ws + L.krem);

@@ -50,3 +50,19 @@ def test_selection_is_exact(kind, n):
             want = np.sort(np.lexsort((np.arange(n), -x.astype(np.float64)))[:k])
             np.testing.assert_array_equal(idx[q].cpu().numpy(), want, err_msg=f"{kind} k={k} query {q}")
             np.testing.assert_array_equal(val[q].cpu().numpy(), x[want])
+
+
+@pytest.mark.parametrize("n", [701, 5000, 9001, 40000, 140001])
+def test_half_of_the_rows_and_one_more(n):
+    """Up to half of the rows goes by bins, more by digits alone; cosines of both signs."""
+    g = torch.Generator().manual_seed(n)
+    emb, qry = torch.randn((n, 32), generator=g).to(DEV), torch.randn((2, 32), generator=g).to(DEV)
+    sim = binding.reform_gather_similarity(emb, qry)
+    for k in (n // 2, n // 2 + 1):
+        idx, val, _, _ = binding.reform_gather_topk(emb, qry, k, 0, 0, 0)
+        torch.cuda.synchronize()
+        for q in range(2):
+            x = sim[q].cpu().numpy()
+            want = np.sort(np.lexsort((np.arange(n), -x.astype(np.float64)))[:k])
+            np.testing.assert_array_equal(idx[q].cpu().numpy(), want)
+            np.testing.assert_array_equal(val[q].cpu().numpy(), x[want])
