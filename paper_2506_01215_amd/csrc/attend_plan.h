@@ -282,7 +282,7 @@ inline size_t fwd_short_bytes(const P &p)
 //   - Shares pay their merge, 3 us (less with the score's launch, see merge_with_score), and need a tile for every wave.
 //   - K and V have to come from memory once at least, and longer ones than an XCD's L2 holds come oftener: 23 rows over 26798
 //     keys, 24/8 heads of 128 30.1 us by the plan, 35.3 so.  There row blocks that walk the same keys also have to meet on an
-//     XCD, so shares come in multiples of what brings the next block back to it, or up to 4.5 MB of K and V a head less than one (109
+//     XCD, so shares come in multiples of what brings the next block back to it, or up to 3.8 MB of K and V a head less than one (109
 //     rows over 24245 keys, 9/3 heads of 128 34.6 us by the plan, 53.0 with seven shares; 384 over 5971, 6/3, 3.1 MB 41.6, 38.9 with three).
 //   - With a key tile or two of the plans and rows for one to three waves the estimates say too little for this form, whose waves
 //     but one are idle and meet all the same.  Forward pass traced, us, plan / this: 8 rows over 8 keys, 32/8 heads of 128 5.6 / 6.6,
@@ -318,7 +318,7 @@ inline int fwd_short(P &p, int cus, double est, bool scored, size_t scratch = (s
     if (blocks > 1 && p.n * 4.0 * p.D > 3e6) while (step * p.Hkv % 8) step *= 2;
     const double stream = 7.0 + 0.29 * mb;
     for (long s = 2; s * groups <= cus && 8 * s <= (long)first; ++s) {
-        if (s % step && (s > step || p.n * 4.0 * p.D > 4.5e6)) continue;
+        if (s % step && (s > step || p.n * 4.0 * p.D > 3.8e6)) continue;
         q.shares = (int)s;
         if (fwd_short_bytes(q) > scratch) break;
         double launch = 0.0;

@@ -135,6 +135,7 @@ def test_pieces_fit_the_room_there_is(plan):
     # heads that do not divide by the XCDs, each longer than an L2 holds
     (9, 3, 128, 24136, 109, False),   # 34.6, 53.0 with seven shares
     (10, 5, 128, 11981, 130, False),
+    (10, 5, 64, 15229, 237, False),   # 46.0, 47.9 with the score
     (6, 3, 128, 29745, 152, True),    # 38.4, 37.5 with eight
     # a key tile or two of the plans and few rows
     (32, 8, 128, 0, 8, False),        # 5.6, 6.6
