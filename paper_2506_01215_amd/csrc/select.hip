@@ -794,7 +794,9 @@ __global__ __launch_bounds__(256) void select_write_rest(SelParams p)
 // chip with workgroups that wait for others which find no room; so may other programs.  The
 // waits are therefore bounded, and a workgroup whose wait expires goes on alone: the row lies in memory
 // as the launch before left it, so it selects from the whole row by itself (select_alone) and then
-// emits its own part like the others.  The outcome is the same, only late.  It also sets *gave_up, on which
+// emits its own part like the others.  A row that is pooled on the way in does not: the workgroups of this launch write it
+// (p.vals) without an order between them, so there it is pooled anew from the similarities, which the launch before left
+// (select_alone_pooled), and p.vals is not read.  The outcome is the same, only late.  It also sets *gave_up, on which
 // the other waits of the call end as well: what they wait for will not come.
 template <bool BINS> constexpr int kSelList = BINS ? 508 : 256;
 // Entries of a list shared between workgroups that take their places one by one.  Atomics on one word queue, so of more each
@@ -1213,10 +1215,12 @@ __device__ __forceinline__ void select_alone(const SelParams &p, const float *s,
 }
 
 // BINS: a pass of bins before the digits (see kBins).  POOL: the row is max-pooled on the way in.  These launches are so short that
-// code counts which is fetched and skipped: with the bins in every form 12000 of 15000 scores 50.4 -> 51.3 us.
+// code counts which is fetched and skipped: with the bins in every form 12000 of 15000 scores 50.4 -> 51.3 us.  What is
+// pooled are similarities, so a row with POOL always has bins, and its first exchange is theirs.
 template <bool MULTI, bool BINS, bool POOL>
 __global__ __launch_bounds__(1024) void select_row(SelParams p, int parts, int nit, PoolSrc pool)
 {
+    static_assert(BINS || !POOL, "pooled values are stored in the exchange of the bins");
     extern __shared__ v4u keys[];                                 // [nit * 1024], with POOL its LDS behind them
     f32x4 *quads = (f32x4 *)(keys + nit * 1024);
     __shared__ __attribute__((aligned(16))) int h[2048];
@@ -1250,15 +1254,15 @@ __global__ __launch_bounds__(1024) void select_row(SelParams p, int parts, int n
     // three passes; the bins and the last digits behind them share the first.
     int *rh = p.hist + (size_t)q * 3 * 2048;
     // The workgroups' histograms together, in place of this one's.
-    auto exchange = [&](int *gh, int digits, bool first) {
+    auto exchange = [&](int *gh, int digits, bool bins) {
         __syncthreads();
         if constexpr (MULTI) {
             for (int i = tid; i < digits; i += 1024)
                 if (h[i]) atomicAdd(&gh[i], h[i]);
-            if (POOL && first) store_pooled(pool, N, wg_lo, nit, pooled);   // while the others' counts are on their way
+            if (POOL && bins) store_pooled(pool, N, wg_lo, nit, pooled);    // while the others' counts are on their way
             __syncthreads();
             alone = !multi_wait_hist(p, gh, digits, in_bin, h, wtot[0], &stop);
-        } else if (POOL && first) {
+        } else if (POOL && bins) {
             store_pooled(pool, N, wg_lo, nit, pooled);
         }
     };
@@ -1289,7 +1293,7 @@ __global__ __launch_bounds__(1024) void select_row(SelParams p, int parts, int n
             __syncthreads();
         }
         radix_hist(mine, N, w_lo, nit, shift, bits, prefix, h);
-        exchange(!BINS ? rh + (pass - 1) * 2048 : pass == 3 ? rh + 1024 : rh + pass * 2048, 1 << bits, POOL && !BINS && pass == 1);
+        exchange(!BINS ? rh + (pass - 1) * 2048 : pass == 3 ? rh + 1024 : rh + pass * 2048, 1 << bits, false);
         if (!alone) bin_pick(bits, prefix, krem, in_bin, h, wtot[0], sel);
     }
     // here prefix holds the threshold's bits from `shift` up, shared by in_bin candidates
