@@ -84,13 +84,40 @@ extern "C" int replay_eight(int Hkv, int G, int D, int M, int Ct, int cus)
     return p.shares ? check<kFwdRows>(p) : 1;
 }
 
-// The forward pass as it is launched.  Bit 0: four waves; bit 1: shared out; bit 2: merged by the score's launch.
-// scored: the call wants both.
-extern "C" int form(int Hkv, int G, int D, int M, int Ct, int W, int scored, int cus)
+// Plans the forward pass as the launcher does, with that much room for partial results; the waves of attn_fwd_short where that
+// takes the plan's place, else 0.
+static int place(Plan &p, int scored, int cus, size_t scratch)
+{
+    const double est = fwd_choose(p, cus, scored != 0, scratch);
+    return fwd_short(p, cus, est, scored != 0, scratch);
+}
+
+static int form_bits(const Plan &p, int scored)
+{
+    return (p.shares ? 2 : 0) + (p.shares && scored && merge_with_score(p) ? 4 : 0);
+}
+
+// The plan of the forward pass by row blocks of 256 or 128, which attn_fwd_short may take the place of.  Bit 0: four waves; bit 1:
+// shared out; bit 2: merged by the score's launch.  scored: the call wants both.
+extern "C" int plan_form(int Hkv, int G, int D, int M, int Ct, int W, int scored, int cus)
 {
     Plan p = problem(Hkv, G, D, M, Ct, W);
     fwd_choose(p, cus, scored != 0);
-    return p.narrow + (p.shares ? 2 : 0) + (p.shares && scored && merge_with_score(p) ? 4 : 0);
+    return p.narrow + form_bits(p, scored);
+}
+
+// The forward pass as it is launched with that many bytes for partial results (negative: as many as it wants): as above, and
+// 8 where attn_fwd_short forms it, with bits 1 and 2 for its shares.
+extern "C" int form_in(int Hkv, int G, int D, int M, int Ct, int W, int scored, int cus, long scratch)
+{
+    Plan p = problem(Hkv, G, D, M, Ct, W);
+    const int waves = place(p, scored, cus, room(scratch));
+    return (waves ? 8 : p.narrow) + form_bits(p, scored);
+}
+
+extern "C" int form(int Hkv, int G, int D, int M, int Ct, int W, int scored, int cus)
+{
+    return form_in(Hkv, G, D, M, Ct, W, scored, cus, -1);
 }
 
 // Shares of the forward pass with that many bytes for partial results (negative: as many as it wants), bytes: what they take.
@@ -127,8 +154,7 @@ extern "C" int score_slices(int Hkv, int G, int D, int M, int Ct, int W, int cus
 extern "C" int short_form(int Hkv, int G, int D, int M, int Ct, int W, int scored, int cus)
 {
     Plan p = problem(Hkv, G, D, M, Ct, W);
-    const double est = fwd_choose(p, cus, scored != 0);
-    const int waves = fwd_short(p, cus, est, scored != 0);
+    const int waves = place(p, scored, cus, (size_t)-1);
     if (!waves) return 0;
     return waves + 100 * std::max(p.shares, 1) + (p.shares && scored && merge_with_score(p) ? 10000 : 0);
 }
@@ -137,6 +163,5 @@ extern "C" int short_form(int Hkv, int G, int D, int M, int Ct, int W, int score
 extern "C" long short_bytes(int Hkv, int G, int D, int M, int Ct, int scored, int cus, long scratch)
 {
     Plan p = problem(Hkv, G, D, M, Ct, 0);
-    const double est = fwd_choose(p, cus, scored != 0, room(scratch));
-    return fwd_short(p, cus, est, scored != 0, room(scratch)) ? (long)fwd_short_bytes(p) : 0;
+    return place(p, scored, cus, room(scratch)) ? (long)fwd_short_bytes(p) : 0;
 }

@@ -1,15 +1,17 @@
-"""The form that the forward pass takes, eight waves or four, replayed on the CPU: every key tile of every row block belongs to
-exactly one workgroup and the merge reads the slots that were written; the GPU tests' shapes take the form they are for;
-and shapes measured in both forms take the faster one."""
+"""The form that the forward pass takes, replayed on the CPU: every key tile of every row block of a plan of eight or four waves
+belongs to exactly one workgroup and the merge reads the slots that were written; the GPU tests' shapes take the form they are
+for, as it is launched; and of the two plans shapes measured in both have the faster one."""
+import ctypes
 import random
 
 import pytest
+import torch
 
 import helpers
 import test_gpu_attend_fwd_narrow
 import test_gpu_attend_merge_score
 import test_gpu_attend_split
-
+from paper_2506_01215_amd import binding
 
 
 @pytest.fixture(scope="module")
@@ -27,7 +29,7 @@ def test_every_tile_has_one_workgroup(plan, G):
         Ct = rng.choice([rng.randint(1, 40), rng.randint(1, 400), rng.randint(1, 6000)])
         scored, cus = rng.randint(0, 1), rng.choice([256, 256, 32, 304])
         assert plan.replay_chosen(Hkv, G, d, M, Ct, scored, cus) == 0, (Hkv, G, d, M, Ct, scored, cus)
-        narrow += plan.form(Hkv, G, d, M, Ct, 0, scored, cus) & 1
+        narrow += plan.plan_form(Hkv, G, d, M, Ct, 0, scored, cus) & 1
     assert narrow > 20
 
 
@@ -53,7 +55,8 @@ def test_lists_too_long_for_every_share_are_shared_by_fewer(plan, Hkv, G, d, M, 
     assert plan.replay_chosen(Hkv, G, d, M, Ct, 0, 256) == 0
 
 
-@pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W,form", test_gpu_attend_fwd_narrow.NARROW)
+@pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W,form", test_gpu_attend_fwd_narrow.NARROW +
+                         test_gpu_attend_fwd_narrow.BY_THE_SHORT_FORM)
 def test_the_shapes_of_the_gpu_test_take_the_form_they_are_for(plan, Hq, Hkv, d, M, Ct, W, form):
     assert plan.form(Hkv, Hq // Hkv, d, M, Ct, W, 1, 256) == form
 
@@ -62,6 +65,21 @@ def test_the_shapes_of_the_gpu_test_take_the_form_they_are_for(plan, Hq, Hkv, d,
                          test_gpu_attend_merge_score.WHOLE)
 def test_the_shapes_of_the_tests_of_shares_and_merging_take_the_form_they_are_for(plan, Hq, Hkv, d, M, Ct, W, form):
     assert plan.form(Hkv, Hq // Hkv, d, M, Ct, W, 1, 256) == form
+
+
+def test_less_room_than_all_reaches_every_form(plan):
+    """The forms that a workspace between none and all leads to, as in test_gpu_attend_split."""
+    reached = set()
+    for Hq, Hkv, d, M, Ct, W, form in test_gpu_attend_split.PARTLY:
+        args = (Hkv, Hq // Hkv, d, M, Ct, W, 1, 256)
+        assert plan.form(*args) == form, args
+        q, k = torch.empty((Hq, Ct, d), dtype=torch.bfloat16), torch.empty((Hkv, M + Ct, d), dtype=torch.bfloat16)
+        need = binding.attend_workspace_bytes(binding.attn_desc(q, k, q, M, 0.1, W)) - (Hq * Ct * 4 + 255) // 256 * 256
+        at = [plan.form_in(*args, ctypes.c_long(int(part * need))) for part in test_gpu_attend_split.PARTS]
+        reached |= {(f & 9, f & 6) for f in at}
+    # eight waves, four, attn_fwd_short: whole, shared out, merged by the score's launch; what four waves share out, attn_fwd_short
+    # takes whole
+    assert reached == {(form, bits) for form in (0, 1, 8) for bits in (0, 2, 6)} - {(1, 0)}
 
 
 @pytest.mark.parametrize("Hq,Hkv,d,M,Ct", test_gpu_attend_split.MANY)
@@ -106,5 +124,5 @@ def test_shared_out_row_blocks_of_eight_waves_have_their_shapes():
     (8, 8, 64, 31055, 281, 3),        # 48.4, 44.1
     (12, 4, 64, 14271, 117, 3),       # 26.1, 22.2
 ])
-def test_the_faster_form_is_taken(plan, Hq, Hkv, d, M, Ct, form):
-    assert plan.form(Hkv, Hq // Hkv, d, M, Ct, 0, 0, 256) == form
+def test_the_faster_plan_is_taken(plan, Hq, Hkv, d, M, Ct, form):
+    assert plan.plan_form(Hkv, Hq // Hkv, d, M, Ct, 0, 0, 256) == form

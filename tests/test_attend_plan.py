@@ -229,7 +229,7 @@ def test_one_head_to_a_group_stays_uncut_where_that_was_measured_faster(plan, Hq
     (8, 8, 128, 4096, 17, 0, True),
 ])
 def test_merging_in_the_score_launch_where_it_was_measured_faster(plan, Hq, Hkv, d, M, Ct, W, merged):
-    assert plan.form(Hkv, Hq // Hkv, d, M, Ct, W, 1, 256) == (6 if merged else 2)
+    assert plan.plan_form(Hkv, Hq // Hkv, d, M, Ct, W, 1, 256) == (6 if merged else 2)
 
 
 @pytest.mark.parametrize("Hq,Hkv,d,M,Ct,shared", [

@@ -13,24 +13,39 @@ from paper_2506_01215_amd import binding
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
-# Which form a shape takes is checked on the CPU (test_attend_fwd_choice.py).  The last entry of a shape: 1 whole row blocks,
-# 3 shared out, 7 merged by the score's launch.
+# Which form a shape takes with a workspace that holds all pieces is checked on the CPU (test_attend_fwd_choice.py).  The last
+# entry of a shape: 1 whole row blocks, 3 shared out, 7 merged by the score's launch.
 NARROW = [
-    (32, 8, 128, 0, 96, 0, 1),        # 384 rows: three full row blocks, four heads to a workgroup
-    (14, 2, 128, 0, 164, 0, 1),       # seven heads: rows of a wave from several
-    (24, 8, 64, 0, 266, 0, 1),        # 798 rows: 30 in the last block; 266 keys
-    (8, 2, 64, 0, 400, 0, 1),
-    (1, 1, 128, 500, 129, 0, 3),      # one row over; 629 keys
-    (4, 1, 64, 427, 54, 0, 3),        # heads divide the waves, the chunk rows do not fill the second block
-    (5, 1, 128, 1000, 200, 0, 3),
-    (2, 2, 128, 1000, 300, 128, 7),
+    (176, 44, 128, 0, 64, 0, 1),      # 256 rows: two full row blocks, four heads to a workgroup
+    (308, 44, 128, 0, 23, 0, 1),      # seven heads: rows of a wave from several
+    (3, 1, 64, 0, 20, 0, 1),          # 60 rows of one block, 20 keys
+    (3, 1, 64, 0, 43, 0, 1),          # 129 rows: one in the last block
+    (4, 1, 64, 14, 20, 0, 1),
+    (1, 1, 128, 513, 129, 0, 3),      # one row over; 642 keys
+    (12, 3, 64, 15362, 82, 0, 3),     # heads divide the waves, the chunk rows do not fill the third block
+    (5, 1, 128, 633, 26, 0, 3),
+    (1, 1, 128, 0, 129, 128, 7),      # 128 observing rows in two row blocks
     (8, 2, 128, 776, 41, 17, 7),
-    (1, 1, 64, 3000, 300, 128, 7),    # 128 observing rows in two row blocks
-    (1, 1, 128, 5000, 260, 128, 7),
+    (1, 1, 64, 342, 1540, 128, 7),
+    (1, 1, 128, 0, 131, 1, 7),
+]
+# Row counts around the same edges that attn_fwd_short takes where all its pieces have room: 8, 10 with keys shared out, 14
+# merged by the score's launch.  Without room some of them run by four waves.
+BY_THE_SHORT_FORM = [
+    (32, 8, 128, 0, 96, 0, 8),
+    (14, 2, 128, 0, 164, 0, 8),
+    (24, 8, 64, 0, 266, 0, 8),
+    (8, 2, 64, 0, 400, 0, 8),
+    (1, 1, 128, 500, 129, 0, 8),
+    (4, 1, 64, 427, 54, 0, 8),
+    (5, 1, 128, 1000, 200, 0, 10),
+    (2, 2, 128, 1000, 300, 128, 14),
+    (1, 1, 64, 3000, 300, 128, 14),
+    (1, 1, 128, 5000, 260, 128, 14),
 ]
 
 
-@pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W,form", NARROW)
+@pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W,form", NARROW + BY_THE_SHORT_FORM)
 @pytest.mark.parametrize("room", [True, False])
 def test_one_call_matches_oracle(Hq, Hkv, d, M, Ct, W, form, room):
     g = torch.Generator().manual_seed(Hq + M + Ct + W)

@@ -12,11 +12,23 @@ from paper_2506_01215_amd import binding
 
 DEV = "cuda:0"
 SHAPES = [
-    (8, 8, 128, 300, 2049),           # last row block of one row
-    (12, 4, 64, 100, 1500),           # of 148
-    (14, 2, 128, 333, 1301),          # of 147, three pieces and more to a row
-    (10, 2, 64, 2000, 1700),          # of 52
-    (6, 3, 64, 500, 3001),            # three KV heads
+    (33, 33, 128, 3210, 257),         # last row block of one row
+    (24, 8, 64, 3041, 683),           # of one, three heads to a group
+    (28, 4, 128, 857, 599),           # of 97, seven heads to a group
+    (28, 4, 128, 949, 586),           # of six
+    (24, 8, 64, 3225, 684),           # of four
+    (40, 8, 64, 3051, 410),           # of two
+    (12, 4, 64, 300, 3001),           # of 43
+    (6, 3, 64, 2500, 3001),           # three KV heads
+    (4, 2, 64, 129, 4099),            # two
+]
+# As many rows, which attn_fwd_short takes whole.
+BY_THE_SHORT_FORM = [
+    (8, 8, 128, 300, 2049),
+    (12, 4, 64, 100, 1500),
+    (14, 2, 128, 333, 1301),
+    (10, 2, 64, 2000, 1700),
+    (6, 3, 64, 500, 3001),
 ]
 
 
@@ -28,7 +40,7 @@ def test_shapes_take_the_form(Hq, Hkv, d, M, Ct, tmp_path_factory):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("Hq,Hkv,d,M,Ct", SHAPES)
+@pytest.mark.parametrize("Hq,Hkv,d,M,Ct", SHAPES + BY_THE_SHORT_FORM)
 def test_matches_oracle(Hq, Hkv, d, M, Ct):
     n, G = M + Ct, Hq // Hkv
     g = torch.Generator().manual_seed(M + Ct)

@@ -15,23 +15,30 @@ DEV = "cuda:0"
 
 
 # The last entry of a shape is the form of the forward pass, which is checked on the CPU (test_attend_fwd_choice.py): 6 shared
-# out and merged by the score's launch, 7 the same with row blocks of 128; 1 whole row blocks of 128.
+# out and merged by the score's launch, 7 the same with row blocks of 128, 14 the same by attn_fwd_short; 1 whole row blocks of
+# 128, 8 of 32.
 MERGED = [
-    (2, 2, 128, 1000, 300, 100, 7),   # rows 200..299: two row blocks
-    (2, 2, 64, 0, 500, 128, 6),       # no cache: row blocks of few pieces
+    (1, 1, 128, 0, 129, 100, 7),      # rows 29..128: two row blocks
+    (2, 2, 128, 1000, 300, 100, 14),
+    (1, 1, 64, 0, 1153, 32, 6),       # no cache: row blocks of few pieces
     (4, 1, 128, 3000, 20, 20, 6),     # eight blocks of rows, half of each empty
-    (14, 2, 64, 900, 16, 16, 6),
+    (14, 2, 64, 900, 16, 16, 14),
+    (7, 1, 64, 1365, 5, 1, 6),
     (8, 1, 128, 700, 1, 1, 6),        # one token
-    (1, 1, 128, 5000, 260, 1, 7),     # only the last row observes
+    (1, 1, 128, 5000, 260, 1, 14),    # only the last row observes
+    (1, 1, 128, 0, 129, 1, 7),
     (8, 8, 128, 4096, 17, 17, 6),
-    (3, 1, 64, 400, 31, 5, 6),
+    (3, 1, 64, 196, 5, 5, 6),
     (14, 2, 128, 9000, 1, 1, 6),      # seven rows of many pieces, 32 lanes each
     (1, 1, 64, 3000, 40, 3, 6),       # three rows, 64 lanes each
-    (2, 2, 64, 0, 300, 128, 6),       # the observing rows end the first row block and are the second
-    (4, 4, 128, 8351, 397, 128, 6),
+    (1, 1, 64, 443, 809, 128, 6),     # the observing rows end a row block and are the last
+    (4, 4, 128, 8351, 397, 128, 14),
+    (3, 3, 128, 11034, 387, 128, 6),
     (8, 2, 128, 300, 40, 16, 7),
 ]
-WHOLE = [(2, 2, 64, 0, 200, 128, 1), (3, 1, 64, 130, 31, 5, 1), (3, 1, 64, 200, 31, 5, 1)]     # chunks that are not split
+# chunks that are not split
+WHOLE = [(1, 1, 64, 0, 17, 5, 1), (3, 1, 64, 0, 6, 6, 1), (2, 2, 64, 0, 200, 128, 8), (3, 1, 64, 130, 31, 5, 8), (3, 1, 64, 200, 31, 5, 8),
+         (2, 2, 64, 0, 500, 128, 8), (3, 1, 64, 400, 31, 5, 8), (2, 2, 64, 0, 300, 128, 8)]
 
 
 @pytest.mark.parametrize("Hq,Hkv,d,M,Ct,W,form", MERGED + WHOLE)

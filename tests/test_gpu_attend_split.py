@@ -20,22 +20,30 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 # Hq, Hkv, d, cache, chunk, window and the form of the forward pass, which is checked on the CPU (test_attend_fwd_choice.py):
-# 1 four waves (else eight), 2 shared out, 4 merged by the score's launch.
+# 1 four waves (else eight), 8 attn_fwd_short, 2 shared out, 4 merged by the score's launch.
 SHAPES = [
     (8, 2, 128, 1000, 1, 0, 6),       # one token: every workgroup holds a few tiles of one row block
     (8, 2, 64, 127, 1, 0, 0),         # two tiles a head: one workgroup, nothing to merge
     (8, 8, 128, 4096, 17, 0, 6),
-    (14, 2, 64, 2000, 300, 128, 3),   # seven query heads per KV head
+    (14, 2, 64, 2000, 300, 128, 8),   # seven query heads per KV head
+    (21, 3, 64, 15224, 46, 46, 3),
     (1, 1, 128, 0, 1500, 0, 3),       # no cache: ranges begin on tiles that rows do not see
-    (1, 1, 64, 900, 257, 0, 2),       # last row block of one row
+    (1, 1, 64, 900, 257, 0, 8),       # last row block of one row
+    (1, 1, 64, 13827, 1025, 0, 2),
     (4, 1, 128, 900, 65, 0, 3),
-    (6, 3, 128, 2003, 513, 77, 3),    # two heads of a group in one workgroup
+    (6, 3, 128, 2003, 513, 77, 10),   # two heads of a group in one workgroup
+    (2, 1, 128, 583, 79, 77, 3),
     (2, 1, 128, 6001, 40, 40, 6),
-    (2, 2, 128, 12747, 386, 0, 2),    # eight waves, two row blocks and more
-    (32, 8, 128, 3199, 99, 99, 2),
-    (6, 2, 128, 12738, 131, 128, 2),
-    (3, 1, 64, 366, 90, 0, 2),
-    (2, 1, 64, 351, 132, 128, 2),
+    (3, 3, 128, 8845, 385, 0, 2),     # eight waves, two row blocks and more
+    (12, 3, 128, 9117, 100, 100, 2),
+    (9, 3, 128, 9117, 132, 128, 2),
+    (3, 1, 64, 15189, 353, 0, 2),
+    (2, 1, 64, 14917, 518, 128, 2),
+    (2, 2, 128, 12747, 386, 0, 10),   # keys shared out by attn_fwd_short, and not
+    (32, 8, 128, 3199, 99, 99, 10),
+    (6, 2, 128, 12738, 131, 128, 10),
+    (3, 1, 64, 366, 90, 0, 8),
+    (2, 1, 64, 351, 132, 128, 8),
 ]
 
 
@@ -93,23 +101,34 @@ def test_many_row_blocks_match_oracle(shape):
         assert_close(to_np(lse)[g * G:(g + 1) * G], l_ref, 1e-5, "lse")
 
 
-@pytest.mark.parametrize("shape", [
-    (8, 2, 128, 1000, 1, 0),
-    (14, 2, 64, 2000, 300, 128),
-    (6, 3, 128, 2003, 513, 77),
-    (2, 1, 128, 6001, 40, 40),
-    (16, 2, 128, 1000, 600, 301),
-    (2, 2, 64, 0, 1600, 0),
-], ids=lambda s: "x".join(map(str, s)))
+# With the form of the forward pass where all its pieces have room, as above; what it is where they do not is checked on the CPU.
+PARTS = (0.9, 0.5, 0.2, 0.05)
+PARTLY = [
+    (8, 2, 128, 1000, 1, 0, 6),
+    (14, 2, 64, 2000, 300, 128, 8),
+    (6, 3, 128, 2003, 513, 77, 10),
+    (2, 1, 128, 6001, 40, 40, 6),
+    (16, 2, 128, 1000, 600, 301, 8),
+    (2, 2, 64, 0, 1600, 0, 8),
+    (1, 1, 128, 0, 1500, 0, 3),
+    (5, 1, 128, 633, 26, 26, 3),
+    (1, 1, 64, 310, 1561, 128, 7),
+    (9, 3, 128, 9117, 132, 128, 2),
+    (7, 1, 64, 3441, 31, 17, 10),
+    (1, 1, 128, 485, 120, 120, 14),
+]
+
+
+@pytest.mark.parametrize("shape", PARTLY, ids=lambda s: "x".join(map(str, s)))
 def test_a_workspace_between_none_and_all(shape):
     """Room for some of the shares and slices: a cut that fits, and nothing behind its end is touched."""
-    Hq, Hkv, d, M, Ct, W = shape
+    Hq, Hkv, d, M, Ct, W, _ = shape
     q, k, v = inputs(Hq, Hkv, d, M, Ct, seed=5 + M + Ct)
     scale = 1.0 / math.sqrt(d)
     o_ref, l_ref, s_ref = oracle.attend_score(to_np(q), to_np(k), to_np(v), M, scale, W=W)
     lse_bytes = (Hq * Ct * 4 + 255) // 256 * 256
     need = binding.attend_workspace_bytes(binding.attn_desc(q, k, q, M, scale, W)) - lse_bytes
-    for part in (0.9, 0.5, 0.2, 0.05):
+    for part in PARTS:
         nbytes = lse_bytes + int(part * need)
         ws = torch.full((nbytes + 4096,), 0xa5, dtype=torch.uint8, device=DEV)
         out, lse, score = binding.reform_chunk_attend_score(q, k, v, M, scale, obs_window=W, workspace=ws[:nbytes])
