@@ -706,8 +706,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_fwd_short(AttnParams p)
     const int group = blockIdx.x / p.Hkv, share = SPLIT ? group % p.shares : 0;
     const int rb = p.n_row_blocks - 1 - (SPLIT ? group / p.shares : group);        // late (long) ones first
     const int row0 = rb * R, rows_here = min(R, rows - row0);
-    const int all = (p.M + (row0 + rows_here - 1) / p.G) / 32 + 1;
-    const int begin = SPLIT ? (int)((long)all * share / p.shares) : 0, tiles = SPLIT ? (int)((long)all * (share + 1) / p.shares) : all;
+    const int all = fwd_short_tiles(p, rb);
+    const int begin = SPLIT ? fwd_short_begin(p, all, share) : 0, tiles = SPLIT ? fwd_short_begin(p, all, share + 1) : all;
     const u16 *Kg = (const u16 *)p.k + (size_t)kvh * p.cap * D;
     const u16 *Vg = (const u16 *)p.v + (size_t)kvh * p.cap * D;
 

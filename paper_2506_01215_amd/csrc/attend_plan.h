@@ -247,6 +247,18 @@ inline double fwd_choose(P &p, int cus, bool scored, size_t scratch = (size_t)-1
 
 constexpr int kFwdShortRows = 32;                        // query rows of a workgroup of attn_fwd_short
 
+// 32-key tiles of row block rb of attn_fwd_short, up to the last key its last row sees.
+template <class P>
+RF_PLAN int fwd_short_tiles(const P &p, int rb)
+{
+    const int rows = p.G * p.Ct, end = (rb + 1) * kFwdShortRows;
+    return (p.M + ((end < rows ? end : rows) - 1) / p.G) / 32 + 1;
+}
+
+// Of `tiles` share j holds [fwd_short_begin(j), fwd_short_begin(j + 1)).
+template <class P>
+RF_PLAN int fwd_short_begin(const P &p, int tiles, int j) { return (int)((long)tiles * j / p.shares); }
+
 // The pieces of row block rb where attn_fwd_short's key tiles are shared out: each block's own, in equal parts.
 template <class P>
 struct ShortPieces {

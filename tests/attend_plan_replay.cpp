@@ -165,3 +165,42 @@ extern "C" long short_bytes(int Hkv, int G, int D, int M, int Ct, int scored, in
     Plan p = problem(Hkv, G, D, M, Ct, 0);
     return place(p, scored, cus, room(scratch)) ? (long)fwd_short_bytes(p) : 0;
 }
+
+// 0 if the workgroups of attn_fwd_short, shared out, cover every key tile of every row block of every KV head exactly once, and
+// leave their pieces in slots of their own inside its bytes, the ones that the merge reads; 1: it is not launched or not
+// shared out; else a number that tells what failed.
+extern "C" int replay_short(int Hkv, int G, int D, int M, int Ct, int scored, int cus, long scratch)
+{
+    Plan p = problem(Hkv, G, D, M, Ct, 0);
+    if (!place(p, scored, cus, room(scratch)) || !p.shares) return 1;
+    const long rows = (long)G * Ct, blocks = (rows + 31) / 32;
+    if (kFwdShortRows != 32 || p.n_row_blocks != blocks || p.part_rows != 32) return 2;
+    if (fwd_short_bytes(p) > room(scratch)) return 3;
+    const long slots = (long)p.shares * Hkv * blocks;
+    if (slots * 32 * (D + 2) * (long)sizeof(float) != (long)fwd_short_bytes(p)) return 4;
+    std::vector<std::vector<Piece>> got(blocks * Hkv);
+    for (long b = 0; b < slots; ++b) {                   // as the kernel reads blockIdx
+        const int kvh = (int)(b % Hkv), group = (int)(b / Hkv), share = group % p.shares, rb = p.n_row_blocks - 1 - group / p.shares;
+        if (rb < 0) return 5;
+        const int all = fwd_short_tiles(p, rb);
+        if (all != ((long)M + (std::min((rb + 1l) * 32, rows) - 1) / G) / 32 + 1) return 6;
+        got[rb * Hkv + kvh].push_back({fwd_short_begin(p, all, share), fwd_short_begin(p, all, share + 1),
+                                       ShortPieces<Plan>(p, rb).slot(p, share, kvh)});
+    }
+    std::vector<char> used(slots);
+    for (int rb = 0; rb < blocks; ++rb)
+        for (int kvh = 0; kvh < Hkv; ++kvh) {
+            const ShortPieces<Plan> pieces(p, rb);
+            const std::vector<Piece> &mine = got[rb * Hkv + kvh];
+            if (pieces.j1 - pieces.j0 + 1 != (long)mine.size()) return 7;
+            long at = 0;
+            for (size_t i = 0; i < mine.size(); ++i) {
+                if (mine[i].t0 != at || mine[i].t1 <= at) return 8;
+                at = mine[i].t1;
+                if (mine[i].slot != pieces.slot(p, pieces.j0 + (int)i, kvh)) return 9;
+                if (mine[i].slot < 0 || mine[i].slot >= slots || used[mine[i].slot]++) return 10;
+            }
+            if (at != fwd_short_tiles(p, rb)) return 11;
+        }
+    return 0;
+}

@@ -103,6 +103,23 @@ def test_pieces_fit_the_room_there_is(plan):
     assert less > 50
 
 
+@pytest.mark.parametrize("G", [1, 2, 3, 4, 7, 8, 16, 71])
+def test_every_tile_of_the_shares_has_one_workgroup_and_its_piece_a_slot(plan, G):
+    rng = random.Random(G)
+    shared = cut = 0
+    for _ in range(1500):
+        Hkv, d, cus = rng.choice([1, 2, 3, 4, 8, 32]), rng.choice([64, 128]), rng.choice([256, 256, 32, 304])
+        M, Ct, scored = rng.randint(100, 30000), int(2 ** rng.uniform(0, 9)), rng.randint(0, 1)
+        plan.short_bytes.restype = ctypes.c_long
+        want = plan.short_bytes(Hkv, G, d, M, Ct, scored, cus, ctypes.c_long(-1))
+        for room in (-1, want, rng.randint(0, want)):
+            rc = plan.replay_short(Hkv, G, d, M, Ct, scored, cus, ctypes.c_long(room))
+            assert rc in (0, 1), (Hkv, G, d, M, Ct, scored, cus, room, rc)
+            shared += rc == 0
+            cut += rc == 0 and 0 <= room < want
+    assert shared > 30 and cut > 3
+
+
 @pytest.mark.parametrize("Hq,Hkv,d,M,Ct,taken", [
     # attention alone, us, plan / short (best number of waves)
     (32, 8, 64, 1000, 60, True),      # 15.4, 9.2
