@@ -296,6 +296,8 @@ inline size_t fwd_short_bytes(const P &p)
 //     keys, 24/8 heads of 128 30.1 us by the plan, 35.3 so.  There row blocks that walk the same keys also have to meet on an
 //     XCD, so shares come in multiples of what brings the next block back to it, or up to 3.8 MB of K and V a head less than one (109
 //     rows over 24245 keys, 9/3 heads of 128 34.6 us by the plan, 53.0 with seven shares; 384 over 5971, 6/3, 3.1 MB 41.6, 38.9 with three).
+//     Beyond 72 MB of K and V nothing is gained: 44 problems at 64 take 0.99 of the plan's time in the mean, at worst 1.04 (52 rows over
+//     320718 keys, 5/1 heads 49.7 us by the plan, 51.7 so); 62 of 54 to 72 MB 0.93, below less; none at 128 is taken there.
 //   - With a key tile or two of the plans and rows for one to three waves the estimates say too little for this form, whose waves
 //     but one are idle and meet all the same.  Forward pass traced, us, plan / this: 8 rows over 8 keys, 32/8 heads of 128 5.6 / 6.6,
 //     14/2 5.4 / 6.1, of 64 4.4 / 4.6; 20 over 20, 24/8 of 128 6.0 / 6.6, 14/2 (140 rows to a head) 7.0 / 6.6; 8 over 98, 32/8 of 128
@@ -329,7 +331,7 @@ inline int fwd_short(P &p, int cus, double est, bool scored, size_t scratch = (s
     long shares = 0, step = 1;
     if (blocks > 1 && p.n * 4.0 * p.D > 3e6) while (step * p.Hkv % 8) step *= 2;
     const double stream = 7.0 + 0.29 * mb;
-    for (long s = 2; s * groups <= cus && 8 * s <= (long)first; ++s) {
+    for (long s = 2; mb <= 72.0 && s * groups <= cus && 8 * s <= (long)first; ++s) {
         if (s % step && (s > step || p.n * 4.0 * p.D > 3.8e6)) continue;
         q.shares = (int)s;
         if (fwd_short_bytes(q) > scratch) break;

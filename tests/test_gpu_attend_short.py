@@ -154,6 +154,10 @@ def test_every_tile_of_the_shares_has_one_workgroup_and_its_piece_a_slot(plan, G
     (10, 5, 128, 11981, 130, False),
     (10, 5, 64, 15229, 237, False),   # 46.0, 47.9 with the score
     (6, 3, 128, 29745, 152, True),    # 38.4, 37.5 with eight
+    # more K and V than shares gain anything on
+    (5, 1, 64, 320666, 52, False),    # 49.7, 51.7
+    (2, 2, 64, 171038, 288, False),   # 52.4, 54.4
+    (3, 1, 64, 82197, 83, True),      # 32.6, 27.8 with the score
     # a key tile or two of the plans and few rows
     (32, 8, 128, 0, 8, False),        # 5.6, 6.6
     (24, 8, 128, 0, 20, False),       # 6.0, 6.6
